@@ -1,7 +1,12 @@
 // cfgzip_build_classes: group tokens with equal signature, number the classes
 // and pick representatives (paper Section 3.1 "Pre-Computation").
 //
-// Pipeline (all on the device, eight launches when no hash collides):
+// Vocabularies of up to 262,144 tokens whose signatures need not be walked again to be compared are first
+// grouped by hash table (class_table.hpp: four launches).  The rest, and every call in which a hash collides or
+// the walk store cannot be used, take the sort below: grouping alone 83 us on 128,256 tokens (table: 35 us) and
+// 103 us on 151,936 (table: 45 us), but exact whatever the hashes are.
+//
+// Sort pipeline (all on the device, eight launches when no hash collides):
 //   1. keys: (low 32 or 40 bits of the hash, first byte of the token), and the digit counts of
 //      the first sort pass per tile;
 //   2. stable LSD radix sort of the keys with the token id as value, 10 bits per pass, one
@@ -29,6 +34,8 @@
 
 #include <algorithm>
 
+#include "class_table.hpp"
+#include "classes_compare.hpp"
 #include "common.hpp"
 #include "walk_device.hpp"
 
@@ -58,15 +65,6 @@ constexpr int kRankLdsWords = 8192;
 // C^2 / 2^(bits+1) such pairs), so small vocabularies sort 32 bits (4 passes) and large ones 40.
 constexpr int32_t kLargeVocabulary = 1 << 18;
 inline int hash_bits_for(int32_t V) { return V > kLargeVocabulary ? 40 : 32; }
-
-struct Counters {
-    int32_t unresolved;
-    int32_t num_classes;
-    int32_t store_state;  // of the walk store handed in: 0 usable, 1 not this call's, 2 overflowed
-    int32_t other_rows;   // links between tokens of different image rows, listed for the kernel after
-    int32_t pad[4];
-};
-constexpr int kStoreForeign = 1, kStoreOverflowed = 2;
 
 // ---------------------------------------------------------------- radix sort
 
@@ -356,145 +354,6 @@ int device_scan(const int32_t *in, int32_t *out, int n, int32_t *tile_tmp, int32
     hipLaunchKernelGGL((scan_final_kernel<MAX, INCLUSIVE>), dim3(nt), dim3(kThreads), 0, stream, in,
                        n, tile_tmp, out, grand_total);
     return check_launch();
-}
-
-// ---------------------------------------------------------------- comparing two tokens' signatures
-
-__device__ __forceinline__ uint64_t hash_part(uint64_t key) { return key >> 8; }
-
-// What the comparisons read when the walk vectors of cfgzip_signatures are at hand.
-struct StoreSource {
-    Tables T;
-    WalkStoreView store;
-    int32_t V, S;
-};
-
-// 0 if the store holds this call's vectors, else why not.
-__device__ __forceinline__ int walk_store_state(const StoreSource &s) {
-    const WalkStore hdr = *s.store.header;
-    if (hdr.magic != kWalkStoreMagic || hdr.V != s.V || hdr.S != s.S ||
-        hdr.stride != walk_store_stride(s.S))
-        return kStoreForeign;
-    return hdr.overflow ? kStoreOverflowed : 0;
-}
-
-// Image row of a token as the store has it (256: the empty token, whose signature is the
-// identity and whose vector is not kept).
-__device__ __forceinline__ uint32_t store_row(const StoreSource &s, int32_t tok) {
-    return min(walk_row_of(s.store.wrow[tok]), 256u);
-}
-
-// Two tokens with the same image row `row` < 256: idx[row] is onto, so their signatures are
-// equal iff their walk vectors are.  One thread, 16 bytes at a time (the padding behind a
-// vector is zero on both sides).
-__device__ __forceinline__ bool store_same_row_differ(const StoreSource &s, int32_t ta, int32_t tb,
-                                                      uint32_t row) {
-    const uint32_t stride = walk_store_stride(s.S);
-    const uint4 *wa = reinterpret_cast<const uint4 *>(s.store.wvec + (size_t)ta * stride);
-    const uint4 *wb = reinterpret_cast<const uint4 *>(s.store.wvec + (size_t)tb * stride);
-    const uint32_t n16 = min(walk_units_of(s.store.wrow[ta]), stride / 8u);  // the same for both: one row
-    bool diff = false;
-    constexpr int kAhead = 4;  // independent 16-byte loads in flight per side
-    for (uint32_t k0 = 0; k0 < n16; k0 += kAhead) {
-        uint4 x[kAhead], y[kAhead];
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            const uint32_t k = min(k0 + u, n16 - 1);  // repeats the last one past the end
-            x[u] = wa[k];
-            y[u] = wb[k];
-        }
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u)
-            diff |= (x[u].x != y[u].x) | (x[u].y != y[u].y) | (x[u].z != y[u].z) | (x[u].w != y[u].w);
-    }
-    return diff;
-}
-
-// Two tokens with different image rows (neighbours at the border between two first bytes inside
-// a segment, or an empty token): sig[q] = w[idx[row][q]] has to be compared for every q; the
-// empty token's signature is sig[q] = q.  One wave; both vectors are staged in the wave's LDS
-// buffers la, lb (kWalkStoreMaxStride entries each).  Returns whether any entry differs
-// (wave-uniform).  `part` of `parts`: the wave looks only at every parts-th stretch of 512 states,
-// starting with stretch `part` (several waves then share one pair; S a multiple of 8 only).
-__device__ __forceinline__ bool store_other_row_differ(const StoreSource &s, int32_t ta, int32_t tb,
-                                                       uint32_t ra, uint32_t rb, uint16_t *la,
-                                                       uint16_t *lb, int part = 0, int parts = 1) {
-    const int lane = threadIdx.x & 63;
-    const int S = s.S;
-    const uint32_t stride = walk_store_stride(S);
-    const bool ida = ra == 256u, idb = rb == 256u;
-    if (ida && idb) return false;
-    if (part * 512 >= S) return false;  // nothing of this pair falls to this wave
-    // positions in a kept vector are below the row's image size, which is at most the stride in a
-    // store that has not overflowed; the bound keeps a corrupt index inside the staged vector
-    const uint32_t na = stride, nb = stride;
-    {
-        // lanes 0..31 copy vector a, lanes 32..63 vector b, 16 bytes each (stride <= 256 entries)
-        const uint32_t half = lane & 31;
-        const bool second = lane >= 32;
-        const uint16_t *src = s.store.wvec + (size_t)(second ? tb : ta) * stride;
-        if (half * 8 < stride && !(second ? idb : ida))
-            reinterpret_cast<uint4 *>(second ? lb : la)[half] = reinterpret_cast<const uint4 *>(src)[half];
-    }
-    // the staged vectors are read below as 16-bit entries by other lanes of this wave
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const uint16_t *ia = s.T.idx + (size_t)ra * S, *ib = s.T.idx + (size_t)rb * S;
-    bool d = false;
-    auto entry_a = [&](uint32_t q, uint32_t j) -> uint32_t { return ida ? q : (j < na ? la[j] : 0xFFFFu); };
-    auto entry_b = [&](uint32_t q, uint32_t j) -> uint32_t { return idb ? q : (j < nb ? lb[j] : 0xFFFFu); };
-    if ((S % 8) == 0) {
-        // 16 bytes of each index row per lane and step (the identity row is not read)
-        const uint4 zero = make_uint4(0, 0, 0, 0);
-        constexpr int kAhead = 2;
-        for (int q0 = lane * 8 + 512 * part; q0 < S; q0 += 512 * parts * kAhead) {
-            uint4 xa[kAhead], xb[kAhead];
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const int q = q0 + 512 * parts * u;
-                xa[u] = (!ida && q < S) ? *reinterpret_cast<const uint4 *>(ia + q) : zero;
-                xb[u] = (!idb && q < S) ? *reinterpret_cast<const uint4 *>(ib + q) : zero;
-            }
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const int q = q0 + 512 * parts * u;
-                if (q >= S) continue;
-                const uint32_t ja[8] = {xa[u].x & 0xFFFFu, xa[u].x >> 16, xa[u].y & 0xFFFFu, xa[u].y >> 16,
-                                        xa[u].z & 0xFFFFu, xa[u].z >> 16, xa[u].w & 0xFFFFu, xa[u].w >> 16};
-                const uint32_t jb[8] = {xb[u].x & 0xFFFFu, xb[u].x >> 16, xb[u].y & 0xFFFFu, xb[u].y >> 16,
-                                        xb[u].z & 0xFFFFu, xb[u].z >> 16, xb[u].w & 0xFFFFu, xb[u].w >> 16};
-#pragma unroll
-                for (int e = 0; e < 8; ++e) d |= entry_a(q + e, ja[e]) != entry_b(q + e, jb[e]);
-            }
-        }
-    } else {
-        for (int q = lane; q < S; q += 64)
-            d |= entry_a(q, ida ? 0u : (uint32_t)ia[q]) != entry_b(q, idb ? 0u : (uint32_t)ib[q]);
-    }
-    const bool any = __ballot(d) != 0ull;
-    __builtin_amdgcn_wave_barrier();  // the next pair restages la, lb
-    return any;
-}
-
-// Stored signature rows of two tokens, one wave.
-__device__ __forceinline__ bool rows_differ(const uint16_t *__restrict__ sig, int S, bool vec,
-                                            int32_t ta, int32_t tb) {
-    const int lane = threadIdx.x & 63;
-    const uint16_t *a = sig + (size_t)ta * S;
-    const uint16_t *b = sig + (size_t)tb * S;
-    bool diff = false;
-    if (vec) {
-        const uint4 *a4 = reinterpret_cast<const uint4 *>(a);
-        const uint4 *b4 = reinterpret_cast<const uint4 *>(b);
-        for (int j = lane; j < S / 8; j += 64) {
-            const uint4 x = a4[j], y = b4[j];
-            diff |= (x.x != y.x) | (x.y != y.y) | (x.z != y.z) | (x.w != y.w);
-        }
-    } else {
-        for (int j = lane; j < S; j += 64) diff |= a[j] != b[j];
-    }
-    return __ballot(diff) != 0ull;
 }
 
 // ---------------------------------------------------------------- per-class minima
@@ -1285,6 +1144,15 @@ struct BuildWorkspace {
     uint64_t *rep_key;
     uint16_t *verify_w;  // walk vectors of the re-walk verification when they do not fit in LDS
     Counters *ctr;
+    // grouping by hash table, the first attempt; shares its memory with the sort's arrays, which
+    // are written only after it has been given up
+    ClassTable table;
+    uint4 *clear_begin;
+    size_t clear_n16;
+    int32_t *tok_ref, *tok_cls, *tok_min, *rep_at, *stretch_marks;
+    int2 *cross_list;
+    uint2 *word_marks;
+    Counters *table_ctr;
     size_t bytes;
 };
 
@@ -1298,6 +1166,7 @@ BuildWorkspace carve_build_ws(void *ws, int32_t V, int32_t S) {
     const size_t nt = (size_t)ceil_div(V, kTile);
     const size_t n_words = (size_t)words_for(V);
     w.sig_ws = c.take<char>(sig_workspace_bytes(0, S));
+    Carver ct = c;
     w.keys[0] = c.take<uint64_t>(n);
     w.keys[1] = c.take<uint64_t>(n);
     w.vals[0] = c.take<int32_t>(n);
@@ -1321,7 +1190,27 @@ BuildWorkspace carve_build_ws(void *ws, int32_t V, int32_t S) {
                      ? c.take<uint16_t>((size_t)kGlobalWalkGrid * walk_cap_for(S))
                      : nullptr;
     w.ctr = c.take<Counters>(1);
-    w.bytes = c.used;
+    const size_t cap = class_table_capacity(V);
+    w.table.mask = (uint32_t)cap - 1;
+    w.table.shift = 64;
+    while ((1ull << (64 - w.table.shift)) < cap) --w.table.shift;
+    const size_t clear_from = ct.used;
+    w.table.group = ct.take<unsigned long long>(cap);  // these four start as all ones
+    w.table.cls = ct.take<unsigned long long>(cap);
+    w.table.cls_rep = ct.take<unsigned long long>(cap);
+    w.table.cls_min = ct.take<uint32_t>(cap);
+    w.clear_begin = reinterpret_cast<uint4 *>(w.table.group);
+    w.clear_n16 = (ct.used - clear_from) / 16;
+    const size_t n_stretches = (size_t)ceil_div(V, kTableThreads);
+    w.tok_ref = ct.take<int32_t>(n);
+    w.tok_cls = ct.take<int32_t>(n);
+    w.tok_min = ct.take<int32_t>(n);
+    w.rep_at = ct.take<int32_t>(n);
+    w.cross_list = ct.take<int2>(n);
+    w.word_marks = ct.take<uint2>(n_stretches * (kTableThreads / 32));
+    w.stretch_marks = ct.take<int32_t>(n_stretches);
+    w.table_ctr = ct.take<Counters>(1);
+    w.bytes = std::max(c.used, V <= kTableMaxTokens ? ct.used : (size_t)0);
     return w;
 }
 
@@ -1420,11 +1309,97 @@ extern "C" int cfgzip_build_classes(const uint8_t *tok_bytes, const int64_t *tok
         ra.ctr = w.ctr;
         return CFGZIP_OK;
     };
-    // re-walking needs its own tables: enqueue them first (independent of the sort)
-    if (source == FROM_REWALK) CFGZIP_TRY(prepare_rewalk(false));
+    const int hash_bits = hash_bits_for(V);
+    static_assert(kTableMaxTokens == kLargeVocabulary, "an entry holds the 32 hash bits that the sort would take");
+
+    // First attempt: grouping by hash table.  Not where signatures have to be walked again to be
+    // compared: the sort puts tokens next to each other, so that each is walked once for its two
+    // neighbours, while against a group's member every token would be walked with a partner.
+    if (source != FROM_REWALK && V <= kTableMaxTokens) {
+        TableClearArgs ca{w.clear_begin, w.clear_n16, w.table_ctr};
+        hipLaunchKernelGGL(table_clear_kernel,
+                           dim3((unsigned)std::min<int64_t>(1024, ceil_div((int64_t)w.clear_n16, kTableThreads))),
+                           dim3(kTableThreads), 0, stream, ca);
+        CFGZIP_TRY(check_launch());
+        TableGroupArgs ga{};
+        ga.hash = hash;
+        ga.tok_off = tok_off;
+        ga.tok_bytes = tok_bytes;
+        ga.n = n;
+        ga.by_first_byte = source == FROM_STORE;
+        ga.t = w.table;
+        ga.tok_ref = w.tok_ref;
+        ga.tok_cls = w.tok_cls;
+        ga.cross_list = w.cross_list;
+        ga.ctr = w.table_ctr;
+        if (n <= kGroupSmallTokens)
+            hipLaunchKernelGGL(table_group_kernel<kGroupBitsSmall>, dim3((unsigned)ceil_div(n, 1 << kGroupBitsSmall)),
+                               dim3(1 << kGroupBitsSmall), 0, stream, ga);
+        else
+            hipLaunchKernelGGL(table_group_kernel<kGroupBitsLarge>, dim3((unsigned)ceil_div(n, 1 << kGroupBitsLarge)),
+                               dim3(1 << kGroupBitsLarge), 0, stream, ga);
+        CFGZIP_TRY(check_launch());
+        TableVerifyArgs va{};
+        va.t = w.table;
+        va.tok_ref = w.tok_ref;
+        va.tok_cls = w.tok_cls;
+        va.n = n;
+        va.mark_blocks = (int)ceil_div(n, kTableThreads);
+        va.cross_list = w.cross_list;
+        va.ctr = w.table_ctr;
+        va.store = store_src;
+        va.sig = sig;
+        va.S = S;
+        va.tok_min = w.tok_min;
+        va.rep_at = w.rep_at;
+        va.word_marks = w.word_marks;
+        va.stretch_marks = w.stretch_marks;
+        if (source == FROM_STORE) {
+            const int pair_blocks = (int)std::min<int64_t>(ceil_div(n, 8 * (kTableThreads / 64)), 2048);
+            va.cross_blocks = (int)std::min<int64_t>(ceil_div(n, 16), 512);
+            hipLaunchKernelGGL(table_verify_kernel<true>, dim3((unsigned)(va.mark_blocks + va.cross_blocks + pair_blocks)),
+                               dim3(kTableThreads), 0, stream, va);
+        } else {
+            const int pair_blocks = (int)std::min<int64_t>(ceil_div(n, 4 * (kTableThreads / 64)), 8192);
+            hipLaunchKernelGGL(table_verify_kernel<false>, dim3((unsigned)(va.mark_blocks + pair_blocks)),
+                               dim3(kTableThreads), 0, stream, va);
+        }
+        CFGZIP_TRY(check_launch());
+        TableAssignArgs aa{};
+        aa.n = n;
+        aa.n_stretches = va.mark_blocks;
+        aa.tok_min = w.tok_min;
+        aa.rep_at = w.rep_at;
+        aa.word_marks = w.word_marks;
+        aa.stretch_marks = w.stretch_marks;
+        aa.ctr = w.table_ctr;
+        aa.host_ctr = pinned;
+        aa.class_of_token = class_of_token;
+        aa.rep_of_class = rep_of_class;
+        aa.num_classes_dev = num_classes_dev;
+        hipLaunchKernelGGL(table_assign_kernel,
+                           dim3((unsigned)ceil_div(n, kTableAssignThreads * kTableAssignItems)),
+                           dim3(kTableAssignThreads), (size_t)aa.n_stretches * sizeof(uint32_t), stream, aa);
+        CFGZIP_TRY(check_launch());
+        CFGZIP_TRY(check_hip(hipStreamSynchronize(stream)));
+        const Counters found = *pinned;
+        if (found.store_state == 0 && found.unresolved == 0) {
+            if (num_classes_host) *num_classes_host = found.num_classes;
+            if (collisions_host) *collisions_host = 0;
+            return CFGZIP_OK;
+        }
+        if (found.store_state) {
+            // the workspace did not hold this call's walk vectors (or they had overflowed): the
+            // next source; an overflowed store still has this call's tables
+            source = sig ? FROM_ROWS : FROM_REWALK;
+            if (source == FROM_REWALK) CFGZIP_TRY(prepare_rewalk(found.store_state == kStoreOverflowed));
+        }
+    } else if (source == FROM_REWALK) {
+        // re-walking needs its own tables: enqueue them first (independent of the sort)
+        CFGZIP_TRY(prepare_rewalk(false));
+    }
 
     // 1. keys and the first pass's digit counts
-    const int hash_bits = hash_bits_for(V);
     const int passes = sort_passes_for(V);
     {
         KeysArgs ka{};
