@@ -2,8 +2,16 @@
 // Section 3.2.1, Algorithm 1) and the stack-adjacency relation that prunes the stack
 // backtrack (Section 3.2.2, Appendix C).
 //
-// A configuration of Algorithm 1 is (input queue, output stack, symbol consumed last).  A
-// workgroup of one wave owns one token and advances the SET of its live configurations one
+// The tables of a small grammar come out of one launch, those of a large one out of several.  The displacements
+// then take three passes, most of the time only the first of which has anything to do:
+//   1. displacement_shared.hpp: all tokens, by a walk over configuration sets that a workgroup's tokens share;
+//   2. the tokens whose sets did not fit there, one wave each, under small caps (little LDS, many waves per compute
+//      unit);
+//   3. what crosses those, again one wave each, under the caps that the interface states.
+// With more than 255 symbols the first pass only hands all tokens on.
+//
+// In the passes behind the first, a configuration of Algorithm 1 is a record (input queue, output stack, symbol
+// consumed last), and a workgroup of one wave owns one token and advances the SET of its live configurations one
 // byte at a time:
 //   - a configuration with a non-empty output stack pops the top symbol A and pushes the body
 //     of every production A -> a beta whose terminal is the byte read;
@@ -17,15 +25,15 @@
 // builder can group tokens by comparing rows.
 //
 // Everything is bounded: queue, stack, number of successors per byte and row length each have
-// a cap.  All tokens are first taken under small caps (little LDS per token, many waves per
-// compute unit); the few that cross them are queued and taken again under larger ones by a
-// second, persistent kernel.  A token that crosses those too, or whose set does not fit the row,
+// a cap.  A token that crosses the interface's caps, or whose set does not fit the row,
 // gets a row and hash of its own (its class is a singleton, which costs compression and never
 // correctness).
 
 #include <algorithm>
 
 #include "common.hpp"
+#include "displacement_common.hpp"
+#include "displacement_shared.hpp"
 
 namespace cfgzip {
 namespace {
@@ -35,15 +43,11 @@ constexpr int kMaxRowLen = 4096;
 constexpr int kMaxSymbols = 4096;
 constexpr int kMaxByteSymbols = 255;           // up to here a symbol (and "none") fits a byte
 
-// caps of the first pass over all tokens and of the second pass over those it could not finish.
-// The second pass runs in two steps: with the first pass's frontier capacity (half the LDS, twice
-// the waves per compute unit; enough for most of what the first pass hands on), then with the full
-// one for what is still left.  A token that gets through the narrower step would have got through
-// the wider one with the same result, so the two steps together are one pass under kFrontier2.
+// caps of the second pass (over what the shared walk hands on) and of the third (over what the second could not
+// finish), which are the interface's
 constexpr int kIn1 = 12, kOut1 = 12, kFrontier1 = 128;
 constexpr int kIn2 = 32, kOut2 = 32, kFrontier2 = 256;
-constexpr int kFrontier2Narrow = 128;
-// the second pass keeps the current byte's productions and the relation in LDS when they fit
+// the third pass keeps the current byte's productions and the relation in LDS when they fit
 constexpr int kStageCap = 128;      // productions of one terminal
 constexpr int kStageBodyCap = 512;  // body symbols of those productions together
 constexpr int kAdjLdsWords = 512;   // N * W(N) words: N <= 128
@@ -64,29 +68,6 @@ struct Rec {
     static constexpr int kNone = (1 << kBits) - 1;
 };
 
-constexpr int kStatusOk = 0;
-constexpr int kStatusOverflow = 1;
-constexpr int kStatusBadGrammar = 2;
-
-struct GrammarHeader {
-    int32_t invalid;      // set by the index kernel when the productions break a stated rule
-    // two lists of tokens handed on: by the first pass, and by the pass after it
-    int32_t retry_count[2];
-    int32_t retry_next[2];  // next entry of each list to be taken
-    int32_t pad[59];
-};
-
-struct Grammar {
-    const uint16_t *head;
-    const uint8_t *byte;
-    const int32_t *body_off;  // [P + 1]: the body of production i is body[body_off[i] .. body_off[i+1])
-    const uint16_t *body;
-    int P, N, W;              // W = words per bit row over the symbols
-    int body_total;           // body symbols the caller says there are (the offsets are checked against it)
-};
-
-__device__ __forceinline__ int body_len(const Grammar &g, int i) { return g.body_off[i + 1] - g.body_off[i]; }
-
 struct GrammarWorkspace {
     GrammarHeader *hdr;
     int32_t *byte_off;  // [257]: productions with terminal b are byte_off[b] .. byte_off[b+1]-1
@@ -94,6 +75,8 @@ struct GrammarWorkspace {
     uint32_t *reach[2]; // [N][W]: reachability over "right-most body symbol" edges
     uint32_t *adj;      // [N][W]: bit Y of row Z <=> (Y, Z) stack-adjacent
     int32_t *pair_first;  // [256][N]: 1 + index of the first production with (terminal, head), 0 = none
+    uint8_t *byte_like;   // [256]: the first byte with the same productions
+    unsigned long long *prod_packed;  // [P]: the production in one word
     uint4 *prod_short;    // [P]: first four body symbols (16 bits each), body length, body offset: one load per production
     int32_t *retry_list[2];  // [V] each: ids of the tokens handed on
     size_t clear_words; // words from hdr to the end that start at zero
@@ -117,6 +100,8 @@ GrammarWorkspace carve_grammar_ws(void *ws, int N, int V, int P) {
     g.pair_first = reinterpret_cast<int32_t *>(take((size_t)256 * N * 4));
     g.clear_words = off / 4;
     g.reach[1] = reinterpret_cast<uint32_t *>(take((size_t)N * W * 4));  // fully written
+    g.byte_like = reinterpret_cast<uint8_t *>(take(256));  // fully written for a valid grammar
+    g.prod_packed = reinterpret_cast<unsigned long long *>(take((size_t)P * 8));  // fully written for a valid grammar
     g.prod_short = reinterpret_cast<uint4 *>(take((size_t)P * sizeof(uint4)));  // fully written for a valid grammar
     g.retry_list[0] = reinterpret_cast<int32_t *>(take((size_t)V * 4));
     g.retry_list[1] = reinterpret_cast<int32_t *>(take((size_t)V * 4));
@@ -142,6 +127,31 @@ __device__ bool production_less(const Grammar &g, int i, int j) {
     return li < lj;
 }
 
+// Whether production i keeps the rules, as far as it and the one before it show; its body's place comes back.
+__device__ bool production_valid(const Grammar &g, int i, int &off, int &end) {
+    off = g.body_off[i];
+    end = g.body_off[i + 1];
+    bool ok = g.head[i] < g.N && off >= 0 && end >= off && end <= g.body_total;
+    if (ok && i == 0) ok = off == 0;
+    if (ok && i == g.P - 1) ok = end == g.body_total;
+    if (ok && i > 0) {  // the body before this one must be in bounds before it is compared
+        const int poff = g.body_off[i - 1];
+        ok = poff >= 0 && poff <= off;
+    }
+    if (ok)
+        for (int k = off; k < end; ++k) ok = ok && g.body[k] < g.N;
+    if (ok && i > 0) ok = production_less(g, i - 1, i);
+    return ok;
+}
+
+// A production as the displacement kernels read it.
+__device__ void write_records(const Grammar &g, const GrammarWorkspace &w, int i, int off, int len) {
+    uint32_t sym[4] = {0, 0, 0, 0};
+    for (int k = 0; k < min(len, 4); ++k) sym[k] = g.body[off + k];
+    w.prod_short[i] = make_uint4(sym[0] | (sym[1] << 16), sym[2] | (sym[3] << 16), (uint32_t)len, (uint32_t)off);
+    w.prod_packed[i] = pack_production(g, i, off, len);
+}
+
 // One thread per production and per symbol: checks the rules the other kernels rely on
 // (body offsets ascending from 0 to the stated total, symbols < N, strictly ascending order of
 // the productions), finds where each terminal's productions start, marks unary symbols and
@@ -151,18 +161,9 @@ __global__ void grammar_index_kernel(Grammar g, GrammarWorkspace w) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < g.N) atomicOr(&w.reach[0][(size_t)i * g.W + (i >> 5)], 1u << (i & 31));
     if (i >= g.P) return;
-    const int off = g.body_off[i], end = g.body_off[i + 1];
-    bool ok = g.head[i] < g.N && off >= 0 && end >= off && end <= g.body_total;
-    if (ok && i == 0) ok = off == 0;
-    if (ok && i == g.P - 1) ok = end == g.body_total;
-    if (ok && i > 0) {  // the body before this one must be in bounds before it is compared
-        const int poff = g.body_off[i - 1];
-        ok = poff >= 0 && poff <= off;
-    }
+    int off, end;
+    const bool ok = production_valid(g, i, off, end);
     const int len = end - off;
-    if (ok)
-        for (int k = 0; k < len; ++k) ok = ok && g.body[off + k] < g.N;
-    if (ok && i > 0) ok = production_less(g, i - 1, i);
     if (!ok) {
         w.hdr->invalid = 1;
         return;
@@ -174,17 +175,138 @@ __global__ void grammar_index_kernel(Grammar g, GrammarWorkspace w) {
         for (int x = b + 1; x <= 256; ++x) w.byte_off[x] = g.P;
     const int A = g.head[i];
     if (i == 0 || g.byte[i - 1] != b || g.head[i - 1] != A) w.pair_first[(size_t)b * g.N + A] = i + 1;
-    {
-        uint32_t sym[4] = {0, 0, 0, 0};
-        for (int k = 0; k < min(len, 4); ++k) sym[k] = g.body[off + k];
-        w.prod_short[i] = make_uint4(sym[0] | (sym[1] << 16), sym[2] | (sym[3] << 16), (uint32_t)len, (uint32_t)off);
-    }
+    write_records(g, w, i, off, len);
     if (len == 0) {
         atomicOr(&w.unary[A >> 5], 1u << (A & 31));
     } else {
         const int last = g.body[end - 1];
         atomicOr(&w.reach[0][(size_t)A * g.W + (last >> 5)], 1u << (last & 31));
     }
+}
+
+// Bytes with the same productions (heads and bodies) lead every set of configurations to the same set: byte_like[b]
+// is the first of them.  By one workgroup of at least 256 threads; a hash of all productions of a byte picks the
+// candidate, the productions decide.  byte_off: first production of every byte (and P), readable by everybody.
+__device__ void find_like_bytes(const Grammar &g, const GrammarWorkspace &w, const int32_t *byte_off, uint32_t *hash) {
+    const int tid = threadIdx.x;
+    if (tid < 256) hash[tid] = (uint32_t)(byte_off[tid + 1] - byte_off[tid]);
+    __syncthreads();
+    for (int i = tid; i < g.P; i += blockDim.x) {
+        uint32_t h = g.head[i] * 0x01000193u;
+        for (int k = g.body_off[i]; k < g.body_off[i + 1]; ++k) h = (h ^ (g.body[k] + 1u)) * 0x01000193u;
+        const int b = g.byte[i];
+        atomicAdd(&hash[b], (h ^ (h >> 15)) * (2u * (uint32_t)(i - byte_off[b]) + 1u));
+    }
+    __syncthreads();
+    if (tid >= 256) return;
+    int like = 256;  // the first byte with the same hash, itself at the latest
+    const uint32_t mine = hash[tid];
+#pragma unroll 8
+    for (int c = 252; c >= 0; c -= 4) {  // all of them: reads that wait for nothing
+        const uint4 h = *reinterpret_cast<const uint4 *>(hash + c);
+        like = h.w == mine ? c + 3 : like;
+        like = h.z == mine ? c + 2 : like;
+        like = h.y == mine ? c + 1 : like;
+        like = h.x == mine ? c : like;
+    }
+    if (like != tid) {
+        const int lo = byte_off[tid], n = byte_off[tid + 1] - lo, other = byte_off[like];
+        bool same = byte_off[like + 1] - other == n;
+        for (int i = 0; same && i < n; ++i) {
+            same = w.prod_packed[lo + i] == w.prod_packed[other + i];  // all there is of a short production
+            const int len = body_len(g, lo + i);
+            if (same && len > 4) {
+                same = body_len(g, other + i) == len;
+                for (int k = 0; same && k < len; ++k) same = g.body[g.body_off[lo + i] + k] == g.body[g.body_off[other + i] + k];
+            }
+        }
+        if (!same) like = tid;
+    }
+    w.byte_like[tid] = (uint8_t)like;
+}
+
+__global__ __launch_bounds__(1024) void byte_like_kernel(Grammar g, GrammarWorkspace w) {
+    __shared__ __align__(16) uint32_t hash[256];
+    if (w.hdr->invalid) return;  // the same for every thread
+    find_like_bytes(g, w, w.byte_off, hash);
+}
+
+// All tables of a small grammar in one launch, by one workgroup with the two matrices in LDS (eleven launches
+// otherwise, each a few us of waiting for the one before).
+constexpr int kSmallSymbols = 128;
+constexpr int kSmallWords = kSmallSymbols / 32;
+constexpr int kSmallProductions = 4096;
+__global__ __launch_bounds__(1024) void grammar_tables_kernel(Grammar g, GrammarWorkspace w) {
+    __shared__ uint32_t reach[2][kSmallSymbols * kSmallWords];
+    __shared__ uint32_t adj[kSmallSymbols * kSmallWords];
+    __shared__ uint32_t unary[kSmallWords];
+    __shared__ int32_t byte_off[257];
+    __shared__ __align__(16) uint32_t hash[256];
+    __shared__ int invalid;
+    const int tid = threadIdx.x, threads = blockDim.x, words = g.N * g.W;
+    for (int i = tid; i < words; i += threads) {
+        const int X = i / g.W, word = i - X * g.W;
+        reach[0][i] = (X >> 5) == word ? 1u << (X & 31) : 0u;
+        adj[i] = 0;
+    }
+    if (tid < kSmallWords) unary[tid] = 0;
+    if (tid == 0) invalid = 0;
+    for (int i = tid; i < 256 * g.N; i += threads) w.pair_first[i] = 0;
+    for (int i = tid; i < (int)(sizeof(GrammarHeader) / 4); i += threads) reinterpret_cast<int32_t *>(w.hdr)[i] = 0;
+    __syncthreads();
+    for (int i = tid; i < g.P; i += threads) {
+        int off, end;
+        if (!production_valid(g, i, off, end)) {
+            invalid = 1;
+            continue;
+        }
+        const int b = g.byte[i], A = g.head[i];
+        for (int x = i == 0 ? 0 : g.byte[i - 1] + 1; x <= b; ++x) byte_off[x] = i;
+        if (i == g.P - 1)
+            for (int x = b + 1; x <= 256; ++x) byte_off[x] = g.P;
+        if (i == 0 || g.byte[i - 1] != b || g.head[i - 1] != A) w.pair_first[(size_t)b * g.N + A] = i + 1;
+        write_records(g, w, i, off, end - off);
+        if (off == end) {
+            atomicOr(&unary[A >> 5], 1u << (A & 31));
+        } else {
+            const int last = g.body[end - 1];
+            atomicOr(&reach[0][A * g.W + (last >> 5)], 1u << (last & 31));
+        }
+    }
+    __syncthreads();
+    if (invalid) {  // the same for every thread
+        if (tid == 0) w.hdr->invalid = 1;
+        for (int i = tid; i < words; i += threads) w.adj[i] = 0;
+        return;
+    }
+    // closure by doubling: every row holds its own symbol, so ceil(log2 N) rounds reach every path
+    int cur = 0;
+    for (int span = 1; span < g.N; span <<= 1, cur ^= 1) {
+        for (int i = tid; i < words; i += threads) {
+            const int X = i / g.W, word = i - X * g.W;
+            uint32_t acc = 0;
+            for (int v = 0; v < g.W; ++v)
+                for (uint32_t bits = reach[cur][X * g.W + v]; bits; bits &= bits - 1) {
+                    const int Y = v * 32 + __ffs(bits) - 1;
+                    acc |= reach[cur][Y * g.W + word];
+                }
+            reach[cur ^ 1][i] = acc;
+        }
+        __syncthreads();
+    }
+    // Appendix C over the neighbouring pairs of every body
+    for (int i = tid; i < g.P; i += threads)
+        for (int p = g.body_off[i]; p + 1 < g.body_off[i + 1]; ++p) {
+            const int Bn = g.body[p], Z = g.body[p + 1];
+            for (int word = 0; word < g.W; ++word) {
+                const uint32_t bits = reach[cur][Bn * g.W + word] & unary[word];
+                if (bits) atomicOr(&adj[Z * g.W + word], bits);
+            }
+        }
+    if (tid < 257) w.byte_off[tid] = byte_off[tid];
+    find_like_bytes(g, w, byte_off, hash);
+    __syncthreads();
+    for (int i = tid; i < words; i += threads) w.adj[i] = adj[i];
 }
 
 // One doubling step of the transitive closure: out[X] = union of in[Y] over Y in in[X].  Every
@@ -233,6 +355,10 @@ __global__ void copy_words_kernel(const uint32_t *__restrict__ src, int32_t *__r
 }
 
 int enqueue_grammar_tables(const Grammar &g, const GrammarWorkspace &w, hipStream_t stream) {
+    if (g.N <= kSmallSymbols && g.P <= kSmallProductions) {
+        hipLaunchKernelGGL(grammar_tables_kernel, dim3(1), dim3(1024), 0, stream, g, w);
+        return check_launch();
+    }
     hipLaunchKernelGGL(clear_words_kernel, dim3((unsigned)std::min<int64_t>(1024, ceil_div((int64_t)w.clear_words, 256))),
                        dim3(256), 0, stream, reinterpret_cast<uint32_t *>(w.hdr), w.clear_words);
     CFGZIP_TRY(check_launch());
@@ -248,45 +374,14 @@ int enqueue_grammar_tables(const Grammar &g, const GrammarWorkspace &w, hipStrea
         CFGZIP_TRY(check_launch());
     }
     const int64_t items = (int64_t)g.P * g.W;
+    hipLaunchKernelGGL(byte_like_kernel, dim3(1), dim3(1024), 0, stream, g, w);
+    CFGZIP_TRY(check_launch());
     hipLaunchKernelGGL(adjacency_kernel, dim3((unsigned)ceil_div(items, 256)), dim3(256), 0, stream,
                        g, w, w.reach[cur]);
     return check_launch();
 }
 
 // ---- per-token displacement --------------------------------------------------------------
-
-struct DisplacementArgs {
-    Grammar g;
-    GrammarHeader *hdr;
-    const int32_t *byte_off;
-    const int32_t *pair_first;
-    const uint4 *prod_short;
-    const uint32_t *adj;
-    const uint8_t *tok_bytes;
-    const int64_t *tok_off;
-    uint16_t *rows;
-    uint64_t *hash;
-    int32_t *status;
-    int32_t *retry_list[2];
-    uint64_t seed;
-    int V, row_len;
-};
-
-// 64-bit mix of a record's entries ni, no, queue, stack (FNV-1a style pass, SplitMix64 finaliser)
-struct RecordMix {
-    uint64_t h;
-    __device__ explicit RecordMix(uint64_t seed) : h(seed ^ 0x9E3779B97F4A7C15ull) {}
-    __device__ void add(uint32_t x) { h = (h ^ x) * 0x100000001B3ull; }
-    __device__ uint64_t done() const {
-        uint64_t z = h;
-        z ^= z >> 30;
-        z *= 0xBF58476D1CE4E5B9ull;
-        z ^= z >> 27;
-        z *= 0x94D049BB133111EBull;
-        z ^= z >> 31;
-        return z;
-    }
-};
 
 template <typename R>
 __device__ inline bool records_equal(const uint32_t *a, const uint32_t *b) {
@@ -549,11 +644,7 @@ __device__ void token_displacement(const DisplacementArgs &a, int t,
 
     if (overflow) {
         if (lane == 0) {
-            RecordMix mix(a.seed);
-            mix.add(0xFFFFu);
-            mix.add((uint32_t)t & 0xFFFFu);
-            mix.add((uint32_t)t >> 16);
-            a.hash[t] = mix.done();
+            a.hash[t] = overflow_hash(a.seed, t);
             if (a.status) a.status[t] = kStatusOverflow;
             if (HAND_ON >= 0 && caps_crossed)
                 a.retry_list[HAND_ON < 0 ? 0 : HAND_ON][atomicAdd(&a.hdr->retry_count[HAND_ON < 0 ? 0 : HAND_ON], 1)] = t;
@@ -620,31 +711,14 @@ __device__ void token_displacement(const DisplacementArgs &a, int t,
     __syncthreads();  // the next token of a persistent workgroup starts from settled LDS
 }
 
-// first pass: a workgroup of one wave per token
-template <typename Sym>
-__global__ __launch_bounds__(64) void displacement_kernel(DisplacementArgs a) {
-    __shared__ TokenLds<Sym, Rec<Sym, kIn1, kOut1>, kFrontier1, false> lds;
-    const int t = blockIdx.x;
-    if (a.hdr->invalid) {  // the same value for every lane
-        for (int base = 0; base < a.row_len; base += kRowChunk)
-            reinterpret_cast<uint2 *>(a.rows + (size_t)t * a.row_len + base)[threadIdx.x] = make_uint2(0, 0);
-        if (threadIdx.x == 0) {
-            a.hash[t] = 0;
-            if (a.status) a.status[t] = kStatusBadGrammar;
-        }
-        return;
-    }
-    token_displacement<Sym, kIn1, kOut1, kFrontier1, 0, false>(a, t, lds, false);
-}
-
-// second pass: persistent workgroups of one wave take retry list LIST entry by entry; what they
-// cannot finish goes to list HAND_ON (none if negative)
-template <typename Sym, int FRONTIER, int LIST, int HAND_ON>
+// The passes behind the shared walk: persistent workgroups of one wave take retry list LIST entry by entry; what
+// they cannot finish goes to list HAND_ON (none if negative)
+template <typename Sym, int MAX_IN, int MAX_OUT, int FRONTIER, int LIST, int HAND_ON, bool STAGE>
 __global__ __launch_bounds__(64) void displacement_retry_kernel(DisplacementArgs a) {
-    __shared__ TokenLds<Sym, Rec<Sym, kIn2, kOut2>, FRONTIER, true> lds;
+    __shared__ TokenLds<Sym, Rec<Sym, MAX_IN, MAX_OUT>, FRONTIER, STAGE> lds;
     const int count = min(a.hdr->retry_count[LIST], a.V);
     if (count == 0) return;
-    const bool adj_in_lds = a.g.N * a.g.W <= kAdjLdsWords;
+    const bool adj_in_lds = STAGE && a.g.N * a.g.W <= kAdjLdsWords;
     if (adj_in_lds)
         for (int i = threadIdx.x; i < a.g.N * a.g.W; i += 64) lds.adj[i] = a.adj[i];
     for (;;) {
@@ -653,26 +727,54 @@ __global__ __launch_bounds__(64) void displacement_retry_kernel(DisplacementArgs
         const int i = lds.next_item;
         __syncthreads();
         if (i >= count) break;  // the same for every lane
-        token_displacement<Sym, kIn2, kOut2, FRONTIER, HAND_ON, true>(a, a.retry_list[LIST][i], lds, adj_in_lds);
+        token_displacement<Sym, MAX_IN, MAX_OUT, FRONTIER, HAND_ON, STAGE>(a, a.retry_list[LIST][i], lds, adj_in_lds);
     }
+}
+
+template <typename Sym, int MAX_IN, int MAX_OUT, int FRONTIER, int LIST, int HAND_ON, bool STAGE>
+int launch_retry(const DisplacementArgs &a, int n_cu, hipStream_t stream) {
+    // as many one-wave workgroups as the LDS of all compute units holds at once
+    const size_t lds = sizeof(TokenLds<Sym, Rec<Sym, MAX_IN, MAX_OUT>, FRONTIER, STAGE>);
+    const int64_t per_cu = std::min<int64_t>(32, (160 * 1024) / lds);
+    hipLaunchKernelGGL((displacement_retry_kernel<Sym, MAX_IN, MAX_OUT, FRONTIER, LIST, HAND_ON, STAGE>),
+                       dim3((unsigned)std::min<int64_t>(a.V, n_cu * std::max<int64_t>(1, per_cu))), dim3(64), 0, stream, a);
+    return check_launch();
+}
+
+// Every token onto the first list; with a grammar that breaks the rules, every token's outputs instead.
+__global__ void hand_all_kernel(DisplacementArgs a) {
+    const int step = gridDim.x * blockDim.x, first = blockIdx.x * blockDim.x + threadIdx.x;
+    if (!a.hdr->invalid) {
+        for (int t = first; t < a.V; t += step) a.retry_list[0][t] = t;
+        if (first == 0) a.hdr->retry_count[0] = a.V;
+        return;
+    }
+    for (int t = first; t < a.V; t += step) {
+        a.hash[t] = 0;
+        if (a.status) a.status[t] = kStatusBadGrammar;
+    }
+    const size_t units = (size_t)a.V * a.row_len / 4;
+    for (size_t u = first; u < units; u += step) reinterpret_cast<uint2 *>(a.rows)[u] = make_uint2(0, 0);
 }
 
 template <typename Sym>
 int launch_displacements(const DisplacementArgs &a, int n_cu, hipStream_t stream) {
-    hipLaunchKernelGGL(displacement_kernel<Sym>, dim3((unsigned)a.V), dim3(64), 0, stream, a);
+    if (a.g.N <= kShMaxSymbols) {
+        // a workgroup of sixteen waves per compute unit, the tokens spread evenly
+        const int64_t groups = std::min<int64_t>(n_cu, ceil_div(a.V, kShWaves));
+        const int per_group = (int)ceil_div(a.V, groups);
+        const int round = (int)std::min<int64_t>(kShRound, ceil_div(per_group, kShWaves));
+        const unsigned grid = (unsigned)ceil_div(a.V, per_group);
+        if (aligned_to(a.rows, 16))
+            hipLaunchKernelGGL(displacement_shared_kernel<true>, dim3(grid), dim3(kShThreads), 0, stream, a, per_group, round);
+        else
+            hipLaunchKernelGGL(displacement_shared_kernel<false>, dim3(grid), dim3(kShThreads), 0, stream, a, per_group, round);
+    } else {  // more symbols than a shared cell holds: every token is taken alone
+        hipLaunchKernelGGL(hand_all_kernel, dim3((unsigned)std::min<int64_t>(1024, ceil_div(a.V, 256))), dim3(256), 0, stream, a);
+    }
     CFGZIP_TRY(check_launch());
-    // as many one-wave workgroups as the LDS of all compute units holds at once
-    auto grid_for_lds = [&](size_t lds) {
-        return (unsigned)std::min<int64_t>(a.V, (int64_t)n_cu * std::max<size_t>(1, (160 * 1024) / lds));
-    };
-    hipLaunchKernelGGL((displacement_retry_kernel<Sym, kFrontier2Narrow, 0, 1>),
-                       dim3(grid_for_lds(sizeof(TokenLds<Sym, Rec<Sym, kIn2, kOut2>, kFrontier2Narrow, true>))),
-                       dim3(64), 0, stream, a);
-    CFGZIP_TRY(check_launch());
-    hipLaunchKernelGGL((displacement_retry_kernel<Sym, kFrontier2, 1, -1>),
-                       dim3(grid_for_lds(sizeof(TokenLds<Sym, Rec<Sym, kIn2, kOut2>, kFrontier2, true>))),
-                       dim3(64), 0, stream, a);
-    return check_launch();
+    CFGZIP_TRY((launch_retry<Sym, kIn1, kOut1, kFrontier1, 0, 1, false>(a, n_cu, stream)));
+    return launch_retry<Sym, kIn2, kOut2, kFrontier2, 1, -1, true>(a, n_cu, stream);
 }
 
 int check_grammar_args(const uint16_t *prod_head, const uint8_t *prod_byte, const int32_t *prod_body_off,
@@ -744,6 +846,8 @@ extern "C" int cfgzip_displacements(const uint8_t *tok_bytes, const int64_t *tok
     a.byte_off = w.byte_off;
     a.pair_first = w.pair_first;
     a.prod_short = w.prod_short;
+    a.byte_like = w.byte_like;
+    a.prod_packed = w.prod_packed;
     a.adj = w.adj;
     a.tok_bytes = tok_bytes;
     a.tok_off = tok_off;

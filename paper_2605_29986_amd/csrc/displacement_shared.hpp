@@ -1,0 +1,689 @@
+// Displacement sets by a walk over shared configuration sets: the first pass of cfgzip_displacements (paper
+// Section 3.2.1, Algorithm 1).
+//
+// After p bytes of a token Algorithm 1 holds a SET of configurations (input queue, output stack, symbol consumed
+// last), and the set after the next byte depends on nothing but that set and the byte.  Tokens of a vocabulary
+// meet few different sets (the 128,256 tokens of the measured vocabulary 230 over the JSON grammar), so a
+// workgroup keeps the sets it has met in LDS, numbers them, and remembers which set follows which on which byte.
+// A lane then walks its token like a word over a deterministic automaton, one look-up a byte; only where a
+// successor is not known yet do the 64 lanes of the wave work it out together, a lane per configuration, and add
+// it to what all sixteen waves of the workgroup share.
+//
+// Queues and stacks are lists of shared cells: a cell is one 32-bit word (the rest of the list, a symbol, the
+// length), its number is its slot in a hash table keyed by that very word, and equal lists have equal numbers.  A
+// configuration is therefore one 32-bit word, a set some of them, and comparing two sets comparing words.  Nothing waits for anything: an entry is published by one compare-and-swap after what it refers to has
+// been written, and two waves that work out the same thing at the same time agree on the first entry.
+//
+// What a token's set is written as (the canonical row and its hash) is worked out once per set too; writing a row
+// is then a copy out of LDS, and writing the rows is what bounds the kernel on a large vocabulary.
+//
+// Measured: 128,256 tokens over the JSON grammar with rows of 1,024 entries 184 us (a wave per token took 510 us for
+// most tokens and 276 us for long digit runs), 32,000 over the statement grammar with rows of 256 101 us (210 us).
+// What bounds it: the longest chain of new sets in a workgroup (a digit run of 25 bytes makes a new set at every
+// byte), each link of which is some thirty dependent LDS accesses, and writing the rows (262 MB, 45 us).
+//
+// Everything in LDS is bounded.  A token that would need more (more than 128 successors at a byte, more cells,
+// sets or row entries than there is room for) goes to the list of the passes behind this one, which take it alone.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "displacement_common.hpp"
+
+namespace cfgzip {
+namespace {
+
+constexpr int kShThreads = 1024;
+constexpr int kShWaves = kShThreads / 64;
+constexpr int kShCells = 2048;      // list cells (8 KB)
+constexpr int kShNext = 2048;       // known successors (8 KB)
+constexpr int kShSets = 1024;       // sets (8 KB, and 16 KB for what they are written as)
+constexpr int kShPool = 6144;       // configurations of all sets (24 KB)
+constexpr int kShOut = 18432;       // row entries of all sets written so far (36 KB)
+constexpr int kShProds = 1024;      // productions kept in LDS (8 KB); of a larger grammar none are
+constexpr int kShAdj = 512;         // words of the relation kept in LDS (2 KB); of a larger one none are
+constexpr int kShRound = 8;         // tokens a wave takes at a time: few, so that few wait for a long one
+constexpr int kShBytes = 256;       // token bytes of a wave's round kept in LDS; a round with more reads memory
+constexpr int kShSeen = 256;        // slots of a wave's table of the successors found so far: at most half full
+constexpr int kShProbes = 48;       // slots looked at before a table counts as full
+constexpr int kShFrontier = 128;    // successors of a set at one byte: two a lane
+constexpr int kShMaxList = 32;      // symbols of a queue or stack (the interface's bound)
+constexpr int kShMaxSymbols = 255;  // symbols, and "none", fit a byte
+
+typedef unsigned long long u64;
+
+// a configuration: queue and stack as cell numbers (slot + 1, 0 = empty; 12 bits each), the symbol consumed last
+constexpr int kCellIdBits = 12;
+constexpr uint32_t kCellIdMask = (1u << kCellIdBits) - 1;
+constexpr uint32_t kNoSymbol = 0xFF;
+__device__ __forceinline__ uint32_t sh_config(uint32_t queue, uint32_t stack, uint32_t last) {
+    return queue | (stack << kCellIdBits) | (last << (2 * kCellIdBits));
+}
+__device__ __forceinline__ uint32_t sh_queue(uint32_t c) { return c & kCellIdMask; }
+__device__ __forceinline__ uint32_t sh_stack(uint32_t c) { return (c >> kCellIdBits) & kCellIdMask; }
+__device__ __forceinline__ uint32_t sh_last(uint32_t c) { return c >> (2 * kCellIdBits); }
+
+// a cell: the number of the rest (12 bits), the symbol (8), the length of the list (6); never 0
+__device__ __forceinline__ uint32_t cell_rest(uint32_t w) { return w & kCellIdMask; }
+__device__ __forceinline__ uint32_t cell_symbol(uint32_t w) { return (w >> kCellIdBits) & 0xFFu; }
+__device__ __forceinline__ uint32_t cell_length(uint32_t w) { return w >> (kCellIdBits + 8); }
+
+// a set: 24 hash bits, the position of its configurations in the pool (16 bits), how many (8)
+constexpr u64 kShEmpty = ~0ull;
+__device__ __forceinline__ uint32_t set_at(u64 w) { return (uint32_t)(w >> 8) & 0xFFFFu; }
+__device__ __forceinline__ uint32_t set_size(u64 w) { return (uint32_t)w & 0xFFu; }
+
+// a known successor: set (10 bits) and byte (8) above the following set (14 bits) or one of these
+constexpr uint32_t kNextBits = 14;
+constexpr uint32_t kGiveUp = 0x3FFE;    // more room needed than there is: the token goes to the next pass
+constexpr uint32_t kCrossed = 0x3FFD;   // a bound of the interface is broken: the token overflows
+constexpr uint32_t kWorkedOut = 0x3FFC; // another wave is at it
+constexpr uint32_t kNextEmpty = ~0u;
+
+// what a set is written as: position of its row entries (in units of four), their number, or one of these
+constexpr u64 kRowUnknown = ~0ull;
+constexpr u64 kRowGiveUp = ~0ull - 1;
+constexpr u64 kRowTooLong = ~0ull - 2;
+constexpr u64 kRowWorkedOut = ~0ull - 3;  // another wave is at it
+
+struct SharedLds {
+    __align__(16) uint16_t out[kShOut];
+    uint32_t pool[kShPool];
+    u64 sets[kShSets];
+    u64 row[kShSets];
+    u64 row_hash[kShSets];
+    uint32_t work[kShWaves][2 * kShFrontier];
+    uint32_t seen[kShWaves][kShSeen];
+    uint32_t cells[kShCells];
+    uint32_t next[kShNext];
+    u64 prods[kShProds];
+    uint32_t adj[kShAdj];
+    uint32_t byte_off[257];
+    uint32_t pool_top, out_top, cursor;
+    uint8_t byte_like[256];  // the first byte with the same productions
+    uint8_t bytes[kShWaves][kShBytes];  // already as byte_like has them
+};
+
+template <typename T>
+__device__ __forceinline__ T lds_look(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// what this wave has written to LDS comes before what it publishes next, and what it reads after a look at
+// something published is what was written before that (LDS operations of a wave are done in order)
+__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup"); }
+
+__device__ __forceinline__ uint32_t wave_read(uint32_t v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+__device__ __forceinline__ u64 wave_read64(u64 v, int lane) {
+    return ((u64)wave_read((uint32_t)(v >> 32), lane) << 32) | wave_read((uint32_t)v, lane);
+}
+__device__ __forceinline__ u64 wave_sum64(u64 v) {
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+// Sum over the 64 lanes (all of them active), the same for every lane: row shifts by 1, 2, 4, 8, then across rows.
+__device__ __forceinline__ uint32_t wave_sum32(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, true);
+    return wave_read(v, 63);
+}
+
+// The number of the list of `length` symbols that is `symbol` in front of `rest`; 0 if the table is full (`full` is
+// set).
+__device__ __forceinline__ uint32_t sh_cons(SharedLds &L, uint32_t rest, uint32_t symbol, uint32_t length, bool &full) {
+    const uint32_t w = rest | (symbol << kCellIdBits) | (length << (kCellIdBits + 8));
+    uint32_t at = (w * 0x9E3779B1u) >> (32 - 11);
+    static_assert(kShCells == 1 << 11, "eleven bits of hash; a number (slot + 1) fits twelve");
+    for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShCells - 1)) {
+        uint32_t seen = lds_look(&L.cells[at]);
+        if (seen == 0u) seen = atomicCAS(&L.cells[at], 0u, w);
+        if (seen == 0u || seen == w) return at + 1;
+    }
+    full = true;
+    return 0;
+}
+
+__device__ __forceinline__ uint32_t list_length(const SharedLds &L, uint32_t id) {
+    return id ? cell_length(lds_look(&L.cells[id - 1])) : 0u;
+}
+
+__device__ __forceinline__ uint32_t next_slot(uint32_t key) { return (key * 0x9E3779B1u) >> (32 - 11); }
+static_assert(kShNext == 1 << 11, "eleven bits of hash");
+
+// The set that follows `set` on byte `like`, if known: its number, kGiveUp or kCrossed; kNextEmpty if not.
+__device__ __forceinline__ uint32_t sh_known(const SharedLds &L, uint32_t set, uint32_t like) {
+    const uint32_t key = (set << 8) | like;
+    uint32_t at = next_slot(key);
+    for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShNext - 1)) {
+        const uint32_t w = lds_look(&L.next[at]);
+        if (w == kNextEmpty) return kNextEmpty;
+        if ((w >> kNextBits) == key) return w & ((1u << kNextBits) - 1);
+    }
+    return kNextEmpty;
+}
+
+// Takes on working out what follows `set` on `like`: the slot to publish it in, -1 if another wave was faster, -2
+// if the table is full (the successor is then worked out again by everybody who comes here).
+__device__ __forceinline__ int sh_claim(SharedLds &L, uint32_t set, uint32_t like) {
+    const uint32_t key = (set << 8) | like;
+    uint32_t at = next_slot(key);
+    for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShNext - 1)) {
+        uint32_t seen = lds_look(&L.next[at]);
+        if (seen == kNextEmpty) seen = atomicCAS(&L.next[at], kNextEmpty, (key << kNextBits) | kWorkedOut);
+        if (seen == kNextEmpty) return (int)at;
+        if ((seen >> kNextBits) == key) return -1;
+    }
+    return -2;
+}
+
+// Different words of a wave, two a lane at the most: which of them are the first of their value, where they go when
+// packed, how many there are, and a hash that does not depend on their order.
+struct Different {
+    uint32_t word[2];
+    bool first[2];
+    int at[2];
+    int n;
+    uint32_t sum;
+};
+constexpr uint32_t kNoWord = ~0u;  // no configuration: cell numbers are below 2^12 - 1
+
+__device__ __forceinline__ uint32_t seen_slot(uint32_t word) { return (word * 0x9E3779B1u) >> 24; }
+static_assert(kShSeen == 256, "eight bits of hash");
+
+// `seen` starts empty (all kNoWord) and holds the words afterwards; seen_clear empties it.  One pass of
+// compare-and-swaps instead of a sort: comparing 45 words with each other one readlane after the other took as long as
+// all the rest of a step.
+__device__ __forceinline__ Different find_different(uint32_t *seen, uint32_t a, uint32_t b, int lane) {
+    Different d;
+    d.word[0] = a;
+    d.word[1] = b;
+    uint32_t h = 0;
+    d.n = 0;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const uint32_t w = d.word[u];
+        d.first[u] = false;
+        if (w != kNoWord) {
+            uint32_t at = seen_slot(w);
+            for (int probe = 0; probe < kShSeen; ++probe, at = (at + 1) & (kShSeen - 1)) {
+                const uint32_t old = atomicCAS(&seen[at], kNoWord, w);
+                d.first[u] = old == kNoWord;
+                if (old == kNoWord || old == w) break;
+            }
+            if (d.first[u]) h += (w * 0x85EBCA6Bu) ^ (w >> 13) ^ ((w >> 7) * 0x9E3779B1u);
+        }
+        const u64 mask = __ballot(d.first[u]);
+        d.at[u] = d.n + (int)__popcll(mask & ((1ull << lane) - 1ull));
+        d.n += (int)__popcll(mask);
+    }
+    d.sum = wave_sum32(h);
+    return d;
+}
+__device__ __forceinline__ bool seen_has(const uint32_t *seen, uint32_t word) {
+    uint32_t at = seen_slot(word);
+    for (int probe = 0; probe < kShSeen; ++probe, at = (at + 1) & (kShSeen - 1)) {
+        const uint32_t x = seen[at];
+        if (x == word) return true;
+        if (x == kNoWord) return false;
+    }
+    return false;
+}
+__device__ __forceinline__ void seen_clear(uint32_t *seen, int lane) {
+#pragma unroll
+    for (int u = 0; u < kShSeen / 64; ++u) seen[lane + 64 * u] = kNoWord;
+    lds_order();
+}
+
+// The number of the set of the words `d` (which `seen` holds); kGiveUp if there is no room.  Two sets of equal size
+// are equal if each word of one is in the other.
+__device__ __forceinline__ uint32_t sh_set_number(SharedLds &L, const uint32_t *seen, const Different &d, int lane) {
+    const uint32_t h = (d.sum ^ (d.sum >> 15)) * 0x2C1B3C6Du + (uint32_t)d.n;
+    const u64 tag = (u64)(h >> 8) << 24;
+    uint32_t at = h & (kShSets - 1);
+    int reserved = -1;
+    for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShSets - 1)) {
+        u64 found = lds_look(&L.sets[at]);
+        if (found == kShEmpty) {
+            if (reserved < 0) {
+                int top = 0;
+                if (lane == 0) top = (int)atomicAdd(&L.pool_top, (uint32_t)d.n);
+                reserved = __builtin_amdgcn_readfirstlane(top);
+                if (reserved + d.n > kShPool) return kGiveUp;
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    if (d.first[u]) L.pool[reserved + d.at[u]] = d.word[u];
+                lds_order();
+            }
+            const u64 w = tag | ((u64)reserved << 8) | (u64)d.n;
+            if (lane == 0) found = atomicCAS(&L.sets[at], kShEmpty, w);
+            found = wave_read64(found, 0);
+            if (found == kShEmpty) return at;
+        }
+        if ((found >> 24 << 24) == tag && (int)set_size(found) == d.n) {
+            lds_order();
+            const uint32_t *other = L.pool + set_at(found);
+            bool same = true;
+            for (int i = lane; i < d.n; i += 64) same = same && seen_has(seen, other[i]);
+            if (__ballot(!same) == 0ull) return at;
+        }
+    }
+    return kGiveUp;
+}
+
+// One byte of Algorithm 1 on a whole set, by the whole wave: the number of the set that follows.  First the pairs
+// (configuration, production that applies) are listed, then all of them are carried out together, a lane each: the
+// chain of LDS accesses is what this costs, and it is gone through once.
+__device__ __forceinline__ uint32_t sh_step(const DisplacementArgs &a, SharedLds &L, uint32_t *work, uint32_t *seen,
+                                            uint32_t set, int ch, int lane) {
+    const Grammar &g = a.g;
+    const u64 w = lds_look(&L.sets[set]);
+    lds_order();
+    const int n = (int)set_size(w);
+    const uint32_t *configs = L.pool + set_at(w);
+    const int lo = (int)L.byte_off[ch], hi = (int)L.byte_off[ch + 1], per = hi - lo;
+    const bool prods_here = g.P <= kShProds, adj_here = g.N * g.W <= kShAdj;
+    auto prod = [&](int i) -> u64 { return prods_here ? L.prods[i] : a.prod_packed[i]; };
+    const u64 below = (1ull << lane) - 1ull;
+    uint32_t *pairs = work, *out = work + kShFrontier;  // a pair: configuration (7 bits), production above
+    int m = 0, empties = 0;
+    auto list = [&](bool on, int c, int i) {
+        const u64 mask = __ballot(on);
+        const int slot = m + (int)__popcll(mask & below);
+        if (on && slot < kShFrontier) pairs[slot] = (uint32_t)c | ((uint32_t)i << 7);
+        m += (int)__popcll(mask);
+    };
+
+    // pops: the productions of (byte, top of the stack), which lie behind each other
+    for (int c0 = 0; c0 < n; c0 += 64) {
+        const int c = c0 + lane;
+        const uint32_t config = c < n ? configs[c] : 0u, stack = sh_stack(config);
+        uint32_t top = 0;
+        int i = hi;
+        if (stack) {
+            top = cell_symbol(lds_look(&L.cells[stack - 1]));
+            i = lo;
+            for (int count = per; count > 0;) {  // the first whose head is not below `top`
+                const int half = count >> 1;
+                const bool right = packed_head(prod(i + half)) < top;
+                i = right ? i + half + 1 : i;
+                count = right ? count - half - 1 : half;
+            }
+        }
+        for (;;) {
+            const bool on = i < hi && packed_head(prod(i)) == top;
+            if (!__ballot(on)) break;
+            list(on, c, i);
+            i = on ? i + 1 : hi;
+        }
+        const bool empty = c < n && !stack;
+        const u64 mask = __ballot(empty);
+        if (empty) out[empties + __popcll(mask & below)] = (uint32_t)c;
+        empties += (int)__popcll(mask);
+    }
+    lds_order();
+    // stack backtracks: every production of the byte whose head may come right after the symbol consumed last, for
+    // every configuration with an empty stack
+    // (four looks at a time, none of which waits for another)
+    constexpr int kAhead = 4;
+    const float inverse = 1.0f / (float)per;
+    for (int x0 = 0; x0 < empties * per && m <= kShFrontier; x0 += 64 * kAhead) {
+        bool on[kAhead];
+        int c[kAhead], i[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int x = x0 + 64 * u + lane;
+            on[u] = x < empties * per;
+            int e = min((int)(((float)x + 0.5f) * inverse), empties - 1);  // x / per, up to rounding where x is large
+            e = e * per > x ? e - 1 : ((e + 1) * per <= x ? e + 1 : e);
+            c[u] = on[u] ? (int)out[e] : 0;
+            i[u] = on[u] ? lo + (x - e * per) : lo;
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (on[u]) {
+                const uint32_t last = sh_last(configs[c[u]]);
+                if (last != kNoSymbol) {
+                    const uint32_t word = packed_head(prod(i[u])) * (uint32_t)g.W + (last >> 5);
+                    on[u] = ((adj_here ? L.adj[word] : a.adj[word]) >> (last & 31)) & 1u;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) list(on[u], c[u], i[u]);
+    }
+    // (the passes behind this one also find whether a bound is broken)
+    if (m > kShFrontier) return kGiveUp;
+    lds_order();
+    bool full = false, crossed = false;
+    auto carry_out = [&](int x) -> uint32_t {
+        if (x >= m) return kNoWord;
+        const uint32_t config = configs[pairs[x] & 0x7Fu];
+        const int i = (int)(pairs[x] >> 7);
+        const u64 p = prod(i);
+        const uint32_t head = packed_head(p), stack = sh_stack(config);
+        uint32_t queue = sh_queue(config), rest = 0, rest_length = 0;
+        const uint32_t cell = stack ? lds_look(&L.cells[stack - 1]) : (queue ? lds_look(&L.cells[queue - 1]) : 0u);
+        int length = (int)packed_length(p);
+        const bool is_long = length == (int)kLongBody;
+        if (is_long) length = body_len(g, i);
+        if (stack) {
+            rest = cell_rest(cell);
+            rest_length = cell_length(cell) - 1u;
+        } else {
+            const uint32_t queued = cell_length(cell) + 1u;
+            if (queued > (uint32_t)kShMaxList) crossed = true;
+            else queue = sh_cons(L, queue, head, queued, full);
+        }
+        if (rest_length + (uint32_t)length > (uint32_t)kShMaxList) {
+            crossed = true;
+        } else {
+            const int off = is_long ? g.body_off[i] : 0;
+            for (int k = length - 1; k >= 0; --k) {
+                const uint32_t s = is_long ? (uint32_t)g.body[off + k] & 0xFFu : packed_symbol(p, k);
+                rest = sh_cons(L, rest, s, ++rest_length, full);
+            }
+        }
+        return sh_config(queue, rest, head);
+    };
+    const uint32_t first = carry_out(lane);
+    uint32_t second = kNoWord;
+    if (m > 64) second = carry_out(lane + 64);
+    if (__ballot(crossed)) return kCrossed;
+    if (__ballot(full)) return kGiveUp;
+    const Different d = find_different(seen, first, second, lane);
+    const uint32_t number = sh_set_number(L, seen, d, lane);
+    seen_clear(seen, lane);
+    return number;
+}
+
+// Which of two different lists of one length comes first: queues (a cell holds the LAST symbol) ...
+__device__ __forceinline__ bool queue_less(const SharedLds &L, uint32_t x, uint32_t y) {
+    bool less = false;
+    while (x != y) {  // the difference closest to the front decides
+        const uint32_t a = lds_look(&L.cells[x - 1]), b = lds_look(&L.cells[y - 1]);
+        if (cell_symbol(a) != cell_symbol(b)) less = cell_symbol(a) < cell_symbol(b);
+        x = cell_rest(a);
+        y = cell_rest(b);
+    }
+    return less;
+}
+// ... and stacks (a cell holds the FIRST symbol)
+__device__ __forceinline__ bool stack_less(const SharedLds &L, uint32_t x, uint32_t y) {
+    while (x != y) {
+        const uint32_t a = lds_look(&L.cells[x - 1]), b = lds_look(&L.cells[y - 1]);
+        if (cell_symbol(a) != cell_symbol(b)) return cell_symbol(a) < cell_symbol(b);
+        x = cell_rest(a);
+        y = cell_rest(b);
+    }
+    return false;
+}
+
+// What the set is written as: the row's entries and the hash, by the whole wave.
+__device__ __forceinline__ u64 sh_write_set(const DisplacementArgs &a, SharedLds &L, uint32_t *work, uint32_t *seen,
+                                            uint32_t set, int lane) {
+    const u64 w = lds_look(&L.sets[set]);
+    lds_order();
+    int n = (int)set_size(w);
+    // the displacement forgets the symbol consumed last
+    constexpr uint32_t kPair = (1u << (2 * kCellIdBits)) - 1;
+    const uint32_t *configs = L.pool + set_at(w);
+    {
+        const Different d = find_different(seen, lane < n ? configs[lane] & kPair : kNoWord,
+                                           lane + 64 < n ? configs[lane + 64] & kPair : kNoWord, lane);
+        n = d.n;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (d.first[u]) work[d.at[u]] = d.word[u];
+        seen_clear(seen, lane);
+    }
+    // canonical order by counting: a record starts behind all smaller ones
+    uint32_t mine[2], order[2], start[2] = {1, 1}, total = 1;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        mine[u] = lane + 64 * u < n ? work[lane + 64 * u] : 0u;
+        order[u] = (list_length(L, sh_queue(mine[u])) << 8) | list_length(L, sh_stack(mine[u]));
+    }
+    for (int j = 0; j < n; ++j) {
+        const uint32_t c = j < 64 ? wave_read(mine[0], j) : wave_read(mine[1], j - 64);
+        const uint32_t other = j < 64 ? wave_read(order[0], j) : wave_read(order[1], j - 64);
+        const uint32_t entries = 2 + (other >> 8) + (other & 0xFFu);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (64 * u >= n) break;  // the same for every lane
+            bool before = other < order[u];
+            if (other == order[u] && c != mine[u] && lane + 64 * u < n)
+                before = sh_queue(c) != sh_queue(mine[u]) ? queue_less(L, sh_queue(c), sh_queue(mine[u]))
+                                                          : stack_less(L, sh_stack(c), sh_stack(mine[u]));
+            start[u] += before ? entries : 0u;
+        }
+        total += entries;
+    }
+    u64 result;
+    if (total > (uint32_t)a.row_len) {
+        result = kRowTooLong;
+    } else {
+        const uint32_t room = (total + 7u) & ~7u;  // whole 16-byte units, zeros behind the entries
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&L.out_top, room);
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (at + room > (uint32_t)kShOut) {
+            result = kRowGiveUp;
+        } else {
+            if (lane == 0) L.out[at] = (uint16_t)n;
+            if (lane < 8 && total + lane < room) L.out[at + total + lane] = 0;
+            u64 h = 0;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (lane + 64 * u >= n) continue;
+                const uint32_t ni = order[u] >> 8, no = order[u] & 0xFFu;
+                uint16_t *rec = L.out + at + start[u];
+                rec[0] = (uint16_t)ni;
+                rec[1] = (uint16_t)no;
+                uint32_t id = sh_queue(mine[u]);
+                for (int k = (int)ni - 1; k >= 0; --k) {
+                    const uint32_t cell = lds_look(&L.cells[id - 1]);
+                    rec[2 + k] = (uint16_t)cell_symbol(cell);
+                    id = cell_rest(cell);
+                }
+                id = sh_stack(mine[u]);
+                for (uint32_t k = 0; k < no; ++k) {
+                    const uint32_t cell = lds_look(&L.cells[id - 1]);
+                    rec[2 + ni + k] = (uint16_t)cell_symbol(cell);
+                    id = cell_rest(cell);
+                }
+                RecordMix mix(a.seed);
+                for (uint32_t k = 0; k < 2 + ni + no; ++k) mix.add(rec[k]);
+                h += mix.done();
+            }
+            h = wave_sum64(h);
+            if (lane == 0) L.row_hash[set] = h;
+            result = ((u64)at << 16) | total;
+        }
+    }
+    lds_order();
+    if (lane == 0) __hip_atomic_store(&L.row[set], result, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return result;
+}
+
+// A workgroup takes `per_group` consecutive tokens, a wave `round` of them at a time.
+template <bool ROWS16>  // rows start at multiples of 16 bytes
+__global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(DisplacementArgs a, int per_group, int round) {
+    __shared__ SharedLds L;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool invalid = a.hdr->invalid != 0;  // the same for everybody
+    for (int i = tid; i < kShCells; i += kShThreads) L.cells[i] = 0;
+    for (int i = tid; i < kShNext; i += kShThreads) L.next[i] = kNextEmpty;
+    for (int i = tid; i < kShSets; i += kShThreads) {
+        L.sets[i] = kShEmpty;
+        L.row[i] = kRowUnknown;
+    }
+    if (!invalid) {
+        if (tid < 256) L.byte_like[tid] = a.byte_like[tid];
+        if (tid < 257) L.byte_off[tid] = (uint32_t)a.byte_off[tid];
+        if (a.g.P <= kShProds)
+            for (int i = tid; i < a.g.P; i += kShThreads) L.prods[i] = a.prod_packed[i];
+        if (a.g.N * a.g.W <= kShAdj)
+            for (int i = tid; i < a.g.N * a.g.W; i += kShThreads) L.adj[i] = a.adj[i];
+    }
+    if (tid == 0) {
+        L.pool_top = 0;
+        L.out_top = 0;
+        L.cursor = 0;
+    }
+    __syncthreads();
+    uint32_t *work = L.work[wave], *seen = L.seen[wave];
+    seen_clear(seen, lane);
+    // the start set: nothing consumed, nothing pushed; and the set that no configuration is left in (there is room
+    // for these two: they are the first)
+    const Different one = find_different(seen, lane == 0 ? sh_config(0, 0, kNoSymbol) : kNoWord, kNoWord, lane);
+    const uint32_t start = sh_set_number(L, seen, one, lane);
+    seen_clear(seen, lane);
+    const uint32_t dead = sh_set_number(L, seen, find_different(seen, kNoWord, kNoWord, lane), lane);
+
+    const int64_t group0 = (int64_t)blockIdx.x * per_group;
+    const int in_group = (int)min((int64_t)per_group, (int64_t)a.V - group0);
+    for (;;) {
+        int taken = 0;
+        if (lane == 0) taken = (int)atomicAdd(&L.cursor, (uint32_t)round);
+        taken = __builtin_amdgcn_readfirstlane(taken);
+        if (taken >= in_group) break;
+        const int64_t t0 = group0 + taken, t = t0 + lane;
+        const int count = min(round, in_group - taken);
+        const bool in = lane < count;
+        int64_t pos = 0, end = 0;
+        if (in && !invalid) {
+            pos = a.tok_off[t];
+            end = a.tok_off[t + 1];
+        }
+        // the round's bytes lie behind each other: into LDS if there is room
+        const int64_t from_byte = invalid ? 0 : a.tok_off[t0], to_byte = invalid ? 0 : a.tok_off[t0 + count];
+        uint8_t *bytes = L.bytes[wave];
+        const bool staged = to_byte - from_byte <= kShBytes;
+        lds_order();
+        if (staged)
+            for (int x = lane; x < (int)(to_byte - from_byte); x += 64) bytes[x] = L.byte_like[a.tok_bytes[from_byte + x]];
+        lds_order();
+        auto byte_at = [&](int64_t p) -> uint32_t {
+            if (staged) return bytes[min(max(p - from_byte, (int64_t)0), (int64_t)kShBytes - 1)];  // in bounds whatever the offsets are
+            return L.byte_like[a.tok_bytes[p]];
+        };
+        uint32_t set = start;
+        bool give_up = false, crossed = false;
+        uint32_t like = pos < end ? byte_at(pos) : 0u;
+        for (;;) {
+            // every lane as far as what follows is known
+            uint32_t waits = 0;  // kNextEmpty or kWorkedOut: what the lane has come to
+            auto advance = [&](uint32_t following) {
+                if (following >= kCrossed) {
+                    give_up = following == kGiveUp;
+                    crossed = following == kCrossed;
+                    pos = end;
+                } else {
+                    set = following;
+                    if (++pos < end) like = byte_at(pos);
+                }
+            };
+            while (pos < end && !waits) {
+                if (set == dead) {  // so it stays
+                    pos = end;
+                    break;
+                }
+                const uint32_t following = sh_known(L, set, like);
+                if (following == kNextEmpty || following == kWorkedOut) waits = following;
+                else advance(following);
+            }
+            const u64 unknown = __ballot(waits == kNextEmpty);
+            if (!unknown) {
+                if (!__ballot(waits != 0u)) break;
+                // another wave is at all that is left; it waits for nothing while it works
+                __builtin_amdgcn_s_sleep(2);
+                continue;
+            }
+            // what the first lane waits for, by the whole wave
+            const int first = __ffsll(unknown) - 1;
+            const uint32_t from = wave_read(set, first), on = wave_read(like, first);
+            int slot = 0;
+            if (lane == 0) slot = sh_claim(L, from, on);
+            slot = __builtin_amdgcn_readfirstlane(slot);
+            if (slot == -1) continue;  // taken meanwhile
+            const uint32_t following = sh_step(a, L, work, seen, from, (int)on, lane);
+            lds_order();
+            if (slot >= 0 && lane == 0)
+                __hip_atomic_store(&L.next[slot], (((from << 8) | on) << kNextBits) | following, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (waits && set == from && like == on) advance(following);
+        }
+        // what the sets reached are written as
+        const bool wanted = in && !invalid && !give_up && !crossed;
+        u64 row = kRowUnknown;
+        for (;;) {
+            if (wanted && (row == kRowUnknown || row == kRowWorkedOut)) row = lds_look(&L.row[set]);
+            const u64 unknown = __ballot(wanted && row == kRowUnknown);
+            if (!unknown) {
+                if (!__ballot(wanted && row == kRowWorkedOut)) break;
+                __builtin_amdgcn_s_sleep(2);  // as above
+                continue;
+            }
+            const uint32_t s = wave_read(set, __ffsll(unknown) - 1);
+            u64 state = 0;
+            if (lane == 0) state = atomicCAS(&L.row[s], kRowUnknown, kRowWorkedOut);
+            if (wave_read64(state, 0) == kRowUnknown) sh_write_set(a, L, work, seen, s, lane);
+        }
+        lds_order();
+        if (row == kRowGiveUp) give_up = true;
+        if (row == kRowTooLong) crossed = true;
+        const bool done = in && !give_up;
+        if (done) {
+            u64 h = 0;
+            int32_t status = kStatusOk;
+            if (invalid) {
+                status = kStatusBadGrammar;
+            } else if (crossed) {
+                h = overflow_hash(a.seed, (int)t);
+                status = kStatusOverflow;
+            } else {
+                h = L.row_hash[set];
+            }
+            a.hash[t] = h;
+            if (a.status) a.status[t] = status;
+        }
+        const u64 handed = __ballot(in && give_up);
+        if (handed) {
+            int32_t at = 0;
+            if (lane == 0) at = atomicAdd(&a.hdr->retry_count[0], (int)__popcll(handed));
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (in && give_up) a.retry_list[0][at + __popcll(handed & ((1ull << lane) - 1ull))] = (int32_t)t;
+        }
+        // the rows, one after the other by the whole wave
+        const u64 plain = __ballot(done && !invalid && !crossed);
+        for (u64 left = __ballot(done); left; left &= left - 1) {
+            const int k = __ffsll(left) - 1;
+            const int64_t tk = t0 + k;
+            uint16_t *out_row = a.rows + (size_t)tk * a.row_len;
+            const bool copy = (plain >> k) & 1ull;
+            const u64 rk = wave_read64(row, k);
+            const uint32_t units = copy ? (((uint32_t)rk & 0xFFFFu) + 7u) / 8u : 0u;  // 16 bytes each
+            const uint4 *src = reinterpret_cast<const uint4 *>(L.out + (copy ? (uint32_t)(rk >> 16) : 0u));
+            const bool marked = !copy && !invalid;  // the row of a token that overflowed
+            for (uint32_t u = lane; u < (uint32_t)a.row_len / 8u; u += 64) {
+                uint4 v = make_uint4(0, 0, 0, 0);
+                if (u < units) v = src[u];
+                if (marked && u == 0) v = make_uint4(0xFFFFu | ((uint32_t)tk << 16), (uint32_t)tk >> 16, 0, 0);
+                if (ROWS16) {
+                    reinterpret_cast<uint4 *>(out_row)[u] = v;
+                } else {
+                    reinterpret_cast<uint2 *>(out_row)[2 * u] = make_uint2(v.x, v.y);
+                    reinterpret_cast<uint2 *>(out_row)[2 * u + 1] = make_uint2(v.z, v.w);
+                }
+            }
+        }
+    }
+}
+
+}  // namespace
+}  // namespace cfgzip

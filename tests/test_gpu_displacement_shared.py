@@ -1,0 +1,97 @@
+"""GPU parity of the shared walk of cfgzip_displacements where it can go wrong: vocabulary sizes around its waves
+and workgroups, sets of one and two configurations a lane and of more than it takes, grammars whose productions or
+relation do not fit its LDS, bytes with equal productions, rows that are only 8-byte aligned, and vocabularies that
+exhaust its tables, so that some tokens are taken alone by the passes behind it.  Compared like every other
+displacement: status, row and hash of every token against the oracle, and the classes."""
+
+import ctypes
+
+import numpy as np
+import pytest
+
+from synthetic_inputs.grammar import (grammar_from_productions, make_bracket_gnf, make_json_gnf, make_random_gnf,
+                                      make_token_strings)
+from synthetic_inputs.vocab import vocab_from_tokens
+from test_gpu_displacement import _check_adjacency, _check_rows, _grammar_dev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2605_29986_amd as p
+    p.load_library()
+    return p
+
+
+@pytest.mark.parametrize("V", [1, 15, 16, 17, 255, 4095, 4097])
+def test_vocabulary_sizes(lib, V):
+    print(f"case V={V}", flush=True)
+    g, atoms = make_bracket_gnf(3)
+    _check_rows(lib, g, make_token_strings(V, V, atoms + b"()[]{},+", 9))
+
+
+@pytest.mark.parametrize("n", [63, 64, 65, 100, 127, 128, 129, 200])
+def test_sets_of_many_configurations(lib, n):
+    """n alternatives for the first byte, all of them alive after every further one; on 'b' every second goes."""
+    print(f"case n={n}", flush=True)
+    prods = [(A, ord("a"), (A,)) for A in range(n)] + [(A, ord("b"), (A,)) for A in range(0, n, 2)]
+    prods += [(A, ord("c"), ()) for A in range(n)]
+    g = grammar_from_productions(n, prods)
+    vocab = vocab_from_tokens([b"", b"a", b"aa", b"ab", b"aab", b"aba", b"abb", b"ac", b"acc", b"c", b"cc", b"b", b"z"])
+    _check_rows(lib, g, vocab, row_len=1024)
+
+
+@pytest.mark.parametrize("n_nt,n_prod", [(40, 1023), (40, 1024), (40, 1025), (128, 900), (129, 900), (200, 1100),
+                                         (255, 700), (256, 700)])
+def test_grammars_around_what_is_kept_in_lds(lib, n_nt, n_prod):
+    print(f"case N={n_nt} P={n_prod}", flush=True)
+    alphabet = bytes(range(97, 123)) + b"0123456789"
+    g = make_random_gnf(n_nt + n_prod, n_nt, alphabet, n_prod, 5)
+    _check_adjacency(lib, g)
+    _check_rows(lib, g, make_token_strings(7, 300, alphabet, 5), row_len=512)
+
+
+def test_bytes_with_equal_productions(lib):
+    """Digits 0-4 behave alike, 5 differs in a body, 6 in the fifth symbol of a long one, 7 in the number of
+    productions."""
+    prods = [(0, d, (1, 2)) for d in b"01234567"] + [(1, d, (2, 2, 2, 2, 2)) for d in b"012345"]
+    prods += [(1, ord("6"), (2, 2, 2, 2, 1)), (1, ord("7"), (2, 2, 2, 2, 2)), (2, ord("7"), (0,))]
+    prods += [(2, d, ()) for d in b"012346"] + [(2, ord("5"), (1,)), (2, ord("7"), ())]
+    g = grammar_from_productions(3, prods)
+    _check_rows(lib, g, make_token_strings(1, 600, b"012345678", 5), row_len=1024)
+
+
+def test_vocabulary_that_exhausts_the_tables(lib):
+    """Every symbol may follow every other, so a token's queue is the token itself: every prefix of every token is a
+    set of its own."""
+    n = 26
+    prods = [(A, 97 + A, ()) for A in range(n)] + [(n, 65, (A, B)) for A in range(n) for B in range(n)]
+    g = grammar_from_productions(n + 1, prods)
+    rng = np.random.default_rng(2)
+    toks = [bytes(rng.integers(97, 123, size=int(k), dtype=np.uint8)) for k in rng.integers(24, 36, size=12_000)]
+    _check_rows(lib, g, vocab_from_tokens(toks), expect_overflow=True)
+
+
+def test_rows_that_are_only_8_byte_aligned(lib):
+    from gpu_util import dev
+    g = make_json_gnf()
+    vocab = make_token_strings(4, 500, b'{}[]:,"0123456789tfnrue ', 8)
+    tb, to, gd = dev(vocab.tok_bytes), dev(vocab.tok_off), _grammar_dev(g)
+    want, want_hash, want_status = lib.cfgzip_displacements(tb, to, *gd, g.N)
+    raw = lib.load_library()
+    buf = torch.full((vocab.V * 256 + 8,), 7, dtype=torch.int16, device="cuda")
+    h = torch.empty(vocab.V, dtype=torch.int64, device="cuda")
+    st = torch.empty(vocab.V, dtype=torch.int32, device="cuda")
+    ws = torch.empty(raw.cfgzip_displacements_workspace_bytes(vocab.V, g.N, g.P), dtype=torch.uint8, device="cuda")
+    rc = raw.cfgzip_displacements(tb.data_ptr(), to.data_ptr(), vocab.V, *[x.data_ptr() for x in gd], gd[3].numel(),
+                                  g.P, g.N, buf.data_ptr() + 8, 256, h.data_ptr(), st.data_ptr(),
+                                  ctypes.c_uint64(lib.DEFAULT_HASH_SEED), ws.data_ptr(), ws.numel(),
+                                  torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    got = buf.cpu().numpy()
+    assert (got[4:-4].reshape(vocab.V, 256) == want.view(torch.int16).cpu().numpy()).all()
+    assert (got[:4] == 7).all() and (got[-4:] == 7).all()
+    assert torch.equal(h, want_hash) and torch.equal(st, want_status)
