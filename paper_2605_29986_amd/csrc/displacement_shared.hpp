@@ -548,6 +548,7 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
     const int64_t group0 = (int64_t)blockIdx.x * per_group;
     const int in_group = (int)min((int64_t)per_group, (int64_t)a.V - group0);
     for (;;) {
+        __builtin_amdgcn_wave_barrier();  // the wave goes round together: no branch on the lane is joined with the next one
         int taken = 0;
         if (lane == 0) taken = (int)atomicAdd(&L.cursor, (uint32_t)round);
         taken = __builtin_amdgcn_readfirstlane(taken);

@@ -1,15 +1,15 @@
-// Signatures over a non-deterministic byte automaton (paper Section 3.2.1 for a right-linear
-// grammar with several productions q -> a q' per state and byte).  The displacement of token t
-// is then the relation R_t = {(q, q') : q' reachable from q on bytes(t)}, the boolean product of
-// the per-byte transition relations; it is kept as one bit row per start state.
+// Signatures over a non-deterministic byte automaton (paper Section 3.2.1 for a right-linear grammar with
+// several productions q -> a q' per state and byte).  The displacement of token t is then the relation
+// R_t = {(q, q') : q' reachable from q on bytes(t)}, the boolean product of the per-byte transition relations; it is
+// kept as one bit row per start state.
 //
-// A thread owns one (token, start state) pair and carries the set of current states as W words
-// in registers.  Per byte it ORs together the successor rows of the set's members, visiting set
-// bits only, so the cost follows the number of live states (one or a few for a lexer), not S;
-// a set that has become empty stops early.  Automata of more than 256 states (up to 1,024) keep
-// the sets in LDS instead.  The 64-bit hash is the same multilinear form as for
-// the byte walk, over the relation read as 16-bit entries, so any split over threads gives the
-// same bits.
+// Start states that the first byte sends to the same set of states have the same row for the whole token, and a
+// lexer's bytes leave few different sets (about 30 of 256 states).  Up to 256 states a wave therefore walks its token
+// from the different successor sets of the first byte only, a lane each, and every start state's row is a copy of its
+// set's (the image walk of the deterministic case).  A set is W words in registers; per byte the successor rows of
+// its members are ORed together, so the cost follows the size of the sets and not S.  Automata of more than 256 states
+// (up to 1,024) walk from every state and keep the sets in LDS.  The 64-bit hash is the same multilinear form as for
+// the byte walk, over the relation read as 16-bit entries, so any split over threads gives the same bits.
 
 #include <algorithm>
 
@@ -22,8 +22,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kMaxRegisterStates = 256;  // up to here a thread keeps its set in registers
 constexpr int kMaxNfaStates = 1024;
-constexpr int kStagedBytes = 64;  // token bytes read once into LDS; longer tokens go on from global
-
 struct NfaArgs {
     const uint8_t *tok_bytes;
     const int64_t *tok_off;
@@ -32,96 +30,310 @@ struct NfaArgs {
     uint64_t *hash;       // [V] or null
     uint64_t seed;
     int V, S;
-    int threads_per_token;  // 64, 128 or 256: S rounded up
     uint32_t last_word_mask;  // the bits of a row's last word that are states
 };
 
-// A thread owns one (token, start state) pair.  (Two or four start states per thread, for more
-// row reads in flight, made the kernel slower - 209 and 277 us against 164 us on 32,000 tokens x
-// 256 states: it is bound by instruction issue, not by the latency of its reads.)
+constexpr int kImageThreads = 1024;
+constexpr int kImageWaves = kImageThreads / 64;
+constexpr int kImageSets = 96;           // different successor sets of a byte that the walk shares
+constexpr int kImageSlots = 512;         // slots of the table in which a byte's sets are told apart (256 states at most)
+constexpr uint32_t kImageUnknown = 0, kImageWorkedOut = 1, kImageMany = 2, kImageReady = 3;  // kImageReady + how many
+
 template <int W>
-__global__ __launch_bounds__(kThreads) void nfa_walk_kernel(NfaArgs a) {
-    __shared__ unsigned long long hash_sum[kThreads / 64];
-    __shared__ uint8_t head_bytes[kThreads / 64][kStagedBytes];  // each token's first bytes
-    const int slot = threadIdx.x / a.threads_per_token;
-    const int q = threadIdx.x % a.threads_per_token;
-    const int t = blockIdx.x * (kThreads / a.threads_per_token) + slot;
-    if (threadIdx.x < kThreads / 64) hash_sum[threadIdx.x] = 0;
-    int64_t b0 = 0, b1 = 0;
-    if (t < a.V) {
-        b0 = a.tok_off[t];
-        b1 = a.tok_off[t + 1];
-        if (q < kStagedBytes && b0 + q < b1) head_bytes[slot][q] = a.tok_bytes[b0 + q];
+struct ImageLds {
+    // per wave: the sets its token's walk has come to, and what the hash needs of them; while a byte's sets are told
+    // apart, the table for that and the numbers of the states that stand for a set
+    static constexpr int kSetWords = kImageSets * W > kImageSlots + 64 ? kImageSets * W : kImageSlots + 64;
+    __align__(16) uint32_t sets[kImageWaves][kSetWords];
+    uint32_t members[kImageWaves][kImageSets];  // how many, and the first and the last of them
+    uint32_t state[256];                        // of the two tables below, per byte
+    uint32_t cursor;
+    uint8_t set_of[256][256];                   // [byte][start state]: number of its successor set
+    uint8_t first_with[256][kImageSets];        // [byte][set]: the first state that has it
+};
+
+// How many members a set has, the first and the last.
+template <int W>
+__device__ __forceinline__ void set_members(const uint32_t (&set)[W], uint32_t &count, uint32_t &first, uint32_t &last) {
+    count = 0, first = 0, last = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) count += __popc(set[w]);
+#pragma unroll
+    for (int w = W - 1; w >= 0; --w) first = set[w] ? 32u * w + (uint32_t)__ffs(set[w]) - 1u : first;
+#pragma unroll
+    for (int w = 0; w < W; ++w) last = set[w] ? 32u * w + 31u - (uint32_t)__clz(set[w]) : last;
+}
+
+template <int W>
+__device__ __forceinline__ void add_row(uint32_t (&set)[W], const uint32_t *row) {
+    if (W % 4 == 0) {  // rows are whole 16-byte units (the base is 16-byte aligned)
+#pragma unroll
+        for (int k = 0; k < W / 4; ++k) {
+            const uint4 v = reinterpret_cast<const uint4 *>(row)[k];
+            set[4 * k] |= v.x;
+            set[4 * k + 1] |= v.y;
+            set[4 * k + 2] |= v.z;
+            set[4 * k + 3] |= v.w;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < W; ++k) set[k] |= row[k];
     }
-    __syncthreads();
+}
+
+// One byte: the union of the successor rows of the members.  One or two members, as a lexer's sets have, are found
+// without going through the words.
+template <int W>
+__device__ __forceinline__ void set_step(uint32_t (&set)[W], const uint32_t *step, uint32_t last_word_mask) {
+    uint32_t count, first, last;
+    set_members<W>(set, count, first, last);
+    uint32_t next[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) next[w] = 0;
+    if (count) add_row<W>(next, step + first * W);
+    if (count > 1) add_row<W>(next, step + last * W);
+    if (count > 2) {
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            for (uint32_t bits = set[w]; bits; bits &= bits - 1) add_row<W>(next, step + (w * 32 + __ffs(bits) - 1) * W);
+    }
+    next[W - 1] &= last_word_mask;  // a stray pad bit must not become a state number
+#pragma unroll
+    for (int w = 0; w < W; ++w) set[w] = next[w];
+}
+
+// The bytes of a token, 64 at a time in the lanes of the wave.
+struct WaveBytes {
+    const uint8_t *bytes;
+    int64_t beg, end, chunk;
+    uint32_t mine;
+    __device__ WaveBytes(const uint8_t *tok_bytes, int64_t b0, int64_t b1) : bytes(tok_bytes), beg(b0), end(b1), chunk(b0) { load(); }
+    __device__ void load() {
+        const int64_t p = chunk + (threadIdx.x & 63);
+        mine = p < end ? bytes[p] : 0u;
+    }
+    __device__ int at(int64_t p) {  // p does not decrease from call to call
+        if (p >= chunk + 64) {
+            chunk = p;
+            load();
+        }
+        return (int)__builtin_amdgcn_readlane(mine, (int)(p - chunk));
+    }
+};
+
+// A row's part of the hash: the terms of empty words are zero.
+template <int W>
+__device__ __forceinline__ uint64_t row_hash(const uint32_t (&set)[W], int q, uint64_t seed) {
     uint64_t h = 0;
-    if (t < a.V && q < a.S) {
-        uint32_t cur[W];
 #pragma unroll
-        for (int w = 0; w < W; ++w) cur[w] = (q >> 5) == w ? 1u << (q & 31) : 0u;
-        const size_t matrix = (size_t)a.S * W;
-        for (int64_t p = b0; p < b1; ++p) {
-            const int ch = p - b0 < kStagedBytes ? head_bytes[slot][p - b0] : a.tok_bytes[p];
-            const uint32_t *step = a.nfa + ch * matrix;
-            uint32_t nxt[W];
+    for (int w = 0; w < W; ++w) {
+        if (set[w]) {
+            const uint32_t e = 2u * (uint32_t)(q * W + w);  // 16-bit entries 2(qW+w), 2(qW+w)+1
+            if (set[w] & 0xFFFFu) h += (splitmix64_at(seed, e) | 1ull) * (uint64_t)(set[w] & 0xFFFFu);
+            if (set[w] >> 16) h += (splitmix64_at(seed, e + 1u) | 1ull) * (uint64_t)(set[w] >> 16);
+        }
+    }
+    return h;
+}
+// The same for a set of one member y: its bit's place in the entry y / 16 of the row.
+__device__ __forceinline__ uint64_t member_hash(uint32_t q, uint32_t W, uint32_t y, uint64_t seed) {
+    return (splitmix64_at(seed, 2u * W * q + (y >> 4)) | 1ull) << (y & 15u);
+}
+
+__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup"); }
+
+// Tells the successor sets of byte b apart, by the whole wave: numbers them by the first state that has them.
+template <int W>
+__device__ __forceinline__ uint32_t number_sets(const NfaArgs &a, ImageLds<W> &L, uint32_t *scratch, int b) {
+    const int lane = threadIdx.x & 63;
+    uint32_t *table = scratch;                                                // [kImageSlots]: hash above the state
+    uint8_t *number = reinterpret_cast<uint8_t *>(scratch + kImageSlots);     // [256]
+    for (int i = lane; i < kImageSlots; i += 64) table[i] = ~0u;
+    lds_order();
+    const uint32_t *step = a.nfa + (size_t)b * a.S * W;
+    uint32_t n = 0;
+    for (int q0 = 0; q0 < a.S; q0 += 64) {
+        const int q = q0 + lane;
+        const bool in = q < a.S;
+        uint32_t row[W];
 #pragma unroll
-            for (int w = 0; w < W; ++w) nxt[w] = 0;
+        for (int w = 0; w < W; ++w) row[w] = 0;
+        if (in) add_row<W>(row, step + (size_t)q * W);
+        uint32_t h = 0;
 #pragma unroll
-            for (int w = 0; w < W; ++w) {
-                uint32_t bits = cur[w];
-                while (bits) {
-                    const int x = w * 32 + __ffs(bits) - 1;
-                    bits &= bits - 1;
-                    const uint32_t *row = step + (size_t)x * W;
-                    if (W % 4 == 0) {  // rows are whole 16-byte units (the base is 16-byte aligned)
+        for (int w = 0; w < W; ++w) h = (h ^ row[w]) * 0x9E3779B1u + (h >> 15);
+        h = (h ^ (h >> 13)) & 0x7FFFFFFFu;  // so that no entry looks like an empty slot
+        int like = q;
+        if (in) {
+            uint32_t at = h % kImageSlots;
+            for (int probe = 0; probe < kImageSlots; ++probe, at = (at + 1) % kImageSlots) {
+                const uint32_t seen = atomicCAS(&table[at], ~0u, (h & ~0xFFu) | (uint32_t)q);
+                if (seen == ~0u) break;
+                if (((seen ^ h) >> 8) == 0u) {
+                    const uint32_t *other = step + (size_t)(seen & 0xFFu) * W;
+                    bool same = true;
 #pragma unroll
-                        for (int k = 0; k < W / 4; ++k) {
-                            const uint4 v = reinterpret_cast<const uint4 *>(row)[k];
-                            nxt[4 * k] |= v.x;
-                            nxt[4 * k + 1] |= v.y;
-                            nxt[4 * k + 2] |= v.z;
-                            nxt[4 * k + 3] |= v.w;
-                        }
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < W; ++k) nxt[k] |= row[k];
+                    for (int w = 0; w < W; ++w) same = same && other[w] == row[w];
+                    if (same) {
+                        like = (int)(seen & 0xFFu);
+                        break;
                     }
                 }
             }
-            nxt[W - 1] &= a.last_word_mask;  // a stray pad bit must not become a state number
-            uint32_t any = 0;
-#pragma unroll
-            for (int w = 0; w < W; ++w) {
-                cur[w] = nxt[w];
-                any |= nxt[w];
-            }
-            if (!any) break;  // no state left: the row stays empty
         }
-        uint32_t *out = a.rel + ((size_t)t * a.S + q) * W;
-        if (W % 4 == 0) {
-#pragma unroll
-            for (int k = 0; k < W / 4; ++k)
-                reinterpret_cast<uint4 *>(out)[k] =
-                    make_uint4(cur[4 * k], cur[4 * k + 1], cur[4 * k + 2], cur[4 * k + 3]);
-        } else {
-#pragma unroll
-            for (int w = 0; w < W; ++w) out[w] = cur[w];
+        const uint64_t fresh = __ballot(in && like == q);
+        if (in && like == q) {
+            const uint32_t k = n + (uint32_t)__popcll(fresh & ((1ull << lane) - 1ull));
+            number[q] = (uint8_t)k;
+            if (k < (uint32_t)kImageSets) L.first_with[b][k] = (uint8_t)q;
         }
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-            if (a.hash && cur[w]) {  // most words of a relation are empty: their terms are zero
-                const uint32_t e = 2u * (uint32_t)(q * W + w);  // 16-bit entries 2(qW+w), 2(qW+w)+1
-                if (cur[w] & 0xFFFFu)
-                    h += (splitmix64_at(a.seed, e) | 1ull) * (uint64_t)(cur[w] & 0xFFFFu);
-                if (cur[w] >> 16)
-                    h += (splitmix64_at(a.seed, e + 1u) | 1ull) * (uint64_t)(cur[w] >> 16);
-            }
-        }
+        n += (uint32_t)__popcll(fresh);
+        lds_order();
+        if (in) L.set_of[b][q] = number[like];
     }
-    if (a.hash) {
-        if (h) atomicAdd(&hash_sum[slot], (unsigned long long)h);
-        __syncthreads();
-        if (q == 0 && t < a.V) a.hash[t] = hash_sum[slot];
+    lds_order();
+    return n <= (uint32_t)kImageSets ? kImageReady + n : kImageMany;
+}
+
+// Up to 256 states.  A workgroup of sixteen waves takes `per_group` consecutive tokens, a wave one at a time; which
+// successor sets a byte has is worked out once per workgroup and first byte, by the wave that first needs it.
+// 32,000 tokens x 256 states: 154 us with a thread per (token, start state), bound by instruction issue (75.6 M wave
+// instructions); what is left is mostly writing the rows (262 MB, 45 us).
+template <int W>
+__global__ __launch_bounds__(kImageThreads) void nfa_image_kernel(NfaArgs a, int per_group) {
+    __shared__ ImageLds<W> L;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid < 256) L.state[tid] = kImageUnknown;
+    if (tid == 0) L.cursor = 0;
+    __syncthreads();
+    uint32_t *sets = L.sets[wave], *members = L.members[wave];
+    const int group0 = (int)blockIdx.x * per_group, in_group = min(per_group, a.V - group0);
+    const size_t matrix = (size_t)a.S * W;
+    for (;;) {
+        // Keeps the wave together: without it the compiler joins the branch below with the one that ends the round
+        // (lane 0 stores the hash), and the other lanes go round alone, reading a `taken` that is never theirs.
+        __builtin_amdgcn_wave_barrier();
+        int taken = 0;
+        if (lane == 0) taken = (int)atomicAdd(&L.cursor, 1u);
+        taken = __builtin_amdgcn_readfirstlane(taken);
+        if (taken >= in_group) break;
+        const int t = group0 + taken;
+        const int64_t b0 = a.tok_off[t], b1 = a.tok_off[t + 1];
+        uint32_t *out = a.rel + (size_t)t * matrix;
+        uint64_t h = 0;
+        uint32_t state = kImageMany;
+        int b = 0;
+        WaveBytes bytes(a.tok_bytes, b0, b1);
+        if (b1 > b0) {
+            b = bytes.at(b0);
+            for (;;) {
+                state = __hip_atomic_load(&L.state[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                state = __builtin_amdgcn_readfirstlane(state);
+                if (state == kImageUnknown) {
+                    uint32_t was = 0;
+                    if (lane == 0) was = atomicCAS(&L.state[b], kImageUnknown, kImageWorkedOut);
+                    was = __builtin_amdgcn_readfirstlane(was);
+                    if (was == kImageUnknown) {
+                        state = number_sets<W>(a, L, sets, b);
+                        if (lane == 0)
+                            __hip_atomic_store(&L.state[b], state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                    continue;
+                }
+                if (state != kImageWorkedOut) break;
+                __builtin_amdgcn_s_sleep(2);  // another wave is at it, and waits for nothing while it works
+            }
+            lds_order();
+        }
+        if (state >= kImageReady) {
+            const int n = (int)(state - kImageReady);
+            for (int j0 = 0; j0 < n; j0 += 64) {
+                const int j = j0 + lane;
+                uint32_t set[W];
+#pragma unroll
+                for (int w = 0; w < W; ++w) set[w] = 0;
+                if (j < n) add_row<W>(set, a.nfa + b * matrix + (size_t)L.first_with[b][j] * W);
+                set[W - 1] &= a.last_word_mask;
+                for (int64_t p = b0 + 1; p < b1; ++p) {
+                    uint32_t any = 0;
+#pragma unroll
+                    for (int w = 0; w < W; ++w) any |= set[w];
+                    if (__ballot(any != 0u) == 0ull) break;  // no state left anywhere: the rows stay empty
+                    set_step<W>(set, a.nfa + (size_t)bytes.at(p) * matrix, a.last_word_mask);
+                }
+                if (j < n) {
+                    uint32_t count, first, last;
+                    set_members<W>(set, count, first, last);
+                    members[j] = min(count, 3u) | (first << 8) | (last << 16);
+#pragma unroll
+                    for (int w = 0; w < W; ++w) sets[j * W + w] = set[w];
+                }
+                if (j0 + 64 < n) bytes = WaveBytes(a.tok_bytes, b0, b1);  // once more from the front
+            }
+            lds_order();
+            const uint8_t *set_of = L.set_of[b];
+            // the rows, as one run of 16-byte units (or words) over the lanes
+            if (W % 4 == 0) {
+                constexpr int kPerRow = W / 4 > 0 ? W / 4 : 1;
+                const int units = a.S * kPerRow;
+                for (int x = lane; x < units; x += 64)
+                    reinterpret_cast<uint4 *>(out)[x] =
+                        reinterpret_cast<const uint4 *>(sets)[set_of[x / kPerRow] * kPerRow + x % kPerRow];
+            } else {
+                const int units = a.S * W;
+                for (int x = lane; x < units; x += 64) out[x] = sets[set_of[x / W] * W + x % W];
+            }
+            if (a.hash) {
+                for (int q = lane; q < a.S; q += 64) {
+                    const uint32_t k = set_of[q], m = members[k], count = m & 0xFFu;
+                    if (count == 0) continue;
+                    if (count <= 2) {
+                        h += member_hash((uint32_t)q, W, (m >> 8) & 0xFFu, a.seed);
+                        if (count == 2) h += member_hash((uint32_t)q, W, m >> 16, a.seed);
+                    } else {
+                        uint32_t set[W];
+#pragma unroll
+                        for (int w = 0; w < W; ++w) set[w] = sets[k * W + w];
+                        h += row_hash<W>(set, q, a.seed);
+                    }
+                }
+            }
+        } else {
+            // the empty token (its relation is the identity), or a first byte that leaves many different sets: every
+            // start state walks for itself
+            for (int q0 = 0; q0 < a.S; q0 += 64) {
+                const int q = q0 + lane;
+                uint32_t set[W];
+#pragma unroll
+                for (int w = 0; w < W; ++w) set[w] = (q < a.S && (q >> 5) == w) ? 1u << (q & 31) : 0u;
+                WaveBytes from_front(a.tok_bytes, b0, b1);
+                for (int64_t p = b0; p < b1; ++p) {
+                    uint32_t any = 0;
+#pragma unroll
+                    for (int w = 0; w < W; ++w) any |= set[w];
+                    if (__ballot(any != 0u) == 0ull) break;
+                    set_step<W>(set, a.nfa + (size_t)from_front.at(p) * matrix, a.last_word_mask);
+                }
+                if (q >= a.S) continue;
+                uint32_t *row = out + (size_t)q * W;
+                if (W % 4 == 0) {
+#pragma unroll
+                    for (int k = 0; k < W / 4; ++k)
+                        reinterpret_cast<uint4 *>(row)[k] =
+                            make_uint4(set[4 * k], set[4 * k + 1], set[4 * k + 2], set[4 * k + 3]);
+                } else {
+#pragma unroll
+                    for (int w = 0; w < W; ++w) row[w] = set[w];
+                }
+                if (a.hash) h += row_hash<W>(set, q, a.seed);
+            }
+        }
+        if (a.hash) {
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) h += __shfl_xor(h, off, 64);
+            if (lane == 0) a.hash[t] = h;
+        }
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -188,10 +400,12 @@ __global__ void clear_u64_kernel(uint64_t *p, int n) {
 }
 
 template <int W>
-int launch_nfa(const NfaArgs &a, hipStream_t stream) {
-    const int per_block = kThreads / a.threads_per_token;
-    hipLaunchKernelGGL(nfa_walk_kernel<W>, dim3((unsigned)ceil_div(a.V, per_block)), dim3(kThreads), 0,
-                       stream, a);
+int launch_nfa(const NfaArgs &a, int n_cu, hipStream_t stream) {
+    // a workgroup per compute unit (its LDS is what there is), the tokens spread evenly
+    const int64_t groups = std::min<int64_t>(n_cu, ceil_div(a.V, kImageWaves));
+    const int per_group = (int)ceil_div(a.V, groups);
+    hipLaunchKernelGGL(nfa_image_kernel<W>, dim3((unsigned)ceil_div(a.V, per_group)), dim3(kImageThreads), 0, stream, a,
+                       per_group);
     return check_launch();
 }
 
@@ -217,8 +431,6 @@ extern "C" int cfgzip_nfa_signatures(const uint8_t *tok_bytes, const int64_t *to
     a.seed = hash_seed;
     a.V = V;
     a.S = S;
-    a.threads_per_token = 64;  // whole waves, a power of two so that a block holds whole tokens
-    while (a.threads_per_token < S) a.threads_per_token *= 2;
     a.last_word_mask = (S & 31) ? (1u << (S & 31)) - 1u : 0xFFFFFFFFu;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     if (S > kMaxRegisterStates) {
@@ -237,14 +449,18 @@ extern "C" int cfgzip_nfa_signatures(const uint8_t *tok_bytes, const int64_t *to
                            a, W, q_blocks);
         return check_launch();
     }
+    int dev = 0, n_cu = 256;
+    CFGZIP_TRY(check_hip(hipGetDevice(&dev)));
+    CFGZIP_TRY(check_hip(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev)));
+    if (n_cu <= 0) n_cu = 256;
     switch ((S + 31) / 32) {
-        case 1: return launch_nfa<1>(a, stream);
-        case 2: return launch_nfa<2>(a, stream);
-        case 3: return launch_nfa<3>(a, stream);
-        case 4: return launch_nfa<4>(a, stream);
-        case 5: return launch_nfa<5>(a, stream);
-        case 6: return launch_nfa<6>(a, stream);
-        case 7: return launch_nfa<7>(a, stream);
-        default: return launch_nfa<8>(a, stream);
+        case 1: return launch_nfa<1>(a, n_cu, stream);
+        case 2: return launch_nfa<2>(a, n_cu, stream);
+        case 3: return launch_nfa<3>(a, n_cu, stream);
+        case 4: return launch_nfa<4>(a, n_cu, stream);
+        case 5: return launch_nfa<5>(a, n_cu, stream);
+        case 6: return launch_nfa<6>(a, n_cu, stream);
+        case 7: return launch_nfa<7>(a, n_cu, stream);
+        default: return launch_nfa<8>(a, n_cu, stream);
     }
 }
