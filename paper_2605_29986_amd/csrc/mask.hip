@@ -29,15 +29,20 @@ constexpr int kMaxRowsPerBlock = 16;           // the larger of the two
 
 enum : int { LOGITS_NONE = 0, LOGITS_BF16 = 1, LOGITS_F32 = 2 };
 
-// native 16-byte vector (the nontemporal builtins do not take HIP's uint4 struct)
+// native 16-byte vector (the nontemporal builtins do not take HIP's uint4 struct), and the same at any even address:
+// global memory takes 16-byte accesses at every alignment, and a wave's 1 KB run then touches one cache line more.
+// So rows of an odd length take the same path as aligned ones (64 rows of 50,003 bf16 logits, one by one where
+// unaligned: 11.2 us).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 // streaming 16-byte accesses: every logit is touched exactly once per call
 __device__ __forceinline__ u32x4 load16(const void *p) {
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+    return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any *>(p));
 }
 __device__ __forceinline__ void store16(void *p, u32x4 v) {
-    __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(p));
+    __builtin_nontemporal_store(v, reinterpret_cast<u32x4_any *>(p));
 }
 
 struct MaskArgs {
@@ -75,8 +80,7 @@ __device__ __forceinline__ uint32_t select_bf16_pair(uint32_t x, uint32_t two_bi
 // LOGITS: which logits to mask (none = mask expansion only).
 // FROM_CLASS: bits_in is a class-level mask gathered through class_of_token.
 // WRITE_BITS: also store the token-level mask.
-// VEC: logits rows and class_of_token allow 16-byte accesses at column multiples of 8.
-template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS, bool VEC>
+template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS>
 __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) {
 
     const int ct = blockIdx.x % a.col_tiles;
@@ -127,9 +131,9 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
     uint32_t woff[kCols], shift[kCols];
     if (FROM_CLASS) {
         int32_t k[kCols];
-        if (VEC && full) {
-            const int4 *p = reinterpret_cast<const int4 *>(a.class_of_token + col0);
-            int4 lo = p[0], hi = p[1];
+        if (full) {
+            const i32x4_any *p = reinterpret_cast<const i32x4_any *>(a.class_of_token + col0);
+            const i32x4_any lo = p[0], hi = p[1];
             k[0] = lo.x; k[1] = lo.y; k[2] = lo.z; k[3] = lo.w;
             k[4] = hi.x; k[5] = hi.y; k[6] = hi.z; k[7] = hi.w;
         } else {
@@ -168,7 +172,7 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
         return;
     }
 
-    if (VEC && full) {
+    if (full) {
         if (LOGITS == LOGITS_BF16) {
             uint16_t *base = reinterpret_cast<uint16_t *>(a.logits) + (int64_t)r0 * a.row_stride + col0;
             auto masked = [](u32x4 x, uint32_t m) -> u32x4 {
@@ -232,7 +236,7 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
         return;
     }
 
-    // element-wise path: ragged last columns of a row, or rows that are not 16-byte aligned
+    // element by element: the ragged last columns of a row
     for (int r = 0; r < nrows; ++r) {
         uint32_t m = row_mask(r);
         if (LOGITS == LOGITS_BF16) {
@@ -257,10 +261,10 @@ __device__ __forceinline__ int32_t representative_of(int32_t t, const int32_t *c
     return (k >= 0 && k < C) ? rep_of_class[k] : -1;
 }
 
-template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS, bool VEC>
+template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS>
 __global__ __launch_bounds__(kThreads) void mask_kernel(MaskArgs a) {
     extern __shared__ uint32_t cls_lds[];  // [rows_per_block][Wc] when FROM_CLASS
-    mask_tile<LOGITS, FROM_CLASS, WRITE_BITS, VEC>(a, cls_lds);
+    mask_tile<LOGITS, FROM_CLASS, WRITE_BITS>(a, cls_lds);
     // The first workgroup is the first to be scheduled and to finish its rows; the B dependent
     // look-ups then overlap with the streaming of all the others.
     if (a.map_tok && blockIdx.x == 0)
@@ -277,9 +281,9 @@ __global__ void map_to_rep_kernel(const int32_t *tok, int32_t B, const int32_t *
 
 constexpr size_t kMaxLds = 160 * 1024;
 
-template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS, bool VEC>
+template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS>
 int launch_mask(const MaskArgs &args, int grid, size_t lds_bytes, hipStream_t stream) {
-    auto kern = mask_kernel<LOGITS, FROM_CLASS, WRITE_BITS, VEC>;
+    auto kern = mask_kernel<LOGITS, FROM_CLASS, WRITE_BITS>;
     if (lds_bytes > 64 * 1024) {
         CFGZIP_TRY(check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -290,15 +294,10 @@ int launch_mask(const MaskArgs &args, int grid, size_t lds_bytes, hipStream_t st
 }
 
 template <int LOGITS, bool FROM_CLASS>
-int dispatch_mask(const MaskArgs &args, bool write_bits, bool vec, int grid, size_t lds,
-                  hipStream_t stream) {
-    if (write_bits) {
-        return vec ? launch_mask<LOGITS, FROM_CLASS, true, true>(args, grid, lds, stream)
-                   : launch_mask<LOGITS, FROM_CLASS, true, false>(args, grid, lds, stream);
-    }
+int dispatch_mask(const MaskArgs &args, bool write_bits, int grid, size_t lds, hipStream_t stream) {
+    if (write_bits) return launch_mask<LOGITS, FROM_CLASS, true>(args, grid, lds, stream);
     if (LOGITS == LOGITS_NONE) return CFGZIP_E_INVALID;  // nothing to do
-    return vec ? launch_mask<LOGITS, FROM_CLASS, false, true>(args, grid, lds, stream)
-               : launch_mask<LOGITS, FROM_CLASS, false, false>(args, grid, lds, stream);
+    return launch_mask<LOGITS, FROM_CLASS, false>(args, grid, lds, stream);
 }
 
 // Shared host path of cfgzip_expand_mask and cfgzip_apply_mask.
@@ -363,22 +362,16 @@ int run_mask(void *logits, int logits_kind, int32_t B, int32_t V, int64_t row_st
     if (grid > 0x7FFFFFFF) return CFGZIP_E_INVALID;
     size_t lds = from_class ? (size_t)rows * row_bytes : 0;
 
-    size_t esz = logits_kind == LOGITS_BF16 ? 2 : 4;
-    bool vec = true;
-    if (logits_kind != LOGITS_NONE)
-        vec = aligned_to(logits, 16) && (row_stride * (int64_t)esz) % 16 == 0;
-    if (from_class) vec = vec && aligned_to(class_of_token, 16);
-
     const bool wb = tok_bits_out != nullptr;
     switch (logits_kind) {
         case LOGITS_NONE:
-            return dispatch_mask<LOGITS_NONE, true>(a, wb, vec, (int)grid, lds, stream);
+            return dispatch_mask<LOGITS_NONE, true>(a, wb, (int)grid, lds, stream);
         case LOGITS_BF16:
-            return from_class ? dispatch_mask<LOGITS_BF16, true>(a, wb, vec, (int)grid, lds, stream)
-                              : dispatch_mask<LOGITS_BF16, false>(a, wb, vec, (int)grid, lds, stream);
+            return from_class ? dispatch_mask<LOGITS_BF16, true>(a, wb, (int)grid, lds, stream)
+                              : dispatch_mask<LOGITS_BF16, false>(a, wb, (int)grid, lds, stream);
         default:
-            return from_class ? dispatch_mask<LOGITS_F32, true>(a, wb, vec, (int)grid, lds, stream)
-                              : dispatch_mask<LOGITS_F32, false>(a, wb, vec, (int)grid, lds, stream);
+            return from_class ? dispatch_mask<LOGITS_F32, true>(a, wb, (int)grid, lds, stream)
+                              : dispatch_mask<LOGITS_F32, false>(a, wb, (int)grid, lds, stream);
     }
 }
 

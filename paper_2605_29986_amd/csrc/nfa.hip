@@ -37,7 +37,9 @@ constexpr int kImageThreads = 1024;
 constexpr int kImageWaves = kImageThreads / 64;
 constexpr int kImageSets = 96;           // different successor sets of a byte that the walk shares
 constexpr int kImageSlots = 512;         // slots of the table in which a byte's sets are told apart (256 states at most)
-constexpr uint32_t kImageUnknown = 0, kImageWorkedOut = 1, kImageMany = 2, kImageReady = 3;  // kImageReady + how many
+constexpr int kImageBytes = 64;          // first bytes that a workgroup keeps the sets of
+constexpr int kImageGroup = 96;          // tokens of a workgroup at the most: they begin with fewer bytes than that
+constexpr uint32_t kImageUnknown = 0, kImageWorkedOut = 1, kImageMany = 2;  // ready: how many in bits 8.., the slot below
 
 template <int W>
 struct ImageLds {
@@ -46,10 +48,10 @@ struct ImageLds {
     static constexpr int kSetWords = kImageSets * W > kImageSlots + 64 ? kImageSets * W : kImageSlots + 64;
     __align__(16) uint32_t sets[kImageWaves][kSetWords];
     uint32_t members[kImageWaves][kImageSets];  // how many, and the first and the last of them
-    uint32_t state[256];                        // of the two tables below, per byte
-    uint32_t cursor;
-    uint8_t set_of[256][256];                   // [byte][start state]: number of its successor set
-    uint8_t first_with[256][kImageSets];        // [byte][set]: the first state that has it
+    uint32_t state[256];                        // per byte: whether and where the two tables below have it
+    uint32_t cursor, slots;
+    uint8_t set_of[kImageBytes][256];           // [slot][start state]: number of its successor set
+    uint8_t first_with[kImageBytes][kImageSets];  // [slot][set]: the first state that has it
 };
 
 // How many members a set has, the first and the last.
@@ -142,23 +144,35 @@ __device__ __forceinline__ uint64_t member_hash(uint32_t q, uint32_t W, uint32_t
 
 __device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup"); }
 
-// Tells the successor sets of byte b apart, by the whole wave: numbers them by the first state that has them.
+// Tells the successor sets of byte b apart, by the whole wave: numbers them by the first state that has them.  Returns
+// the byte's state.
 template <int W>
 __device__ __forceinline__ uint32_t number_sets(const NfaArgs &a, ImageLds<W> &L, uint32_t *scratch, int b) {
     const int lane = threadIdx.x & 63;
+    int slot = 0;
+    if (lane == 0) slot = (int)atomicAdd(&L.slots, 1u);
+    slot = __builtin_amdgcn_readfirstlane(slot);
+    if (slot >= kImageBytes) return kImageMany;
     uint32_t *table = scratch;                                                // [kImageSlots]: hash above the state
     uint8_t *number = reinterpret_cast<uint8_t *>(scratch + kImageSlots);     // [256]
     for (int i = lane; i < kImageSlots; i += 64) table[i] = ~0u;
     lds_order();
     const uint32_t *step = a.nfa + (size_t)b * a.S * W;
     uint32_t n = 0;
+    uint32_t ahead[W];  // the next states' rows, on their way while these are told apart
+#pragma unroll
+    for (int w = 0; w < W; ++w) ahead[w] = 0;
+    if (lane < a.S) add_row<W>(ahead, step + (size_t)lane * W);
     for (int q0 = 0; q0 < a.S; q0 += 64) {
         const int q = q0 + lane;
         const bool in = q < a.S;
         uint32_t row[W];
 #pragma unroll
-        for (int w = 0; w < W; ++w) row[w] = 0;
-        if (in) add_row<W>(row, step + (size_t)q * W);
+        for (int w = 0; w < W; ++w) {
+            row[w] = ahead[w];
+            ahead[w] = 0;
+        }
+        if (q + 64 < a.S) add_row<W>(ahead, step + (size_t)(q + 64) * W);
         uint32_t h = 0;
 #pragma unroll
         for (int w = 0; w < W; ++w) h = (h ^ row[w]) * 0x9E3779B1u + (h >> 15);
@@ -170,11 +184,13 @@ __device__ __forceinline__ uint32_t number_sets(const NfaArgs &a, ImageLds<W> &L
                 const uint32_t seen = atomicCAS(&table[at], ~0u, (h & ~0xFFu) | (uint32_t)q);
                 if (seen == ~0u) break;
                 if (((seen ^ h) >> 8) == 0u) {
-                    const uint32_t *other = step + (size_t)(seen & 0xFFu) * W;
-                    bool same = true;
+                    uint32_t other[W], differ = 0;
 #pragma unroll
-                    for (int w = 0; w < W; ++w) same = same && other[w] == row[w];
-                    if (same) {
+                    for (int w = 0; w < W; ++w) other[w] = 0;
+                    add_row<W>(other, step + (size_t)(seen & 0xFFu) * W);
+#pragma unroll
+                    for (int w = 0; w < W; ++w) differ |= other[w] ^ row[w];
+                    if (!differ) {
                         like = (int)(seen & 0xFFu);
                         break;
                     }
@@ -185,14 +201,14 @@ __device__ __forceinline__ uint32_t number_sets(const NfaArgs &a, ImageLds<W> &L
         if (in && like == q) {
             const uint32_t k = n + (uint32_t)__popcll(fresh & ((1ull << lane) - 1ull));
             number[q] = (uint8_t)k;
-            if (k < (uint32_t)kImageSets) L.first_with[b][k] = (uint8_t)q;
+            if (k < (uint32_t)kImageSets) L.first_with[slot][k] = (uint8_t)q;
         }
         n += (uint32_t)__popcll(fresh);
         lds_order();
-        if (in) L.set_of[b][q] = number[like];
+        if (in) L.set_of[slot][q] = number[like];
     }
     lds_order();
-    return n <= (uint32_t)kImageSets ? kImageReady + n : kImageMany;
+    return n <= (uint32_t)kImageSets ? (n << 8) | (uint32_t)slot : kImageMany;
 }
 
 // Up to 256 states.  A workgroup of sixteen waves takes `per_group` consecutive tokens, a wave one at a time; which
@@ -200,11 +216,14 @@ __device__ __forceinline__ uint32_t number_sets(const NfaArgs &a, ImageLds<W> &L
 // 32,000 tokens x 256 states: 154 us with a thread per (token, start state), bound by instruction issue (75.6 M wave
 // instructions); what is left is mostly writing the rows (262 MB, 45 us).
 template <int W>
-__global__ __launch_bounds__(kImageThreads) void nfa_image_kernel(NfaArgs a, int per_group) {
+__global__ __launch_bounds__(kImageThreads, 8) void nfa_image_kernel(NfaArgs a, int per_group) {
     __shared__ ImageLds<W> L;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid < 256) L.state[tid] = kImageUnknown;
-    if (tid == 0) L.cursor = 0;
+    if (tid == 0) {
+        L.cursor = 0;
+        L.slots = 0;
+    }
     __syncthreads();
     uint32_t *sets = L.sets[wave], *members = L.members[wave];
     const int group0 = (int)blockIdx.x * per_group, in_group = min(per_group, a.V - group0);
@@ -245,14 +264,14 @@ __global__ __launch_bounds__(kImageThreads) void nfa_image_kernel(NfaArgs a, int
             }
             lds_order();
         }
-        if (state >= kImageReady) {
-            const int n = (int)(state - kImageReady);
+        if (state > 0xFFu) {
+            const int n = (int)(state >> 8), slot = (int)(state & 0xFFu);
             for (int j0 = 0; j0 < n; j0 += 64) {
                 const int j = j0 + lane;
                 uint32_t set[W];
 #pragma unroll
                 for (int w = 0; w < W; ++w) set[w] = 0;
-                if (j < n) add_row<W>(set, a.nfa + b * matrix + (size_t)L.first_with[b][j] * W);
+                if (j < n) add_row<W>(set, a.nfa + b * matrix + (size_t)L.first_with[slot][j] * W);
                 set[W - 1] &= a.last_word_mask;
                 for (int64_t p = b0 + 1; p < b1; ++p) {
                     uint32_t any = 0;
@@ -271,7 +290,7 @@ __global__ __launch_bounds__(kImageThreads) void nfa_image_kernel(NfaArgs a, int
                 if (j0 + 64 < n) bytes = WaveBytes(a.tok_bytes, b0, b1);  // once more from the front
             }
             lds_order();
-            const uint8_t *set_of = L.set_of[b];
+            const uint8_t *set_of = L.set_of[slot];
             // the rows, as one run of 16-byte units (or words) over the lanes
             if (W % 4 == 0) {
                 constexpr int kPerRow = W / 4 > 0 ? W / 4 : 1;
@@ -401,9 +420,9 @@ __global__ void clear_u64_kernel(uint64_t *p, int n) {
 
 template <int W>
 int launch_nfa(const NfaArgs &a, int n_cu, hipStream_t stream) {
-    // a workgroup per compute unit (its LDS is what there is), the tokens spread evenly
-    const int64_t groups = std::min<int64_t>(n_cu, ceil_div(a.V, kImageWaves));
-    const int per_group = (int)ceil_div(a.V, groups);
+    // two workgroups per compute unit (their LDS is what there is), the tokens spread evenly
+    const int64_t groups = std::min<int64_t>(2 * n_cu, ceil_div(a.V, kImageWaves));
+    const int per_group = (int)std::min<int64_t>(kImageGroup, ceil_div(a.V, groups));
     hipLaunchKernelGGL(nfa_image_kernel<W>, dim3((unsigned)ceil_div(a.V, per_group)), dim3(kImageThreads), 0, stream, a,
                        per_group);
     return check_launch();
