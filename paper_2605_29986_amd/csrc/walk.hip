@@ -5,12 +5,13 @@
 //
 // Per call:  one kernel transposes the table and builds the per-first-byte image
 // tables (a workgroup per image row), then
-// one kernel in which a workgroup takes 64 consecutive tokens at a time, stages
+// one kernel in which a workgroup takes 32 consecutive tokens at a time, stages
 // their bytes in LDS, walks all (token, image state) pairs as one flat list of
 // independent lanes, reduces the hash in LDS and expands w through idx into the
-// stored signature rows with 16-byte stores.  Automata whose transposed table
-// fits next to that in LDS are walked from LDS, larger ones from the
-// L2-resident copy in the workspace.  Two variants of the call share these kernels:
+// stored signature rows with 16-byte stores.  The transposed table is read from its
+// L2-resident copy in the workspace, also where it would fit in LDS: so few of its entries are read
+// (32,000 tokens x 256 states: 867 K) that copying it there costs more (kernel 18.2 us with the table in
+// LDS, 11.7 without; on an automaton without structure the whole call 37.2 and 37.0).  Two variants of the call share these kernels:
 // cfgzip_signatures_composed (longer tokens continue the walk of a short token that is a
 // prefix of theirs; paper Appendix A, Lemma 1) and cfgzip_signatures_static (tables in
 // memory that belongs to the library, for callers that cannot allocate).
@@ -27,7 +28,7 @@ namespace {
 // native 16-byte vector (the nontemporal builtins do not take HIP's uint4 struct)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// table read from L2 (S > 256): threads per workgroup and tokens per chunk
+// threads per workgroup and tokens per chunk
 constexpr int kWalkThreads = 256;
 constexpr int kWalkChunkTokens = 32;  // (measured 16, 24, 32, 40, 48, 64: 32 is best when rows are stored, flat otherwise)
 
@@ -171,21 +172,14 @@ __global__ __launch_bounds__(1024) void tables_kernel(const uint16_t *__restrict
         for (uint32_t r = tid; r < n && r < kAccCap; r += 1024) wsum[(size_t)b * S + r] = acc[r];
 }
 
-template <bool LDS_TABLE>
-__global__ __launch_bounds__(LDS_TABLE ? 1024 : kWalkThreads) void signatures_kernel(WalkArgs a) {
-    extern __shared__ __align__(16) uint16_t dyn_lds[];  // [table S*256 if LDS_TABLE][w wcap]
+__global__ __launch_bounds__(kWalkThreads) void signatures_kernel(WalkArgs a) {
+    extern __shared__ __align__(16) uint16_t dyn_lds[];  // w: wcap entries when rows are expanded from it, else nothing
     __shared__ Batch B;
     __shared__ uint8_t ldsb[kByteCap];
     const int S = a.S;
-    if (LDS_TABLE) {
-        const int n16 = S * 32;  // S*512 bytes / 16
-        const uint4 *src = reinterpret_cast<const uint4 *>(a.T.Tt);
-        uint4 *dst = reinterpret_cast<uint4 *>(dyn_lds);
-        for (int i = threadIdx.x; i < n16; i += blockDim.x) dst[i] = src[i];
-    }
-    const uint16_t *tab = LDS_TABLE ? dyn_lds : a.T.Tt;
+    const uint16_t *tab = a.T.Tt;
     // the walk vectors go through LDS only when rows are expanded from them
-    uint16_t *w = (LDS_TABLE || a.sig_out) ? dyn_lds + (LDS_TABLE ? (size_t)S * 256 : 0) : nullptr;
+    uint16_t *w = a.sig_out ? dyn_lds : nullptr;
     const int lane = threadIdx.x & 63;
     const bool first_wave = threadIdx.x < 64;
     const bool vec = (S % 8) == 0 && (reinterpret_cast<uintptr_t>(a.sig_out) % 16) == 0;
@@ -195,7 +189,7 @@ __global__ __launch_bounds__(LDS_TABLE ? 1024 : kWalkThreads) void signatures_ke
         const int64_t t_end = min((int64_t)a.V, (chunk + 1) * a.chunk_tokens);
         int64_t tcur = chunk * a.chunk_tokens;
         while (tcur < t_end) {  // workgroup-uniform
-            __syncthreads();    // previous batch fully consumed (and the table loaded)
+            __syncthreads();    // previous batch fully consumed
             if (first_wave) {
                 const int64_t t = tcur + lane;
                 int64_t beg = 0, len = -1;
@@ -216,11 +210,19 @@ __global__ __launch_bounds__(LDS_TABLE ? 1024 : kWalkThreads) void signatures_ke
                 const int kk = batch_fill(B, a.T, a.tok_bytes, beg, other_launch ? -1 : len, a.wcap, 1, 1,
                                           parent, parent_len);
                 if (lane < kk) B.aux[lane] = (len >= 0 && !other_launch) ? 1 : 0;
+            } else if (a.phase == 0) {
+                // Meanwhile the other waves stage the bytes.  Consecutive tokens' bytes lie behind each other, so
+                // what the batch will hold (if it holds its bytes in LDS) is a prefix of this run.
+                const int64_t from = a.tok_off[tcur];
+                const int total = (int)min((int64_t)kByteCap, a.tok_off[t_end] - from);
+                for (int x = (int)threadIdx.x - 64; x < total; x += (int)blockDim.x - 64) ldsb[x] = a.tok_bytes[from + x];
             }
             __syncthreads();
             const int k = (int)min((int64_t)B.k, t_end - tcur);
-            batch_stage_bytes(B, a.tok_bytes, ldsb);
-            __syncthreads();
+            if (a.phase != 0) {  // the tokens of the other launch leave gaps
+                batch_stage_bytes(B, a.tok_bytes, ldsb);
+                __syncthreads();
+            }
             // the walk vectors are also kept for the class builder: token t at t * stride
             const uint32_t stride = walk_store_stride(S);
             uint16_t *keep = a.store.header ? a.store.wvec + (size_t)tcur * stride : nullptr;
@@ -377,17 +379,6 @@ ComposeWorkspace carve_compose_ws(void *ws, int32_t V) {
     return w;
 }
 
-constexpr size_t kLdsTableLimit = 128 * 1024;  // S <= 256
-
-int device_cu_count(int *out) {
-    int dev = 0;
-    CFGZIP_TRY(check_hip(hipGetDevice(&dev)));
-    int n = 0;
-    CFGZIP_TRY(check_hip(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev)));
-    *out = n > 0 ? n : 256;
-    return CFGZIP_OK;
-}
-
 // Layout of the signature workspace.
 struct SigWorkspace {
     uint16_t *Tt;
@@ -489,44 +480,22 @@ int run_signatures(const uint8_t *tok_bytes, const int64_t *tok_off, int32_t V, 
     a.hash_out = hash_out;
     CFGZIP_TRY(prepare_tables(table, S, hash_seed, hash_out != nullptr, store_V, ws, &a.T, &a.store, stream));
 
-    int n_cu = 256;
-    CFGZIP_TRY(device_cu_count(&n_cu));
-    const bool lds_table = (size_t)S * 512 <= kLdsTableLimit;
-    a.chunk_tokens = lds_table ? kBatchTokens : kWalkChunkTokens;
+    a.chunk_tokens = kWalkChunkTokens;
     const int64_t n_chunks = ceil_div(V, a.chunk_tokens);
     // the signatures kernel walks one token at a time in the worst case: S entries suffice
     a.wcap = std::max(kMinWalkCap, (S + kWalkGroup - 1) / kWalkGroup * kWalkGroup);
-    if (lds_table) {
-        const size_t dyn = (size_t)S * 512 + (size_t)a.wcap * 2;
-        auto kern = signatures_kernel<true>;
-        if (dyn > 48 * 1024)
-            CFGZIP_TRY(check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     (int)dyn)));
-        // loading the table costs a workgroup about as much as walking a few batches
-        const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(2, (150 * 1024) / (dyn + 8192)));
-        const int64_t grid = std::min<int64_t>(ceil_div(n_chunks, 2), (int64_t)n_cu * per_cu);
-        for (int phase = compose_ws ? 1 : 0; phase <= (compose_ws ? 2 : 0); ++phase) {
-            a.phase = phase;
-            hipLaunchKernelGGL(kern, dim3((unsigned)std::max<int64_t>(1, grid)), dim3(1024), dyn, stream, a);
-            CFGZIP_TRY(check_launch());
-        }
-    } else {
-        const size_t dyn = sig_out ? (size_t)a.wcap * 2 : 0;
-        if (!sig_out) a.wcap = 0x3FFFFFFF;  // no LDS buffer bounds a batch's walks
-        auto kern = signatures_kernel<false>;
-        if (dyn > 48 * 1024)
-            CFGZIP_TRY(check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     (int)dyn)));
-        // one workgroup per chunk: the hardware hands out chunks as workgroups retire, which
-        // balances chunks of very different cost
-        const int64_t grid = std::min<int64_t>(n_chunks, 0x7FFFFFFF);
-        for (int phase = compose_ws ? 1 : 0; phase <= (compose_ws ? 2 : 0); ++phase) {
-            a.phase = phase;
-            hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kWalkThreads), dyn, stream, a);
-            CFGZIP_TRY(check_launch());
-        }
+    const size_t dyn = sig_out ? (size_t)a.wcap * 2 : 0;
+    if (!sig_out) a.wcap = 0x3FFFFFFF;  // no LDS buffer bounds a batch's walks
+    if (dyn > 48 * 1024)
+        CFGZIP_TRY(check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(signatures_kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn)));
+    // one workgroup per chunk: the hardware hands out chunks as workgroups retire, which
+    // balances chunks of very different cost
+    const int64_t grid = std::min<int64_t>(n_chunks, 0x7FFFFFFF);
+    for (int phase = compose_ws ? 1 : 0; phase <= (compose_ws ? 2 : 0); ++phase) {
+        a.phase = phase;
+        hipLaunchKernelGGL(signatures_kernel, dim3((unsigned)grid), dim3(kWalkThreads), dyn, stream, a);
+        CFGZIP_TRY(check_launch());
     }
     return CFGZIP_OK;
 }
