@@ -123,6 +123,8 @@ def _check(fn: str, rc: int) -> None:
 
 
 def _dev(t: torch.Tensor, dtype, name: str) -> int:
+    if type(t) is torch.Tensor and t.dtype is dtype and t.is_cuda and t.is_contiguous():
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a tensor in GPU memory")
     if t.dtype != dtype:
@@ -132,8 +134,16 @@ def _dev(t: torch.Tensor, dtype, name: str) -> int:
     return t.data_ptr()
 
 
+# The handle of the current stream without the stream object around it: of a call that launches one small kernel
+# (11.2 us) torch.cuda.current_stream() took 2.7 us, this takes 0.2.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and _current_device is not None:
+            return _raw_stream(_current_device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
@@ -331,7 +341,10 @@ def cfgzip_decode_step(logits: torch.Tensor, cls_bits: torch.Tensor, class_of_to
     if rep_of_class.numel() != C or class_of_token.numel() != V:
         raise ValueError("class_of_token must be [V] and rep_of_class [C]")
     if rep_out is None:
-        rep_out = torch.empty((B,), dtype=torch.int32, device=tok.device)
+        if tok.dim() == 1 and tok.dtype is torch.int32:
+            rep_out = torch.empty_like(tok)
+        else:
+            rep_out = torch.empty((B,), dtype=torch.int32, device=tok.device)
     rc = lib.cfgzip_decode_step(
         logits.data_ptr(), dt, B, V, int(logits.stride(0)), _dev(cls_bits, torch.int32, "cls_bits"),
         _dev(class_of_token, torch.int32, "class_of_token"), int(C),
