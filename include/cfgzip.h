@@ -99,7 +99,7 @@ int cfgzip_version(void);
  *   ws         cfgzip_signatures_workspace_bytes(V, S) bytes, 256-byte aligned.  After the call
  *              it holds, besides tables, the compressed form in which the signatures were
  *              computed (per token the states reached from the distinct states its first
- *              byte leaves; up to 512 bytes per token).  Handing the untouched workspace
+ *              byte leaves; up to 1,024 bytes per token).  Handing the untouched workspace
  *              to cfgzip_build_classes lets it compare those instead of walking again.
  */
 size_t cfgzip_signatures_workspace_bytes(int32_t V, int32_t S);

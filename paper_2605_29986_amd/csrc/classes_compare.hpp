@@ -90,12 +90,12 @@ __device__ __forceinline__ bool store_other_row_differ(const StoreSource &s, int
     // store that has not overflowed; the bound keeps a corrupt index inside the staged vector
     const uint32_t na = stride, nb = stride;
     {
-        // lanes 0..31 copy vector a, lanes 32..63 vector b, 16 bytes each (stride <= 256 entries)
-        const uint32_t half = lane & 31;
+        // lanes 0..31 copy vector a, lanes 32..63 vector b, 16 bytes each and round
         const bool second = lane >= 32;
         const uint16_t *src = s.store.wvec + (size_t)(second ? tb : ta) * stride;
-        if (half * 8 < stride && !(second ? idb : ida))
-            reinterpret_cast<uint4 *>(second ? lb : la)[half] = reinterpret_cast<const uint4 *>(src)[half];
+        if (!(second ? idb : ida))
+            for (uint32_t u = lane & 31; u * 8 < stride; u += 32)
+                reinterpret_cast<uint4 *>(second ? lb : la)[u] = reinterpret_cast<const uint4 *>(src)[u];
     }
     // the staged vectors are read below as 16-bit entries by other lanes of this wave
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

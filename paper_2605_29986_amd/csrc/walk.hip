@@ -79,14 +79,27 @@ __global__ __launch_bounds__(1024) void tables_kernel(const uint16_t *__restrict
     if (wsum)
         for (int i = tid; i < kAccCap && i < S; i += 1024) acc[i] = 0ull;
     __syncthreads();
+    // the first 4,096 states of the column stay in registers (all of them, for most automata)
+    constexpr int kHeld = 4;
+    uint32_t held[kHeld];
     if (b < 256) {
-        for (int q = tid; q < S; q += 1024) {
-            const uint32_t s = table[(size_t)q * 256 + b];
+#pragma unroll
+        for (int u = 0; u < kHeld; ++u) {
+            const int q = tid + 1024 * u;
+            held[u] = q < S ? (uint32_t)table[(size_t)q * 256 + b] : 0u;
+        }
+        auto enter = [&](int q, uint32_t s) {
             col[q] = (uint16_t)s;
             // most states of a lexer's column are the same few: look before the atomic
             if (!((present[s >> 5] >> (s & 31)) & 1u)) atomicOr(&present[s >> 5], 1u << (s & 31));
-        }
+        };
+#pragma unroll
+        for (int u = 0; u < kHeld; ++u)
+            if (tid + 1024 * u < S) enter(tid + 1024 * u, held[u]);
+        for (int q = tid + 1024 * kHeld; q < S; q += 1024) enter(q, (uint32_t)table[(size_t)q * 256 + b]);
     } else {
+#pragma unroll
+        for (int u = 0; u < kHeld; ++u) held[u] = (uint32_t)(tid + 1024 * u);
         for (int w = tid; w < kStateWords; w += 1024) {
             const int lo = w * 32;
             present[w] = lo + 32 <= S ? 0xFFFFFFFFu : (lo < S ? (1u << (S - lo)) - 1u : 0u);
@@ -132,10 +145,8 @@ __global__ __launch_bounds__(1024) void tables_kernel(const uint16_t *__restrict
     if (wsum)
         for (uint32_t r = kAccCap + tid; r < n; r += 1024) wsum[(size_t)b * S + r] = 0ull;
     __syncthreads();
-    for (int q0 = 0; q0 < S; q0 += 1024) {  // whole waves go round together: they vote below
-        const int q = q0 + tid;
+    auto rank_state = [&](int q, uint32_t s) {  // whole waves together: they vote below
         const bool in = q < S;
-        const uint32_t s = in ? state_of(q) : 0u;
         const uint32_t r = wprefix[s >> 5] + __popc(present[s >> 5] & ((1u << (s & 31)) - 1u));
         if (in) idx[(size_t)b * S + q] = (uint16_t)r;
         if (wsum) {
@@ -152,9 +163,7 @@ __global__ __launch_bounds__(1024) void tables_kernel(const uint16_t *__restrict
                 const uint32_t r0 = __shfl(r, leader, 64);
                 const bool mine = pending && r == r0;
                 if (__popcll(__ballot(mine)) < 4) break;  // not worth the reduction
-                unsigned long long sum = mine ? a : 0ull;
-#pragma unroll
-                for (int off = 1; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
+                const unsigned long long sum = wave_sum_u64(mine ? a : 0ull);
                 if (mine) pending = false;
                 if (lane == leader) {
                     if (r0 < kAccCap) atomicAdd(&acc[r0], sum);
@@ -166,7 +175,11 @@ __global__ __launch_bounds__(1024) void tables_kernel(const uint16_t *__restrict
                 else atomicAdd(reinterpret_cast<unsigned long long *>(wsum + (size_t)b * S + r), a);
             }
         }
-    }
+    };
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u)
+        if (1024 * u < S) rank_state(tid + 1024 * u, tid + 1024 * u < S ? held[u] : 0u);
+    for (int q0 = 1024 * kHeld; q0 < S; q0 += 1024) rank_state(q0 + tid, q0 + tid < S ? state_of(q0 + tid) : 0u);
     __syncthreads();
     if (wsum)
         for (uint32_t r = tid; r < n && r < kAccCap; r += 1024) wsum[(size_t)b * S + r] = acc[r];

@@ -27,6 +27,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace cfgzip {
 
 // Tt is over-allocated by this many entries so that a table entry >= S (a
@@ -62,7 +64,9 @@ struct WalkStore {
     uint32_t pad[3];
 };
 constexpr uint32_t kWalkStoreMagic = 0xCF621A1Cu;
-constexpr int kWalkStoreMaxStride = 256;  // entries kept per token at most (512 bytes)
+// Entries kept per token at most (1 KB).  A byte of a 4,096-state lexer leaves up to about 260 states: at 256 one such
+// byte made the whole store unusable and the class build walk every token again (318 us instead of 232).
+constexpr int kWalkStoreMaxStride = 512;
 __host__ __device__ inline uint32_t walk_store_stride(int32_t S) {
     const uint32_t s8 = ((uint32_t)S + 7u) & ~7u;
     return s8 < (uint32_t)kWalkStoreMaxStride ? s8 : (uint32_t)kWalkStoreMaxStride;
@@ -113,6 +117,23 @@ __device__ __forceinline__ int wave_inclusive_sum(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, true);  // row_bcast:15 into rows 1 and 3
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, true);  // row_bcast:31 into rows 2 and 3
     return v;
+}
+
+// Sum over the 64 lanes of a wave, all of them active, the same way.
+__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
+    auto moved = [](uint64_t x, auto ctrl, auto rows) -> uint64_t {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, decltype(ctrl)::value, decltype(rows)::value, 0xF, true);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), decltype(ctrl)::value, decltype(rows)::value, 0xF, true);
+        return ((uint64_t)hi << 32) | lo;
+    };
+    v += moved(v, std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{});
+    v += moved(v, std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{});
+    v += moved(v, std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{});
+    v += moved(v, std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{});
+    v += moved(v, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});
+    v += moved(v, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, 63), hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), 63);
+    return ((uint64_t)hi << 32) | lo;
 }
 
 // A batch of up to kBatchTokens byte strings that a workgroup walks together.
@@ -221,7 +242,7 @@ __device__ __forceinline__ void batch_stage_bytes(const Batch &B, const uint8_t 
 // while the current reads are outstanding.  With HASH, adds the group's part of
 // sum_j wsum[row][j] * w[j] to B.hash[m] (order-free).  `keep` (or null) is where slot 0's
 // walk vector is kept, slot m's follows keep_stride entries on (keep_stride a multiple of
-// kWalkGroup; a vector longer than that is cut off).
+// kWalkGroup; a vector longer than that is not kept).
 // `kept` (or null): kept walk vectors of finished tokens, kept_stride entries apart, from which
 // the slots with a parent start.
 template <bool LDS_BYTES, bool HASH>
@@ -292,7 +313,7 @@ __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t 
         // region in w starts at a multiple of the group size, a kept vector at a multiple of 8 entries)
         const uint2 packed = make_uint2(cur[0] | (cur[1] << 16), cur[2] | (cur[3] << 16));
         if (w) *reinterpret_cast<uint2 *>(w + (uint32_t)B.wstart[m] + j0) = packed;  // null: only hash and `keep` are wanted
-        if (keep && j0 < keep_stride) {
+        if (keep && n <= keep_stride) {  // (a vector that does not fit makes the store unusable: nothing of it is kept)
             uint16_t *kd = keep + (size_t)m * keep_stride + j0;
             *reinterpret_cast<uint2 *>(kd) = packed;
             // a kept vector is compared 8 entries at a time: the token's last group also zeroes

@@ -50,6 +50,21 @@ def test_sizes_and_shapes(lib, V, shape):
         assert C == 1
 
 
+@pytest.mark.parametrize("n", [255, 256, 257, 264, 511, 512, 513])
+def test_widest_images_that_are_kept(lib, n):
+    """Bytes that leave n of 600 states: up to 512 states per token are kept for the comparison, beyond that the
+    builder walks again."""
+    print(f"case n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    S = 600
+    table = rng.integers(0, S, size=(S, 256)).astype(np.uint16)
+    for b in range(8):
+        table[:, b] = rng.permutation(S)[:n][np.arange(S) % n]
+    toks = [rng.integers(0, 8, size=int(k), dtype=np.uint8).tobytes() for k in rng.integers(0, 4, size=700)]
+    _check_build(lib, vocab_from_tokens(toks), table)
+    _check_build(lib, vocab_from_tokens(toks), table, stored=False)
+
+
 @pytest.mark.parametrize("stored", [True, False])
 def test_colliding_hashes_are_settled(lib, stored):
     vocab, table = _case("last byte", 1500, 5)
