@@ -145,11 +145,13 @@ __device__ bool production_valid(const Grammar &g, int i, int &off, int &end) {
 }
 
 // A production as the displacement kernels read it.
-__device__ void write_records(const Grammar &g, const GrammarWorkspace &w, int i, int off, int len) {
+__device__ unsigned long long write_records(const Grammar &g, const GrammarWorkspace &w, int i, int off, int len) {
     uint32_t sym[4] = {0, 0, 0, 0};
     for (int k = 0; k < min(len, 4); ++k) sym[k] = g.body[off + k];
     w.prod_short[i] = make_uint4(sym[0] | (sym[1] << 16), sym[2] | (sym[3] << 16), (uint32_t)len, (uint32_t)off);
-    w.prod_packed[i] = pack_production(g, i, off, len);
+    const unsigned long long packed = pack_production(g, i, off, len);
+    w.prod_packed[i] = packed;
+    return packed;
 }
 
 // One thread per production and per symbol: checks the rules the other kernels rely on
@@ -186,14 +188,17 @@ __global__ void grammar_index_kernel(Grammar g, GrammarWorkspace w) {
 
 // Bytes with the same productions (heads and bodies) lead every set of configurations to the same set: byte_like[b]
 // is the first of them.  By one workgroup of at least 256 threads; a hash of all productions of a byte picks the
-// candidate, the productions decide.  byte_off: first production of every byte (and P), readable by everybody.
-__device__ void find_like_bytes(const Grammar &g, const GrammarWorkspace &w, const int32_t *byte_off, uint32_t *hash) {
+// candidate, the productions decide.  byte_off: first production of every byte (and P), packed(i): production i in
+// one word, both readable by everybody.
+template <typename Packed>
+__device__ __forceinline__ void find_like_bytes(const Grammar &g, const GrammarWorkspace &w, const int32_t *byte_off, uint32_t *hash,
+                                                const Packed &packed) {
     const int tid = threadIdx.x;
     if (tid < 256) hash[tid] = (uint32_t)(byte_off[tid + 1] - byte_off[tid]);
     __syncthreads();
     for (int i = tid; i < g.P; i += blockDim.x) {
-        uint32_t h = g.head[i] * 0x01000193u;
-        for (int k = g.body_off[i]; k < g.body_off[i + 1]; ++k) h = (h ^ (g.body[k] + 1u)) * 0x01000193u;
+        const unsigned long long p = packed(i);  // of a long body only that it is one: the comparison tells them apart
+        const uint32_t h = ((uint32_t)p ^ ((uint32_t)(p >> 32) * 0x85EBCA6Bu)) * 0x9E3779B1u;
         const int b = g.byte[i];
         atomicAdd(&hash[b], (h ^ (h >> 15)) * (2u * (uint32_t)(i - byte_off[b]) + 1u));
     }
@@ -212,13 +217,19 @@ __device__ void find_like_bytes(const Grammar &g, const GrammarWorkspace &w, con
     if (like != tid) {
         const int lo = byte_off[tid], n = byte_off[tid + 1] - lo, other = byte_off[like];
         bool same = byte_off[like + 1] - other == n;
-        for (int i = 0; same && i < n; ++i) {
-            same = w.prod_packed[lo + i] == w.prod_packed[other + i];  // all there is of a short production
-            const int len = body_len(g, lo + i);
-            if (same && len > 4) {
-                same = body_len(g, other + i) == len;
-                for (int k = 0; same && k < len; ++k) same = g.body[g.body_off[lo + i] + k] == g.body[g.body_off[other + i] + k];
+        bool any_long = false;
+        if (same)
+#pragma unroll 4
+            for (int i = 0; i < n; ++i) {  // to the end: reads that wait for nothing
+                const unsigned long long p = packed(lo + i);
+                same = same & (p == packed(other + i));
+                any_long = any_long | (packed_length(p) == kLongBody);
             }
+        for (int i = 0; any_long && same && i < n; ++i) {
+            const int len = body_len(g, lo + i);
+            if (len <= 4) continue;
+            same = body_len(g, other + i) == len;
+            for (int k = 0; same && k < len; ++k) same = g.body[g.body_off[lo + i] + k] == g.body[g.body_off[other + i] + k];
         }
         if (!same) like = tid;
     }
@@ -228,7 +239,18 @@ __device__ void find_like_bytes(const Grammar &g, const GrammarWorkspace &w, con
 __global__ __launch_bounds__(1024) void byte_like_kernel(Grammar g, GrammarWorkspace w) {
     __shared__ __align__(16) uint32_t hash[256];
     if (w.hdr->invalid) return;  // the same for every thread
-    find_like_bytes(g, w, w.byte_off, hash);
+    find_like_bytes(g, w, w.byte_off, hash, [&](int i) { return w.prod_packed[i]; });
+}
+
+// OR over the 64 lanes (all of them active), the same for every lane.
+__device__ __forceinline__ uint32_t wave_or32(uint32_t v) {
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, true);
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
 // All tables of a small grammar in one launch, by one workgroup with the two matrices in LDS (eleven launches
@@ -240,6 +262,7 @@ __global__ __launch_bounds__(1024) void grammar_tables_kernel(Grammar g, Grammar
     __shared__ uint32_t reach[2][kSmallSymbols * kSmallWords];
     __shared__ uint32_t adj[kSmallSymbols * kSmallWords];
     __shared__ uint32_t unary[kSmallWords];
+    __shared__ unsigned long long packed[kSmallProductions];
     __shared__ int32_t byte_off[257];
     __shared__ __align__(16) uint32_t hash[256];
     __shared__ int invalid;
@@ -265,7 +288,7 @@ __global__ __launch_bounds__(1024) void grammar_tables_kernel(Grammar g, Grammar
         if (i == g.P - 1)
             for (int x = b + 1; x <= 256; ++x) byte_off[x] = g.P;
         if (i == 0 || g.byte[i - 1] != b || g.head[i - 1] != A) w.pair_first[(size_t)b * g.N + A] = i + 1;
-        write_records(g, w, i, off, end - off);
+        packed[i] = write_records(g, w, i, off, end - off);
         if (off == end) {
             atomicOr(&unary[A >> 5], 1u << (A & 31));
         } else {
@@ -279,18 +302,27 @@ __global__ __launch_bounds__(1024) void grammar_tables_kernel(Grammar g, Grammar
         for (int i = tid; i < words; i += threads) w.adj[i] = 0;
         return;
     }
-    // closure by doubling: every row holds its own symbol, so ceil(log2 N) rounds reach every path
+    // closure by doubling: every row holds its own symbol, so ceil(log2 N) rounds reach every path.  A wave per row, a
+    // lane per pair of symbols of the row: what they reach is ORed together by register moves.
     int cur = 0;
     for (int span = 1; span < g.N; span <<= 1, cur ^= 1) {
-        for (int i = tid; i < words; i += threads) {
-            const int X = i / g.W, word = i - X * g.W;
-            uint32_t acc = 0;
-            for (int v = 0; v < g.W; ++v)
-                for (uint32_t bits = reach[cur][X * g.W + v]; bits; bits &= bits - 1) {
-                    const int Y = v * 32 + __ffs(bits) - 1;
-                    acc |= reach[cur][Y * g.W + word];
+        for (int X = tid >> 6; X < g.N; X += threads >> 6) {
+            uint32_t acc[kSmallWords];
+#pragma unroll
+            for (int word = 0; word < kSmallWords; ++word) acc[word] = 0;
+#pragma unroll
+            for (int h = 0; h < kSmallSymbols / 64; ++h) {
+                const int Y = (tid & 63) + 64 * h;
+                if (Y < g.N && ((reach[cur][X * g.W + (Y >> 5)] >> (Y & 31)) & 1u))
+                    for (int word = 0; word < kSmallWords; ++word)
+                        if (word < g.W) acc[word] |= reach[cur][Y * g.W + word];
+            }
+#pragma unroll
+            for (int word = 0; word < kSmallWords; ++word)
+                if (word < g.W) {  // the same for every lane
+                    const uint32_t all = wave_or32(acc[word]);
+                    if ((tid & 63) == 0) reach[cur ^ 1][X * g.W + word] = all;
                 }
-            reach[cur ^ 1][i] = acc;
         }
         __syncthreads();
     }
@@ -304,7 +336,7 @@ __global__ __launch_bounds__(1024) void grammar_tables_kernel(Grammar g, Grammar
             }
         }
     if (tid < 257) w.byte_off[tid] = byte_off[tid];
-    find_like_bytes(g, w, byte_off, hash);
+    find_like_bytes(g, w, byte_off, hash, [&](int i) { return packed[i]; });
     __syncthreads();
     for (int i = tid; i < words; i += threads) w.adj[i] = adj[i];
 }

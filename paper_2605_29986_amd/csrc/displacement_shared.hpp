@@ -43,6 +43,7 @@ constexpr int kShPool = 6144;       // configurations of all sets (24 KB)
 constexpr int kShOut = 18432;       // row entries of all sets written so far (36 KB)
 constexpr int kShProds = 1024;      // productions kept in LDS (8 KB); of a larger grammar none are
 constexpr int kShAdj = 512;         // words of the relation kept in LDS (2 KB); of a larger one none are
+constexpr int kShPairs = 2048;      // (byte, symbol) pairs whose productions are looked up directly (4 KB)
 constexpr int kShRound = 8;         // tokens a wave takes at a time: few, so that few wait for a long one
 constexpr int kShBytes = 256;       // token bytes of a wave's round kept in LDS; a round with more reads memory
 constexpr int kShSeen = 256;        // slots of a wave's table of the successors found so far: at most half full
@@ -100,6 +101,11 @@ struct SharedLds {
     u64 prods[kShProds];
     uint32_t adj[kShAdj];
     uint32_t byte_off[257];
+    uint16_t pair[kShPairs];  // [number of the byte among those with productions of their own][symbol]: first production
+                              // (10 bits), how many (6)
+    uint8_t byte_number[256];
+    uint32_t own[8];          // bytes that are their own byte_like
+    uint32_t pairs_kept;      // whether `pair` holds what the productions say
     uint32_t pool_top, out_top, cursor;
     uint8_t byte_like[256];  // the first byte with the same productions
     uint8_t bytes[kShWaves][kShBytes];  // already as byte_like has them
@@ -173,8 +179,7 @@ __device__ __forceinline__ int sh_claim(SharedLds &L, uint32_t set, uint32_t lik
     const uint32_t key = (set << 8) | like;
     uint32_t at = next_slot(key);
     for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShNext - 1)) {
-        uint32_t seen = lds_look(&L.next[at]);
-        if (seen == kNextEmpty) seen = atomicCAS(&L.next[at], kNextEmpty, (key << kNextBits) | kWorkedOut);
+        const uint32_t seen = atomicCAS(&L.next[at], kNextEmpty, (key << kNextBits) | kWorkedOut);
         if (seen == kNextEmpty) return (int)at;
         if ((seen >> kNextBits) == key) return -1;
     }
@@ -286,6 +291,8 @@ __device__ __forceinline__ uint32_t sh_step(const DisplacementArgs &a, SharedLds
     const int n = (int)set_size(w);
     const uint32_t *configs = L.pool + set_at(w);
     const int lo = (int)L.byte_off[ch], hi = (int)L.byte_off[ch + 1], per = hi - lo;
+    const bool pairs_kept = L.pairs_kept != 0u;
+    const uint32_t byte_number = L.byte_number[ch];
     const bool prods_here = g.P <= kShProds, adj_here = g.N * g.W <= kShAdj;
     auto prod = [&](int i) -> u64 { return prods_here ? L.prods[i] : a.prod_packed[i]; };
     const u64 below = (1ull << lane) - 1ull;
@@ -303,22 +310,28 @@ __device__ __forceinline__ uint32_t sh_step(const DisplacementArgs &a, SharedLds
         const int c = c0 + lane;
         const uint32_t config = c < n ? configs[c] : 0u, stack = sh_stack(config);
         uint32_t top = 0;
-        int i = hi;
-        if (stack) {
-            top = cell_symbol(lds_look(&L.cells[stack - 1]));
-            i = lo;
-            for (int count = per; count > 0;) {  // the first whose head is not below `top`
-                const int half = count >> 1;
-                const bool right = packed_head(prod(i + half)) < top;
-                i = right ? i + half + 1 : i;
-                count = right ? count - half - 1 : half;
+        if (stack) top = cell_symbol(lds_look(&L.cells[stack - 1]));
+        if (pairs_kept) {
+            const uint32_t e = stack ? L.pair[byte_number * (uint32_t)g.N + top] : 0u;
+            const int first = (int)(e & 0x3FFu), count = (int)(e >> 10);
+            for (int k = 0; __ballot(k < count); ++k) list(k < count, c, first + k);
+        } else {
+            int i = hi;
+            if (stack) {
+                i = lo;
+                for (int count = per; count > 0;) {  // the first whose head is not below `top`
+                    const int half = count >> 1;
+                    const bool right = packed_head(prod(i + half)) < top;
+                    i = right ? i + half + 1 : i;
+                    count = right ? count - half - 1 : half;
+                }
             }
-        }
-        for (;;) {
-            const bool on = i < hi && packed_head(prod(i)) == top;
-            if (!__ballot(on)) break;
-            list(on, c, i);
-            i = on ? i + 1 : hi;
+            for (;;) {
+                const bool on = i < hi && packed_head(prod(i)) == top;
+                if (!__ballot(on)) break;
+                list(on, c, i);
+                i = on ? i + 1 : hi;
+            }
         }
         const bool empty = c < n && !stack;
         const u64 mask = __ballot(empty);
@@ -530,10 +543,39 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
         if (a.g.N * a.g.W <= kShAdj)
             for (int i = tid; i < a.g.N * a.g.W; i += kShThreads) L.adj[i] = a.adj[i];
     }
+    if (tid < 8) L.own[tid] = 0;
+    for (int i = tid; i < kShPairs; i += kShThreads) L.pair[i] = 0;
     if (tid == 0) {
         L.pool_top = 0;
         L.out_top = 0;
         L.cursor = 0;
+    }
+    __syncthreads();
+    if (!invalid && tid < 256 && L.byte_like[tid] == tid) atomicOr(&L.own[tid >> 5], 1u << (tid & 31));
+    __syncthreads();
+    {
+        // the productions of a (byte, symbol) lie behind each other: where, if all of this fits
+        int own = 0;
+        for (int w = 0; w < 8; ++w) own += __popc(L.own[w]);
+        const bool fits = !invalid && a.g.P <= kShProds && own * a.g.N <= kShPairs;
+        if (tid == 0) L.pairs_kept = fits ? 1u : 0u;
+        if (tid < 256) {
+            int number = 0;
+            for (int w = 0; w < (tid >> 5); ++w) number += __popc(L.own[w]);
+            L.byte_number[tid] = (uint8_t)(number + __popc(L.own[tid >> 5] & ((1u << (tid & 31)) - 1u)));
+        }
+        __syncthreads();
+        if (fits)
+            for (int i = tid; i < a.g.P; i += kShThreads) {
+                const uint32_t b = a.g.byte[i], head = packed_head(L.prods[i]);
+                if (L.byte_like[b] != b) continue;
+                const int lo = (int)L.byte_off[b], hi = (int)L.byte_off[b + 1];
+                if (i > lo && packed_head(L.prods[i - 1]) == head) continue;
+                int end = i + 1;
+                while (end < hi && packed_head(L.prods[end]) == head) ++end;
+                if (end - i < 64) L.pair[L.byte_number[b] * (uint32_t)a.g.N + head] = (uint16_t)(i | ((end - i) << 10));
+                else L.pairs_kept = 0;  // more than six bits
+            }
     }
     __syncthreads();
     uint32_t *work = L.work[wave], *seen = L.seen[wave];
