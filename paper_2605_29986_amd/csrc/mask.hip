@@ -45,17 +45,9 @@ __device__ __forceinline__ void store16(void *p, u32x4 v) {
     __builtin_nontemporal_store(v, reinterpret_cast<u32x4_any *>(p));
 }
 
-// The same store written through the L2 cache to the memory side: 16 bytes at `offset` bytes into a 16-byte aligned
-// row (the row the same for the whole wave).
-__device__ __forceinline__ void store16_through(void *row, uint32_t offset, u32x4 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(row, 0, -1, 0x00027000), (int)offset, 0,
-                                           16 /* sc1 */);
-}
-
 struct MaskArgs {
     void *logits;
     int64_t row_stride;  // elements
-    bool through;        // how masked logits are stored (see kThroughBytes)
     int32_t B, V;
     const int32_t *bits_in;  // class bits [B][Wc] or token bits [B][Wv]
     int32_t Wc, Wv;
@@ -183,11 +175,6 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
     if (full) {
         if (LOGITS == LOGITS_BF16) {
             uint16_t *base = reinterpret_cast<uint16_t *>(a.logits) + (int64_t)r0 * a.row_stride + col0;
-            auto put = [&](int r, u32x4 v) {
-                if (a.through)
-                    store16_through(reinterpret_cast<uint16_t *>(a.logits) + (int64_t)(r0 + r) * a.row_stride, 2u * (uint32_t)col0, v);
-                else store16(base + (int64_t)r * a.row_stride, v);
-            };
             auto masked = [](u32x4 x, uint32_t m) -> u32x4 {
                 u32x4 y;
                 y.x = select_bf16_pair(x.x, m & 3u);
@@ -204,13 +191,13 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
 #pragma unroll
                 for (int u = 0; u < kUnroll; ++u) {
                     const uint32_t m = row_mask(r + u);
-                    put(r + u, masked(x[u], m));
+                    store16(base + (int64_t)(r + u) * a.row_stride, masked(x[u], m));
                     store_bits(r + u, m);
                 }
             }
             for (; r < nrows; ++r) {
                 const uint32_t m = row_mask(r);
-                put(r, masked(load16(base + (int64_t)r * a.row_stride), m));
+                store16(base + (int64_t)r * a.row_stride, masked(load16(base + (int64_t)r * a.row_stride), m));
                 store_bits(r, m);
             }
         } else {  // fp32: two 16-byte accesses per thread and row
@@ -294,14 +281,6 @@ __global__ void map_to_rep_kernel(const int32_t *tok, int32_t B, const int32_t *
 
 constexpr size_t kMaxLds = 160 * 1024;
 
-// Logits of up to this many bytes are stored through the L2 cache, larger ones as a stream past it.  A serving loop
-// masks what its LM head has just written, so up to about half of the 256 MB memory-side cache the logits are there.
-// Batch 256 x 128,256 bf16 (66 MB), a step: 24.1 us as a stream and 21.1 us through (1 to 3 buffers in turn); where
-// eight buffers in turn (525 MB) come from HBM each time, 24.6 and 25.5 us.  Batch 128: 13.5 and 12.3, eight buffers
-// 14.1 and 13.0.  bf16 only: a wave's store there is 1 KB in one run, while each of the two stores of an fp32 row
-// touches every other 16 bytes, and half lines written through cost more (batch 64: 20.3 us as a stream, 23.4 through).
-constexpr int64_t kThroughBytes = 128 << 20;
-
 template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS>
 int launch_mask(const MaskArgs &args, int grid, size_t lds_bytes, hipStream_t stream) {
     auto kern = mask_kernel<LOGITS, FROM_CLASS, WRITE_BITS>;
@@ -366,8 +345,6 @@ int run_mask(void *logits, int logits_kind, int32_t B, int32_t V, int64_t row_st
     a.class_of_token = class_of_token;
     a.tok_bits_out = tok_bits_out;
 
-    a.through = logits_kind == LOGITS_BF16 && B <= kThroughBytes / 2 / row_stride && aligned_to(logits, 16) &&
-                row_stride % 8 == 0;
     size_t row_bytes = (size_t)a.Wc * 4;
     // Measured on MI355X at batch 256 x 128,256 bf16: small row chunks (many workgroups, two
     // rows in flight per thread) stream fastest; the class ids of a tile are re-read from L2.
