@@ -214,7 +214,7 @@ __device__ __forceinline__ uint32_t number_sets(const NfaArgs &a, ImageLds<W> &L
 // Up to 256 states.  A workgroup of sixteen waves takes `per_group` consecutive tokens, a wave one at a time; which
 // successor sets a byte has is worked out once per workgroup and first byte, by the wave that first needs it.
 // 32,000 tokens x 256 states: 154 us with a thread per (token, start state), bound by instruction issue (75.6 M wave
-// instructions); what is left is mostly writing the rows (262 MB, 45 us).
+// instructions), 90 us so; half of what is left is writing the rows (262 MB, 39-45 us).
 template <int W>
 __global__ __launch_bounds__(kImageThreads, 8) void nfa_image_kernel(NfaArgs a, int per_group) {
     __shared__ ImageLds<W> L;
