@@ -27,6 +27,8 @@ namespace {
 
 // native 16-byte vector (the nontemporal builtins do not take HIP's uint4 struct)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// the same at any even address
+typedef uint32_t u32x4_pad __attribute__((ext_vector_type(4), aligned(2)));
 
 // threads per workgroup and tokens per chunk
 constexpr int kWalkThreads = 256;
@@ -63,6 +65,11 @@ constexpr int kAccCap = 4096;            // ranks whose multiplier sums are redu
 // .., so what it reads back later is what it wrote), then the distinct states of the column, their
 // ranks, and the multiplier sum of every rank.  Row 256 (the identity map of the empty token)
 // also clears the padding behind Tt and writes the walk store's header.
+// Bound by its chain: the column read with a stride of 512 bytes, five barriers, the LDS atomics of the ranks.
+// Workgroups go to the eight XCDs in turn, so workgroup i takes column 32 (i mod 8) + i / 8: an XCD then reads two
+// of the eight 128-byte lines of a table row and not all of them (4,096 states: 15.6 -> 14.8 us).  The padding is
+// cleared 16 bytes at a time: it alone kept the last workgroup 0.6 us longer than the others (60 to 256 states:
+// 5.6 -> 5.0 and 7.1 -> 6.5 us, 1,024 states 8.1 -> 7.5).
 __global__ __launch_bounds__(1024) void tables_kernel(const uint16_t *__restrict__ table,
                                                       uint16_t *Tt, int S, uint64_t seed,
                                                       int32_t *nimg, uint16_t *img, uint16_t *idx,
@@ -71,7 +78,8 @@ __global__ __launch_bounds__(1024) void tables_kernel(const uint16_t *__restrict
     __shared__ uint32_t wprefix[kStateWords];
     __shared__ uint32_t wave_tot[16];
     __shared__ unsigned long long acc[kAccCap];
-    const int b = blockIdx.x, tid = threadIdx.x;
+    const int b = blockIdx.x < 256 ? (int)((blockIdx.x & 7) * 32 + (blockIdx.x >> 3)) : 256;
+    const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     uint16_t *col = Tt + (size_t)b * S;  // rows 0..255 only
 
@@ -105,7 +113,7 @@ __global__ __launch_bounds__(1024) void tables_kernel(const uint16_t *__restrict
             present[w] = lo + 32 <= S ? 0xFFFFFFFFu : (lo < S ? (1u << (S - lo)) - 1u : 0u);
         }
         uint16_t *pad = Tt + (size_t)256 * S;
-        for (int i = tid; i < kTablePad; i += 1024) pad[i] = 0;
+        for (int i = tid; i < kTablePad / 8; i += 1024) reinterpret_cast<u32x4_pad *>(pad)[i] = u32x4_pad{0u, 0u, 0u, 0u};
         if (store && tid == 0) {
             store->magic = kWalkStoreMagic;
             store->V = V;
