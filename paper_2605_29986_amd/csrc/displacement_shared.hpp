@@ -253,7 +253,9 @@ __device__ __forceinline__ uint32_t sh_set_number(SharedLds &L, const uint32_t *
     uint32_t at = h & (kShSets - 1);
     int reserved = -1;
     for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShSets - 1)) {
-        u64 found = lds_look(&L.sets[at]);
+        // one lane's look for the whole wave: the lanes of a read need not see the same moment of a slot that another
+        // wave is filling, and the branch below takes the whole wave (its words go to the pool together)
+        u64 found = wave_read64(lds_look(&L.sets[at]), 0);
         if (found == kShEmpty) {
             if (reserved < 0) {
                 int top = 0;
