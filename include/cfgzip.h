@@ -101,6 +101,8 @@ int cfgzip_version(void);
  *              computed (per token the states reached from the distinct states its first
  *              byte leaves; up to 1,024 bytes per token).  Handing the untouched workspace
  *              to cfgzip_build_classes lets it compare those instead of walking again.
+ *              A workspace with room for only 512 of those bytes per token is taken too; then
+ *              tokens whose first byte leaves up to 256 states are kept, instead of 512.
  */
 size_t cfgzip_signatures_workspace_bytes(int32_t V, int32_t S);
 int cfgzip_signatures(const uint8_t *tok_bytes, const int64_t *tok_off, int32_t V,

@@ -307,7 +307,7 @@ __global__ __launch_bounds__(kTableThreads) void table_verify_kernel(TableVerify
         const int64_t waves = ((int64_t)gridDim.x - a.mark_blocks - a.cross_blocks) * kWaves;
         if (STORE) {
             // eight pairs per wave, eight lanes a pair, 16 bytes a lane and round
-            const uint32_t stride = walk_store_stride(a.S);
+            const uint32_t stride = store_stride(a.store);
             const uint32_t sub = lane & 7, pair = lane >> 3;
             for (int64_t t0 = gw * 8; t0 < a.n; t0 += waves * 8) {
                 const int64_t t = t0 + pair;

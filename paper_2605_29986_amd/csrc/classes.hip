@@ -495,7 +495,7 @@ __global__ __launch_bounds__(kThreads) void link_kernel(LinkArgs a) {
     // round is asked for before the rows are known (every token has a slot of `stride` entries;
     // what turns out not to be wanted is not looked at), so that it overlaps the row reads and
     // the search below.
-    const uint32_t stride = SRC == SRC_STORE ? walk_store_stride(a.S) : 8u;
+    const uint32_t stride = SRC == SRC_STORE && store_state == 0 ? store_stride(a.store) : 8u;
     const uint32_t sub = lane & 7, group = lane >> 3;
     const uint4 zero = make_uint4(0, 0, 0, 0);
     uint16_t wa_row = 0, wb_row = 0;

@@ -34,10 +34,14 @@ struct StoreSource {
 __device__ __forceinline__ int walk_store_state(const StoreSource &s) {
     const WalkStore hdr = *s.store.header;
     if (hdr.magic != kWalkStoreMagic || hdr.V != s.V || hdr.S != s.S ||
-        hdr.stride != walk_store_stride(s.S))
+        (hdr.stride != walk_store_stride(s.S, kWalkStoreMaxStride) &&
+         hdr.stride != walk_store_stride(s.S, kWalkStoreSmallStride)))
         return kStoreForeign;
     return hdr.overflow ? kStoreOverflowed : 0;
 }
+
+// Entries per token in a store that holds this call's vectors.
+__device__ __forceinline__ uint32_t store_stride(const StoreSource &s) { return s.store.header->stride; }
 
 // Image row of a token as the store has it (256: the empty token, whose signature is the
 // identity and whose vector is not kept).
@@ -50,7 +54,7 @@ __device__ __forceinline__ uint32_t store_row(const StoreSource &s, int32_t tok)
 // vector is zero on both sides).
 __device__ __forceinline__ bool store_same_row_differ(const StoreSource &s, int32_t ta, int32_t tb,
                                                       uint32_t row) {
-    const uint32_t stride = walk_store_stride(s.S);
+    const uint32_t stride = store_stride(s);
     const uint4 *wa = reinterpret_cast<const uint4 *>(s.store.wvec + (size_t)ta * stride);
     const uint4 *wb = reinterpret_cast<const uint4 *>(s.store.wvec + (size_t)tb * stride);
     const uint32_t n16 = min(walk_units_of(s.store.wrow[ta]), stride / 8u);  // the same for both: one row
@@ -82,7 +86,7 @@ __device__ __forceinline__ bool store_other_row_differ(const StoreSource &s, int
                                                        uint16_t *lb, int part = 0, int parts = 1) {
     const int lane = threadIdx.x & 63;
     const int S = s.S;
-    const uint32_t stride = walk_store_stride(S);
+    const uint32_t stride = store_stride(s);
     const bool ida = ra == 256u, idb = rb == 256u;
     if (ida && idb) return false;
     if (part * 512 >= S) return false;  // nothing of this pair falls to this wave

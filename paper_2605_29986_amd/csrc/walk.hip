@@ -43,6 +43,7 @@ struct WalkArgs {
     int32_t chunk_tokens;  // consecutive tokens a workgroup takes at a time, <= kBatchTokens
     Tables T;
     WalkStoreView store;
+    uint32_t stride;     // entries per token in the walk store
     uint16_t *sig_out;   // [V][S] or null
     uint64_t *hash_out;  // [V] or null
     // composition over token prefixes (null / 0: plain walks of all tokens)
@@ -73,7 +74,8 @@ constexpr int kAccCap = 4096;            // ranks whose multiplier sums are redu
 __global__ __launch_bounds__(1024) void tables_kernel(const uint16_t *__restrict__ table,
                                                       uint16_t *Tt, int S, uint64_t seed,
                                                       int32_t *nimg, uint16_t *img, uint16_t *idx,
-                                                      uint64_t *wsum, WalkStore *store, int V) {
+                                                      uint64_t *wsum, WalkStore *store, int V,
+                                                      uint32_t stride) {
     __shared__ uint32_t present[kStateWords];
     __shared__ uint32_t wprefix[kStateWords];
     __shared__ uint32_t wave_tot[16];
@@ -118,7 +120,7 @@ __global__ __launch_bounds__(1024) void tables_kernel(const uint16_t *__restrict
             store->magic = kWalkStoreMagic;
             store->V = V;
             store->S = S;
-            store->stride = walk_store_stride(S);
+            store->stride = stride;
             store->overflow = 0;
         }
     }
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(kWalkThreads) void signatures_kernel(WalkArgs a) {
                 __syncthreads();
             }
             // the walk vectors are also kept for the class builder: token t at t * stride
-            const uint32_t stride = walk_store_stride(S);
+            const uint32_t stride = a.stride;
             uint16_t *keep = a.store.header ? a.store.wvec + (size_t)tcur * stride : nullptr;
             // launch 2 of a composed call: slots with a parent start from its kept vector
             const uint16_t *kept = (a.phase == 2 && a.parent && a.store.header) ? a.store.wvec : nullptr;
@@ -412,7 +414,7 @@ struct SigWorkspace {
 
 // The header comes first, so that a reader that only knows "this is some signature workspace"
 // can look at it before trusting any size-dependent offset.
-SigWorkspace carve_sig_ws(void *ws, int32_t V, int32_t S) {
+SigWorkspace carve_sig_ws(void *ws, int32_t V, int32_t S, int limit) {
     Carver c(ws);
     SigWorkspace w;
     WalkStore *header = c.take<WalkStore>(1);
@@ -425,7 +427,7 @@ SigWorkspace carve_sig_ws(void *ws, int32_t V, int32_t S) {
     if (V > 0) {
         w.store.header = header;
         w.store.wrow = c.take<uint16_t>((size_t)V);
-        w.store.wvec = c.take<uint16_t>((size_t)V * walk_store_stride(S));
+        w.store.wvec = c.take<uint16_t>((size_t)V * walk_store_stride(S, limit));
     }
     w.bytes = c.used;
     return w;
@@ -434,10 +436,10 @@ SigWorkspace carve_sig_ws(void *ws, int32_t V, int32_t S) {
 }  // namespace
 
 int prepare_tables(const uint16_t *table, int32_t S, uint64_t hash_seed, bool want_wsum, int32_t V,
-                   void *ws, Tables *out, WalkStoreView *store, hipStream_t stream) {
-    SigWorkspace w = carve_sig_ws(ws, V, S);
+                   void *ws, Tables *out, WalkStoreView *store, hipStream_t stream, int limit) {
+    SigWorkspace w = carve_sig_ws(ws, V, S, limit);
     hipLaunchKernelGGL(tables_kernel, dim3(kImageRows), dim3(1024), 0, stream, table, w.Tt, S, hash_seed,
-                       w.nimg, w.img, w.idx, want_wsum ? w.wsum : nullptr, w.store.header, V);
+                       w.nimg, w.img, w.idx, want_wsum ? w.wsum : nullptr, w.store.header, V, walk_store_stride(S, limit));
     CFGZIP_TRY(check_launch());
     out->Tt = w.Tt;
     out->nimg = w.nimg;
@@ -448,10 +450,10 @@ int prepare_tables(const uint16_t *table, int32_t S, uint64_t hash_seed, bool wa
     return CFGZIP_OK;
 }
 
-size_t sig_workspace_bytes(int32_t V, int32_t S) { return carve_sig_ws(nullptr, V, S).bytes; }
+size_t sig_workspace_bytes(int32_t V, int32_t S, int limit) { return carve_sig_ws(nullptr, V, S, limit).bytes; }
 
 void view_signature_workspace(void *ws, int32_t V, int32_t S, Tables *tables, WalkStoreView *store) {
-    SigWorkspace w = carve_sig_ws(ws, V, S);
+    SigWorkspace w = carve_sig_ws(ws, V, S, kWalkStoreMaxStride);
     tables->Tt = w.Tt;
     tables->nimg = w.nimg;
     tables->img = w.img;
@@ -471,14 +473,14 @@ extern "C" size_t cfgzip_signatures_workspace_bytes(int32_t V, int32_t S) {
 
 namespace {
 
-// Shared by both entry points: `ws` holds at least sig_workspace_bytes(store_V, S) bytes;
-// store_V = V keeps the walk vectors for the class builder, store_V = 0 keeps nothing.
+// Shared by both entry points: `ws` holds at least sig_workspace_bytes(store_V, S, limit) bytes;
+// store_V = V keeps the walk vectors (of up to `limit` entries) for the class builder, store_V = 0 keeps nothing.
 // `compose_ws` (or null): the composition's part of the workspace; the tokens are then walked
 // in two launches, the longer ones starting from the kept vector of a short token that is a
 // prefix of theirs (needs store_V = V).
 int run_signatures(const uint8_t *tok_bytes, const int64_t *tok_off, int32_t V, const uint16_t *table,
                    int32_t S, uint16_t *sig_out, uint64_t *hash_out, uint64_t hash_seed, void *ws,
-                   int32_t store_V, hipStream_t stream, void *compose_ws = nullptr) {
+                   int32_t store_V, int limit, hipStream_t stream, void *compose_ws = nullptr) {
     WalkArgs a{};
     if (compose_ws) {
         const ComposeWorkspace cw = carve_compose_ws(compose_ws, V);
@@ -499,7 +501,8 @@ int run_signatures(const uint8_t *tok_bytes, const int64_t *tok_off, int32_t V, 
     a.S = S;
     a.sig_out = sig_out;
     a.hash_out = hash_out;
-    CFGZIP_TRY(prepare_tables(table, S, hash_seed, hash_out != nullptr, store_V, ws, &a.T, &a.store, stream));
+    CFGZIP_TRY(prepare_tables(table, S, hash_seed, hash_out != nullptr, store_V, ws, &a.T, &a.store, stream, limit));
+    a.stride = walk_store_stride(S, limit);
 
     a.chunk_tokens = kWalkChunkTokens;
     const int64_t n_chunks = ceil_div(V, a.chunk_tokens);
@@ -519,6 +522,16 @@ int run_signatures(const uint8_t *tok_bytes, const int64_t *tok_off, int32_t V, 
         CFGZIP_TRY(check_launch());
     }
     return CFGZIP_OK;
+}
+
+// The longest vectors that a workspace of `ws_bytes`, `behind` of them for something else, has room for.
+bool store_limit_for(int32_t V, int32_t S, size_t ws_bytes, size_t behind, int *limit) {
+    for (int l : {kWalkStoreMaxStride, kWalkStoreSmallStride})
+        if (ws_bytes >= sig_workspace_bytes(V, S, l) + behind) {
+            *limit = l;
+            return true;
+        }
+    return false;
 }
 
 int check_signature_args(const int64_t *tok_off, int32_t V, const uint16_t *table, int32_t S,
@@ -570,9 +583,10 @@ extern "C" int cfgzip_signatures(const uint8_t *tok_bytes, const int64_t *tok_of
                                  uint64_t *hash_out, uint64_t hash_seed, void *ws, size_t ws_bytes,
                                  void *stream_) {
     CFGZIP_TRY(check_signature_args(tok_off, V, table, S, sig_out, hash_out));
-    if (!ws || ws_bytes < sig_workspace_bytes(V, S) || !aligned_to(ws, 256)) return CFGZIP_E_WORKSPACE;
+    int limit = 0;
+    if (!ws || !aligned_to(ws, 256) || !store_limit_for(V, S, ws_bytes, 0, &limit)) return CFGZIP_E_WORKSPACE;
     // tok_bytes may be null only if every token is empty; the kernels never read it then.
-    return run_signatures(tok_bytes, tok_off, V, table, S, sig_out, hash_out, hash_seed, ws, V,
+    return run_signatures(tok_bytes, tok_off, V, table, S, sig_out, hash_out, hash_seed, ws, V, limit,
                           static_cast<hipStream_t>(stream_));
 }
 
@@ -586,11 +600,13 @@ extern "C" int cfgzip_signatures_composed(const uint8_t *tok_bytes, const int64_
                                           uint64_t *hash_out, uint64_t hash_seed, void *ws,
                                           size_t ws_bytes, void *stream_) {
     CFGZIP_TRY(check_signature_args(tok_off, V, table, S, sig_out, hash_out));
-    const size_t sig_bytes = sig_workspace_bytes(V, S);
-    if (!ws || !aligned_to(ws, 256) || ws_bytes < sig_bytes + carve_compose_ws(nullptr, V).bytes)
+    int limit = 0;
+    if (!ws || !aligned_to(ws, 256) ||
+        !store_limit_for(V, S, ws_bytes, carve_compose_ws(nullptr, V).bytes, &limit))
         return CFGZIP_E_WORKSPACE;
-    return run_signatures(tok_bytes, tok_off, V, table, S, sig_out, hash_out, hash_seed, ws, V,
-                          static_cast<hipStream_t>(stream_), static_cast<char *>(ws) + sig_bytes);
+    return run_signatures(tok_bytes, tok_off, V, table, S, sig_out, hash_out, hash_seed, ws, V, limit,
+                          static_cast<hipStream_t>(stream_),
+                          static_cast<char *>(ws) + sig_workspace_bytes(V, S, limit));
 }
 
 extern "C" int cfgzip_signatures_static(const uint8_t *tok_bytes, const int64_t *tok_off, int32_t V,
@@ -603,5 +619,5 @@ extern "C" int cfgzip_signatures_static(const uint8_t *tok_bytes, const int64_t 
     // every table entry the kernels read is written by this call's own table kernels first, so
     // what the previous call left in the array does not matter
     return run_signatures(tok_bytes, tok_off, V, table, S, sig_out, hash_out, hash_seed, ws, 0,
-                          static_cast<hipStream_t>(stream_));
+                          kWalkStoreMaxStride, static_cast<hipStream_t>(stream_));
 }

@@ -59,17 +59,19 @@ struct Tables {
 struct WalkStore {
     uint32_t magic;     // kWalkStoreMagic once the header is written for this (V, S)
     int32_t V, S;
-    uint32_t stride;    // entries per token, a multiple of 8
+    uint32_t stride;    // entries per token, a multiple of 8: walk_store_stride of one of the two limits
     uint32_t overflow;  // 1: some vector did not fit
     uint32_t pad[3];
 };
 constexpr uint32_t kWalkStoreMagic = 0xCF621A1Cu;
 // Entries kept per token at most (1 KB).  A byte of a 4,096-state lexer leaves up to about 260 states: at 256 one such
-// byte made the whole store unusable and the class build walk every token again (318 us instead of 232).
+// byte made the whole store unusable and the class build walk every token again (318 us instead of 232).  A workspace
+// with room for half of that only (512 bytes a token) is taken too: then vectors of up to 256 states are kept.
 constexpr int kWalkStoreMaxStride = 512;
-__host__ __device__ inline uint32_t walk_store_stride(int32_t S) {
+constexpr int kWalkStoreSmallStride = 256;
+__host__ __device__ inline uint32_t walk_store_stride(int32_t S, int limit) {
     const uint32_t s8 = ((uint32_t)S + 7u) & ~7u;
-    return s8 < (uint32_t)kWalkStoreMaxStride ? s8 : (uint32_t)kWalkStoreMaxStride;
+    return s8 < (uint32_t)limit ? s8 : (uint32_t)limit;
 }
 
 struct WalkStoreView {
@@ -86,11 +88,13 @@ __host__ __device__ inline uint32_t walk_row_of(uint16_t packed) { return packed
 __host__ __device__ inline uint32_t walk_units_of(uint16_t packed) { return packed >> 9; }
 
 // Builds all tables in the signature workspace.  Host functions, defined in walk.hip.
-// V > 0 also lays out (and resets) the walk store for V tokens.
+// V > 0 also lays out (and resets) the walk store for V tokens, with vectors of up to `limit` entries.
 int prepare_tables(const uint16_t *table, int32_t S, uint64_t hash_seed, bool want_wsum, int32_t V,
-                   void *ws, Tables *out, WalkStoreView *store, hipStream_t stream);
-size_t sig_workspace_bytes(int32_t V, int32_t S);
-// Views of a workspace that a finished cfgzip_signatures(V, S) call left behind.
+                   void *ws, Tables *out, WalkStoreView *store, hipStream_t stream,
+                   int limit = kWalkStoreMaxStride);
+size_t sig_workspace_bytes(int32_t V, int32_t S, int limit = kWalkStoreMaxStride);
+// Views of a workspace that a finished cfgzip_signatures(V, S) call left behind (its header says with which stride; the
+// vectors come last, so no other place depends on it).
 void view_signature_workspace(void *ws, int32_t V, int32_t S, Tables *tables, WalkStoreView *store);
 // Entries of w a batch may hold for an automaton of S states: room for any two tokens, each
 // padded to a whole number of walk groups.

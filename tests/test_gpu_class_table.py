@@ -6,6 +6,7 @@ fullest), from both comparison sources, and with hashes that collide (the sort t
 import numpy as np
 import pytest
 
+import oracle
 from synthetic_inputs.vocab import vocab_from_tokens
 from test_gpu_build import _check_build
 
@@ -70,3 +71,43 @@ def test_colliding_hashes_are_settled(lib, stored):
     vocab, table = _case("last byte", 1500, 5)
     _, coll = _check_build(lib, vocab, table, stored=stored, hash_override=lambda h: h & 1)
     assert coll > 0
+
+
+@pytest.mark.parametrize("composed", [False, True])
+@pytest.mark.parametrize("S,n", [(600, 250), (600, 256), (600, 257), (600, 300), (300, 300), (4096, 256)])
+def test_workspaces_with_room_for_512_bytes_a_token(lib, S, n, composed):
+    """A signature workspace with half the room that the query asks for per token keeps vectors of up to 256 states:
+    the same signatures and classes, from the kept vectors or (n > 256) by the next source, and nothing written behind
+    the workspace.  One byte less is refused."""
+    from gpu_util import vocab_dev, hash_np
+    print(f"case S={S} n={n} composed={composed}", flush=True)
+    rng = np.random.default_rng(S + n)
+    table = np.zeros((S, 256), np.uint16)
+    for b in range(8):
+        table[:, b] = rng.permutation(S)[:n][np.arange(S) % n]
+    vocab = vocab_from_tokens([rng.integers(0, 8, size=int(k), dtype=np.uint8).tobytes()
+                               for k in rng.integers(0, 6, size=701)])
+    V, raw = vocab.V, lib.load_library()
+    query = raw.cfgzip_signatures_composed_workspace_bytes if composed else raw.cfgzip_signatures_workspace_bytes
+
+    def vectors(stride):
+        return (2 * V * min((S + 7) // 8 * 8, stride) + 255) // 256 * 256
+
+    small = query(V, S) - vectors(512) + vectors(256)
+    buf = torch.full((small + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    tb, to, tt = vocab_dev(vocab, table)
+    with pytest.raises(lib.CfgzipError):
+        lib.cfgzip_signatures(tb, to, tt, workspace=buf[:small - 1], composed=composed)
+    sig, h = lib.cfgzip_signatures(tb, to, tt, workspace=buf[:small], composed=composed)
+    want_sig = oracle.signatures(vocab.tok_bytes, vocab.tok_off, table)
+    want_c, want_r = oracle.build_classes(want_sig, vocab.tok_off)
+    assert (sig.cpu().numpy() == want_sig).all()
+    assert (hash_np(h) == oracle.signature_hash(want_sig, lib.DEFAULT_HASH_SEED)).all()
+    assert bool((buf[small:] == 0x5A).all())
+    header = buf[:32].cpu().numpy().view(np.uint32)
+    assert header[3] == 256 and header[4] == (1 if n > 256 else 0)
+    for rows in (None, sig):
+        for cut in (h, h & 7):  # and hashes that collide: the sort's comparisons
+            c, r, C, _ = lib.cfgzip_build_classes(tb, to, tt, rows, cut, signatures_workspace=buf[:small])
+            assert C == len(want_r)
+            assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
