@@ -280,8 +280,9 @@ __global__ __launch_bounds__(kTableThreads) void table_verify_kernel(TableVerify
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int block = (int)blockIdx.x - a.mark_blocks;
     constexpr int kWaves = kTableThreads / 64;
+    uint32_t stride = 0;  // of the walk store
     if (STORE) {
-        const int state = walk_store_state(a.store);
+        const int state = walk_store_state(a.store, stride);
         if (state) {
             if (block == 0 && threadIdx.x == 0) a.ctr->store_state = state;
             return;
@@ -296,9 +297,9 @@ __global__ __launch_bounds__(kTableThreads) void table_verify_kernel(TableVerify
             const int2 pair = a.cross_list[e / parts];
             const uint32_t ra = store_row(a.store, pair.x), rb = store_row(a.store, pair.y);
             if (ra == rb && ra != 256u) {
-                if (e % parts == 0) differs |= store_same_row_differ(a.store, pair.x, pair.y, ra);
+                if (e % parts == 0) differs |= store_same_row_differ(a.store, stride, pair.x, pair.y);
             } else {
-                differs |= store_other_row_differ(a.store, pair.x, pair.y, ra, rb, staged[wave][0], staged[wave][1],
+                differs |= store_other_row_differ(a.store, stride, pair.x, pair.y, ra, rb, staged[wave][0], staged[wave][1],
                                                   (int)(e % parts), parts);
             }
         }
@@ -307,7 +308,6 @@ __global__ __launch_bounds__(kTableThreads) void table_verify_kernel(TableVerify
         const int64_t waves = ((int64_t)gridDim.x - a.mark_blocks - a.cross_blocks) * kWaves;
         if (STORE) {
             // eight pairs per wave, eight lanes a pair, 16 bytes a lane and round
-            const uint32_t stride = store_stride(a.store);
             const uint32_t sub = lane & 7, pair = lane >> 3;
             for (int64_t t0 = gw * 8; t0 < a.n; t0 += waves * 8) {
                 const int64_t t = t0 + pair;
@@ -337,7 +337,7 @@ __global__ __launch_bounds__(kTableThreads) void table_verify_kernel(TableVerify
                 while (list) {
                     const int l = __ffsll((unsigned long long)list) - 1;
                     list &= list - 1;
-                    differs |= store_other_row_differ(a.store, (int32_t)(t0 + (l >> 3)), __shfl(ref, l, 64),
+                    differs |= store_other_row_differ(a.store, stride, (int32_t)(t0 + (l >> 3)), __shfl(ref, l, 64),
                                                       __shfl(ra, l, 64), __shfl(rb, l, 64), staged[wave][0],
                                                       staged[wave][1]);
                 }

@@ -484,8 +484,9 @@ __global__ __launch_bounds__(kThreads) void link_kernel(LinkArgs a) {
 
     // SRC_STORE: is the store this call's?  The same answer in every workgroup.
     int store_state = 0;
+    uint32_t stride = 8;  // of the walk store
     if (SRC == SRC_STORE) {
-        store_state = walk_store_state(a.store);
+        store_state = walk_store_state(a.store, stride);
         if (store_state && blockIdx.x == 0 && threadIdx.x == 0) a.ctr->store_state = store_state;
     }
     const bool verify = in && !start && SRC != SRC_NONE && store_state == 0;
@@ -495,7 +496,6 @@ __global__ __launch_bounds__(kThreads) void link_kernel(LinkArgs a) {
     // round is asked for before the rows are known (every token has a slot of `stride` entries;
     // what turns out not to be wanted is not looked at), so that it overlaps the row reads and
     // the search below.
-    const uint32_t stride = SRC == SRC_STORE && store_state == 0 ? store_stride(a.store) : 8u;
     const uint32_t sub = lane & 7, group = lane >> 3;
     const uint4 zero = make_uint4(0, 0, 0, 0);
     uint16_t wa_row = 0, wb_row = 0;
@@ -718,7 +718,8 @@ struct StoreVerifyArgs {
 // which wave settles a position never depends on what another wave has settled meanwhile).
 __global__ __launch_bounds__(kThreads) void verify_store_kernel(StoreVerifyArgs a) {
     __shared__ __align__(16) uint16_t staged[kThreads / 64][2][kWalkStoreMaxStride];
-    const int state = walk_store_state(a.src);
+    uint32_t stride = 0;
+    const int state = walk_store_state(a.src, stride);
     if (state) {
         if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->store_state = state;
         return;
@@ -736,7 +737,7 @@ __global__ __launch_bounds__(kThreads) void verify_store_kernel(StoreVerifyArgs 
     }
     const bool same = todo && ra == rb && ra != 256u;
     if (same) {
-        if (store_same_row_differ(a.src, ta, tb, ra)) {
+        if (store_same_row_differ(a.src, stride, ta, tb)) {
             a.mismatch[i] = 1;
             atomicAdd(&a.ctr->unresolved, 1);
         } else {
@@ -747,7 +748,7 @@ __global__ __launch_bounds__(kThreads) void verify_store_kernel(StoreVerifyArgs 
     while (list) {
         const int l = __ffsll((unsigned long long)list) - 1;
         list &= list - 1;
-        const bool d = store_other_row_differ(a.src, __shfl(ta, l, 64), __shfl(tb, l, 64),
+        const bool d = store_other_row_differ(a.src, stride, __shfl(ta, l, 64), __shfl(tb, l, 64),
                                               __shfl(ra, l, 64), __shfl(rb, l, 64), staged[wave][0],
                                               staged[wave][1]);
         settle(d, blockIdx.x * kThreads + wave * 64 + l, a.resolved, a.mismatch, a.ctr);
@@ -1027,13 +1028,15 @@ __global__ __launch_bounds__(kThreads) void mark_heads_kernel(MarkArgs a) {
     const int wave = threadIdx.x >> 6;
     const int parts = (a.store.S % 8) == 0 ? kListedParts : 1;
     const int count = min(a.ctr->other_rows, a.n);
+    uint32_t stride = 0;
+    if (walk_store_state(a.store, stride)) return;  // then nothing is listed
     const int waves = ((int)gridDim.x - a.mark_blocks) * (kThreads / 64);
     for (int64_t e = ((int)blockIdx.x - a.mark_blocks) * (kThreads / 64) + wave; e < (int64_t)count * parts;
          e += waves) {
         const int4 link = a.other_list[e / parts];
         const int i = link.x;
         if (i <= 0 || i >= a.n) continue;  // never listed; stay in bounds
-        const bool d = store_other_row_differ(a.store, link.y, link.z, (uint32_t)link.w & 0xFFFFu,
+        const bool d = store_other_row_differ(a.store, stride, link.y, link.z, (uint32_t)link.w & 0xFFFFu,
                                               (uint32_t)link.w >> 16, staged[wave][0], staged[wave][1],
                                               (int)(e % parts), parts);
         if (d && (threadIdx.x & 63) == 0) {  // the first wave to find a difference counts it

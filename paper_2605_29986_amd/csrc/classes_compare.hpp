@@ -30,9 +30,10 @@ struct StoreSource {
     int32_t V, S;
 };
 
-// 0 if the store holds this call's vectors, else why not.
-__device__ __forceinline__ int walk_store_state(const StoreSource &s) {
+// 0 if the store holds this call's vectors, `stride` entries per token, else why not.
+__device__ __forceinline__ int walk_store_state(const StoreSource &s, uint32_t &stride) {
     const WalkStore hdr = *s.store.header;
+    stride = hdr.stride;
     if (hdr.magic != kWalkStoreMagic || hdr.V != s.V || hdr.S != s.S ||
         (hdr.stride != walk_store_stride(s.S, kWalkStoreMaxStride) &&
          hdr.stride != walk_store_stride(s.S, kWalkStoreSmallStride)))
@@ -40,21 +41,16 @@ __device__ __forceinline__ int walk_store_state(const StoreSource &s) {
     return hdr.overflow ? kStoreOverflowed : 0;
 }
 
-// Entries per token in a store that holds this call's vectors.
-__device__ __forceinline__ uint32_t store_stride(const StoreSource &s) { return s.store.header->stride; }
-
 // Image row of a token as the store has it (256: the empty token, whose signature is the
 // identity and whose vector is not kept).
 __device__ __forceinline__ uint32_t store_row(const StoreSource &s, int32_t tok) {
     return min(walk_row_of(s.store.wrow[tok]), 256u);
 }
 
-// Two tokens with the same image row `row` < 256: idx[row] is onto, so their signatures are
+// Two tokens with the same image row < 256: idx[row] is onto, so their signatures are
 // equal iff their walk vectors are.  One thread, 16 bytes at a time (the padding behind a
 // vector is zero on both sides).
-__device__ __forceinline__ bool store_same_row_differ(const StoreSource &s, int32_t ta, int32_t tb,
-                                                      uint32_t row) {
-    const uint32_t stride = store_stride(s);
+__device__ __forceinline__ bool store_same_row_differ(const StoreSource &s, uint32_t stride, int32_t ta, int32_t tb) {
     const uint4 *wa = reinterpret_cast<const uint4 *>(s.store.wvec + (size_t)ta * stride);
     const uint4 *wb = reinterpret_cast<const uint4 *>(s.store.wvec + (size_t)tb * stride);
     const uint32_t n16 = min(walk_units_of(s.store.wrow[ta]), stride / 8u);  // the same for both: one row
@@ -81,12 +77,11 @@ __device__ __forceinline__ bool store_same_row_differ(const StoreSource &s, int3
 // buffers la, lb (kWalkStoreMaxStride entries each).  Returns whether any entry differs
 // (wave-uniform).  `part` of `parts`: the wave looks only at every parts-th stretch of 512 states,
 // starting with stretch `part` (several waves then share one pair; S a multiple of 8 only).
-__device__ __forceinline__ bool store_other_row_differ(const StoreSource &s, int32_t ta, int32_t tb,
+__device__ __forceinline__ bool store_other_row_differ(const StoreSource &s, uint32_t stride, int32_t ta, int32_t tb,
                                                        uint32_t ra, uint32_t rb, uint16_t *la,
                                                        uint16_t *lb, int part = 0, int parts = 1) {
     const int lane = threadIdx.x & 63;
     const int S = s.S;
-    const uint32_t stride = store_stride(s);
     const bool ida = ra == 256u, idb = rb == 256u;
     if (ida && idb) return false;
     if (part * 512 >= S) return false;  // nothing of this pair falls to this wave
