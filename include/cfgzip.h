@@ -185,7 +185,8 @@ int cfgzip_signatures_static(const uint8_t *tok_bytes, const int64_t *tok_off, i
  *   num_classes_host out, int32 [1] HOST, or NULL
  *   collisions_host  out, int32 [1] HOST, or NULL: number of tokens whose signature
  *                    differed from that of their left neighbour in an equal-hash
- *                    segment (0 unless hashes collide)
+ *                    segment (0 unless hashes collide in the bits that were looked at:
+ *                    37 in the hash table, 32 or, above 262,144 tokens, 40 in the sort)
  *   ws         cfgzip_build_classes_workspace_bytes(V, S) bytes, 256-byte aligned
  * Synchronises `stream` before returning.
  */

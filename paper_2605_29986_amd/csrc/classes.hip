@@ -1313,8 +1313,6 @@ extern "C" int cfgzip_build_classes(const uint8_t *tok_bytes, const int64_t *tok
         return CFGZIP_OK;
     };
     const int hash_bits = hash_bits_for(V);
-    static_assert(kTableMaxTokens == kLargeVocabulary, "an entry holds the 32 hash bits that the sort would take");
-
     // First attempt: grouping by hash table.  Not where signatures have to be walked again to be
     // compared: the sort puts tokens next to each other, so that each is walked once for its two
     // neighbours, while against a group's member every token would be walked with a partner.

@@ -111,3 +111,25 @@ def test_workspaces_with_room_for_512_bytes_a_token(lib, S, n, composed):
             c, r, C, _ = lib.cfgzip_build_classes(tb, to, tt, rows, cut, signatures_workspace=buf[:small])
             assert C == len(want_r)
             assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
+
+
+@pytest.mark.parametrize("shift", [0, 5, 31, 32, 36, 37, 59])
+def test_hash_bits_that_tell_classes_apart(lib, shift):
+    """Hashes that differ in five bits only: up to the 37th bit the table tells the classes apart and nothing collides;
+    above it every class collides with every other, and the sort, which looks at 32 bits here, settles it."""
+    from gpu_util import dev, vocab_dev
+    S = 31  # tokens end in one of 31 states or, if empty, keep all
+    table = np.tile((np.arange(256) % S).astype(np.uint16), (S, 1))
+    rng = np.random.default_rng(shift)
+    vocab = vocab_from_tokens([rng.integers(0, 256, size=int(k), dtype=np.uint8).tobytes()
+                               for k in rng.integers(0, 4, size=3000)])
+    want_c, want_r = oracle.build_classes(oracle.signatures(vocab.tok_bytes, vocab.tok_off, table), vocab.tok_off)
+    assert len(want_r) == 32
+    h = dev(want_c.astype(np.uint64) << np.uint64(shift))
+    tb, to, tt = vocab_dev(vocab, table)
+    ws = torch.empty(lib.load_library().cfgzip_signatures_workspace_bytes(vocab.V, S), dtype=torch.uint8, device="cuda")
+    sig, _ = lib.cfgzip_signatures(tb, to, tt, workspace=ws)
+    for rows, store in ((None, ws), (sig, None)):
+        c, r, C, coll = lib.cfgzip_build_classes(tb, to, tt, rows, h, signatures_workspace=store)
+        assert C == 32 and (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
+        assert (coll == 0) == (shift <= 32)
