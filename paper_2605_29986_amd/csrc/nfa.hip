@@ -22,6 +22,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kMaxRegisterStates = 256;  // up to here a thread keeps its set in registers
 constexpr int kMaxNfaStates = 1024;
+constexpr int kStagedBytes = 64;  // token bytes read once into LDS by nfa_walk_kernel; longer tokens go on from memory
 struct NfaArgs {
     const uint8_t *tok_bytes;
     const int64_t *tok_off;
@@ -33,6 +34,14 @@ struct NfaArgs {
     uint32_t last_word_mask;  // the bits of a row's last word that are states
 };
 
+// Up to here a thread per (token, start state) is faster than walking from the different successor sets only.  It fills
+// the chip (524,288 threads) less than twice, so what counts is the chain of a token, and telling sets apart comes on
+// top: lexers of 96 / 128 / 200 / 256 states with 4,000 tokens 30 / 32 / 44 / 48 us against 33 / 35 / 46 / 46, with
+// 1,000 tokens 28 / 28 / 33 / 34 against 32 / 34 / 44 / 43; with 32,000 tokens 73 / 83 / 151 / 167 against 63 / 66 /
+// 108 / 104.  With up to 64 states a wave has all of a token's states in its lanes, and walking fewer saves nothing: 24
+// states 38 us against 42, 64 states 51 against 55 (32,000 tokens).
+constexpr int64_t kWalkPairs = 7 << 17;
+constexpr int kWalkStates = 64;
 constexpr int kImageThreads = 1024;
 constexpr int kImageWaves = kImageThreads / 64;
 constexpr int kImageSets = 96;           // different successor sets of a byte that the walk shares
@@ -80,6 +89,18 @@ __device__ __forceinline__ void add_row(uint32_t (&set)[W], const uint32_t *row)
     } else {
 #pragma unroll
         for (int k = 0; k < W; ++k) set[k] |= row[k];
+    }
+}
+
+template <int W>
+__device__ __forceinline__ void store_set(uint32_t *row, const uint32_t (&set)[W]) {
+    if (W % 4 == 0) {
+#pragma unroll
+        for (int k = 0; k < W / 4; ++k)
+            reinterpret_cast<uint4 *>(row)[k] = make_uint4(set[4 * k], set[4 * k + 1], set[4 * k + 2], set[4 * k + 3]);
+    } else {
+#pragma unroll
+        for (int w = 0; w < W; ++w) row[w] = set[w];
     }
 }
 
@@ -334,16 +355,7 @@ __global__ __launch_bounds__(kImageThreads, 8) void nfa_image_kernel(NfaArgs a, 
                     set_step<W>(set, a.nfa + (size_t)from_front.at(p) * matrix, a.last_word_mask);
                 }
                 if (q >= a.S) continue;
-                uint32_t *row = out + (size_t)q * W;
-                if (W % 4 == 0) {
-#pragma unroll
-                    for (int k = 0; k < W / 4; ++k)
-                        reinterpret_cast<uint4 *>(row)[k] =
-                            make_uint4(set[4 * k], set[4 * k + 1], set[4 * k + 2], set[4 * k + 3]);
-                } else {
-#pragma unroll
-                    for (int w = 0; w < W; ++w) row[w] = set[w];
-                }
+                store_set<W>(out + (size_t)q * W, set);
                 if (a.hash) h += row_hash<W>(set, q, a.seed);
             }
         }
@@ -353,6 +365,58 @@ __global__ __launch_bounds__(kImageThreads, 8) void nfa_image_kernel(NfaArgs a, 
             if (lane == 0) a.hash[t] = h;
         }
         __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// A thread owns one (token, start state) pair.  (Two or four start states per thread, for more row reads in flight, made
+// it slower: it is bound by instruction issue where it fills the chip, not by the latency of its reads.)
+template <int W>
+__global__ __launch_bounds__(kThreads) void nfa_walk_kernel(NfaArgs a, int threads_per_token) {
+    __shared__ unsigned long long hash_sum[kThreads / 64];
+    __shared__ uint8_t head_bytes[kThreads / 64][kStagedBytes];  // each token's first bytes
+    const int slot = threadIdx.x / threads_per_token;
+    const int q = threadIdx.x % threads_per_token;
+    const int t = blockIdx.x * (kThreads / threads_per_token) + slot;
+    if (threadIdx.x < kThreads / 64) hash_sum[threadIdx.x] = 0;
+    int64_t b0 = 0, b1 = 0;
+    if (t < a.V) {
+        b0 = a.tok_off[t];
+        b1 = a.tok_off[t + 1];
+        if (q < kStagedBytes && b0 + q < b1) head_bytes[slot][q] = a.tok_bytes[b0 + q];
+    }
+    __syncthreads();
+    uint64_t h = 0;
+    if (t < a.V && q < a.S) {
+        uint32_t set[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) set[w] = (q >> 5) == w ? 1u << (q & 31) : 0u;
+        const size_t matrix = (size_t)a.S * W;
+        for (int64_t p = b0; p < b1; ++p) {
+            const int ch = p - b0 < kStagedBytes ? head_bytes[slot][p - b0] : a.tok_bytes[p];
+            const uint32_t *step = a.nfa + ch * matrix;
+            uint32_t next[W];
+#pragma unroll
+            for (int w = 0; w < W; ++w) next[w] = 0;
+#pragma unroll
+            for (int w = 0; w < W; ++w)
+                for (uint32_t bits = set[w]; bits; bits &= bits - 1)
+                    add_row<W>(next, step + (size_t)(w * 32 + __ffs(bits) - 1) * W);
+            next[W - 1] &= a.last_word_mask;  // a stray pad bit must not become a state number
+            uint32_t any = 0;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                set[w] = next[w];
+                any |= next[w];
+            }
+            if (!any) break;  // no state left: the row stays empty
+        }
+        store_set<W>(a.rel + ((size_t)t * a.S + q) * W, set);
+        if (a.hash) h = row_hash<W>(set, q, a.seed);
+    }
+    if (a.hash) {
+        if (h) atomicAdd(&hash_sum[slot], (unsigned long long)h);
+        __syncthreads();
+        if (q == 0 && t < a.V) a.hash[t] = hash_sum[slot];
     }
 }
 
@@ -420,11 +484,21 @@ __global__ void clear_u64_kernel(uint64_t *p, int n) {
 
 template <int W>
 int launch_nfa(const NfaArgs &a, int n_cu, hipStream_t stream) {
-    // two workgroups per compute unit (their LDS is what there is), the tokens spread evenly
-    const int64_t groups = std::min<int64_t>(2 * n_cu, ceil_div(a.V, kImageWaves));
-    const int per_group = (int)std::min<int64_t>(kImageGroup, ceil_div(a.V, groups));
-    hipLaunchKernelGGL(nfa_image_kernel<W>, dim3((unsigned)ceil_div(a.V, per_group)), dim3(kImageThreads), 0, stream, a,
-                       per_group);
+    constexpr bool kWalkOnly = W * 32 <= kWalkStates;
+    if (kWalkOnly || (int64_t)a.V * a.S <= kWalkPairs) {
+        int threads_per_token = 64;  // whole waves, a power of two so that a workgroup holds whole tokens
+        while (threads_per_token < a.S) threads_per_token *= 2;
+        hipLaunchKernelGGL(nfa_walk_kernel<W>, dim3((unsigned)ceil_div(a.V, kThreads / threads_per_token)), dim3(kThreads),
+                           0, stream, a, threads_per_token);
+        return check_launch();
+    }
+    if constexpr (!kWalkOnly) {
+        // two workgroups per compute unit (their LDS is what there is), the tokens spread evenly
+        const int64_t groups = std::min<int64_t>(2 * n_cu, ceil_div(a.V, kImageWaves));
+        const int per_group = (int)std::min<int64_t>(kImageGroup, ceil_div(a.V, groups));
+        hipLaunchKernelGGL(nfa_image_kernel<W>, dim3((unsigned)ceil_div(a.V, per_group)), dim3(kImageThreads), 0, stream, a,
+                           per_group);
+    }
     return check_launch();
 }
 
