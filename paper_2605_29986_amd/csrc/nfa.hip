@@ -47,7 +47,8 @@ constexpr int kImageWaves = kImageThreads / 64;
 constexpr int kImageSets = 96;           // different successor sets of a byte that the walk shares
 constexpr int kImageSlots = 512;         // slots of the table in which a byte's sets are told apart (256 states at most)
 constexpr int kImageBytes = 64;          // first bytes that a workgroup keeps the sets of
-constexpr int kImageGroup = 96;          // tokens of a workgroup at the most: they begin with fewer bytes than that
+constexpr int kImageGroup = 96;          // tokens of a workgroup at the most; those that begin with a byte beyond the
+                                         // kImageBytes first met are walked from every state
 constexpr uint32_t kImageUnknown = 0, kImageWorkedOut = 1, kImageMany = 2;  // ready: how many in bits 8.., the slot below
 
 template <int W>
@@ -59,6 +60,10 @@ struct ImageLds {
     uint32_t members[kImageWaves][kImageSets];  // how many, and the first and the last of them
     uint32_t state[256];                        // per byte: whether and where the two tables below have it
     uint32_t cursor, slots;
+    // where the waves share out the tokens that every state walks for itself: which tokens, how many, of how many tokens
+    // it is known whether they are one; per token the hash so far and the chunks done
+    uint32_t alone[kImageWaves], alones, known, done[kImageWaves];
+    unsigned long long hash[kImageWaves];
     uint8_t set_of[kImageBytes][256];           // [slot][start state]: number of its successor set
     uint8_t first_with[kImageBytes][kImageSets];  // [slot][set]: the first state that has it
 };
@@ -237,18 +242,31 @@ __device__ __forceinline__ uint32_t number_sets(const NfaArgs &a, ImageLds<W> &L
 // 32,000 tokens x 256 states: 154 us with a thread per (token, start state), bound by instruction issue (75.6 M wave
 // instructions), 90 us so; half of what is left is writing the rows (262 MB, 39-45 us).
 template <int W>
-__global__ __launch_bounds__(kImageThreads, 8) void nfa_image_kernel(NfaArgs a, int per_group) {
+// `split`: a token that every state walks for itself is shared out among the waves, 64 states each.  So where there is a
+// wave per token or less (per_group <= 16), which would leave the others idle behind it: 8,000 tokens x 256 states
+// without structure 95 us, 105 otherwise, and 1,060 against 1,280 with sets that grow.  With more tokens the waves are
+// busy anyway, and a wave that walks all of a token's states finds their rows in its cache (32,000 tokens: 269 us split,
+// 254 otherwise).  What that costs against a thread per pair, on sets that grow: 3.2 ms, 2.6 there; the tokens are dealt
+// out beforehand and their work differs.  Without structure it is 254 against 329, on lexers 106 against 167.
+__global__ __launch_bounds__(kImageThreads, 8) void nfa_image_kernel(NfaArgs a, int per_group, bool split) {
     __shared__ ImageLds<W> L;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid < 256) L.state[tid] = kImageUnknown;
+    if (tid < kImageWaves) {
+        L.done[tid] = 0;
+        L.hash[tid] = 0;
+    }
     if (tid == 0) {
         L.cursor = 0;
         L.slots = 0;
+        L.alones = 0;
+        L.known = 0;
     }
     __syncthreads();
     uint32_t *sets = L.sets[wave], *members = L.members[wave];
     const int group0 = (int)blockIdx.x * per_group, in_group = min(per_group, a.V - group0);
     const size_t matrix = (size_t)a.S * W;
+    const int chunks = (a.S + 63) >> 6;
     for (;;) {
         // Keeps the wave together: without it the compiler joins the branch below with the one that ends the round
         // (lane 0 stores the hash), and the other lanes go round alone, reading a `taken` that is never theirs.
@@ -256,15 +274,28 @@ __global__ __launch_bounds__(kImageThreads, 8) void nfa_image_kernel(NfaArgs a, 
         int taken = 0;
         if (lane == 0) taken = (int)atomicAdd(&L.cursor, 1u);
         taken = __builtin_amdgcn_readfirstlane(taken);
-        if (taken >= in_group) break;
-        const int t = group0 + taken;
+        int item = taken, chunk = -1;
+        if (taken >= in_group) {
+            if (!split) break;
+            // All tokens are taken.  What is left is those that every state walks for itself, once the waves that have
+            // the last tokens have said which those are (they wait for nothing but a numbering).
+            while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&L.known, __ATOMIC_RELAXED,
+                                                                    __HIP_MEMORY_SCOPE_WORKGROUP)) < (uint32_t)in_group)
+                __builtin_amdgcn_s_sleep(2);
+            lds_order();
+            const int alones = (int)__builtin_amdgcn_readfirstlane(L.alones), rest = taken - in_group;
+            if (rest >= alones * chunks) break;
+            item = (int)__builtin_amdgcn_readfirstlane(L.alone[rest / chunks]);
+            chunk = rest % chunks;
+        }
+        const int t = group0 + item;
         const int64_t b0 = a.tok_off[t], b1 = a.tok_off[t + 1];
         uint32_t *out = a.rel + (size_t)t * matrix;
         uint64_t h = 0;
         uint32_t state = kImageMany;
         int b = 0;
         WaveBytes bytes(a.tok_bytes, b0, b1);
-        if (b1 > b0) {
+        if (chunk < 0 && b1 > b0) {
             b = bytes.at(b0);
             for (;;) {
                 state = __hip_atomic_load(&L.state[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -284,6 +315,14 @@ __global__ __launch_bounds__(kImageThreads, 8) void nfa_image_kernel(NfaArgs a, 
                 __builtin_amdgcn_s_sleep(2);  // another wave is at it, and waits for nothing while it works
             }
             lds_order();
+        }
+        if (split && chunk < 0) {
+            if (lane == 0) {
+                if (state <= 0xFFu) L.alone[atomicAdd(&L.alones, 1u)] = (uint32_t)item;
+                lds_order();
+                atomicAdd(&L.known, 1u);
+            }
+            if (state <= 0xFFu) continue;
         }
         if (state > 0xFFu) {
             const int n = (int)(state >> 8), slot = (int)(state & 0xFFu);
@@ -341,7 +380,7 @@ __global__ __launch_bounds__(kImageThreads, 8) void nfa_image_kernel(NfaArgs a, 
         } else {
             // the empty token (its relation is the identity), or a first byte that leaves many different sets: every
             // start state walks for itself
-            for (int q0 = 0; q0 < a.S; q0 += 64) {
+            for (int q0 = split ? 64 * chunk : 0, q1 = split ? q0 + 64 : a.S; q0 < q1; q0 += 64) {
                 const int q = q0 + lane;
                 uint32_t set[W];
 #pragma unroll
@@ -362,7 +401,16 @@ __global__ __launch_bounds__(kImageThreads, 8) void nfa_image_kernel(NfaArgs a, 
         if (a.hash) {
 #pragma unroll
             for (int off = 1; off < 64; off <<= 1) h += __shfl_xor(h, off, 64);
-            if (lane == 0) a.hash[t] = h;
+            if (chunk < 0) {
+                if (lane == 0) a.hash[t] = h;
+            } else if (lane == 0) {  // the last of the token's chunks to be done writes
+                atomicAdd(&L.hash[item], (unsigned long long)h);
+                lds_order();
+                if ((int)atomicAdd(&L.done[item], 1u) + 1 == chunks) {
+                    lds_order();
+                    a.hash[t] = __hip_atomic_load(&L.hash[item], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            }
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -497,7 +545,7 @@ int launch_nfa(const NfaArgs &a, int n_cu, hipStream_t stream) {
         const int64_t groups = std::min<int64_t>(2 * n_cu, ceil_div(a.V, kImageWaves));
         const int per_group = (int)std::min<int64_t>(kImageGroup, ceil_div(a.V, groups));
         hipLaunchKernelGGL(nfa_image_kernel<W>, dim3((unsigned)ceil_div(a.V, per_group)), dim3(kImageThreads), 0, stream, a,
-                           per_group);
+                           per_group, per_group <= kImageWaves);
     }
     return check_launch();
 }

@@ -32,7 +32,8 @@ def _tokens(rng, V):
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 95, 96, 97])
 def test_numbers_of_sets(lib, S, n):
     """On byte k the states fall into n groups, each with a set of 0 to 4 successors.  As many tokens as it takes to come
-    to the image walk."""
+    to the image walk; with 128 states and more they are one a wave at the most, and a token that every state walks for
+    itself is then shared out among the waves."""
     print(f"case S={S} n={n}", flush=True)
     rng = np.random.default_rng(1000 * S + n)
     nfa = np.zeros((256, S, (S + 31) // 32), np.uint32)
