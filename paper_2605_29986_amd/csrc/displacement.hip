@@ -747,6 +747,13 @@ __device__ void token_displacement(const DisplacementArgs &a, int t,
     __syncthreads();  // the next token of a persistent workgroup starts from settled LDS
 }
 
+// Entries of a long list that a workgroup of the second pass takes at a time.  The atomics on the list's one cursor are
+// served one after the other, 14 ns each, which is more than a short token's share of the chip: 32,000 entries of 8
+// bytes over a simple grammar 273 us in fours (467 one by one, 226 dealt out beforehand, 174 as a workgroup each), of
+// 32,000 over 500 symbols, whose work differs, 3.45 ms (3.73, 4.49).  The few long tokens of the third pass are taken
+// one by one.
+constexpr int kRetryChunk = 4;
+
 // The passes behind the shared walk: persistent workgroups of one wave take retry list LIST entry by entry; what
 // they cannot finish goes to list HAND_ON (none if negative)
 template <typename Sym, int MAX_IN, int MAX_OUT, int FRONTIER, int LIST, int HAND_ON, bool STAGE>
@@ -757,13 +764,15 @@ __global__ __launch_bounds__(64) void displacement_retry_kernel(DisplacementArgs
     const bool adj_in_lds = STAGE && a.g.N * a.g.W <= kAdjLdsWords;
     if (adj_in_lds)
         for (int i = threadIdx.x; i < a.g.N * a.g.W; i += 64) lds.adj[i] = a.adj[i];
+    const int chunk = HAND_ON < 0 ? 1 : min(max(count / (int)gridDim.x, 1), kRetryChunk);
     for (;;) {
-        if (threadIdx.x == 0) lds.next_item = atomicAdd(&a.hdr->retry_next[LIST], 1);
+        if (threadIdx.x == 0) lds.next_item = atomicAdd(&a.hdr->retry_next[LIST], chunk);
         __syncthreads();
-        const int i = lds.next_item;
+        const int first = lds.next_item;
         __syncthreads();
-        if (i >= count) break;  // the same for every lane
-        token_displacement<Sym, MAX_IN, MAX_OUT, FRONTIER, HAND_ON, STAGE>(a, a.retry_list[LIST][i], lds, adj_in_lds);
+        if (first >= count) break;  // the same for every lane
+        for (int i = first; i < min(first + chunk, count); ++i)
+            token_displacement<Sym, MAX_IN, MAX_OUT, FRONTIER, HAND_ON, STAGE>(a, a.retry_list[LIST][i], lds, adj_in_lds);
     }
 }
 
