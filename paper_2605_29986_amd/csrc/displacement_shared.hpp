@@ -40,6 +40,10 @@ constexpr int kShWaves = kShThreads / 64;
 constexpr int kShCells = 2048;      // list cells (8 KB)
 constexpr int kShNext = 2048;       // known successors (8 KB)
 constexpr int kShSets = 1024;       // sets (8 KB, and 16 KB for what they are written as)
+// Steps that a wave works out before its lanes try alone.  The waves of a workgroup with 125 tokens over the JSON or the
+// statement grammar work out 6 to 8 steps, with 501 tokens 10 to 14; from the first step on it costs them 1.3 %, from
+// the 7th 0.8, from here nothing that could be measured.
+constexpr int kShShared = 12;
 constexpr int kShPool = 6144;       // configurations of all sets (24 KB)
 constexpr int kShOut = 18432;       // row entries of all sets written so far (36 KB)
 constexpr int kShProds = 1024;      // productions kept in LDS (8 KB); of a larger grammar none are
@@ -81,6 +85,7 @@ constexpr uint32_t kNextBits = 14;
 constexpr uint32_t kGiveUp = 0x3FFE;    // more room needed than there is: the token goes to the next pass
 constexpr uint32_t kCrossed = 0x3FFD;   // a bound of the interface is broken: the token overflows
 constexpr uint32_t kWorkedOut = 0x3FFC; // another wave is at it
+constexpr uint32_t kByTheWave = 0x3FFB; // never published: what follows takes a whole wave to work out
 constexpr uint32_t kNextEmpty = ~0u;
 
 // what a set is written as: position of its row entries (in units of four), their number, or one of these
@@ -187,6 +192,16 @@ __device__ __forceinline__ int sh_claim(SharedLds &L, uint32_t set, uint32_t lik
     return -2;
 }
 
+// Says what follows `set` on `like`, unless somebody has or is about to.
+__device__ __forceinline__ void sh_publish(SharedLds &L, uint32_t set, uint32_t like, uint32_t following) {
+    const uint32_t key = (set << 8) | like;
+    uint32_t at = next_slot(key);
+    for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShNext - 1)) {
+        const uint32_t seen = atomicCAS(&L.next[at], kNextEmpty, (key << kNextBits) | following);
+        if (seen == kNextEmpty || (seen >> kNextBits) == key) return;
+    }
+}
+
 // Different words of a wave, two a lane at the most: which of them are the first of their value, where they go when
 // packed, how many there are, and a hash that does not depend on their order.
 struct Different {
@@ -198,6 +213,7 @@ struct Different {
 };
 constexpr uint32_t kNoWord = ~0u;  // no configuration: cell numbers are below 2^12 - 1
 
+__device__ __forceinline__ uint32_t word_hash(uint32_t w) { return (w * 0x85EBCA6Bu) ^ (w >> 13) ^ ((w >> 7) * 0x9E3779B1u); }
 __device__ __forceinline__ uint32_t seen_slot(uint32_t word) { return (word * 0x9E3779B1u) >> 24; }
 static_assert(kShSeen == 256, "eight bits of hash");
 
@@ -221,7 +237,7 @@ __device__ __forceinline__ Different find_different(uint32_t *seen, uint32_t a, 
                 d.first[u] = old == kNoWord;
                 if (old == kNoWord || old == w) break;
             }
-            if (d.first[u]) h += (w * 0x85EBCA6Bu) ^ (w >> 13) ^ ((w >> 7) * 0x9E3779B1u);
+            if (d.first[u]) h += word_hash(w);
         }
         const u64 mask = __ballot(d.first[u]);
         d.at[u] = d.n + (int)__popcll(mask & ((1ull << lane) - 1ull));
@@ -245,10 +261,12 @@ __device__ __forceinline__ void seen_clear(uint32_t *seen, int lane) {
     lds_order();
 }
 
+__device__ __forceinline__ uint32_t set_hash(uint32_t sum, uint32_t n) { return (sum ^ (sum >> 15)) * 0x2C1B3C6Du + n; }
+
 // The number of the set of the words `d` (which `seen` holds); kGiveUp if there is no room.  Two sets of equal size
 // are equal if each word of one is in the other.
 __device__ __forceinline__ uint32_t sh_set_number(SharedLds &L, const uint32_t *seen, const Different &d, int lane) {
-    const uint32_t h = (d.sum ^ (d.sum >> 15)) * 0x2C1B3C6Du + (uint32_t)d.n;
+    const uint32_t h = set_hash(d.sum, (uint32_t)d.n);
     const u64 tag = (u64)(h >> 8) << 24;
     uint32_t at = h & (kShSets - 1);
     int reserved = -1;
@@ -283,6 +301,103 @@ __device__ __forceinline__ uint32_t sh_set_number(SharedLds &L, const uint32_t *
     return kGiveUp;
 }
 
+__device__ __forceinline__ u64 sh_production(const DisplacementArgs &a, const SharedLds &L, int i) {
+    return a.g.P <= kShProds ? L.prods[i] : a.prod_packed[i];
+}
+// Whether the head of production `p` may come right after the symbol `last` when the stack is empty.
+__device__ __forceinline__ bool sh_may_follow(const DisplacementArgs &a, const SharedLds &L, u64 p, uint32_t last) {
+    const uint32_t word = packed_head(p) * (uint32_t)a.g.W + (last >> 5);
+    return ((a.g.N * a.g.W <= kShAdj ? L.adj[word] : a.adj[word]) >> (last & 31)) & 1u;
+}
+
+// A configuration after production i.  `crossed`: a bound of the interface is broken; `full`: there is no room.
+__device__ __forceinline__ uint32_t sh_carry_out(const DisplacementArgs &a, SharedLds &L, uint32_t config, int i, bool &full,
+                                                 bool &crossed) {
+    const Grammar &g = a.g;
+    const u64 p = sh_production(a, L, i);
+    const uint32_t head = packed_head(p), stack = sh_stack(config);
+    uint32_t queue = sh_queue(config), rest = 0, rest_length = 0;
+    const uint32_t cell = stack ? lds_look(&L.cells[stack - 1]) : (queue ? lds_look(&L.cells[queue - 1]) : 0u);
+    int length = (int)packed_length(p);
+    const bool is_long = length == (int)kLongBody;
+    if (is_long) length = body_len(g, i);
+    if (stack) {
+        rest = cell_rest(cell);
+        rest_length = cell_length(cell) - 1u;
+    } else {
+        const uint32_t queued = cell_length(cell) + 1u;
+        if (queued > (uint32_t)kShMaxList) crossed = true;
+        else queue = sh_cons(L, queue, head, queued, full);
+    }
+    if (rest_length + (uint32_t)length > (uint32_t)kShMaxList) {
+        crossed = true;
+    } else {
+        const int off = is_long ? g.body_off[i] : 0;
+        for (int k = length - 1; k >= 0; --k) {
+            const uint32_t s = is_long ? (uint32_t)g.body[off + k] & 0xFFu : packed_symbol(p, k);
+            rest = sh_cons(L, rest, s, ++rest_length, full);
+        }
+    }
+    return sh_config(queue, rest, head);
+}
+
+// One byte of Algorithm 1 by one lane, where it is simple enough: a set of one configuration that one production at
+// the most applies to.  The number of the set that follows, or kByTheWave.  Every lane has a token of its own here, so
+// a vocabulary whose tokens share no sets (every prefix of every token a set of its own: 32,000 tokens of 4, 8, 12 bytes
+// over such a grammar) is not worked out one token after the other: 184, 323, 501 us instead of 227, 495, 722; a wave
+// per token, without the shared walk, 125, 172, 220.  What is left is that the tables fill up (from 8 bytes on) and that
+// every token's row is its own.  Nothing is claimed first: two lanes that work out the same come to the same.
+constexpr int kFewProductions = 4;
+__device__ __forceinline__ uint32_t sh_step_alone(const DisplacementArgs &a, SharedLds &L, uint32_t set, uint32_t like,
+                                                  uint32_t dead) {
+    const u64 w = lds_look(&L.sets[set]);
+    lds_order();
+    if (set_size(w) != 1u) return kByTheWave;
+    const uint32_t config = L.pool[set_at(w)], stack = sh_stack(config), last = sh_last(config);
+    int i = 0, n = 0;
+    if (stack) {
+        if (L.pairs_kept == 0u) return kByTheWave;
+        const uint32_t top = cell_symbol(lds_look(&L.cells[stack - 1]));
+        const uint32_t e = L.pair[L.byte_number[like] * (uint32_t)a.g.N + top];
+        i = (int)(e & 0x3FFu);
+        n = (int)(e >> 10);
+    } else {
+        const int lo = (int)L.byte_off[like], hi = (int)L.byte_off[like + 1];
+        if (hi - lo > kFewProductions) return kByTheWave;
+        for (int k = lo; k < hi; ++k) {
+            if (last != kNoSymbol && !sh_may_follow(a, L, sh_production(a, L, k), last)) continue;
+            i = k;
+            ++n;
+        }
+    }
+    if (n == 0) return dead;
+    if (n > 1) return kByTheWave;
+    bool full = false, crossed = false;
+    const uint32_t word = sh_carry_out(a, L, config, i, full, crossed);
+    if (crossed) return kCrossed;
+    if (full) return kGiveUp;
+    const uint32_t h = set_hash(word_hash(word), 1u);
+    const u64 tag = (u64)(h >> 8) << 24;
+    uint32_t at = h & (kShSets - 1);
+    int reserved = -1;
+    for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShSets - 1)) {
+        u64 found = lds_look(&L.sets[at]);
+        if (found == kShEmpty) {
+            if (reserved < 0) {
+                reserved = (int)atomicAdd(&L.pool_top, 1u);
+                if (reserved >= kShPool) return kGiveUp;
+                L.pool[reserved] = word;
+            }
+            lds_order();
+            found = atomicCAS(&L.sets[at], kShEmpty, tag | ((u64)reserved << 8) | 1ull);
+            if (found == kShEmpty) return at;
+        }
+        lds_order();
+        if ((found >> 24 << 24) == tag && set_size(found) == 1u && L.pool[set_at(found)] == word) return at;
+    }
+    return kGiveUp;
+}
+
 // One byte of Algorithm 1 on a whole set, by the whole wave: the number of the set that follows.  First the pairs
 // (configuration, production that applies) are listed, then all of them are carried out together, a lane each: the
 // chain of LDS accesses is what this costs, and it is gone through once.
@@ -296,8 +411,7 @@ __device__ __forceinline__ uint32_t sh_step(const DisplacementArgs &a, SharedLds
     const int lo = (int)L.byte_off[ch], hi = (int)L.byte_off[ch + 1], per = hi - lo;
     const bool pairs_kept = L.pairs_kept != 0u;
     const uint32_t byte_number = L.byte_number[ch];
-    const bool prods_here = g.P <= kShProds, adj_here = g.N * g.W <= kShAdj;
-    auto prod = [&](int i) -> u64 { return prods_here ? L.prods[i] : a.prod_packed[i]; };
+    auto prod = [&](int i) -> u64 { return sh_production(a, L, i); };
     const u64 below = (1ull << lane) - 1ull;
     uint32_t *pairs = work, *out = work + kShFrontier;  // a pair: configuration (7 bits), production above
     int m = 0, empties = 0;
@@ -363,10 +477,7 @@ __device__ __forceinline__ uint32_t sh_step(const DisplacementArgs &a, SharedLds
         for (int u = 0; u < kAhead; ++u) {
             if (on[u]) {
                 const uint32_t last = sh_last(configs[c[u]]);
-                if (last != kNoSymbol) {
-                    const uint32_t word = packed_head(prod(i[u])) * (uint32_t)g.W + (last >> 5);
-                    on[u] = ((adj_here ? L.adj[word] : a.adj[word]) >> (last & 31)) & 1u;
-                }
+                if (last != kNoSymbol) on[u] = sh_may_follow(a, L, prod(i[u]), last);
             }
         }
 #pragma unroll
@@ -378,33 +489,7 @@ __device__ __forceinline__ uint32_t sh_step(const DisplacementArgs &a, SharedLds
     bool full = false, crossed = false;
     auto carry_out = [&](int x) -> uint32_t {
         if (x >= m) return kNoWord;
-        const uint32_t config = configs[pairs[x] & 0x7Fu];
-        const int i = (int)(pairs[x] >> 7);
-        const u64 p = prod(i);
-        const uint32_t head = packed_head(p), stack = sh_stack(config);
-        uint32_t queue = sh_queue(config), rest = 0, rest_length = 0;
-        const uint32_t cell = stack ? lds_look(&L.cells[stack - 1]) : (queue ? lds_look(&L.cells[queue - 1]) : 0u);
-        int length = (int)packed_length(p);
-        const bool is_long = length == (int)kLongBody;
-        if (is_long) length = body_len(g, i);
-        if (stack) {
-            rest = cell_rest(cell);
-            rest_length = cell_length(cell) - 1u;
-        } else {
-            const uint32_t queued = cell_length(cell) + 1u;
-            if (queued > (uint32_t)kShMaxList) crossed = true;
-            else queue = sh_cons(L, queue, head, queued, full);
-        }
-        if (rest_length + (uint32_t)length > (uint32_t)kShMaxList) {
-            crossed = true;
-        } else {
-            const int off = is_long ? g.body_off[i] : 0;
-            for (int k = length - 1; k >= 0; --k) {
-                const uint32_t s = is_long ? (uint32_t)g.body[off + k] & 0xFFu : packed_symbol(p, k);
-                rest = sh_cons(L, rest, s, ++rest_length, full);
-            }
-        }
-        return sh_config(queue, rest, head);
+        return sh_carry_out(a, L, configs[pairs[x] & 0x7Fu], (int)(pairs[x] >> 7), full, crossed);
     };
     const uint32_t first = carry_out(lane);
     uint32_t second = kNoWord;
@@ -592,6 +677,7 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
 
     const int64_t group0 = (int64_t)blockIdx.x * per_group;
     const int in_group = (int)min((int64_t)per_group, (int64_t)a.V - group0);
+    int steps = 0;  // that this wave has worked out
     for (;;) {
         __builtin_amdgcn_wave_barrier();  // the wave goes round together: no branch on the lane is joined with the next one
         int taken = 0;
@@ -620,6 +706,7 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
         };
         uint32_t set = start;
         bool give_up = false, crossed = false;
+        bool by_the_wave = false;  // the next step has turned out to take a whole wave
         uint32_t like = pos < end ? byte_at(pos) : 0u;
         for (;;) {
             // every lane as far as what follows is known
@@ -631,6 +718,7 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
                     pos = end;
                 } else {
                     set = following;
+                    by_the_wave = false;
                     if (++pos < end) like = byte_at(pos);
                 }
             };
@@ -642,6 +730,21 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
                 const uint32_t following = sh_known(L, set, like);
                 if (following == kNextEmpty || following == kWorkedOut) waits = following;
                 else advance(following);
+            }
+            // where the tokens share few sets: what follows by the lanes alone, as far as it is simple
+            const bool alone = waits == kNextEmpty && !by_the_wave && steps > kShShared;
+            if (__ballot(alone)) {
+                if (alone) {
+                    const uint32_t following = sh_step_alone(a, L, set, like, dead);
+                    if (following == kByTheWave) {
+                        by_the_wave = true;
+                    } else {
+                        sh_publish(L, set, like, following);
+                        waits = 0;
+                        advance(following);
+                    }
+                }
+                if (__ballot(alone && !by_the_wave)) continue;
             }
             const u64 unknown = __ballot(waits == kNextEmpty);
             if (!unknown) {
@@ -658,6 +761,7 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
             slot = __builtin_amdgcn_readfirstlane(slot);
             if (slot == -1) continue;  // taken meanwhile
             const uint32_t following = sh_step(a, L, work, seen, from, (int)on, lane);
+            ++steps;
             lds_order();
             if (slot >= 0 && lane == 0)
                 __hip_atomic_store(&L.next[slot], (((from << 8) | on) << kNextBits) | following, __ATOMIC_RELAXED,

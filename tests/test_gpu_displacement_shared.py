@@ -75,6 +75,22 @@ def test_vocabulary_that_exhausts_the_tables(lib):
     _check_rows(lib, g, vocab_from_tokens(toks), expect_overflow=True)
 
 
+@pytest.mark.parametrize("n", [26, 120])
+def test_tokens_that_share_no_sets(lib, n):
+    """Sets of one configuration that a lane works out alone, after its wave has worked out a few: pops, backtracks on
+    an empty stack, bodies of none to six symbols, bytes that nothing applies to, and lists past their bound."""
+    rng = np.random.default_rng(n)
+    prods = [(A, 97 + A % 26, ()) for A in range(n)]                                          # pop, one or more per byte
+    prods += [(A, 65 + (A + 7) % 26, tuple(int(x) for x in rng.integers(0, n, size=A % 7))) for A in range(n)]
+    prods += [(n, 35, (A, B)) for A in range(min(n, 26)) for B in range(min(n, 26))]          # any may follow any of these
+    g = grammar_from_productions(n + 1, prods)
+    alphabet = np.frombuffer(b"abcdefghijklmnopqrstuvwxyzABCDEFGHIJKLMNOPQRSTUVWXYZ", np.uint8)
+    toks = [bytes(alphabet[rng.integers(0, 26 if k % 3 else 52, size=int(m))])
+            for k, m in enumerate(rng.integers(1, 10, size=9_000))]
+    toks += [b"ab!cd", b"!", b"a" * 33, b"ab" * 20, b"#ab", b"abc#"] * 8
+    _check_rows(lib, g, vocab_from_tokens(toks))
+
+
 def test_rows_that_are_only_8_byte_aligned(lib):
     from gpu_util import dev
     g = make_json_gnf()
