@@ -804,7 +804,8 @@ __global__ void hand_all_kernel(DisplacementArgs a) {
 
 template <typename Sym>
 int launch_displacements(const DisplacementArgs &a, int n_cu, hipStream_t stream) {
-    if (a.g.N <= kShMaxSymbols) {
+    static_assert(kShMaxSymbols == kMaxByteSymbols, "the shared walk takes every grammar whose symbols fit a byte");
+    if constexpr (sizeof(Sym) == 1) {
         // a workgroup of sixteen waves per compute unit, the tokens spread evenly
         const int64_t groups = std::min<int64_t>(n_cu, ceil_div(a.V, kShWaves));
         const int per_group = (int)ceil_div(a.V, groups);
