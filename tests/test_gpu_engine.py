@@ -239,6 +239,37 @@ def test_closed_decode_loop_in_one_launch_per_step(lib, config, dtype):
     assert (states_np[[3, 5]] == -1).all()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("extra,shift", [(0, 0), (1, 0), (3, 1), (8, 3)])
+def test_engine_step_on_rows_of_any_alignment(lib, dtype, extra, shift):
+    """Row strides and bases that are whole elements only: every row starts at another alignment, the tiles are full
+    ones and a ragged last one, and nothing beside the rows is written."""
+    from gpu_util import dev, logits_dev, logits_bits
+    print(f"case dtype={dtype} extra={extra} shift={shift}", flush=True)
+    rng = np.random.default_rng(10 * extra + shift)
+    B, V, C, S = 7, 2 * 2048 + 5, 300, 40
+    c = np.concatenate([np.arange(C), rng.integers(0, C, size=V - C)]).astype(np.int32)
+    sig_rep = rng.integers(0, S, size=(C, S)).astype(np.uint16)
+    live = (rng.random(S) < 0.5).astype(np.uint8)
+    state_mask = lib.cfgzip_state_masks(dev(sig_rep), dev(live))
+    states = rng.integers(0, S, size=B).astype(np.int32)
+    tok = rng.integers(0, V, size=B).astype(np.int32)
+    want_states = oracle.advance_states(sig_rep, c, tok, states)
+    want_bits = oracle.expand_mask(oracle.class_masks(oracle.state_masks(sig_rep, live), C, want_states), c, C)
+    n = shift + B * (V + extra)
+    x = rng.integers(0, 2**32, size=n, dtype=np.uint32) if dtype == "f32" else rng.integers(0, 2**16, size=n, dtype=np.uint16)
+    buf = logits_dev(x, dtype)
+    rows = buf[shift:].view(B, V + extra)[:, :V]
+    tok_bits = torch.full((B, words_for(V)), -1, dtype=torch.int32, device="cuda")
+    out = lib.cfgzip_engine_step(rows, state_mask, C, dev(c), dev(sig_rep), dev(tok), dev(states), tok_bits_out=tok_bits)
+    assert (out.cpu().numpy() == want_states).all()
+    assert (tok_bits.cpu().numpy() == want_bits).all()
+    want = x.copy()
+    want[shift:].reshape(B, V + extra)[:, :V] = oracle.apply_mask(
+        np.ascontiguousarray(x[shift:].reshape(B, V + extra)[:, :V]), want_bits, dtype)
+    assert (logits_bits(buf) == want).all()
+
+
 def test_engine_step_argument_errors(lib):
     raw = lib.load_library()
     t = torch.zeros(256, dtype=torch.int32, device="cuda")
