@@ -133,3 +133,40 @@ def test_hash_bits_that_tell_classes_apart(lib, shift):
         c, r, C, coll = lib.cfgzip_build_classes(tb, to, tt, rows, h, signatures_workspace=store)
         assert C == 32 and (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
         assert (coll == 0) == (shift <= 32)
+
+
+def test_rows_of_a_large_vocabulary(lib):
+    """Rows as the source and so many tokens that the waves that compare them go round more than once."""
+    import synthetic_inputs as si
+    cfg = si.make_config(1, V=262_144)
+    _, coll = _check_build(lib, cfg["vocab"], cfg["table"], use_store=False)
+    assert coll == 0
+
+
+@pytest.mark.parametrize("stored", [True, False])
+@pytest.mark.parametrize("case", ["zeroed", "overflowed"])
+def test_sort_starts_over_when_the_store_cannot_be_used(lib, case, stored):
+    """One token more than the table takes, so the sort is first to find that the workspace is not a signature call's,
+    or that its vectors overflowed (one byte leaves 520 states); from rows and by walking again."""
+    from gpu_util import vocab_dev
+    print(f"case {case} stored={stored}", flush=True)
+    rng = np.random.default_rng(9)
+    S = 520 if case == "overflowed" else 24
+    table = np.tile((np.arange(256) % 7).astype(np.uint16), (S, 1))
+    table[:, 200] = rng.permutation(S)
+    lens = rng.integers(0, 3, size=262_145)
+    data = rng.integers(190, 210, size=int(lens.sum()), dtype=np.uint8)
+    cuts = np.concatenate([[0], np.cumsum(lens)])
+    vocab = vocab_from_tokens([data[a:b].tobytes() for a, b in zip(cuts[:-1], cuts[1:])])
+    want_sig = oracle.signatures(vocab.tok_bytes, vocab.tok_off, table)
+    want_c, want_r = oracle.build_classes(want_sig, vocab.tok_off)
+    tb, to, tt = vocab_dev(vocab, table)
+    ws = torch.zeros(lib.load_library().cfgzip_signatures_workspace_bytes(vocab.V, S), dtype=torch.uint8, device="cuda")
+    sig, h = lib.cfgzip_signatures(tb, to, tt, want_sig=stored, workspace=ws)
+    if case == "zeroed":
+        ws.zero_()
+    else:
+        assert ws[:32].cpu().numpy().view(np.uint32)[4] == 1
+    c, r, C, coll = lib.cfgzip_build_classes(tb, to, tt, sig, h, signatures_workspace=ws)
+    assert C == len(want_r) and coll == 0
+    assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()

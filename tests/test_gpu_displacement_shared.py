@@ -75,6 +75,18 @@ def test_vocabulary_that_exhausts_the_tables(lib):
     _check_rows(lib, g, vocab_from_tokens(toks), expect_overflow=True)
 
 
+def test_rounds_of_more_bytes_than_are_staged(lib):
+    """A wave keeps up to 256 bytes of the tokens it has taken in LDS: single tokens around that, and rounds of three
+    tokens that only together have more."""
+    g = grammar_from_productions(1, [(0, ord("a"), (0,)), (0, ord("a"), ()), (0, ord("b"), (0,))])
+    rng = np.random.default_rng(5)
+    long_ones = [b"ab" * 127 + b"a", b"ab" * 128, b"ab" * 128 + b"a", b"a" * 700, b"b" * 255 + b"z" + b"a" * 40]
+    _check_rows(lib, g, vocab_from_tokens(long_ones))
+    toks = [bytes(rng.integers(97, 99, size=int(m), dtype=np.uint8))
+            for m in np.where(rng.random(9_000) < 0.3, rng.integers(80, 140, size=9_000), rng.integers(0, 5, size=9_000))]
+    _check_rows(lib, g, vocab_from_tokens(toks + long_ones))
+
+
 @pytest.mark.parametrize("n", [26, 120])
 def test_tokens_that_share_no_sets(lib, n):
     """Sets of one configuration that a lane works out alone, after its wave has worked out a few: pops, backtracks on
