@@ -411,7 +411,7 @@ __global__ __launch_bounds__(kTableAssignThreads) void table_assign_kernel(Table
     }
 #pragma unroll
     for (int j = 0; j < kTableAssignItems; ++j) marks[j] = a.word_marks[m[j] >> 5];
-    // a scan per workgroup (8 words a thread at the most) instead of a launch of its own
+    // a scan per workgroup (1,024 stretches, two a thread, at the most) instead of a launch of its own
     uint32_t run = 0;
     for (int s0 = 0; s0 < a.n_stretches; s0 += kTableAssignThreads) {
         const int s = s0 + tid;

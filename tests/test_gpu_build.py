@@ -335,8 +335,9 @@ def test_million_token_vocabulary(lib):
 
 @pytest.mark.parametrize("V", [262_144, 262_145])
 def test_vocabulary_sizes_around_the_switch_to_wider_keys(lib, V):
-    """Up to 262,144 tokens the sort key holds 32 hash bits (four passes) and the ranking keeps its
-    bit vector in LDS; one token more and it is 40 bits (five passes) and scan kernels."""
+    """Up to 262,144 tokens the hash table groups where kept vectors are at hand, and where the signatures are walked
+    again the sort key holds 32 hash bits (four passes) and the ranking keeps its bit vector in LDS; one token more and
+    everything is sorted, by 40 bits (five passes) and with scan kernels."""
     print(f"case V={V}", flush=True)
     cfg = si.make_config(1, V=V)
     C, coll = _check_build(lib, cfg["vocab"], cfg["table"], use_store=True)
@@ -348,7 +349,7 @@ def test_vocabulary_sizes_around_the_switch_to_wider_keys(lib, V):
 def test_signature_workspace_that_does_not_match_is_ignored(lib, cfg1, cfg2_small):
     """A workspace left by a call on another vocabulary / automaton, a zeroed one, and one
     whose compressed signatures overflowed (random automaton: ~0.63 S states per token, more
-    than the 256 kept) must all give the same classes as no workspace at all."""
+    than the 512 kept) must all give the same classes as no workspace at all."""
     from gpu_util import vocab_dev
     raw = lib.load_library()
     v1, t1 = cfg1["vocab"], cfg1["table"]

@@ -66,6 +66,20 @@ def test_widest_images_that_are_kept(lib, n):
     _check_build(lib, vocab_from_tokens(toks), table, stored=False)
 
 
+@pytest.mark.parametrize("n", [264, 512])
+def test_wide_images_with_colliding_hashes(lib, n):
+    """The sort's comparisons of kept vectors of more than 256 states, within a first byte and across."""
+    rng = np.random.default_rng(n)
+    S = 600
+    table = np.zeros((S, 256), np.uint16)
+    for b in range(8):
+        table[:, b] = rng.permutation(S)[:n][np.arange(S) % n]
+    toks = [rng.integers(0, 8, size=int(k), dtype=np.uint8).tobytes() for k in rng.integers(0, 5, size=700)]
+    _, coll = _check_build(lib, vocab_from_tokens(toks), table, stored=False, use_store=True,
+                           hash_override=lambda h: h & 3)
+    assert coll > 0
+
+
 @pytest.mark.parametrize("stored", [True, False])
 def test_colliding_hashes_are_settled(lib, stored):
     vocab, table = _case("last byte", 1500, 5)

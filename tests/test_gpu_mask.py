@@ -103,7 +103,8 @@ def test_mask_extreme_densities(lib, p):
 
 
 def test_mask_unaligned_base_pointers(lib):
-    """Views that start 2 / 4 bytes into an allocation take the element-wise path."""
+    """Views that start 2 / 4 bytes into an allocation: the same 16-byte accesses as aligned rows, and the last three
+    columns one by one."""
     from gpu_util import dev, logits_bits
     rng = np.random.default_rng(3)
     B, V, C = 4, 515, 40
