@@ -11,17 +11,23 @@
 //
 // Queues and stacks are lists of shared cells: a cell is one 32-bit word (the rest of the list, a symbol, the
 // length), its number is its slot in a hash table keyed by that very word, and equal lists have equal numbers.  A
-// configuration is therefore one 32-bit word, a set some of them, and comparing two sets comparing words.  Nothing
-// waits for anything: an entry is published by one compare-and-swap after what it refers to has been written,
-// and two waves that work out the same thing at the same time agree on the first entry.
+// configuration is therefore one 32-bit word, a set some of them, and comparing two sets comparing words.  Cells and
+// sets are entered by one compare-and-swap after what they refer to has been written, and two waves that enter the
+// same thing at the same time agree on the first entry.
+//
+// What follows a set on a byte, and what a set is written as, is claimed first: a placeholder goes into the table, the
+// wave works the answer out, and the answer takes the placeholder's place.  Who needs it meanwhile looks again until it
+// is there.  So that every such wait ends, a wave waits for nothing between its claim and the answer, and does not leave
+// without giving it.
 //
 // What a token's set is written as (the canonical row and its hash) is worked out once per set too; writing a row
 // is then a copy out of LDS, and writing the rows is what bounds the kernel on a large vocabulary.
 //
-// Measured: 128,256 tokens over the JSON grammar with rows of 1,024 entries 171 us (a wave per token took 510 us for
-// most tokens and 276 us for long digit runs), 32,000 over the statement grammar with rows of 256 99 us (210 us).
-// What bounds it: the longest chain of new sets in a workgroup (a digit run of 25 bytes makes a new set at every
-// byte), each link of which is some thirty dependent LDS accesses, and writing the rows (262 MB, 45 us).
+// Measured: 128,256 tokens over the JSON grammar with rows of 1,024 entries 171-181 us (a wave per token took 510 us for
+// most tokens and 276 us for long digit runs), 32,000 over the statement grammar with rows of 256 90-100 us (210 us).
+// What bounds it: working out new sets (97 steps in a workgroup with 125 tokens over the JSON grammar, 165 with 501), as
+// much by the instructions of a step as by its chain of LDS accesses: a wave waits in 45 % of its cycles and issues
+// in 39 %, 14 vector and 14 scalar instructions for every LDS one.  Then writing the rows (262 MB, 39-45 us).
 //
 // Everything in LDS is bounded.  A token that would need more (more than 128 successors at a byte, more cells,
 // sets or row entries than there is room for) goes to the list of the passes behind this one, which take it alone.
