@@ -45,7 +45,12 @@ constexpr int kMaxByteSymbols = 255;           // up to here a symbol (and "none
 
 // caps of the second pass (over what the shared walk hands on) and of the third (over what the second could not
 // finish), which are the interface's
-constexpr int kIn1 = 12, kOut1 = 12, kFrontier1 = 128;
+// The second pass's queue and stack: what a token needs there sets how many waves a compute unit holds.  8-bit symbols:
+// 24 (12 waves; 32,000 tokens that share no sets, of 8, 12, 24 bytes: 303, 591, 1,050 us; 32: 296, 644, 1,180; 12, which
+// 20 waves fit with: 326, 504, 2,830, the last because the third pass then takes them all).
+template <typename Sym>
+constexpr int kLists1 = sizeof(Sym) == 1 ? 24 : 12;
+constexpr int kFrontier1 = 128;
 constexpr int kIn2 = 32, kOut2 = 32, kFrontier2 = 256;
 // the third pass keeps the current byte's productions and the relation in LDS when they fit
 constexpr int kStageCap = 128;      // productions of one terminal
@@ -749,8 +754,8 @@ __device__ void token_displacement(const DisplacementArgs &a, int t,
 
 // Entries of a long list that a workgroup of the second pass takes at a time.  The atomics on the list's one cursor are
 // served one after the other, 14 ns each, which is more than a short token's share of the chip: 32,000 entries of 8
-// bytes over a simple grammar 273 us in fours (467 one by one, 226 dealt out beforehand, 174 as a workgroup each), of
-// 32,000 over 500 symbols, whose work differs, 3.45 ms (3.73, 4.49).  The few long tokens of the third pass are taken
+// bytes over a simple grammar 376 us in fours (445 one by one, 423 dealt out beforehand), of 128,256 over the JSON
+// grammar, whose work differs, 1.39 ms (1.91, 1.92), of 32,000 over 500 symbols 3.45 ms (3.73, 4.49).  The few long tokens of the third pass are taken
 // one by one.
 constexpr int kRetryChunk = 4;
 
@@ -819,7 +824,7 @@ int launch_displacements(const DisplacementArgs &a, int n_cu, hipStream_t stream
         hipLaunchKernelGGL(hand_all_kernel, dim3((unsigned)std::min<int64_t>(1024, ceil_div(a.V, 256))), dim3(256), 0, stream, a);
     }
     CFGZIP_TRY(check_launch());
-    CFGZIP_TRY((launch_retry<Sym, kIn1, kOut1, kFrontier1, 0, 1, false>(a, n_cu, stream)));
+    CFGZIP_TRY((launch_retry<Sym, kLists1<Sym>, kLists1<Sym>, kFrontier1, 0, 1, false>(a, n_cu, stream)));
     return launch_retry<Sym, kIn2, kOut2, kFrontier2, 1, -1, true>(a, n_cu, stream);
 }
 

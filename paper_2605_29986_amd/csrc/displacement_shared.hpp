@@ -350,7 +350,7 @@ __device__ __forceinline__ uint32_t sh_carry_out(const DisplacementArgs &a, Shar
 // One byte of Algorithm 1 by one lane, where it is simple enough: a set of one configuration that one production at
 // the most applies to.  The number of the set that follows, or kByTheWave.  Every lane has a token of its own here, so
 // a vocabulary whose tokens share no sets (every prefix of every token a set of its own: 32,000 tokens of 4, 8, 12 bytes
-// over such a grammar) is not worked out one token after the other: 184, 323, 501 us instead of 227, 495, 722; a wave
+// over such a grammar) is not worked out one token after the other: 185, 303, 591 us (227, 495, 722 before); a wave
 // per token, without the shared walk, 125, 172, 220.  What is left is that the tables fill up (from 8 bytes on) and that
 // every token's row is its own.  Nothing is claimed first: two lanes that work out the same come to the same.
 constexpr int kFewProductions = 4;

@@ -183,9 +183,9 @@ def test_long_tokens(lib):
     assert rows[1][0] > 0 and rows[3][0] > 0 and rows[4][0] == 0
 
 
-# The kernel first takes every token in small buffers (queue 12, stack 12, 128 successors) and
-# again in larger ones when those do not suffice; which attempt finishes a token must not show in
-# any output.  The inputs below sit on both sides of the small sizes and of the interface's limits.
+# Tokens that the shared walk does not take (with more than 255 symbols all of them) are taken in
+# small buffers first (queue and stack 12, with up to 255 symbols 24; 128 successors) and again in
+# larger ones when those do not suffice; which attempt finishes a token must not show in any output.  The inputs below sit on both sides of the small sizes and of the interface's limits.
 KERNEL_FIRST_ATTEMPT = (12, 12, 128)
 
 

@@ -75,6 +75,19 @@ def test_vocabulary_that_exhausts_the_tables(lib):
     _check_rows(lib, g, vocab_from_tokens(toks), expect_overflow=True)
 
 
+def test_deep_stacks_behind_exhausted_tables(lib):
+    """Tokens of a few random symbols (no sets are shared) and then a stack that grows by two with every byte: queues and
+    stacks on both sides of what the passes behind the shared walk hold."""
+    n = 26
+    prods = [(A, 97 + A, ()) for A in range(n)] + [(n, 64, (A, B)) for A in range(n) for B in range(n)]
+    prods += [(n, 64, (A, n + 1)) for A in range(n)] + [(n + 1, ord("+"), (n + 1,) * 3), (n + 1, ord("-"), ())]
+    g = grammar_from_productions(n + 2, prods)
+    rng = np.random.default_rng(3)
+    toks = [bytes(rng.integers(97, 123, size=int(k), dtype=np.uint8)) + b"+" * int(p) + b"-" * int(m)
+            for k, p, m in zip(rng.integers(8, 28, size=9_000), rng.integers(0, 18, size=9_000), rng.integers(0, 4, size=9_000))]
+    _check_rows(lib, g, vocab_from_tokens(toks), expect_overflow=True)
+
+
 def test_rounds_of_more_bytes_than_are_staged(lib):
     """A wave keeps up to 256 bytes of the tokens it has taken in LDS: single tokens around that, and rounds of three
     tokens that only together have more."""
