@@ -755,8 +755,8 @@ __device__ void token_displacement(const DisplacementArgs &a, int t,
 // Entries of a long list that a workgroup of the second pass takes at a time.  The atomics on the list's one cursor are
 // served one after the other, 14 ns each, which is more than a short token's share of the chip: 32,000 entries of 8
 // bytes over a simple grammar 376 us in fours (445 one by one, 423 dealt out beforehand), of 128,256 over the JSON
-// grammar, whose work differs, 1.39 ms (1.91, 1.92), of 32,000 over 500 symbols 3.45 ms (3.73, 4.49).  The few long tokens of the third pass are taken
-// one by one.
+// grammar, whose work differs, 1.39 ms (1.91, 1.92), of 32,000 over 500 symbols 3.45 ms (3.73, 4.49).  The few long
+// tokens of the third pass are taken one by one.
 constexpr int kRetryChunk = 4;
 
 // The passes behind the shared walk: persistent workgroups of one wave take retry list LIST entry by entry; what
