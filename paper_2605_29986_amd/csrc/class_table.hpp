@@ -2,8 +2,8 @@
 // "Pre-Computation").
 //
 // A class is a set of tokens with equal signatures, and equal signatures carry equal hashes, so the
-// tokens are first gathered by 37 bits of it and, inside that, by first byte, because signatures that share the first byte are compared on
-// short vectors.  Four launches:
+// tokens are first gathered by 37 bits of it and, inside that, by first byte, because signatures
+// that share the first byte are compared on short vectors.  Four launches:
 //   1. table_clear_kernel: the two tables start empty;
 //   2. table_group_kernel: a workgroup first gathers its tokens in LDS (a class with a third of
 //      the vocabulary then costs one access to its entry per workgroup and not one per token), then

@@ -219,7 +219,9 @@ struct Different {
 };
 constexpr uint32_t kNoWord = ~0u;  // no configuration: cell numbers are below 2^12 - 1
 
-__device__ __forceinline__ uint32_t word_hash(uint32_t w) { return (w * 0x85EBCA6Bu) ^ (w >> 13) ^ ((w >> 7) * 0x9E3779B1u); }
+__device__ __forceinline__ uint32_t word_hash(uint32_t w) {
+    return (w * 0x85EBCA6Bu) ^ (w >> 13) ^ ((w >> 7) * 0x9E3779B1u);
+}
 __device__ __forceinline__ uint32_t seen_slot(uint32_t word) { return (word * 0x9E3779B1u) >> 24; }
 static_assert(kShSeen == 256, "eight bits of hash");
 
@@ -317,8 +319,8 @@ __device__ __forceinline__ bool sh_may_follow(const DisplacementArgs &a, const S
 }
 
 // A configuration after production i.  `crossed`: a bound of the interface is broken; `full`: there is no room.
-__device__ __forceinline__ uint32_t sh_carry_out(const DisplacementArgs &a, SharedLds &L, uint32_t config, int i, bool &full,
-                                                 bool &crossed) {
+__device__ __forceinline__ uint32_t sh_carry_out(const DisplacementArgs &a, SharedLds &L, uint32_t config, int i,
+                                                 bool &full, bool &crossed) {
     const Grammar &g = a.g;
     const u64 p = sh_production(a, L, i);
     const uint32_t head = packed_head(p), stack = sh_stack(config);

@@ -7,7 +7,8 @@
 // lexer's bytes leave few different sets (about 30 of 256 states).  Up to 256 states a wave therefore walks its token
 // from the different successor sets of the first byte only, a lane each, and every start state's row is a copy of its
 // set's (the image walk of the deterministic case).  A set is W words in registers; per byte the successor rows of
-// its members are ORed together, so the cost follows the size of the sets and not S.  Automata of more than 256 states
+// its members are ORed together, so the cost follows the size of the sets and not S.  Up to 64 states, and with few
+// pairs of token and state, a thread takes a pair instead (kWalkPairs).  Automata of more than 256 states
 // (up to 1,024) walk from every state and keep the sets in LDS.  The 64-bit hash is the same multilinear form as for
 // the byte walk, over the relation read as 16-bit entries, so any split over threads gives the same bits.
 
@@ -23,6 +24,7 @@ constexpr int kThreads = 256;
 constexpr int kMaxRegisterStates = 256;  // up to here a thread keeps its set in registers
 constexpr int kMaxNfaStates = 1024;
 constexpr int kStagedBytes = 64;  // token bytes read once into LDS by nfa_walk_kernel; longer tokens go on from memory
+
 struct NfaArgs {
     const uint8_t *tok_bytes;
     const int64_t *tok_off;
@@ -42,6 +44,7 @@ struct NfaArgs {
 // states 38 us against 42, 64 states 51 against 55 (32,000 tokens).
 constexpr int64_t kWalkPairs = 7 << 17;
 constexpr int kWalkStates = 64;
+
 constexpr int kImageThreads = 1024;
 constexpr int kImageWaves = kImageThreads / 64;
 constexpr int kImageSets = 96;           // different successor sets of a byte that the walk shares
@@ -241,13 +244,14 @@ __device__ __forceinline__ uint32_t number_sets(const NfaArgs &a, ImageLds<W> &L
 // successor sets a byte has is worked out once per workgroup and first byte, by the wave that first needs it.
 // 32,000 tokens x 256 states: 154 us with a thread per (token, start state), bound by instruction issue (75.6 M wave
 // instructions), 90 us so; half of what is left is writing the rows (262 MB, 39-45 us).
-template <int W>
+//
 // `split`: a token that every state walks for itself is shared out among the waves, 64 states each.  So where there is a
 // wave per token or less (per_group <= 16), which would leave the others idle behind it: 8,000 tokens x 256 states
 // without structure 95 us, 105 otherwise, and 1,060 against 1,280 with sets that grow.  With more tokens the waves are
 // busy anyway, and a wave that walks all of a token's states finds their rows in its cache (32,000 tokens: 269 us split,
 // 254 otherwise).  What that costs against a thread per pair, on sets that grow: 3.2 ms, 2.6 there; the tokens are dealt
 // out beforehand and their work differs.  Without structure it is 254 against 329, on lexers 106 against 167.
+template <int W>
 __global__ __launch_bounds__(kImageThreads, 8) void nfa_image_kernel(NfaArgs a, int per_group, bool split) {
     __shared__ ImageLds<W> L;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
