@@ -61,7 +61,7 @@ extern "C" {
 
 #define CFGZIP_OK 0
 #define CFGZIP_E_INVALID (-1)   /* null pointer, non-positive size, S > 65536, bad enum, misaligned pointer */
-#define CFGZIP_E_WORKSPACE (-2) /* ws == NULL or ws_bytes smaller than the query says */
+#define CFGZIP_E_WORKSPACE (-2) /* ws == NULL or ws_bytes smaller than the call takes (the query's size suffices) */
 #define CFGZIP_E_HIP (-3)       /* a HIP call failed; see cfgzip_last_hip_error() */
 #define CFGZIP_E_COLLISION (-4) /* hash collisions could not be resolved within the round limit */
 #define CFGZIP_E_TOO_LARGE (-5) /* a size beyond what an entry point with built-in scratch memory takes */
