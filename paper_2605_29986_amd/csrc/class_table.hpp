@@ -3,23 +3,32 @@
 //
 // A class is a set of tokens with equal signatures, and equal signatures carry equal hashes, so the
 // tokens are first gathered by 37 bits of it and, inside that, by first byte, because signatures
-// that share the first byte are compared on short vectors.  Four launches:
-//   1. table_clear_kernel: the two tables start empty;
-//   2. table_group_kernel: a workgroup first gathers its tokens in LDS (a class with a third of
-//      the vocabulary then costs one access to its entry per workgroup and not one per token), then
-//      enters its distinct (hash, first byte) groups and its distinct hashes into the tables, and
-//      lowers each class's smallest token id and smallest (byte length, token id);
-//   3. table_verify_kernel: every token is compared with one member of its group, and every group's
+// that share the first byte are compared on short vectors.  Three launches, or two:
+//   1. table_gather_kernel: a workgroup takes a run of tokens and gathers them in LDS: what it passes
+//      on are the classes and the groups that it meets, an entry each, and no longer the tokens (a class
+//      with a third of the vocabulary is then one entry of every run).  A small vocabulary does
+//      without: its tokens are the entries;
+//   2. table_merge_kernel: classes and groups are dealt out to buckets, a workgroup each.  Every
+//      workgroup looks at all entries and keeps those of its bucket, which it then tells apart in LDS,
+//      with each class's smallest token id and smallest (byte length, token id): nobody else has an
+//      entry of these, so nothing in memory has to be cleared or shared;
+//   3. table_settle_kernel: every token is compared with one member of its group, and every group's
 //      member with one member of its class (equality is transitive, so all members are equal iff none
-//      of these pairs differs); other workgroups look the tokens' smallest class members up and mark
-//      the tokens that are one;
-//   4. table_assign_kernel: class id = number of marked tokens below the class's smallest member.
-// If any pair differs (a hash collision), or the walk store turns out not to be usable, the host
-// starts over with the sort, which settles collisions exactly; then nothing computed here is used.
+//      of these pairs differs); other workgroups number the classes: a class's id is the number of
+//      classes with a smaller smallest member.
+// If any pair differs (a hash collision), a bucket has no room for its classes, or the walk store turns
+// out not to be usable, the host starts over with the sort, which settles collisions exactly; then
+// nothing computed here is used.
 //
-// What bounds it: the chain of four dependent launches (about 4.6 us each at the least) and, inside
-// each, three to five dependent memory accesses (on 151,936 tokens the waves of the group and verify kernels wait in
-// 79 and 76 % of their cycles); with rows as the source, reading them once.
+// What bounds it: the chain of dependent launches (about 4.6 us each at the least) and, in the last, the comparisons.
+// A table in memory that all workgroups share has to be cleared first and is paid for in atomics on its entries, and
+// which tokens are the smallest of their class is known only at its end, which takes a launch more.  So it was before
+// (clear, group, verify, assign); kernel times then and now, us:
+//      4,096 tokens in 2,980 classes        28 (2 + 17 + 5 + 4)            14 (merge 7, settle 7)
+//     32,000 tokens in   683 classes        22 (2 + 8 + 7 + 4)             20 (gather 6, merge 5, settle 9)
+//    151,936 tokens in 2,559 classes        48 (5.5 + 15 + 23 + 4)         37 (7 + 6 + 24)
+//    128,256 rows of 2 KB in 150 classes    56 (5.4 + 7 + 39 + 4.4)        49 (5 + 5 + 39)
+//     32,000 rows of 8 KB                   73 (5 + 12 + 52 + 4)           59 (5.4 + 5 + 49)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -31,16 +40,6 @@
 namespace cfgzip {
 namespace {
 
-// Tokens per workgroup in table_group_kernel, one per thread: 128 (2^7) or 1,024 (2^10).  Large workgroups meet
-// a class less often, and the accesses to one entry are served one after the other; small ones put more compute
-// units on a small vocabulary, most of whose tokens make an entry.  Measured with 64 / 128 / 1,024 threads:
-// 4,096 tokens in 2,980 classes 14.8 / 14.7 / 22.4 us, 32,000 in 683 classes 16.2 / 8.4 / 8.3 us, 128,256 in
-// 1,460 classes 59.9 / 25.8 / 12.8 us.
-constexpr int kGroupBitsSmall = 7, kGroupBitsLarge = 10;
-constexpr int32_t kGroupSmallTokens = 16384;
-constexpr int kTableThreads = 256;
-constexpr int kTableAssignThreads = 512;
-constexpr int kTableAssignItems = 2;
 // An entry is one 64-bit word, entered with one compare-and-swap: 37 hash bits, 8 bits of first byte
 // and, below them, the id of the token that made it.  More tokens than this would not fit and go to the sort.
 // 37 bits are what leaves one over, so that no entry looks like an empty slot.  A pair of classes that share
@@ -49,326 +48,576 @@ constexpr int kTableAssignItems = 2;
 constexpr int kTokenBits = 18;
 constexpr int kTableHashBits = 37;
 constexpr int32_t kTableMaxTokens = 1 << kTokenBits;
+constexpr unsigned long long kTokenMask = kTableMaxTokens - 1;
 constexpr unsigned long long kNoEntry = ~0ull;
 static_assert(kTableHashBits + 8 + kTokenBits < 64, "an entry is never all ones");
-constexpr int kCrossParts = 4;  // waves that share one comparison across two image rows
+constexpr int kCrossParts = 4;   // waves that share one comparison across two image rows
+constexpr int kGroupBlocks = 4;  // workgroups that share the comparisons of a bucket's groups
 
-// Open addressing, linear probing; the capacity is a power of two and at least 1.25 V, so an
-// insertion always ends.
-struct ClassTable {
-    unsigned long long *group;    // (hash bits, first byte, one member)
-    unsigned long long *cls;      // (hash bits, 0, one member)
-    unsigned long long *cls_rep;  // smallest (byte length << 32 | token id)
-    uint32_t *cls_min;            // smallest token id
-    uint32_t mask;                // capacity - 1
-    int shift;                    // 64 - log2(capacity)
-};
+// Runs of tokens that the gathering workgroups take, a token per thread.
+constexpr int kRunBits = 10;
+constexpr int kRun = 1 << kRunBits;
+constexpr int kMaxRuns = kTableMaxTokens / kRun;
+// Up to here the tokens are the entries: every bucket then looks at every token, which takes longer than a launch from
+// about here on (3,000 / 6,000 / 10,000 / 16,000 tokens: merge 6.9 / 10.1 / 12.4 / 15.8 us; gathered first, gather and
+// merge 10.0 / 10.3 / 10.2 / 10.2).
+constexpr int32_t kDirectTokens = 6144;
 
-inline uint32_t class_table_capacity(int32_t V) {
-    uint32_t cap = 1024;
-    if (V > kTableMaxTokens) return cap;  // not used
-    while ((uint64_t)cap * 4 < (uint64_t)V * 5) cap <<= 1;
-    return cap;
+// Buckets: at most as many as there are compute units, and 64 tokens in each on average (the lists of groups to be
+// compared, kListedLeast a bucket, then stay small against the vocabulary).
+constexpr int kMergeThreads = 1024;
+constexpr int kMergeWaves = kMergeThreads / 64;
+constexpr int kMaxBuckets = 256;
+constexpr int kBucketTokens = 64;
+// A bucket's LDS table.  262,144 tokens of a class each put 1,024 into a bucket, give or take 32, and half full a run
+// of kTableProbes taken slots has a chance of 1e-11 in each place.
+constexpr int kTableSlotBits = 11;
+constexpr int kTableSlots = 1 << kTableSlotBits;
+constexpr int kTableProbes = 128;
+constexpr uint32_t kNoSlot = 0x3FFF;  // fits above an entry's number in a word
+static_assert(kTableSlots <= (int)kNoSlot && kTokenBits + 14 <= 32, "");
+constexpr int kMergeList = 8192;  // entries of a bucket's list (LDS for two workgroups in a compute unit)
+constexpr int kListedLeast = 512;
+
+inline int table_buckets(int32_t V) {
+    int b = 1;
+    while (b < kMaxBuckets && 2 * b * kBucketTokens <= V) b *= 2;
+    return b;
+}
+// Groups that a bucket may list: with what its table has room for, a list of 256 such would take more memory than the
+// sort does on small vocabularies.
+inline int table_list_room(int32_t V) {
+    const int per = 4 * (V / table_buckets(V));
+    return per < kListedLeast ? kListedLeast : (per < kTableSlots ? per : kTableSlots);
 }
 
-__device__ __forceinline__ uint32_t table_home(unsigned long long key, int shift) {
-    return (uint32_t)((key * 0x9E3779B97F4A7C15ull) >> shift);
+// The bucket of a class or a group: all bytes of its 37 hash bits, and the first byte, have a part in it.
+__device__ __forceinline__ uint32_t bucket_of(unsigned long long word, uint32_t mask) {
+    const uint32_t low = (uint32_t)(word >> (8 + kTokenBits)), high = (uint32_t)(word >> (8 + kTokenBits + 32));
+    const uint32_t fb = (uint32_t)(word >> kTokenBits) & 0xFFu;
+    return __builtin_amdgcn_udot4(low, 0x1D0B0501u, high + fb * 37u, false) & mask;
 }
 
-struct TableClearArgs {
-    uint4 *words;  // the arrays of the table lie behind each other
-    size_t n16;
-    Counters *ctr;
-};
-
-__global__ __launch_bounds__(kTableThreads) void table_clear_kernel(TableClearArgs a) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        a.ctr->unresolved = 0;
-        a.ctr->num_classes = 0;
-        a.ctr->store_state = 0;
-        a.ctr->other_rows = 0;
-    }
-    const size_t step = (size_t)gridDim.x * kTableThreads;
-    for (size_t i = (size_t)blockIdx.x * kTableThreads + threadIdx.x; i < a.n16; i += step)
-        a.words[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
-}
-
-struct TableGroupArgs {
+struct TableTokens {
     const uint64_t *hash;
     const int64_t *tok_off;
     const uint8_t *tok_bytes;
     int n;
     bool by_first_byte;  // false: rows are compared whole, the first byte does not matter
-    ClassTable t;
-    int32_t *tok_ref;    // [n] out: a member of the token's group, the same for the whole group
-    int32_t *tok_cls;    // [n] out: its class's entry
-    int2 *cross_list;    // (member of a group, member of its class), to be compared across first bytes
-    Counters *ctr;       // other_rows counts the list
 };
 
-__device__ __forceinline__ unsigned long long table_look(const unsigned long long *entry) {
-    return __hip_atomic_load(entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// A token's entry word and (byte length, id), the latter as one word that orders them.
+struct TokenEntry {
+    unsigned long long word, rep;
+};
+__device__ __forceinline__ TokenEntry token_entry(int t, unsigned long long hash, int64_t beg, int64_t end, uint32_t fb) {
+    const int64_t len = min(max(end - beg, (int64_t)0), (int64_t)0x7FFFFFFF);
+    return {((hash & ((1ull << kTableHashBits) - 1ull)) << (8 + kTokenBits)) | ((unsigned long long)fb << kTokenBits) | (uint32_t)t,
+            ((unsigned long long)len << 32) | (uint32_t)t};
 }
 
-// The entry of `mine`'s key from slot `at` on, whose content was `seen` after any attempt to claim it
-// (kNoEntry: `mine` has claimed it).  Returns the entry as it stands in the table.
-__device__ __forceinline__ unsigned long long table_settle(unsigned long long *table, uint32_t mask, uint32_t &at,
-                                                           unsigned long long mine, unsigned long long seen) {
-    for (uint32_t probes = 0; probes <= mask; ++probes) {
-        if (seen == kNoEntry) return mine;
-        if ((seen >> kTokenBits) == (mine >> kTokenBits)) return seen;
-        at = (at + 1) & mask;
-        seen = table_look(&table[at]);
-        if (seen == kNoEntry) seen = atomicCAS(&table[at], kNoEntry, mine);
-    }
-    return mine;  // not reached: the table has more slots than there are tokens
+__device__ __forceinline__ unsigned long long class_word(unsigned long long word) {  // without the first byte
+    return word & ~(0xFFull << kTokenBits);
 }
 
-// The slot of the key in the workgroup's LDS table, at most half full; `made`: this thread's entry is there.
-template <int SLOT_BITS>
-__device__ __forceinline__ uint32_t lds_enter(unsigned long long *table, unsigned long long mine, bool &made) {
+// The slot of `mine`'s key in an LDS table, where the smallest token id with that key comes to stand.  False: there is
+// no room.  `made`: this thread's was the first.
+template <int SLOT_BITS, int PROBES>
+__device__ __forceinline__ bool lds_enter(unsigned long long *table, unsigned long long mine, uint32_t &at, bool &made) {
     constexpr uint32_t mask = (1u << SLOT_BITS) - 1;
-    uint32_t at = table_home(mine >> kTokenBits, 64 - SLOT_BITS);
+    at = (uint32_t)(((mine >> kTokenBits) * 0x9E3779B97F4A7C15ull) >> (64 - SLOT_BITS));
     made = false;
-    for (uint32_t probes = 0; probes <= mask; ++probes, at = (at + 1) & mask) {
+    for (int probe = 0; probe < PROBES; ++probe, at = (at + 1) & mask) {
         unsigned long long seen = *(volatile unsigned long long *)&table[at];
-        if (seen == kNoEntry) seen = atomicCAS(&table[at], kNoEntry, mine);
         if (seen == kNoEntry) {
-            made = true;
-            return at;
+            seen = atomicCAS(&table[at], kNoEntry, mine);
+            made = seen == kNoEntry;
+            if (made) return true;
         }
-        if ((seen >> kTokenBits) == (mine >> kTokenBits)) return at;
+        if ((seen >> kTokenBits) == (mine >> kTokenBits)) {
+            if (mine < seen) atomicMin(&table[at], mine);
+            return true;
+        }
     }
-    return at;
+    return false;
 }
 
-// The thread whose token made an entry of the LDS tables takes it on to the tables in memory: at most one group
-// and one class per thread, both under way together, two dependent accesses in all.  (A loop over the LDS
-// slots, two per thread, with a look before every compare-and-swap and minimum, and list entries reserved per
-// wave: 45 us on 128,256 tokens with 512 threads; without the loop 24 us; without the looks, which cost a round
-// trip and save nothing while all workgroups run at once, 12.8 us with 1,024 threads.)
-template <int BITS>
-__global__ __launch_bounds__(1 << BITS) void table_group_kernel(TableGroupArgs a) {
-    constexpr int kGroupThreads = 1 << BITS;
-    constexpr int kGroupSlots = 2 * kGroupThreads;  // the LDS tables are at most half full
-    __shared__ unsigned long long group[kGroupSlots], cls[kGroupSlots], crep[kGroupSlots];
-    __shared__ uint32_t cmin[kGroupSlots], centry[kGroupSlots];
-    __shared__ int32_t gref[kGroupSlots], cref[kGroupSlots];
-    __shared__ int32_t wave_listed[kGroupThreads / 64];
-    __shared__ int32_t list_at;
+// The entries of the runs, [runs][kRun] each, those of a run in the order of their buckets; `starts` [buckets + 1][runs]
+// says where in its run a bucket's entries begin (the last row: where they all end).
+struct RunEntries {
+    unsigned long long *word;
+    uint16_t *starts;
+};
+
+struct TableGatherArgs {
+    TableTokens tok;
+    RunEntries cls, group;        // out (groups only where the first byte matters)
+    unsigned long long *cls_rep;  // out, beside cls.word
+    int buckets;
+    int2 *entry_of;               // [n] out: a token's entries, class and group
+    uint8_t *tok_head;            // [n] cleared
+};
+
+// The entries are dealt out here: with their order a bucket's workgroup finds its own by two numbers a run.  (Looking
+// for them by the entries' buckets took it 5 to 11 us on 151,936 tokens, looking at all tokens' hashes 160 us, most of
+// that for the bucket with a third of the tokens.)
+__global__ __launch_bounds__(kRun) void table_gather_kernel(TableGatherArgs a) {
+    constexpr int kSlots = 2 * kRun;  // at most half full
+    __shared__ unsigned long long cls[kSlots], rep[kSlots], group[kSlots];
+    __shared__ uint16_t cls_number[kSlots], group_number[kSlots];
+    __shared__ uint32_t in_bucket[2][kMaxBuckets];  // classes, groups; then where they begin
+    __shared__ uint32_t wave_tot[2 * kMaxBuckets / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int t = blockIdx.x * kRun + tid;
+    const bool in = t < a.tok.n, groups = a.tok.by_first_byte;
+    TokenEntry mine{0, 0};
+    if (in) {
+        const int64_t beg = a.tok.tok_off[t], end = a.tok.tok_off[t + 1];
+        const unsigned long long h = a.tok.hash[t];
+        const uint32_t fb = groups && end > beg ? (uint32_t)a.tok.tok_bytes[beg] : 0u;
+        mine = token_entry(t, h, beg, end, fb);
+        a.tok_head[t] = 0;
+    }
 #pragma unroll
-    for (int s = tid; s < kGroupSlots; s += kGroupThreads) {
-        group[s] = kNoEntry;
-        cls[s] = kNoEntry;
-        crep[s] = ~0ull;
-        cmin[s] = ~0u;
+    for (int s = tid; s < kSlots; s += kRun) {
+        cls[s] = group[s] = kNoEntry;
+        rep[s] = ~0ull;
     }
-    const int t = blockIdx.x * kGroupThreads + tid;
-    const bool in = t < a.n;
-    unsigned long long part = 0, packed = 0;
-    uint32_t fb = 0;
-    if (in) {
-        const int64_t beg = a.tok_off[t];
-        int64_t len = a.tok_off[t + 1] - beg;
-        part = a.hash[t] & ((1ull << kTableHashBits) - 1ull);
-        if (a.by_first_byte && len > 0) fb = (uint32_t)a.tok_bytes[beg];
-        len = len < 0 ? 0 : (len > 0x7FFFFFFF ? 0x7FFFFFFF : len);
-        packed = ((unsigned long long)len << 32) | (uint32_t)t;
-    }
-    const unsigned long long my_cls = (part << (8 + kTokenBits)) | (uint32_t)t;
-    const unsigned long long my_group = my_cls | ((unsigned long long)fb << kTokenBits);
+    if (tid < 2 * kMaxBuckets) in_bucket[tid / kMaxBuckets][tid % kMaxBuckets] = 0;
     __syncthreads();
-    uint32_t g = 0, c = 0;
-    bool made_g = false, made_c = false;
-    if (in) {
-        c = lds_enter<BITS + 1>(cls, my_cls, made_c);
-        if (packed < *(volatile unsigned long long *)&crep[c]) atomicMin(&crep[c], packed);
-        if ((uint32_t)t < *(volatile uint32_t *)&cmin[c]) atomicMin(&cmin[c], (uint32_t)t);
-        g = lds_enter<BITS + 1>(group, my_group, made_g);
-    }
-    __syncthreads();
-    bool new_group = false;
-    {
-        uint32_t ec = table_home(my_cls >> kTokenBits, a.t.shift), eg = table_home(my_group >> kTokenBits, a.t.shift);
-        unsigned long long sc = 0, sg = 0;
-        if (made_c) sc = atomicCAS(&a.t.cls[ec], kNoEntry, my_cls);
-        if (made_g) sg = atomicCAS(&a.t.group[eg], kNoEntry, my_group);
-        if (made_c) sc = table_settle(a.t.cls, a.t.mask, ec, my_cls, sc);
-        if (made_g) sg = table_settle(a.t.group, a.t.mask, eg, my_group, sg);
-        constexpr unsigned long long kToken = kTableMaxTokens - 1;
-        if (made_g) {
-            gref[g] = (int32_t)(sg & kToken);
-            new_group = sg == my_group;
-        }
+    uint32_t c = 0, g = 0, c_bucket = 0, g_bucket = 0, c_at = 0, g_at = 0;
+    bool made_c = false, made_g = false;
+    if (in) {  // (there are more slots than tokens)
+        lds_enter<kRunBits + 1, kSlots>(cls, class_word(mine.word), c, made_c);
+        if (mine.rep < *(volatile unsigned long long *)&rep[c]) atomicMin(&rep[c], mine.rep);
+        if (groups) lds_enter<kRunBits + 1, kSlots>(group, mine.word, g, made_g);
         if (made_c) {
-            centry[c] = ec;
-            cref[c] = (int32_t)(sc & kToken);
-            atomicMin(&a.t.cls_rep[ec], crep[c]);
-            atomicMin(&a.t.cls_min[ec], cmin[c]);
+            c_bucket = bucket_of(class_word(mine.word), (uint32_t)a.buckets - 1u);
+            c_at = atomicAdd(&in_bucket[0][c_bucket], 1u);
+        }
+        if (made_g) {
+            g_bucket = bucket_of(mine.word, (uint32_t)a.buckets - 1u);
+            g_at = atomicAdd(&in_bucket[1][g_bucket], 1u);
         }
     }
     __syncthreads();
-    // a group that this token has made is compared with its class's member, unless that is the token itself
-    const bool listed = a.by_first_byte && new_group && cref[c] != t;
-    const uint64_t lm = __ballot(listed);
-    if (lane == 0) wave_listed[wave] = (int32_t)__popcll(lm);
-    if (in) {
-        a.tok_ref[t] = gref[g];
-        a.tok_cls[t] = (int32_t)centry[c];
+    // where the buckets begin: two scans of 256 counts, four waves each
+    uint32_t count = 0, begin = 0;
+    if (tid < 2 * kMaxBuckets) {
+        count = in_bucket[tid / kMaxBuckets][tid % kMaxBuckets];
+        begin = (uint32_t)wave_inclusive_sum((int)count);
+        if (lane == 63) wave_tot[wave] = begin;
+        begin -= count;
     }
     __syncthreads();
-    int32_t before = 0, all = 0;
-    for (int w = 0; w < kGroupThreads / 64; ++w) {
-        before += w < wave ? wave_listed[w] : 0;
-        all += wave_listed[w];
+    if (tid < 2 * kMaxBuckets) {
+        const int of = tid / kMaxBuckets, b = tid % kMaxBuckets;
+        for (int w = of * (kMaxBuckets / 64); w < wave; ++w) begin += wave_tot[w];
+        in_bucket[of][b] = begin;
+        uint16_t *starts = of ? a.group.starts : a.cls.starts;
+        if (b < a.buckets && (of == 0 || groups)) {
+            starts[(size_t)b * gridDim.x + blockIdx.x] = (uint16_t)begin;
+            if (b + 1 == a.buckets) starts[(size_t)(b + 1) * gridDim.x + blockIdx.x] = (uint16_t)(begin + count);
+        }
     }
-    if (all == 0) return;  // the same for the whole workgroup
-    if (tid == 0) list_at = atomicAdd(&a.ctr->other_rows, all);
     __syncthreads();
-    if (listed) a.cross_list[list_at + before + __popcll(lm & ((1ull << lane) - 1ull))] = make_int2(t, cref[c]);
+    const uint32_t first = blockIdx.x * kRun;
+    if (made_c) {
+        c_at += in_bucket[0][c_bucket];
+        cls_number[c] = (uint16_t)c_at;
+        a.cls.word[first + c_at] = cls[c];
+        a.cls_rep[first + c_at] = rep[c];
+    }
+    if (made_g) {
+        g_at += in_bucket[1][g_bucket];
+        group_number[g] = (uint16_t)g_at;
+        a.group.word[first + g_at] = group[g];
+    }
+    __syncthreads();
+    if (in) a.entry_of[t] = make_int2((int)(first + cls_number[c]), groups ? (int)(first + group_number[g]) : 0);
 }
 
-struct TableVerifyArgs {
-    ClassTable t;
-    const int32_t *tok_ref, *tok_cls;
+struct TableMergeArgs {
+    TableTokens tok;  // DIRECT
+    RunEntries cls, group;  // otherwise
+    const unsigned long long *cls_rep;
     int n;
-    int mark_blocks, cross_blocks;  // the first workgroups mark, the next compare the list, the rest tokens
-    const int2 *cross_list;
-    Counters *ctr;
+    int buckets;         // a power of two; the first workgroups merge classes, as many more groups
+    int32_t *cls_of, *group_of;  // out, per entry: the smallest member of its class / group
+    uint8_t *tok_head;   // [n] out: 1 for the smallest member of a class; DIRECT: cleared as well
+    int32_t *rep_at;     // [n] out, at the smallest member of a class: its representative
+    int32_t *listed_group;  // [buckets][list_room] out: the groups' smallest members
+    int32_t *listed_count;  // [buckets]
+    int list_room;
+    Counters *host_ctr;  // pinned host memory
+};
+
+// DIRECT: the entries are the tokens.  Classes and groups have workgroups of their own: by the hash alone the groups of a
+// class, and with a third of the tokens in it 6,600 of 45,000 entries, would all come to one bucket (27 us).
+template <bool DIRECT>
+__global__ __launch_bounds__(kMergeThreads, 8) void table_merge_kernel(TableMergeArgs a) {
+    __shared__ unsigned long long table[kTableSlots], rep[kTableSlots];
+    __shared__ uint32_t list[kMergeList];
+    __shared__ int32_t wave_tot[kMaxRuns / 64];
+    __shared__ int32_t picked, listed, no_room;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool groups = (int)blockIdx.x >= a.buckets;  // what this workgroup merges
+    const uint32_t bucket = blockIdx.x - (groups ? (uint32_t)a.buckets : 0u), mask = (uint32_t)a.buckets - 1u;
+    const RunEntries from = groups ? a.group : a.cls;
+    int32_t *member_of = groups ? a.group_of : a.cls_of;
+    const int runs = (a.n + kRun - 1) / kRun;
+    for (int s = tid; s < kTableSlots; s += kMergeThreads) {
+        table[s] = kNoEntry;
+        rep[s] = ~0ull;
+    }
+    if (tid == 0) picked = 0, listed = 0, no_room = 0;
+    // A run's entries of this bucket, a run per thread.
+    int first_of = 0, left_of = 0;
+    if (!DIRECT && tid < runs) {
+        const int first = from.starts[(size_t)bucket * runs + tid], last = from.starts[(size_t)(bucket + 1) * runs + tid];
+        first_of = tid * kRun + first;
+        left_of = min(max(last - first, 0), kRun - first);
+    }
+    __syncthreads();
+    // Lists this bucket's entries of runs [run0, run1); beyond the list's end they are counted only.  How many, the same
+    // for everybody.
+    auto pick = [&](int run0, int run1) -> int {
+        if (DIRECT) {  // all tokens at once
+            constexpr int kAhead = 4;
+            for (int t0 = tid; t0 < a.n; t0 += kAhead * kMergeThreads) {
+                unsigned long long hash[kAhead];
+                uint32_t fb[kAhead];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const int t = min(t0 + u * kMergeThreads, a.n - 1);
+                    hash[u] = a.tok.hash[t];
+                    fb[u] = 0;
+                    if (groups) {
+                        const int64_t beg = a.tok.tok_off[t];
+                        if (a.tok.tok_off[t + 1] > beg) fb[u] = (uint32_t)a.tok.tok_bytes[beg];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const int t = t0 + u * kMergeThreads;
+                    if (t < a.n && bucket_of(token_entry(t, hash[u], 0, 0, fb[u]).word, mask) == bucket)
+                        list[atomicAdd(&picked, 1)] = (uint32_t)t;
+                }
+            }
+            __syncthreads();
+            return picked;
+        }
+        const bool mine = tid >= run0 && tid < run1;
+        const int count = mine ? left_of : 0;
+        int at = 0, all = 0;
+        if (tid < kMaxRuns) {
+            at = wave_inclusive_sum(count);
+            if (lane == 63) wave_tot[wave] = at;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kMaxRuns / 64; ++w) {
+            at += w < wave ? wave_tot[w] : 0;
+            all += wave_tot[w];
+        }
+        at -= count;
+        for (int k = 0; k < count && at + k < kMergeList; ++k) list[at + k] = (uint32_t)(first_of + k);
+        __syncthreads();
+        return all;
+    };
+    // The list's entries into the table, where the smallest token of a class or group comes to stand for it; a list's
+    // entry keeps its slot above the entry's number.
+    auto enter = [&](int count) {
+        constexpr int kTogether = 2;
+        for (int i0 = tid; i0 < count; i0 += kTogether * kMergeThreads) {
+            int32_t e[kTogether];
+            TokenEntry x[kTogether];
+#pragma unroll
+            for (int u = 0; u < kTogether; ++u) {
+                const int i = i0 + u * kMergeThreads;
+                e[u] = i < count ? (int32_t)list[i] : 0;  // (an entry of its own: others' are being rewritten)
+                if (DIRECT) {
+                    const int64_t beg = a.tok.tok_off[e[u]], end = a.tok.tok_off[e[u] + 1];
+                    const uint32_t fb = groups && end > beg ? (uint32_t)a.tok.tok_bytes[beg] : 0u;
+                    x[u] = token_entry(e[u], a.tok.hash[e[u]], beg, end, fb);
+                } else {
+                    x[u] = {from.word[e[u]], groups ? 0ull : a.cls_rep[e[u]]};
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kTogether; ++u) {
+                const int i = i0 + u * kMergeThreads;
+                if (i >= count) continue;
+                uint32_t s = kNoSlot;
+                bool made;
+                if (*(volatile int32_t *)&no_room != 0 ||
+                    !lds_enter<kTableSlotBits, kTableProbes>(table, x[u].word, s, made)) {
+                    s = kNoSlot;
+                    no_room = 1;
+                } else if (!groups && x[u].rep < *(volatile unsigned long long *)&rep[s]) {
+                    atomicMin(&rep[s], x[u].rep);
+                }
+                list[i] = (uint32_t)e[u] | (s << kTokenBits);
+                if (DIRECT && !groups) a.tok_head[e[u]] = 0;
+            }
+        }
+        __syncthreads();
+    };
+    auto say_members = [&](int count) {
+        for (int i = tid; i < count; i += kMergeThreads) {
+            const uint32_t s = list[i] >> kTokenBits;
+            member_of[list[i] & (uint32_t)kTokenMask] = s < (uint32_t)kTableSlots ? (int32_t)(table[s] & kTokenMask) : 0;
+        }
+    };
+    const int found = pick(0, runs);
+    static_assert(kDirectTokens <= kMergeList, "all tokens fit the list");
+    if (DIRECT || found <= kMergeList) {
+        enter(found);
+        say_members(found);
+    } else {
+        // more than the list holds: a few runs at a time, and once more when it is known which tokens are the smallest
+        constexpr int kTogether = kMergeList / kRun;
+        for (int round = 0; round < 2; ++round) {
+            for (int run0 = 0; run0 < runs; run0 += kTogether) {
+                __syncthreads();  // everybody is done with the list
+                const int count = pick(run0, min(run0 + kTogether, runs));
+                enter(count);
+                if (round == 1) say_members(count);
+            }
+        }
+    }
+    __syncthreads();
+    for (int s = tid; s < kTableSlots; s += kMergeThreads) {
+        const unsigned long long e = table[s];
+        if (e == kNoEntry) continue;
+        const int32_t smallest = (int32_t)(e & kTokenMask);
+        if (groups) {
+            const int at = atomicAdd(&listed, 1);
+            if (at < a.list_room) a.listed_group[(size_t)bucket * a.list_room + at] = smallest;
+            else no_room = 1;
+        } else {
+            a.rep_at[smallest] = (int32_t)(uint32_t)rep[s];
+            a.tok_head[smallest] = 1;
+        }
+    }
+    __syncthreads();
+    if (tid == 0 && groups) a.listed_count[bucket] = min(listed, a.list_room);
+    if (tid == 0 && no_room) a.host_ctr->no_room = 1;
+}
+
+constexpr int kTableThreads = 512;  // of the settling workgroups
+
+struct TableSettleArgs {
+    const int2 *entry_of;  // a token's entries, class and group, or null: the tokens are the entries
+    const int32_t *cls_of, *group_of, *rep_at;
+    const uint8_t *tok_head;
+    int n;
+    int number_blocks, buckets;  // the first workgroups number, the next compare a bucket's groups, the rest tokens
+    int list_room;
+    const int32_t *listed_group, *listed_count;
     StoreSource store;    // from the walk store
     const uint16_t *sig;  // from rows: [n][S]
     int S;
-    // out, per token and per word of 32 tokens / stretch of kTableThreads tokens
-    int32_t *tok_min, *rep_at;
-    uint2 *word_marks;  // the word's marks, and the number of marks before it in its stretch
-    int32_t *stretch_marks;
+    Counters *host_ctr;  // pinned host memory
+    int32_t *class_of_token, *rep_of_class, *num_classes_dev;
 };
 
-__device__ __forceinline__ void table_mark(const TableVerifyArgs &a) {
-    __shared__ uint32_t wave_marks[kTableThreads / 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int t = blockIdx.x * kTableThreads + threadIdx.x;
-    bool head = false;
-    if (t < a.n) {
-        const int32_t c = a.tok_cls[t];
-        const int32_t m = (int32_t)a.t.cls_min[c];
-        a.tok_min[t] = m;
-        head = m == t;
-        if (head) a.rep_at[t] = (int32_t)(uint32_t)a.t.cls_rep[c];
-    }
-    const uint64_t marks = __ballot(head);
-    if (lane == 0) wave_marks[wave] = (uint32_t)__popcll(marks);
-    __syncthreads();
-    uint32_t before = 0, all = 0;
-    for (int w = 0; w < kTableThreads / 64; ++w) {
-        before += w < wave ? wave_marks[w] : 0u;
-        all += wave_marks[w];
-    }
-    if (lane < 2) {
-        const uint32_t low = (uint32_t)__popcll(marks & 0xFFFFFFFFull);
-        a.word_marks[(size_t)blockIdx.x * (kTableThreads / 32) + wave * 2 + lane] =
-            make_uint2((uint32_t)(marks >> (32 * lane)), before + (lane ? low : 0u));
-    }
-    if (threadIdx.x == 0) a.stretch_marks[blockIdx.x] = (int32_t)all;
+// the smallest member of a token's class / group
+__device__ __forceinline__ int32_t class_member(const TableSettleArgs &a, int t) {
+    return a.cls_of[a.entry_of ? a.entry_of[t].x : t];
 }
+__device__ __forceinline__ int32_t group_member(const TableSettleArgs &a, int t) {
+    return a.group_of[a.entry_of ? a.entry_of[t].y : t];
+}
+
+constexpr int kNumberPer = 2;                                // tokens per thread of the workgroups that number
+constexpr int kRankWords = kTableMaxTokens / 64 / kTableThreads;  // 64 tokens' marks each, a thread's share at the most
+// LDS of the workgroups that number: a bit per token, and the marks before every 64 of them.
+inline size_t table_rank_bytes(int32_t V) {
+    return (size_t)ceil_div(V, 64 * kRankWords) * kRankWords * (sizeof(uint64_t) + sizeof(uint32_t));
+}
+
+__device__ __forceinline__ void table_number(const TableSettleArgs &a, unsigned char *lds) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int shares = (a.n + 64 * kRankWords - 1) / (64 * kRankWords), words = shares * kRankWords;
+    unsigned long long *bits = reinterpret_cast<unsigned long long *>(lds);        // [words]
+    uint32_t *before = reinterpret_cast<uint32_t *>(lds + (size_t)words * 8);      // [words]
+    __shared__ uint32_t wave_tot[kTableThreads / 64];
+    const int base = (int)blockIdx.x * (kTableThreads * kNumberPer);
+    int32_t smallest[kNumberPer];
+#pragma unroll
+    for (int j = 0; j < kNumberPer; ++j) {
+        const int t = base + j * kTableThreads + tid;
+        smallest[j] = class_member(a, min(t, a.n - 1));
+    }
+    // sixteen tokens' marks, a byte each, to sixteen bits
+    for (int x = tid; x < words * 4; x += kTableThreads) {
+        const uint4 v = reinterpret_cast<const uint4 *>(a.tok_head)[x];
+        uint32_t lo = __builtin_amdgcn_udot4(v.x, 0x08040201u, 0u, false);
+        lo = __builtin_amdgcn_udot4(v.y, 0x80402010u, lo, false);
+        uint32_t hi = __builtin_amdgcn_udot4(v.z, 0x08040201u, 0u, false);
+        hi = __builtin_amdgcn_udot4(v.w, 0x80402010u, hi, false);
+        uint32_t m = (lo & 0xFFu) | (hi & 0xFFu) << 8;
+        const int left = a.n - x * 16;  // what lies behind the last token is not a mark
+        if (left < 16) m &= left > 0 ? (1u << left) - 1u : 0u;
+        reinterpret_cast<uint16_t *>(bits)[x] = (uint16_t)m;
+    }
+    __syncthreads();
+    uint32_t pop[kRankWords], mine = 0;
+#pragma unroll
+    for (int w = 0; w < kRankWords; ++w) {
+        pop[w] = tid < shares ? (uint32_t)__popcll(bits[tid * kRankWords + w]) : 0u;
+        mine += pop[w];
+    }
+    const uint32_t incl = (uint32_t)wave_inclusive_sum((int)mine);
+    if (lane == 63) wave_tot[wave] = incl;
+    __syncthreads();
+    uint32_t run = incl - mine, total = 0;
+#pragma unroll
+    for (int w = 0; w < kTableThreads / 64; ++w) {
+        run += w < wave ? wave_tot[w] : 0u;
+        total += wave_tot[w];
+    }
+    if (tid < shares) {
+#pragma unroll
+        for (int w = 0; w < kRankWords; ++w) {
+            before[tid * kRankWords + w] = run;
+            run += pop[w];
+        }
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && tid == 0) {
+        if (a.num_classes_dev) *a.num_classes_dev = (int32_t)total;
+        a.host_ctr->num_classes = (int32_t)total;
+    }
+#pragma unroll
+    for (int j = 0; j < kNumberPer; ++j) {
+        const int t = base + j * kTableThreads + tid;
+        if (t >= a.n) continue;
+        const int32_t m = smallest[j];
+        const int32_t k = (int32_t)(before[m >> 6] + (uint32_t)__popcll(bits[m >> 6] & ((1ull << (m & 63)) - 1ull)));
+        a.class_of_token[t] = k;
+        if (m == t) a.rep_of_class[k] = a.rep_at[t];
+    }
+}
+
+constexpr uint32_t kRowPart = 64;  // 16-byte units of a row that a wave compares
+__host__ __device__ inline int64_t table_row_parts(int32_t S) { return (S / 8 + (int)kRowPart - 1) / (int)kRowPart; }
 
 // STORE: the comparisons read the walk store, otherwise rows.
 template <bool STORE>
-__global__ __launch_bounds__(kTableThreads) void table_verify_kernel(TableVerifyArgs a) {
-    __shared__ __align__(16) uint16_t staged[STORE ? kTableThreads / 64 : 1][2][STORE ? kWalkStoreMaxStride : 8];
-    if ((int)blockIdx.x < a.mark_blocks) {
-        table_mark(a);
+__global__ __launch_bounds__(kTableThreads) void table_settle_kernel(TableSettleArgs a) {
+    extern __shared__ __align__(16) unsigned char lds[];  // table_rank_bytes, or the waves' staged vectors
+    if ((int)blockIdx.x < a.number_blocks) {
+        table_number(a, lds);
         return;
     }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int block = (int)blockIdx.x - a.mark_blocks;
     constexpr int kWaves = kTableThreads / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint16_t *staged = reinterpret_cast<uint16_t *>(lds) + (size_t)wave * 2 * kWalkStoreMaxStride;  // STORE only
+    const int block = (int)blockIdx.x - a.number_blocks;
     uint32_t stride = 0;  // of the walk store
     if (STORE) {
         const int state = walk_store_state(a.store, stride);
         if (state) {
-            if (block == 0 && threadIdx.x == 0) a.ctr->store_state = state;
+            if (block == 0 && tid == 0) a.host_ctr->store_state = state;
             return;
         }
     }
     bool differs = false;
-    if (STORE && block < a.cross_blocks) {
-        // groups against a member of their class: kCrossParts waves share a pair (S a multiple of 8)
+    const int group_blocks = STORE ? kGroupBlocks * a.buckets : 0;
+    if (STORE && block < group_blocks) {
+        // groups against a member of their class, a few workgroups per bucket: kCrossParts waves share a pair (S a
+        // multiple of 8).  A lane looks at a group, and where its smallest member is not its class's the wave compares
+        // the two
         const int parts = (a.S % 8) == 0 ? kCrossParts : 1;
-        const int count = min(a.ctr->other_rows, a.n);
-        for (int64_t e = (int64_t)block * kWaves + wave; e < (int64_t)count * parts; e += (int64_t)a.cross_blocks * kWaves) {
-            const int2 pair = a.cross_list[e / parts];
-            const uint32_t ra = store_row(a.store, pair.x), rb = store_row(a.store, pair.y);
-            if (ra == rb && ra != 256u) {
-                if (e % parts == 0) differs |= store_same_row_differ(a.store, stride, pair.x, pair.y);
-            } else {
-                differs |= store_other_row_differ(a.store, stride, pair.x, pair.y, ra, rb, staged[wave][0], staged[wave][1],
-                                                  (int)(e % parts), parts);
+        const int bucket = block / kGroupBlocks;
+        const int count = min(max(a.listed_count[bucket], 0), a.list_room);
+        const int teams = kGroupBlocks * (kWaves / parts), team = block % kGroupBlocks * (kWaves / parts) + wave / parts;
+        for (int x0 = team; x0 < count; x0 += 64 * teams) {
+            const int x = x0 + lane * teams;
+            int32_t t = 0, other = 0;
+            if (x < count) {
+                t = a.listed_group[(size_t)bucket * a.list_room + x];
+                other = class_member(a, t);
+            }
+            const uint32_t ra = store_row(a.store, t), rb = store_row(a.store, other);
+            for (uint64_t left = __ballot(t != other); left; left &= left - 1) {
+                const int l = __ffsll((unsigned long long)left) - 1;
+                differs |= store_other_row_differ(a.store, stride, __builtin_amdgcn_readlane(t, l),
+                                                  __builtin_amdgcn_readlane(other, l), __builtin_amdgcn_readlane(ra, l),
+                                                  __builtin_amdgcn_readlane(rb, l), staged, staged + kWalkStoreMaxStride,
+                                                  wave % parts, parts);
             }
         }
     } else {
-        const int64_t gw = (int64_t)(block - a.cross_blocks) * kWaves + wave;
-        const int64_t waves = ((int64_t)gridDim.x - a.mark_blocks - a.cross_blocks) * kWaves;
+        const int64_t gw = (int64_t)(block - group_blocks) * kWaves + wave;
+        const int64_t waves = ((int64_t)gridDim.x - a.number_blocks - group_blocks) * kWaves;
         if (STORE) {
-            // eight pairs per wave, eight lanes a pair, 16 bytes a lane and round
+            // eight pairs per wave, eight lanes a pair, 16 bytes a lane and round: what a token's own entry says is
+            // enough to ask for both vectors
             const uint32_t sub = lane & 7, pair = lane >> 3;
             for (int64_t t0 = gw * 8; t0 < a.n; t0 += waves * 8) {
-                const int64_t t = t0 + pair;
-                bool cross = false;
-                uint32_t n16 = 0, ra = 256, rb = 256;
-                int32_t ref = 0;
-                const uint4 *wa = nullptr, *wb = nullptr;
-                uint4 x0 = make_uint4(0, 0, 0, 0);
-                if (t < a.n) {
-                    ref = a.tok_ref[t];
-                    const uint16_t pa = a.store.store.wrow[t];
-                    wa = reinterpret_cast<const uint4 *>(a.store.store.wvec + (size_t)t * stride);
-                    wb = reinterpret_cast<const uint4 *>(a.store.store.wvec + (size_t)ref * stride);
-                    // (asked for before it is known to be wanted: every token has `stride` entries)
-                    if (sub < stride / 8u) x0 = wa[sub];
-                    const uint16_t pb = a.store.store.wrow[ref];
-                    ra = min(walk_row_of(pa), 256u);
-                    rb = min(walk_row_of(pb), 256u);
-                    cross = ra != rb;  // the empty token shares its key with tokens that begin with byte 0
-                    if (ref != t && ra == rb && ra != 256u) n16 = min(walk_units_of(pa), stride / 8u);
+                const int64_t t = min(t0 + pair, (int64_t)a.n - 1);  // repeats the last one past the end
+                const int32_t ref = group_member(a, (int)t);
+                const uint16_t pa = a.store.store.wrow[t];
+                const uint4 *wa = reinterpret_cast<const uint4 *>(a.store.store.wvec + (size_t)t * stride);
+                const uint4 *wb = reinterpret_cast<const uint4 *>(a.store.store.wvec + (size_t)ref * stride);
+                const uint32_t n16 = min(walk_units_of(pa), stride / 8u);  // none of the empty token
+                const uint16_t pb = a.store.store.wrow[ref];
+                constexpr int kAhead = 2;
+                uint32_t diff = 0;
+                for (uint32_t u0 = sub; u0 < n16; u0 += 8 * kAhead) {
+                    uint4 x[kAhead], y[kAhead];
+#pragma unroll
+                    for (int k = 0; k < kAhead; ++k) {
+                        const uint32_t u = min(u0 + 8 * k, n16 - 1);
+                        x[k] = wa[u];
+                        y[k] = wb[u];
+                    }
+#pragma unroll
+                    for (int k = 0; k < kAhead; ++k)
+                        diff |= (x[k].x ^ y[k].x) | (x[k].y ^ y[k].y) | (x[k].z ^ y[k].z) | (x[k].w ^ y[k].w);
                 }
-                for (uint32_t u = sub; u < n16; u += 8) {
-                    const uint4 x = u == sub ? x0 : wa[u], y = wb[u];
-                    differs |= (x.x != y.x) | (x.y != y.y) | (x.z != y.z) | (x.w != y.w);
-                }
-                uint64_t list = __ballot(cross && sub == 0);
-                while (list) {
-                    const int l = __ffsll((unsigned long long)list) - 1;
-                    list &= list - 1;
-                    differs |= store_other_row_differ(a.store, stride, (int32_t)(t0 + (l >> 3)), __shfl(ref, l, 64),
-                                                      __shfl(ra, l, 64), __shfl(rb, l, 64), staged[wave][0],
-                                                      staged[wave][1]);
+                const uint32_t ra = min(walk_row_of(pa), 256u), rb = min(walk_row_of(pb), 256u);
+                const bool cross = ra != rb;  // the empty token shares its key with tokens that begin with byte 0
+                differs |= !cross && diff != 0u;
+                uint64_t left = __ballot(cross && sub == 0);
+                while (left) {
+                    const int l = __ffsll((unsigned long long)left) - 1;
+                    left &= left - 1;
+                    differs |= store_other_row_differ(a.store, stride, __shfl((int32_t)t, l, 64), __shfl(ref, l, 64),
+                                                      __shfl(ra, l, 64), __shfl(rb, l, 64), staged,
+                                                      staged + kWalkStoreMaxStride);
                 }
             }
         } else {
-            // four rows per wave and round against their groups' members' rows, which many share (they
-            // stay in the caches); what there is to read is every row once
+            // four rows per wave against their classes' members' rows, which many share (they stay in the caches); what
+            // there is to read is every row once.  Of rows of more than kRowPart units a wave takes a part: waves that
+            // read whole rows of 8 KB all ask the same memory channels at a time (262 MB in rows of 8 KB: 60 us, 49 us so)
             const bool vec = (a.S % 8) == 0 && (reinterpret_cast<uintptr_t>(a.sig) % 16) == 0;
-            for (int64_t t0 = gw * 4; t0 < a.n; t0 += waves * 4) {
-                const uint16_t *x[4], *y[4];
+            const uint32_t s8 = (uint32_t)a.S / 8u;  // (262,144 rows of 8,192 units: 31 bits)
+            const int64_t parts = vec ? table_row_parts(a.S) : 1, items = ((int64_t)a.n + 3) / 4 * parts;
+            for (int64_t x = gw; x < items; x += waves) {
+                const int64_t t0 = x / parts * 4;
+                int32_t t[4], ref[4];
                 int cnt = 0;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int64_t t = min(t0 + u, (int64_t)a.n - 1);  // repeats the last one past the end
-                    const int32_t ref = a.tok_ref[t];
-                    cnt += ref != t;
-                    x[u] = a.sig + (size_t)t * a.S;
-                    y[u] = a.sig + (size_t)ref * a.S;
+                    t[u] = (int32_t)min(t0 + u, (int64_t)a.n - 1);  // repeats the last one past the end
+                    ref[u] = class_member(a, t[u]);
+                    cnt += ref[u] != t[u];
                 }
-                if (!cnt) continue;  // all four are their groups' members (wave-uniform)
+                if (!cnt) continue;  // all four are their classes' members (wave-uniform)
                 if (vec) {
-                    for (int j = lane; j < a.S / 8; j += 64) {
+                    const uint4 *rows = reinterpret_cast<const uint4 *>(a.sig);
+                    const uint32_t from = (uint32_t)(x % parts) * kRowPart, to = min(s8, from + kRowPart);
+                    for (uint32_t j = from + lane; j < to; j += 64) {
                         uint4 p[4], q[4];
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
-                            p[u] = reinterpret_cast<const uint4 *>(x[u])[j];
-                            q[u] = reinterpret_cast<const uint4 *>(y[u])[j];
+                            p[u] = rows[(uint32_t)t[u] * s8 + j];
+                            q[u] = rows[(uint32_t)ref[u] * s8 + j];
                         }
 #pragma unroll
                         for (int u = 0; u < 4; ++u)
@@ -378,74 +627,14 @@ __global__ __launch_bounds__(kTableThreads) void table_verify_kernel(TableVerify
                 } else {
                     for (int j = lane; j < a.S; j += 64)
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) differs |= x[u][j] != y[u][j];
+                        for (int u = 0; u < 4; ++u)
+                            differs |= a.sig[(size_t)t[u] * a.S + j] != a.sig[(size_t)ref[u] * a.S + j];
                 }
             }
         }
     }
     // whether any pair differs is all that is asked
-    if (__ballot(differs) != 0ull && lane == 0) atomicAdd(&a.ctr->unresolved, 1);
-}
-
-struct TableAssignArgs {
-    int n, n_stretches;
-    const int32_t *tok_min, *rep_at;
-    const uint2 *word_marks;
-    const int32_t *stretch_marks;
-    const Counters *ctr;
-    Counters *host_ctr;  // pinned host memory
-    int32_t *class_of_token, *rep_of_class, *num_classes_dev;
-};
-
-__global__ __launch_bounds__(kTableAssignThreads) void table_assign_kernel(TableAssignArgs a) {
-    extern __shared__ uint32_t before[];  // [n_stretches]: marks before each stretch
-    __shared__ uint32_t wave_tot[kTableAssignThreads / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int base = blockIdx.x * (kTableAssignThreads * kTableAssignItems);
-    int32_t m[kTableAssignItems];
-    uint2 marks[kTableAssignItems];
-#pragma unroll
-    for (int j = 0; j < kTableAssignItems; ++j) {
-        const int t = base + j * kTableAssignThreads + tid;
-        m[j] = t < a.n ? a.tok_min[t] : 0;
-        m[j] = (uint32_t)m[j] < (uint32_t)a.n ? m[j] : 0;  // always: every class has a member
-    }
-#pragma unroll
-    for (int j = 0; j < kTableAssignItems; ++j) marks[j] = a.word_marks[m[j] >> 5];
-    // a scan per workgroup (1,024 stretches, two a thread, at the most) instead of a launch of its own
-    uint32_t run = 0;
-    for (int s0 = 0; s0 < a.n_stretches; s0 += kTableAssignThreads) {
-        const int s = s0 + tid;
-        const uint32_t v = s < a.n_stretches ? (uint32_t)a.stretch_marks[s] : 0u;
-        const uint32_t incl = (uint32_t)wave_inclusive_sum((int)v);
-        if (lane == 63) wave_tot[wave] = incl;
-        __syncthreads();
-        uint32_t pre = run, all = 0;
-#pragma unroll
-        for (int w = 0; w < kTableAssignThreads / 64; ++w) {
-            pre += w < wave ? wave_tot[w] : 0u;
-            all += wave_tot[w];
-        }
-        if (s < a.n_stretches) before[s] = pre + incl - v;
-        run += all;
-        __syncthreads();
-    }
-    if (blockIdx.x == 0 && tid == 0) {
-        if (a.num_classes_dev) *a.num_classes_dev = (int32_t)run;
-        a.host_ctr->unresolved = a.ctr->unresolved;
-        a.host_ctr->store_state = a.ctr->store_state;
-        a.host_ctr->other_rows = a.ctr->other_rows;
-        a.host_ctr->num_classes = (int32_t)run;
-    }
-#pragma unroll
-    for (int j = 0; j < kTableAssignItems; ++j) {
-        const int t = base + j * kTableAssignThreads + tid;
-        if (t >= a.n) continue;
-        const int32_t k = (int32_t)(before[m[j] / kTableThreads] + marks[j].y +
-                                    __popc(marks[j].x & ((1u << (m[j] & 31)) - 1u)));
-        a.class_of_token[t] = k;
-        if (m[j] == t) a.rep_of_class[k] = a.rep_at[t];
-    }
+    if (__ballot(differs) != 0ull && lane == 0) a.host_ctr->unresolved = 1;
 }
 
 }  // namespace

@@ -2,9 +2,9 @@
 // and pick representatives (paper Section 3.1 "Pre-Computation").
 //
 // Vocabularies of up to 262,144 tokens whose signatures need not be walked again to be compared are first
-// grouped by hash table (class_table.hpp: four launches).  The rest, and every call in which a hash collides or
-// the walk store cannot be used, take the sort below: grouping alone 83 us on 128,256 tokens (table: 35 us) and
-// 103 us on 151,936 (table: 45 us), but exact whatever the hashes are.
+// grouped by hash table (class_table.hpp: two or three launches).  The rest, and every call in which a hash collides or
+// the walk store cannot be used, take the sort below: kernels of 103 us on 151,936 tokens (table: 37 us), but exact
+// whatever the hashes are.
 //
 // Sort pipeline (all on the device, eight launches when no hash collides):
 //   1. keys: (low 32 or 40 bits of the hash, first byte of the token), and the digit counts of
@@ -1149,13 +1149,11 @@ struct BuildWorkspace {
     Counters *ctr;
     // grouping by hash table, the first attempt; shares its memory with the sort's arrays, which
     // are written only after it has been given up
-    ClassTable table;
-    uint4 *clear_begin;
-    size_t clear_n16;
-    int32_t *tok_ref, *tok_cls, *tok_min, *rep_at, *stretch_marks;
-    int2 *cross_list;
-    uint2 *word_marks;
-    Counters *table_ctr;
+    RunEntries run_cls, run_group;
+    unsigned long long *run_rep;
+    int2 *entry_of;
+    int32_t *cls_of, *group_of, *rep_at, *listed_group, *listed_count;
+    uint8_t *tok_head;
     size_t bytes;
 };
 
@@ -1193,26 +1191,21 @@ BuildWorkspace carve_build_ws(void *ws, int32_t V, int32_t S) {
                      ? c.take<uint16_t>((size_t)kGlobalWalkGrid * walk_cap_for(S))
                      : nullptr;
     w.ctr = c.take<Counters>(1);
-    const size_t cap = class_table_capacity(V);
-    w.table.mask = (uint32_t)cap - 1;
-    w.table.shift = 64;
-    while ((1ull << (64 - w.table.shift)) < cap) --w.table.shift;
-    const size_t clear_from = ct.used;
-    w.table.group = ct.take<unsigned long long>(cap);  // these four start as all ones
-    w.table.cls = ct.take<unsigned long long>(cap);
-    w.table.cls_rep = ct.take<unsigned long long>(cap);
-    w.table.cls_min = ct.take<uint32_t>(cap);
-    w.clear_begin = reinterpret_cast<uint4 *>(w.table.group);
-    w.clear_n16 = (ct.used - clear_from) / 16;
-    const size_t n_stretches = (size_t)ceil_div(V, kTableThreads);
-    w.tok_ref = ct.take<int32_t>(n);
-    w.tok_cls = ct.take<int32_t>(n);
-    w.tok_min = ct.take<int32_t>(n);
+    const size_t buckets = (size_t)table_buckets(V);
+    const bool direct = V <= kDirectTokens;
+    const size_t runs = direct ? 0 : (size_t)ceil_div(V, kRun), entries = direct ? n : runs * kRun;
+    for (RunEntries *e : {&w.run_cls, &w.run_group}) {
+        e->word = ct.take<unsigned long long>(runs * kRun);
+        e->starts = ct.take<uint16_t>((buckets + 1) * runs);
+    }
+    w.run_rep = ct.take<unsigned long long>(runs * kRun);
+    w.entry_of = ct.take<int2>(direct ? 0 : n);
+    w.cls_of = ct.take<int32_t>(entries);
+    w.group_of = ct.take<int32_t>(entries);
     w.rep_at = ct.take<int32_t>(n);
-    w.cross_list = ct.take<int2>(n);
-    w.word_marks = ct.take<uint2>(n_stretches * (kTableThreads / 32));
-    w.stretch_marks = ct.take<int32_t>(n_stretches);
-    w.table_ctr = ct.take<Counters>(1);
+    w.tok_head = ct.take<uint8_t>((size_t)ceil_div(V, 64 * kRankWords) * 64 * kRankWords);
+    w.listed_group = ct.take<int32_t>(buckets * (size_t)table_list_room(V));
+    w.listed_count = ct.take<int32_t>(buckets);
     w.bytes = std::max(c.used, V <= kTableMaxTokens ? ct.used : (size_t)0);
     return w;
 }
@@ -1317,74 +1310,69 @@ extern "C" int cfgzip_build_classes(const uint8_t *tok_bytes, const int64_t *tok
     // compared: the sort puts tokens next to each other, so that each is walked once for its two
     // neighbours, while against a group's member every token would be walked with a partner.
     if (source != FROM_REWALK && V <= kTableMaxTokens) {
-        TableClearArgs ca{w.clear_begin, w.clear_n16, w.table_ctr};
-        hipLaunchKernelGGL(table_clear_kernel,
-                           dim3((unsigned)std::min<int64_t>(1024, ceil_div((int64_t)w.clear_n16, kTableThreads))),
-                           dim3(kTableThreads), 0, stream, ca);
-        CFGZIP_TRY(check_launch());
-        TableGroupArgs ga{};
-        ga.hash = hash;
-        ga.tok_off = tok_off;
-        ga.tok_bytes = tok_bytes;
-        ga.n = n;
-        ga.by_first_byte = source == FROM_STORE;
-        ga.t = w.table;
-        ga.tok_ref = w.tok_ref;
-        ga.tok_cls = w.tok_cls;
-        ga.cross_list = w.cross_list;
-        ga.ctr = w.table_ctr;
-        if (n <= kGroupSmallTokens)
-            hipLaunchKernelGGL(table_group_kernel<kGroupBitsSmall>, dim3((unsigned)ceil_div(n, 1 << kGroupBitsSmall)),
-                               dim3(1 << kGroupBitsSmall), 0, stream, ga);
-        else
-            hipLaunchKernelGGL(table_group_kernel<kGroupBitsLarge>, dim3((unsigned)ceil_div(n, 1 << kGroupBitsLarge)),
-                               dim3(1 << kGroupBitsLarge), 0, stream, ga);
-        CFGZIP_TRY(check_launch());
-        TableVerifyArgs va{};
-        va.t = w.table;
-        va.tok_ref = w.tok_ref;
-        va.tok_cls = w.tok_cls;
-        va.n = n;
-        va.mark_blocks = (int)ceil_div(n, kTableThreads);
-        va.cross_list = w.cross_list;
-        va.ctr = w.table_ctr;
-        va.store = store_src;
-        va.sig = sig;
-        va.S = S;
-        va.tok_min = w.tok_min;
-        va.rep_at = w.rep_at;
-        va.word_marks = w.word_marks;
-        va.stretch_marks = w.stretch_marks;
-        if (source == FROM_STORE) {
-            const int pair_blocks = (int)std::min<int64_t>(ceil_div(n, 8 * (kTableThreads / 64)), 2048);
-            va.cross_blocks = (int)std::min<int64_t>(ceil_div(n, 16), 512);
-            hipLaunchKernelGGL(table_verify_kernel<true>, dim3((unsigned)(va.mark_blocks + va.cross_blocks + pair_blocks)),
-                               dim3(kTableThreads), 0, stream, va);
+        *pinned = Counters{};
+        const TableTokens tokens{hash, tok_off, tok_bytes, n, source == FROM_STORE};
+        const bool direct = n <= kDirectTokens;
+        TableMergeArgs ma{};
+        ma.tok = tokens;
+        ma.cls = w.run_cls;
+        ma.group = w.run_group;
+        ma.cls_rep = w.run_rep;
+        ma.n = n;
+        ma.buckets = table_buckets(n);
+        ma.cls_of = w.cls_of;
+        ma.group_of = w.group_of;
+        ma.tok_head = w.tok_head;
+        ma.rep_at = w.rep_at;
+        ma.listed_group = w.listed_group;
+        ma.listed_count = w.listed_count;
+        ma.list_room = table_list_room(n);
+        ma.host_ctr = pinned;
+        const dim3 merge_grid((unsigned)(tokens.by_first_byte ? 2 * ma.buckets : ma.buckets));
+        if (direct) {
+            hipLaunchKernelGGL(table_merge_kernel<true>, merge_grid, dim3(kMergeThreads), 0, stream, ma);
         } else {
-            const int pair_blocks = (int)std::min<int64_t>(ceil_div(n, 4 * (kTableThreads / 64)), 8192);
-            hipLaunchKernelGGL(table_verify_kernel<false>, dim3((unsigned)(va.mark_blocks + pair_blocks)),
-                               dim3(kTableThreads), 0, stream, va);
+            TableGatherArgs ga{tokens, w.run_cls, w.run_group, w.run_rep, ma.buckets, w.entry_of, w.tok_head};
+            hipLaunchKernelGGL(table_gather_kernel, dim3((unsigned)ceil_div(n, kRun)), dim3(kRun), 0, stream, ga);
+            CFGZIP_TRY(check_launch());
+            hipLaunchKernelGGL(table_merge_kernel<false>, merge_grid, dim3(kMergeThreads), 0, stream, ma);
         }
         CFGZIP_TRY(check_launch());
-        TableAssignArgs aa{};
-        aa.n = n;
-        aa.n_stretches = va.mark_blocks;
-        aa.tok_min = w.tok_min;
-        aa.rep_at = w.rep_at;
-        aa.word_marks = w.word_marks;
-        aa.stretch_marks = w.stretch_marks;
-        aa.ctr = w.table_ctr;
-        aa.host_ctr = pinned;
-        aa.class_of_token = class_of_token;
-        aa.rep_of_class = rep_of_class;
-        aa.num_classes_dev = num_classes_dev;
-        hipLaunchKernelGGL(table_assign_kernel,
-                           dim3((unsigned)ceil_div(n, kTableAssignThreads * kTableAssignItems)),
-                           dim3(kTableAssignThreads), (size_t)aa.n_stretches * sizeof(uint32_t), stream, aa);
+        TableSettleArgs sa{};
+        sa.entry_of = direct ? nullptr : w.entry_of;
+        sa.cls_of = w.cls_of;
+        sa.group_of = w.group_of;
+        sa.rep_at = w.rep_at;
+        sa.tok_head = w.tok_head;
+        sa.n = n;
+        sa.number_blocks = (int)ceil_div(n, kTableThreads * kNumberPer);
+        sa.list_room = ma.list_room;
+        sa.listed_group = w.listed_group;
+        sa.listed_count = w.listed_count;
+        sa.store = store_src;
+        sa.sig = sig;
+        sa.S = S;
+        sa.host_ctr = pinned;
+        sa.class_of_token = class_of_token;
+        sa.rep_of_class = rep_of_class;
+        sa.num_classes_dev = num_classes_dev;
+        constexpr int kWaves = kTableThreads / 64;
+        size_t lds = table_rank_bytes(n);
+        if (source == FROM_STORE) {
+            const int pair_blocks = (int)std::min<int64_t>(ceil_div(n, 8 * kWaves), 2048);
+            sa.buckets = ma.buckets;
+            lds = std::max(lds, (size_t)kWaves * 2 * kWalkStoreMaxStride * sizeof(uint16_t));
+            hipLaunchKernelGGL(table_settle_kernel<true>, dim3((unsigned)(sa.number_blocks + kGroupBlocks * sa.buckets + pair_blocks)),
+                               dim3(kTableThreads), lds, stream, sa);
+        } else {
+            const int pair_blocks = (int)std::min<int64_t>(ceil_div(ceil_div(n, 4) * std::max<int64_t>(1, table_row_parts(S)), kWaves), 8192);
+            hipLaunchKernelGGL(table_settle_kernel<false>, dim3((unsigned)(sa.number_blocks + pair_blocks)),
+                               dim3(kTableThreads), lds, stream, sa);
+        }
         CFGZIP_TRY(check_launch());
         CFGZIP_TRY(check_hip(hipStreamSynchronize(stream)));
         const Counters found = *pinned;
-        if (found.store_state == 0 && found.unresolved == 0) {
+        if (found.store_state == 0 && found.unresolved == 0 && found.no_room == 0) {
             if (num_classes_host) *num_classes_host = found.num_classes;
             if (collisions_host) *collisions_host = 0;
             return CFGZIP_OK;

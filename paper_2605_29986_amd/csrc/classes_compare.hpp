@@ -15,7 +15,8 @@ struct Counters {
     int32_t num_classes;
     int32_t store_state;  // of the walk store handed in: 0 usable, 1 not this call's, 2 overflowed
     int32_t other_rows;   // links between tokens of different image rows, listed for the kernel after
-    int32_t pad[4];
+    int32_t no_room;      // a bucket of the hash table was too small for its classes
+    int32_t pad[3];
 };
 constexpr int kStoreForeign = 1, kStoreOverflowed = 2;
 
@@ -88,6 +89,23 @@ __device__ __forceinline__ bool store_other_row_differ(const StoreSource &s, uin
     // positions in a kept vector are below the row's image size, which is at most the stride in a
     // store that has not overflowed; the bound keeps a corrupt index inside the staged vector
     const uint32_t na = stride, nb = stride;
+    const uint16_t *ia = s.T.idx + (size_t)ra * S, *ib = s.T.idx + (size_t)rb * S;
+    // 16 bytes of each index row per lane and step (the identity row is not read); the first are asked for together
+    // with the vectors
+    constexpr int kAhead = 2;
+    const bool vec = (S % 8) == 0;
+    uint4 xa[kAhead], xb[kAhead];
+    auto fetch = [&](int q0) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int q = min(q0 + 512 * parts * u, S - 8);  // repeats the last ones past the end
+            xa[u] = xb[u] = make_uint4(0, 0, 0, 0);
+            if (!ida) xa[u] = *reinterpret_cast<const uint4 *>(ia + q);
+            if (!idb) xb[u] = *reinterpret_cast<const uint4 *>(ib + q);
+        }
+    };
+    const int first = lane * 8 + 512 * part;
+    if (vec) fetch(first);
     {
         // lanes 0..31 copy vector a, lanes 32..63 vector b, 16 bytes each and round
         const bool second = lane >= 32;
@@ -100,22 +118,12 @@ __device__ __forceinline__ bool store_other_row_differ(const StoreSource &s, uin
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const uint16_t *ia = s.T.idx + (size_t)ra * S, *ib = s.T.idx + (size_t)rb * S;
     bool d = false;
     auto entry_a = [&](uint32_t q, uint32_t j) -> uint32_t { return ida ? q : (j < na ? la[j] : 0xFFFFu); };
     auto entry_b = [&](uint32_t q, uint32_t j) -> uint32_t { return idb ? q : (j < nb ? lb[j] : 0xFFFFu); };
-    if ((S % 8) == 0) {
-        // 16 bytes of each index row per lane and step (the identity row is not read)
-        const uint4 zero = make_uint4(0, 0, 0, 0);
-        constexpr int kAhead = 2;
-        for (int q0 = lane * 8 + 512 * part; q0 < S; q0 += 512 * parts * kAhead) {
-            uint4 xa[kAhead], xb[kAhead];
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const int q = q0 + 512 * parts * u;
-                xa[u] = (!ida && q < S) ? *reinterpret_cast<const uint4 *>(ia + q) : zero;
-                xb[u] = (!idb && q < S) ? *reinterpret_cast<const uint4 *>(ib + q) : zero;
-            }
+    if (vec) {
+        for (int q0 = first; q0 < S; q0 += 512 * parts * kAhead) {
+            if (q0 != first) fetch(q0);
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
                 const int q = q0 + 512 * parts * u;

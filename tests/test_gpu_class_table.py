@@ -184,3 +184,45 @@ def test_sort_starts_over_when_the_store_cannot_be_used(lib, case, stored):
     c, r, C, coll = lib.cfgzip_build_classes(tb, to, tt, sig, h, signatures_workspace=ws)
     assert C == len(want_r) and coll == 0
     assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
+
+
+@pytest.mark.parametrize("shape", ["one class", "last byte", "distinct"])
+@pytest.mark.parametrize("V", [63, 64, 6143, 6144, 6145, 7168, 7169])
+def test_sizes_around_the_runs_and_buckets(lib, V, shape):
+    """Up to 6,144 tokens the buckets look at the tokens themselves, above at the entries of runs of 1,024."""
+    print(f"case V={V} {shape}", flush=True)
+    vocab, table = _case(shape, V, V + 1)
+    _, coll = _check_build(lib, vocab, table)
+    assert coll == 0
+    _, coll = _check_build(lib, vocab, table, use_store=False)
+    assert coll == 0
+
+
+def _hashes_of_one_bucket(n):
+    """n different values whose bucket, the bytes 1, 5, 11, 29 times added up, is 0 for any number of buckets."""
+    k = np.arange(n, dtype=np.uint64)
+    b1, b2 = k % np.uint64(256), k // np.uint64(256)
+    b0 = (np.uint64(1 << 16) - np.uint64(5) * b1 - np.uint64(11) * b2) % np.uint64(256)
+    return b0 | (b1 << np.uint64(8)) | (b2 << np.uint64(16))
+
+
+@pytest.mark.parametrize("V,classes", [(6000, 900), (6000, 2500), (12_000, 900), (20_000, 900), (20_000, 2049)])
+def test_hashes_that_fall_into_one_bucket(lib, V, classes):
+    """All classes in one bucket: more entries than its list holds (20,000 tokens in runs of 1,024), and more classes than
+    its table does (the sort then takes over)."""
+    from gpu_util import dev
+    print(f"case V={V} classes={classes}", flush=True)
+    rng = np.random.default_rng(V + classes)
+    cls = np.concatenate([np.arange(classes), rng.integers(0, classes, size=V - classes)])
+    rng.shuffle(cls)
+    lens = rng.integers(0, 6, size=V)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    data = rng.integers(0, 256, size=max(1, int(off[-1])), dtype=np.uint8)
+    rows = rng.integers(0, 1 << 16, size=(classes, 16), dtype=np.uint16)
+    rows[:, 3] = np.arange(classes)
+    rows = np.ascontiguousarray(rows[cls])
+    want_c, want_r = oracle.build_classes(rows, off)
+    c, r, C, coll = lib.cfgzip_build_classes(dev(data), dev(off), None, dev(rows),
+                                             dev(_hashes_of_one_bucket(classes)[cls]))
+    assert C == classes == len(want_r) and coll == 0
+    assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
