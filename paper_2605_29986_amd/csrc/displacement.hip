@@ -814,12 +814,11 @@ int launch_displacements(const DisplacementArgs &a, int n_cu, hipStream_t stream
         // a workgroup of sixteen waves per compute unit, the tokens spread evenly
         const int64_t groups = std::min<int64_t>(n_cu, ceil_div(a.V, kShWaves));
         const int per_group = (int)ceil_div(a.V, groups);
-        const int round = (int)std::min<int64_t>(kShRound, ceil_div(per_group, kShWaves));
         const unsigned grid = (unsigned)ceil_div(a.V, per_group);
         if (aligned_to(a.rows, 16))
-            hipLaunchKernelGGL(displacement_shared_kernel<true>, dim3(grid), dim3(kShThreads), 0, stream, a, per_group, round);
+            hipLaunchKernelGGL(displacement_shared_kernel<true>, dim3(grid), dim3(kShThreads), 0, stream, a, per_group);
         else
-            hipLaunchKernelGGL(displacement_shared_kernel<false>, dim3(grid), dim3(kShThreads), 0, stream, a, per_group, round);
+            hipLaunchKernelGGL(displacement_shared_kernel<false>, dim3(grid), dim3(kShThreads), 0, stream, a, per_group);
     } else {  // more symbols than a shared cell holds: every token is taken alone
         hipLaunchKernelGGL(hand_all_kernel, dim3((unsigned)std::min<int64_t>(1024, ceil_div(a.V, 256))), dim3(256), 0, stream, a);
     }

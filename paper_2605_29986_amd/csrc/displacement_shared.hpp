@@ -23,11 +23,14 @@
 // What a token's set is written as (the canonical row and its hash) is worked out once per set too; writing a row
 // is then a copy out of LDS, and writing the rows is what bounds the kernel on a large vocabulary.
 //
-// Measured: 128,256 tokens over the JSON grammar with rows of 1,024 entries 171-181 us (a wave per token took 510 us for
-// most tokens and 276 us for long digit runs), 32,000 over the statement grammar with rows of 256 90-100 us (210 us).
+// Measured: 128,256 tokens over the JSON grammar with rows of 1,024 entries 149 us (a wave per token took 510 us for
+// most tokens and 276 us for long digit runs), 32,000 over the statement grammar with rows of 256 100 us (210 us).
 // What bounds it: working out new sets (97 steps in a workgroup with 125 tokens over the JSON grammar, 165 with 501), as
 // much by the instructions of a step as by its chain of LDS accesses: a wave waits in 45 % of its cycles and issues
-// in 39 %, 14 vector and 14 scalar instructions for every LDS one.  Then writing the rows (262 MB, 39-45 us).
+// in 39 %, 14 vector and 14 scalar instructions for every LDS one.  A step takes 2.5 us on average and up to 3.4 on sets
+// of 45 configurations, and the longest token of a workgroup needs 25 to 32 one after the other.  Then writing the rows
+// (262 MB, 39-45 us).  Slower: the pairs of a step found by bit masks a lane instead of listed (185 us), the symbols of a
+// set's lists in registers to bring them into order (154 us; 5 to 10 % on grammars with large sets).
 //
 // Everything in LDS is bounded.  A token that would need more (more than 128 successors at a byte, more cells,
 // sets or row entries than there is room for) goes to the list of the passes behind this one, which take it alone.
@@ -35,6 +38,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "displacement_common.hpp"
 
@@ -55,8 +60,13 @@ constexpr int kShOut = 18432;       // row entries of all sets written so far (3
 constexpr int kShProds = 1024;      // productions kept in LDS (8 KB); of a larger grammar none are
 constexpr int kShAdj = 512;         // words of the relation kept in LDS (2 KB); of a larger one none are
 constexpr int kShPairs = 2048;      // (byte, symbol) pairs whose productions are looked up directly (4 KB)
-constexpr int kShRound = 8;         // tokens a wave takes at a time: few, so that few wait for a long one
-constexpr int kShBytes = 256;       // token bytes of a wave's round kept in LDS; a round with more reads memory
+constexpr int kShBatch = 1024;      // tokens a workgroup sorts by length at a time
+constexpr int kShBytes = 6144;      // their bytes, kept in LDS; if there are more they are read from memory
+constexpr int kShLengths = 64;      // lengths told apart in sorting
+constexpr int kShTakeMost = 16;     // tokens a wave takes at a time
+// Tokens for every wave up to which they are not sorted and a wave takes its share at once: then every token is begun at
+// the start anyway (32,000 tokens over the statement grammar, 125 a workgroup: 101 us, sorted 110).
+constexpr int kShOnce = 8;
 constexpr int kShSeen = 256;        // slots of a wave's table of the successors found so far: at most half full
 constexpr int kShProbes = 48;       // slots looked at before a table counts as full
 constexpr int kShFrontier = 128;    // successors of a set at one byte: two a lane
@@ -119,8 +129,11 @@ struct SharedLds {
     uint32_t own[8];          // bytes that are their own byte_like
     uint32_t pairs_kept;      // whether `pair` holds what the productions say
     uint32_t pool_top, out_top, cursor;
+    uint32_t scattered;      // some token's bytes do not lie where the token before ends
+    uint32_t of_length[kShLengths];
+    uint16_t order[kShBatch], start[kShBatch + 2];  // the batch's tokens, longest first; where each one's bytes begin
     uint8_t byte_like[256];  // the first byte with the same productions
-    uint8_t bytes[kShWaves][kShBytes];  // already as byte_like has them
+    uint8_t bytes[kShBytes];  // already as byte_like has them
 };
 
 template <typename T>
@@ -151,19 +164,43 @@ __device__ __forceinline__ uint32_t wave_sum32(uint32_t v) {
     return wave_read(v, 63);
 }
 
-// The number of the list of `length` symbols that is `symbol` in front of `rest`; 0 if the table is full (`full` is
-// set).
-__device__ __forceinline__ uint32_t sh_cons(SharedLds &L, uint32_t rest, uint32_t symbol, uint32_t length, bool &full) {
-    const uint32_t w = rest | (symbol << kCellIdBits) | (length << (kCellIdBits + 8));
-    uint32_t at = (w * 0x9E3779B1u) >> (32 - 11);
+// The largest of the lanes' values (all of them active), the same for every lane.
+__device__ __forceinline__ uint32_t wave_max32(uint32_t v) {
+    auto with = [&](auto ctrl, auto rows) {
+        const uint32_t x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xF, true);
+        v = v > x ? v : x;
+    };
+    with(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{});
+    with(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{});
+    with(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{});
+    with(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{});
+    with(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});
+    with(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});
+    return wave_read(v, 63);
+}
+
+__device__ __forceinline__ uint32_t cell_word(uint32_t rest, uint32_t symbol, uint32_t length) {
+    return rest | (symbol << kCellIdBits) | (length << (kCellIdBits + 8));
+}
+__device__ __forceinline__ uint32_t cell_slot(uint32_t w) {
     static_assert(kShCells == 1 << 11, "eleven bits of hash; a number (slot + 1) fits twelve");
-    for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShCells - 1)) {
-        uint32_t seen = lds_look(&L.cells[at]);
-        if (seen == 0u) seen = atomicCAS(&L.cells[at], 0u, w);
+    return (w * 0x9E3779B1u) >> (32 - 11);
+}
+// The number of the cell `w` whose slot `at` was found to hold `seen` after an attempt to claim it (0: claimed); 0 if
+// the table is full (`full` is set).
+__device__ __forceinline__ uint32_t sh_settle_cell(SharedLds &L, uint32_t w, uint32_t at, uint32_t seen, bool &full) {
+    for (int probe = 0; probe < kShProbes; ++probe) {
         if (seen == 0u || seen == w) return at + 1;
+        at = (at + 1) & (kShCells - 1);
+        seen = atomicCAS(&L.cells[at], 0u, w);
     }
     full = true;
     return 0;
+}
+// The number of the list of `length` symbols that is `symbol` in front of `rest`; 0 if the table is full.
+__device__ __forceinline__ uint32_t sh_cons(SharedLds &L, uint32_t rest, uint32_t symbol, uint32_t length, bool &full) {
+    const uint32_t w = cell_word(rest, symbol, length), at = cell_slot(w);
+    return sh_settle_cell(L, w, at, atomicCAS(&L.cells[at], 0u, w), full);
 }
 
 __device__ __forceinline__ uint32_t list_length(const SharedLds &L, uint32_t id) {
@@ -329,22 +366,30 @@ __device__ __forceinline__ uint32_t sh_carry_out(const DisplacementArgs &a, Shar
     int length = (int)packed_length(p);
     const bool is_long = length == (int)kLongBody;
     if (is_long) length = body_len(g, i);
+    uint32_t queued = 0;
     if (stack) {
         rest = cell_rest(cell);
         rest_length = cell_length(cell) - 1u;
     } else {
-        const uint32_t queued = cell_length(cell) + 1u;
-        if (queued > (uint32_t)kShMaxList) crossed = true;
-        else queue = sh_cons(L, queue, head, queued, full);
+        queued = cell_length(cell) + 1u;
     }
-    if (rest_length + (uint32_t)length > (uint32_t)kShMaxList) {
+    if (queued > (uint32_t)kShMaxList || rest_length + (uint32_t)length > (uint32_t)kShMaxList) {
         crossed = true;
-    } else {
-        const int off = is_long ? g.body_off[i] : 0;
-        for (int k = length - 1; k >= 0; --k) {
-            const uint32_t s = is_long ? (uint32_t)g.body[off + k] & 0xFFu : packed_symbol(p, k);
-            rest = sh_cons(L, rest, s, ++rest_length, full);
-        }
+        return kNoWord;
+    }
+    const int off = is_long ? g.body_off[i] : 0;
+    auto symbol = [&](int k) -> uint32_t { return is_long ? (uint32_t)g.body[off + k] & 0xFFu : packed_symbol(p, k); };
+    // the queue's new cell and the stack's first are claimed together: neither needs the other
+    const uint32_t wq = cell_word(queue, head, queued), ws = length ? cell_word(rest, symbol(length - 1), rest_length + 1u) : 0u;
+    const uint32_t at_q = cell_slot(wq), at_s = cell_slot(ws);
+    uint32_t seen_q = 0, seen_s = 0;
+    if (queued) seen_q = atomicCAS(&L.cells[at_q], 0u, wq);
+    if (length) seen_s = atomicCAS(&L.cells[at_s], 0u, ws);
+    if (queued) queue = sh_settle_cell(L, wq, at_q, seen_q, full);
+    if (length) {
+        rest = sh_settle_cell(L, ws, at_s, seen_s, full);
+        ++rest_length;
+        for (int k = length - 2; k >= 0; --k) rest = sh_cons(L, rest, symbol(k), ++rest_length, full);
     }
     return sh_config(queue, rest, head);
 }
@@ -406,30 +451,32 @@ __device__ __forceinline__ uint32_t sh_step_alone(const DisplacementArgs &a, Sha
     return kGiveUp;
 }
 
-// One byte of Algorithm 1 on a whole set, by the whole wave: the number of the set that follows.  First the pairs
-// (configuration, production that applies) are listed, then all of them are carried out together, a lane each: the
-// chain of LDS accesses is what this costs, and it is gone through once.
-__device__ __forceinline__ uint32_t sh_step(const DisplacementArgs &a, SharedLds &L, uint32_t *work, uint32_t *seen,
-                                            uint32_t set, int ch, int lane) {
+// The pairs of the set's configurations and the productions of `ch` that apply to them, listed in `work`: how many there
+// are (of more than kShFrontier only the first are listed).  `seen` starts empty and is left so.
+__device__ __forceinline__ int sh_list_pairs(const DisplacementArgs &a, SharedLds &L, uint32_t *work, uint32_t *seen,
+                                             uint32_t set, int ch, int lane) {
     const Grammar &g = a.g;
-    const u64 w = lds_look(&L.sets[set]);
+    const u64 w = wave_read64(lds_look(&L.sets[set]), 0);  // (what is the same for every lane: in scalar registers)
     lds_order();
     const int n = (int)set_size(w);
     const uint32_t *configs = L.pool + set_at(w);
-    const int lo = (int)L.byte_off[ch], hi = (int)L.byte_off[ch + 1], per = hi - lo;
-    const bool pairs_kept = L.pairs_kept != 0u;
-    const uint32_t byte_number = L.byte_number[ch];
+    const int lo = __builtin_amdgcn_readfirstlane((int)L.byte_off[ch]);
+    const int hi = __builtin_amdgcn_readfirstlane((int)L.byte_off[ch + 1]), per = hi - lo;
+    const bool pairs_kept = __builtin_amdgcn_readfirstlane(L.pairs_kept) != 0u;
+    const uint32_t byte_number = __builtin_amdgcn_readfirstlane((uint32_t)L.byte_number[ch]);
     auto prod = [&](int i) -> u64 { return sh_production(a, L, i); };
     const u64 below = (1ull << lane) - 1ull;
-    uint32_t *pairs = work, *out = work + kShFrontier;  // a pair: configuration (7 bits), production above
+    uint32_t *pair_config = work, *pair_production = work + kShFrontier, *empty = seen;
     int m = 0, empties = 0;
-    auto list = [&](bool on, int c, int i) {
+    auto list = [&](bool on, uint32_t config, int i) {
         const u64 mask = __ballot(on);
         const int slot = m + (int)__popcll(mask & below);
-        if (on && slot < kShFrontier) pairs[slot] = (uint32_t)c | ((uint32_t)i << 7);
+        if (on && slot < kShFrontier) {
+            pair_config[slot] = config;
+            pair_production[slot] = (uint32_t)i;
+        }
         m += (int)__popcll(mask);
     };
-
     // pops: the productions of (byte, top of the stack), which lie behind each other
     for (int c0 = 0; c0 < n; c0 += 64) {
         const int c = c0 + lane;
@@ -439,7 +486,7 @@ __device__ __forceinline__ uint32_t sh_step(const DisplacementArgs &a, SharedLds
         if (pairs_kept) {
             const uint32_t e = stack ? L.pair[byte_number * (uint32_t)g.N + top] : 0u;
             const int first = (int)(e & 0x3FFu), count = (int)(e >> 10);
-            for (int k = 0; __ballot(k < count); ++k) list(k < count, c, first + k);
+            for (int k = 0; __ballot(k < count); ++k) list(k < count, config, first + k);
         } else {
             int i = hi;
             if (stack) {
@@ -454,13 +501,13 @@ __device__ __forceinline__ uint32_t sh_step(const DisplacementArgs &a, SharedLds
             for (;;) {
                 const bool on = i < hi && packed_head(prod(i)) == top;
                 if (!__ballot(on)) break;
-                list(on, c, i);
+                list(on, config, i);
                 i = on ? i + 1 : hi;
             }
         }
-        const bool empty = c < n && !stack;
-        const u64 mask = __ballot(empty);
-        if (empty) out[empties + __popcll(mask & below)] = (uint32_t)c;
+        const bool is_empty = c < n && !stack;
+        const u64 mask = __ballot(is_empty);
+        if (is_empty) empty[empties + __popcll(mask & below)] = config;
         empties += (int)__popcll(mask);
     }
     lds_order();
@@ -471,33 +518,48 @@ __device__ __forceinline__ uint32_t sh_step(const DisplacementArgs &a, SharedLds
     const float inverse = 1.0f / (float)per;
     for (int x0 = 0; x0 < empties * per && m <= kShFrontier; x0 += 64 * kAhead) {
         bool on[kAhead];
-        int c[kAhead], i[kAhead];
+        uint32_t config[kAhead];
+        int i[kAhead];
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
             const int x = x0 + 64 * u + lane;
             on[u] = x < empties * per;
             int e = min((int)(((float)x + 0.5f) * inverse), empties - 1);  // x / per, up to rounding where x is large
             e = e * per > x ? e - 1 : ((e + 1) * per <= x ? e + 1 : e);
-            c[u] = on[u] ? (int)out[e] : 0;
+            config[u] = on[u] ? empty[e] : 0u;
             i[u] = on[u] ? lo + (x - e * per) : lo;
         }
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
             if (on[u]) {
-                const uint32_t last = sh_last(configs[c[u]]);
+                const uint32_t last = sh_last(config[u]);
                 if (last != kNoSymbol) on[u] = sh_may_follow(a, L, prod(i[u]), last);
             }
         }
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) list(on[u], c[u], i[u]);
+        for (int u = 0; u < kAhead; ++u) list(on[u], config[u], i[u]);
     }
+    if (empties) {
+        seen[lane] = kNoWord;
+        seen[lane + 64] = kNoWord;
+        static_assert(kShFrontier == 128, "as many configurations a set has at the most");
+    }
+    return m;
+}
+
+// One byte of Algorithm 1 on a whole set, by the whole wave: the number of the set that follows.  The listed pairs are
+// carried out together, a lane each: the chain of LDS accesses is what this costs, and it is gone through once.
+__device__ __forceinline__ uint32_t sh_step(const DisplacementArgs &a, SharedLds &L, uint32_t *work, uint32_t *seen,
+                                            uint32_t set, int ch, int lane) {
+    const int m = sh_list_pairs(a, L, work, seen, set, ch, lane);
     // (the passes behind this one also find whether a bound is broken)
     if (m > kShFrontier) return kGiveUp;
     lds_order();
+    uint32_t *pair_config = work, *pair_production = work + kShFrontier;
     bool full = false, crossed = false;
     auto carry_out = [&](int x) -> uint32_t {
         if (x >= m) return kNoWord;
-        return sh_carry_out(a, L, configs[pairs[x] & 0x7Fu], (int)(pairs[x] >> 7), full, crossed);
+        return sh_carry_out(a, L, pair_config[x], (int)pair_production[x], full, crossed);
     };
     const uint32_t first = carry_out(lane);
     uint32_t second = kNoWord;
@@ -619,12 +681,81 @@ __device__ __forceinline__ u64 sh_write_set(const DisplacementArgs &a, SharedLds
     return result;
 }
 
-// A workgroup takes `per_group` consecutive tokens, a wave `round` of them at a time.
+// A workgroup takes `per_group` consecutive tokens, the longest first: what a token of 25 bytes needs, set after set that
+// nobody has met, is a chain that nothing shortens, and begun last it was what the workgroup waited for (128,256 tokens
+// over the JSON grammar, in the order they come in, eight a wave at a time: the waves done after 106 us on average, the
+// last one after 177; so 149).  The lanes of a wave hold tokens in all stages.  The wave works out a step that one of them waits for, of the token with most bytes to go; if
+// there is none, writes the rows of those that are through; if none is, takes more tokens; and waits only if there are
+// none left.
 template <bool ROWS16>  // rows start at multiples of 16 bytes
-__global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(DisplacementArgs a, int per_group, int round) {
+__global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(DisplacementArgs a, int per_group) {
     __shared__ SharedLds L;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t group0 = (int64_t)blockIdx.x * per_group;
+    const int in_group = (int)min((int64_t)per_group, (int64_t)a.V - group0);
+    // a batch of tokens, and the thread's share of their bytes: the first is asked for before the tables are set up
+    int64_t from_byte = 0, bytes_here = 0, begins = 0, ends = 0;
+    constexpr int kShare = kShBytes / kShThreads;
+    static_assert(kShBytes % kShThreads == 0, "");
+    uint8_t share[kShare];
+    int batch_size = 0;
+    auto fetch = [&](int batch0) {
+        const int64_t first_token = group0 + batch0;
+        const int in_batch = min(in_group - batch0, kShBatch);
+        batch_size = in_batch;
+        from_byte = a.tok_off[first_token];
+        bytes_here = a.tok_off[first_token + in_batch] - from_byte;
+        begins = a.tok_off[first_token + min(tid, in_batch - 1)] - from_byte;
+        ends = a.tok_off[first_token + min(tid, in_batch - 1) + 1] - from_byte;
+#pragma unroll
+        for (int k = 0; k < kShare; ++k) {
+            const int x = tid + k * kShThreads;
+            share[k] = 0;
+            if (bytes_here <= kShBytes && x < bytes_here) share[k] = a.tok_bytes[from_byte + x];
+        }
+    };
+    fetch(0);
     const bool invalid = a.hdr->invalid != 0;  // the same for everybody
+    const bool sorted = in_group > kShOnce * kShWaves;  // otherwise every wave takes its tokens at once
+    // sorting a batch: four parts with a barrier between them
+    uint32_t shorter = 0, rank = 0;
+    auto fit = [&]() { return bytes_here >= 0 && bytes_here <= kShBytes; };
+    auto clear_batch = [&]() {
+        if (tid == 0) L.cursor = L.scattered = 0;
+        if (tid < kShLengths) L.of_length[tid] = 0;
+    };
+    auto count_lengths = [&]() {
+        if (invalid) from_byte = bytes_here = begins = ends = 0;
+        if (tid < batch_size) {
+            // a number that is smaller for longer ones
+            shorter = (uint32_t)(kShLengths - 1 - min(max(ends - begins, (int64_t)0), (int64_t)kShLengths - 1));
+            if (sorted) rank = atomicAdd(&L.of_length[shorter], 1u);
+            if (begins < 0 || ends < begins || ends > bytes_here) L.scattered = 1;
+        }
+        if (fit())
+#pragma unroll
+            for (int k = 0; k < kShare; ++k)
+                if (tid + k * kShThreads < bytes_here) L.bytes[tid + k * kShThreads] = L.byte_like[share[k]];
+    };
+    auto sum_lengths = [&]() {
+        if (!sorted || wave != 0) return;
+        const uint32_t count = L.of_length[lane];
+        uint32_t before = count;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t x = __shfl_up(before, off, 64);
+            before += lane >= off ? x : 0u;
+        }
+        L.of_length[lane] = before - count;
+    };
+    auto put_in_order = [&]() {
+        if (tid >= batch_size) return;
+        L.order[sorted ? L.of_length[shorter] + rank : (uint32_t)tid] = (uint16_t)tid;
+        if (fit() && L.scattered == 0) {
+            L.start[tid] = (uint16_t)begins;
+            L.start[tid + 1] = (uint16_t)ends;  // (where the next one begins: the same value from both)
+        }
+    };
     for (int i = tid; i < kShCells; i += kShThreads) L.cells[i] = 0;
     for (int i = tid; i < kShNext; i += kShThreads) L.next[i] = kNextEmpty;
     for (int i = tid; i < kShSets; i += kShThreads) {
@@ -644,9 +775,10 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
     if (tid == 0) {
         L.pool_top = 0;
         L.out_top = 0;
-        L.cursor = 0;
     }
+    clear_batch();
     __syncthreads();
+    count_lengths();
     if (!invalid && tid < 256 && L.byte_like[tid] == tid) atomicOr(&L.own[tid >> 5], 1u << (tid & 31));
     __syncthreads();
     {
@@ -660,6 +792,7 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
             for (int w = 0; w < (tid >> 5); ++w) number += __popc(L.own[w]);
             L.byte_number[tid] = (uint8_t)(number + __popc(L.own[tid >> 5] & ((1u << (tid & 31)) - 1u)));
         }
+        sum_lengths();
         __syncthreads();
         if (fits)
             for (int i = tid; i < a.g.P; i += kShThreads) {
@@ -673,6 +806,7 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
                 else L.pairs_kept = 0;  // more than six bits
             }
     }
+    put_in_order();
     __syncthreads();
     uint32_t *work = L.work[wave], *seen = L.seen[wave];
     seen_clear(seen, lane);
@@ -683,40 +817,37 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
     seen_clear(seen, lane);
     const uint32_t dead = sh_set_number(L, seen, find_different(seen, kNoWord, kNoWord, lane), lane);
 
-    const int64_t group0 = (int64_t)blockIdx.x * per_group;
-    const int in_group = (int)min((int64_t)per_group, (int64_t)a.V - group0);
     int steps = 0;  // that this wave has worked out
-    for (;;) {
-        __builtin_amdgcn_wave_barrier();  // the wave goes round together: no branch on the lane is joined with the next one
-        int taken = 0;
-        if (lane == 0) taken = (int)atomicAdd(&L.cursor, (uint32_t)round);
-        taken = __builtin_amdgcn_readfirstlane(taken);
-        if (taken >= in_group) break;
-        const int64_t t0 = group0 + taken, t = t0 + lane;
-        const int count = min(round, in_group - taken);
-        const bool in = lane < count;
-        int64_t pos = 0, end = 0;
-        if (in && !invalid) {
-            pos = a.tok_off[t];
-            end = a.tok_off[t + 1];
+    for (int batch0 = 0; batch0 < in_group; batch0 += kShBatch) {
+        const int64_t first_token = group0 + batch0;
+        const int in_batch = min(in_group - batch0, kShBatch);
+        if (batch0) {  // (the first has been sorted while the tables were set up)
+            __syncthreads();  // the last batch is done with
+            fetch(batch0);
+            clear_batch();
+            __syncthreads();
+            count_lengths();
+            __syncthreads();
+            sum_lengths();
+            __syncthreads();
+            put_in_order();
+            __syncthreads();
         }
-        // the round's bytes lie behind each other: into LDS if there is room
-        const int64_t from_byte = invalid ? 0 : a.tok_off[t0], to_byte = invalid ? 0 : a.tok_off[t0 + count];
-        uint8_t *bytes = L.bytes[wave];
-        const bool staged = to_byte - from_byte <= kShBytes;
-        lds_order();
-        if (staged)
-            for (int x = lane; x < (int)(to_byte - from_byte); x += 64) bytes[x] = L.byte_like[a.tok_bytes[from_byte + x]];
-        lds_order();
-        auto byte_at = [&](int64_t p) -> uint32_t {
-            if (staged) return bytes[min(max(p - from_byte, (int64_t)0), (int64_t)kShBytes - 1)];  // in bounds whatever the offsets are
-            return L.byte_like[a.tok_bytes[p]];
-        };
-        uint32_t set = start;
+        const bool staged = fit() && L.scattered == 0;
+        auto byte_at = [&](int64_t p) -> uint32_t { return staged ? L.bytes[p] : L.byte_like[a.tok_bytes[from_byte + p]]; };
+
+        // the lane's token
+        int token = -1;                         // its number in the batch, -1: none
+        int64_t pos = 0, end = 0;               // its bytes from here on
+        uint32_t set = start, like = 0, after = 0;  // where it is, the next byte and the one behind it
         bool give_up = false, crossed = false;
-        bool by_the_wave = false;  // the next step has turned out to take a whole wave
-        uint32_t like = pos < end ? byte_at(pos) : 0u;
+        bool by_the_wave = false;               // the next step has turned out to take a whole wave
+        u64 row = kRowUnknown;
+        // how many the wave takes next: of sorted ones the longest one by one, else all that are its
+        int take = sorted ? 1 : (in_group + kShWaves - 1) / kShWaves;
+        bool more = true;
         for (;;) {
+            __builtin_amdgcn_wave_barrier();  // the wave goes round together: no branch on the lane is joined with the next one
             // every lane as far as what follows is known
             uint32_t waits = 0;  // kNextEmpty or kWorkedOut: what the lane has come to
             auto advance = [&](uint32_t following) {
@@ -727,7 +858,8 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
                 } else {
                     set = following;
                     by_the_wave = false;
-                    if (++pos < end) like = byte_at(pos);
+                    like = after;
+                    if (++pos + 1 < end) after = byte_at(pos + 1);
                 }
             };
             while (pos < end && !waits) {
@@ -754,91 +886,124 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
                 }
                 if (__ballot(alone && !by_the_wave)) continue;
             }
-            const u64 unknown = __ballot(waits == kNextEmpty);
-            if (!unknown) {
-                if (!__ballot(waits != 0u)) break;
-                // another wave is at all that is left; it waits for nothing while it works
-                __builtin_amdgcn_s_sleep(2);
+            if (__ballot(waits == kNextEmpty)) {
+                // by the whole wave what the lane with most bytes to go waits for
+                const uint32_t to_go = (uint32_t)min(end - pos, (int64_t)0xFFFFFF);
+                const uint32_t key = waits == kNextEmpty ? (to_go << 6) | (uint32_t)(lane ^ 63) : 0u;
+                const int chosen = sorted ? (int)(wave_max32(key) & 63u) ^ 63
+                                          : __ffsll(__ballot(waits == kNextEmpty)) - 1;
+                const uint32_t from = wave_read(set, chosen), on = wave_read(like, chosen);
+                int slot = 0;
+                if (lane == 0) slot = sh_claim(L, from, on);
+                slot = __builtin_amdgcn_readfirstlane(slot);
+                if (slot == -1) continue;  // taken meanwhile
+                const uint32_t following = sh_step(a, L, work, seen, from, (int)on, lane);
+                ++steps;
+                lds_order();
+                if (slot >= 0 && lane == 0)
+                    __hip_atomic_store(&L.next[slot], (((from << 8) | on) << kNextBits) | following, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (waits && set == from && like == on) advance(following);
                 continue;
             }
-            // what the first lane waits for, by the whole wave
-            const int first = __ffsll(unknown) - 1;
-            const uint32_t from = wave_read(set, first), on = wave_read(like, first);
-            int slot = 0;
-            if (lane == 0) slot = sh_claim(L, from, on);
-            slot = __builtin_amdgcn_readfirstlane(slot);
-            if (slot == -1) continue;  // taken meanwhile
-            const uint32_t following = sh_step(a, L, work, seen, from, (int)on, lane);
-            ++steps;
-            lds_order();
-            if (slot >= 0 && lane == 0)
-                __hip_atomic_store(&L.next[slot], (((from << 8) | on) << kNextBits) | following, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (waits && set == from && like == on) advance(following);
-        }
-        // what the sets reached are written as
-        const bool wanted = in && !invalid && !give_up && !crossed;
-        u64 row = kRowUnknown;
-        for (;;) {
-            if (wanted && (row == kRowUnknown || row == kRowWorkedOut)) row = lds_look(&L.row[set]);
-            const u64 unknown = __ballot(wanted && row == kRowUnknown);
-            if (!unknown) {
-                if (!__ballot(wanted && row == kRowWorkedOut)) break;
-                __builtin_amdgcn_s_sleep(2);  // as above
-                continue;
+            // What the sets reached are written as.
+            bool through = token >= 0 && pos >= end;
+            const bool wanted = through && !invalid && !give_up && !crossed;
+            for (;;) {
+                if (wanted && (row == kRowUnknown || row == kRowWorkedOut)) row = lds_look(&L.row[set]);
+                const u64 unknown = __ballot(wanted && row == kRowUnknown);
+                if (!unknown) break;
+                const uint32_t s = wave_read(set, __ffsll(unknown) - 1);
+                u64 state = 0;
+                if (lane == 0) state = atomicCAS(&L.row[s], kRowUnknown, kRowWorkedOut);
+                if (wave_read64(state, 0) == kRowUnknown) sh_write_set(a, L, work, seen, s, lane);
             }
-            const uint32_t s = wave_read(set, __ffsll(unknown) - 1);
-            u64 state = 0;
-            if (lane == 0) state = atomicCAS(&L.row[s], kRowUnknown, kRowWorkedOut);
-            if (wave_read64(state, 0) == kRowUnknown) sh_write_set(a, L, work, seen, s, lane);
-        }
-        lds_order();
-        if (row == kRowGiveUp) give_up = true;
-        if (row == kRowTooLong) crossed = true;
-        const bool done = in && !give_up;
-        if (done) {
-            u64 h = 0;
-            int32_t status = kStatusOk;
-            if (invalid) {
-                status = kStatusBadGrammar;
-            } else if (crossed) {
-                h = overflow_hash(a.seed, (int)t);
-                status = kStatusOverflow;
-            } else {
-                h = L.row_hash[set];
-            }
-            a.hash[t] = h;
-            if (a.status) a.status[t] = status;
-        }
-        const u64 handed = __ballot(in && give_up);
-        if (handed) {
-            int32_t at = 0;
-            if (lane == 0) at = atomicAdd(&a.hdr->retry_count[0], (int)__popcll(handed));
-            at = __builtin_amdgcn_readfirstlane(at);
-            if (in && give_up) a.retry_list[0][at + __popcll(handed & ((1ull << lane) - 1ull))] = (int32_t)t;
-        }
-        // the rows, one after the other by the whole wave
-        const u64 plain = __ballot(done && !invalid && !crossed);
-        for (u64 left = __ballot(done); left; left &= left - 1) {
-            const int k = __ffsll(left) - 1;
-            const int64_t tk = t0 + k;
-            uint16_t *out_row = a.rows + (size_t)tk * a.row_len;
-            const bool copy = (plain >> k) & 1ull;
-            const u64 rk = wave_read64(row, k);
-            const uint32_t units = copy ? (((uint32_t)rk & 0xFFFFu) + 7u) / 8u : 0u;  // 16 bytes each
-            const uint4 *src = reinterpret_cast<const uint4 *>(L.out + (copy ? (uint32_t)(rk >> 16) : 0u));
-            const bool marked = !copy && !invalid;  // the row of a token that overflowed
-            for (uint32_t u = lane; u < (uint32_t)a.row_len / 8u; u += 64) {
-                uint4 v = make_uint4(0, 0, 0, 0);
-                if (u < units) v = src[u];
-                if (marked && u == 0) v = make_uint4(0xFFFFu | ((uint32_t)tk << 16), (uint32_t)tk >> 16, 0, 0);
-                if (ROWS16) {
-                    reinterpret_cast<uint4 *>(out_row)[u] = v;
-                } else {
-                    reinterpret_cast<uint2 *>(out_row)[2 * u] = make_uint2(v.x, v.y);
-                    reinterpret_cast<uint2 *>(out_row)[2 * u + 1] = make_uint2(v.z, v.w);
+            if (wanted && row == kRowWorkedOut) through = false;  // another wave is at it
+            if (__ballot(through)) {
+                lds_order();
+                const int64_t t = first_token + token;
+                if (wanted && row == kRowGiveUp) give_up = true;
+                if (wanted && row == kRowTooLong) crossed = true;
+                const bool done = through && !give_up;
+                if (done) {
+                    u64 h = 0;
+                    int32_t status = kStatusOk;
+                    if (invalid) {
+                        status = kStatusBadGrammar;
+                    } else if (crossed) {
+                        h = overflow_hash(a.seed, (int)t);
+                        status = kStatusOverflow;
+                    } else {
+                        h = L.row_hash[set];
+                    }
+                    a.hash[t] = h;
+                    if (a.status) a.status[t] = status;
                 }
+                const u64 handed = __ballot(through && give_up);
+                if (handed) {
+                    int32_t at = 0;
+                    if (lane == 0) at = atomicAdd(&a.hdr->retry_count[0], (int)__popcll(handed));
+                    at = __builtin_amdgcn_readfirstlane(at);
+                    if (through && give_up) a.retry_list[0][at + __popcll(handed & ((1ull << lane) - 1ull))] = (int32_t)t;
+                }
+                // the rows, one after the other by the whole wave
+                const u64 plain = __ballot(done && !invalid && !crossed);
+                for (u64 left = __ballot(done); left; left &= left - 1) {
+                    const int k = __ffsll(left) - 1;
+                    const int64_t tk = first_token + (int)wave_read((uint32_t)token, k);
+                    uint16_t *out_row = a.rows + (size_t)tk * a.row_len;
+                    const bool copy = (plain >> k) & 1ull;
+                    const u64 rk = wave_read64(row, k);
+                    const uint32_t units = copy ? (((uint32_t)rk & 0xFFFFu) + 7u) / 8u : 0u;  // 16 bytes each
+                    const uint4 *src = reinterpret_cast<const uint4 *>(L.out + (copy ? (uint32_t)(rk >> 16) : 0u));
+                    const bool marked = !copy && !invalid;  // the row of a token that overflowed
+                    for (uint32_t u = lane; u < (uint32_t)a.row_len / 8u; u += 64) {
+                        uint4 v = make_uint4(0, 0, 0, 0);
+                        if (u < units) v = src[u];
+                        if (marked && u == 0) v = make_uint4(0xFFFFu | ((uint32_t)tk << 16), (uint32_t)tk >> 16, 0, 0);
+                        if (ROWS16) {
+                            reinterpret_cast<uint4 *>(out_row)[u] = v;
+                        } else {
+                            reinterpret_cast<uint2 *>(out_row)[2 * u] = make_uint2(v.x, v.y);
+                            reinterpret_cast<uint2 *>(out_row)[2 * u + 1] = make_uint2(v.z, v.w);
+                        }
+                    }
+                }
+                if (through) token = -1;
+                continue;
             }
+            const u64 idle = __ballot(token < 0);
+            if (more && idle) {
+                const int want = min(take, (int)__popcll(idle));
+                int taken = 0;
+                if (lane == 0) taken = (int)atomicAdd(&L.cursor, (uint32_t)want);
+                taken = __builtin_amdgcn_readfirstlane(taken);
+                const int count = min(want, in_batch - taken);
+                more = count > 0;
+                const int rank_idle = (int)__popcll(idle & ((1ull << lane) - 1ull));
+                if (token < 0 && rank_idle < count) {
+                    token = (int)L.order[taken + rank_idle];
+                    if (staged) {
+                        pos = L.start[token];
+                        end = L.start[token + 1];
+                    } else {
+                        pos = end = 0;
+                        if (!invalid) {
+                            pos = a.tok_off[first_token + token] - from_byte;
+                            end = a.tok_off[first_token + token + 1] - from_byte;
+                        }
+                    }
+                    set = start;
+                    give_up = crossed = by_the_wave = false;
+                    row = kRowUnknown;
+                    if (pos < end) like = byte_at(pos);
+                    if (pos + 1 < end) after = byte_at(pos + 1);
+                }
+                take = min(2 * take, kShTakeMost);
+                continue;
+            }
+            if (idle == ~0ull) break;
+            __builtin_amdgcn_s_sleep(2);  // another wave is at all that is left; it waits for nothing while it works
         }
     }
 }

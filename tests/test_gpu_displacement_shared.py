@@ -136,3 +136,35 @@ def test_rows_that_are_only_8_byte_aligned(lib):
     assert (got[4:-4].reshape(vocab.V, 256) == want.view(torch.int16).cpu().numpy()).all()
     assert (got[:4] == 7).all() and (got[-4:] == 7).all()
     assert torch.equal(h, want_hash) and torch.equal(st, want_status)
+
+
+@pytest.mark.parametrize("V,longest", [(32_768, 6), (32_769, 6), (33_100, 80), (262_144, 4), (262_401, 4)])
+def test_groups_around_the_sorted_batches(lib, V, longest):
+    """128 tokens for a workgroup, which its waves take at once, and 129, which are sorted by length; more bytes than are
+    staged (tokens of up to 80); a whole batch of 1,024 tokens and one more.  The vocabulary repeats 700 strings: theirs are
+    compared with the oracle, and every row, hash and status with its string's."""
+    print(f"case V={V} longest={longest}", flush=True)
+    g = make_json_gnf()
+    few = make_token_strings(V, 700, b'{}[]",:0123456789.eE+-truefalsn \\ua', longest)
+    _check_rows(lib, g, few, expect_overflow=None)
+    rng = np.random.default_rng(V)
+    pick = rng.integers(0, few.V, size=V)
+    strings = few.tokens()
+    vocab = vocab_from_tokens([strings[i] for i in pick])
+    gd = _grammar_dev(g)
+
+    def run(v):
+        return lib.cfgzip_displacements(torch.from_numpy(v.tok_bytes).cuda(), torch.from_numpy(v.tok_off).cuda(), *gd, g.N,
+                                        row_len=256)
+
+    rows, h, status = run(few)
+    many_rows, many_h, many_status = run(vocab)
+    p = torch.from_numpy(pick).cuda()
+    assert bool((many_status == status[p]).all())
+    ok = many_status == 0  # a token that overflows has a row and a hash of its own
+    assert bool(ok.any())
+    assert bool((many_h == h[p])[ok].all())
+    for a in range(0, V, 1 << 16):
+        part = slice(a, min(V, a + (1 << 16)))
+        same = (many_rows[part].view(torch.int16) == rows.view(torch.int16)[p[part]]).all(dim=1)
+        assert bool(same[ok[part]].all())
