@@ -7,6 +7,8 @@ stream.  Function names and argument order follow ``include/cfgzip.h``.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional, Tuple
 
@@ -15,6 +17,10 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "lib", "libcfgzip.so")
 _lib: Optional[ctypes.CDLL] = None
+_STEPCALL_PATH = os.path.join(_HERE, "lib", "cfgzip_stepcall.so")
+# the two per-step calls without ctypes, set when the library is loaded
+_decode_step = None
+_engine_step = None
 
 DEFAULT_HASH_SEED = 0x5EED_CF62_1234_ABCD
 
@@ -46,12 +52,13 @@ def library_path() -> str:
 
 def load_library() -> ctypes.CDLL:
     """Loads the built HIP library; raises if it has not been built (there is no fallback)."""
-    global _lib
+    global _lib, _decode_step, _engine_step
     if _lib is not None:
         return _lib
-    if not os.path.exists(_LIB_PATH):
+    missing = [p for p in (_LIB_PATH, _STEPCALL_PATH) if not os.path.exists(p)]
+    if missing:
         raise RuntimeError(
-            f"{_LIB_PATH} is missing: build it with `python -m paper_2605_29986_amd.build` "
+            f"{missing[0]} is missing: build it with `python -m paper_2605_29986_amd.build` "
             "(hipcc, gfx950). The CFGzip path has no CPU fallback.")
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i32, i64, u64, sz = (ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint64,
@@ -105,6 +112,12 @@ def load_library() -> ctypes.CDLL:
     lib.cfgzip_displacements.restype = ctypes.c_int
     lib.cfgzip_displacements.argtypes = [vp, vp, i32, vp, vp, vp, vp, i32, i32, i32, vp, i32, vp, vp, u64,
                                          vp, sz, vp]
+    loader = importlib.machinery.ExtensionFileLoader("cfgzip_stepcall", _STEPCALL_PATH)
+    spec = importlib.util.spec_from_file_location("cfgzip_stepcall", _STEPCALL_PATH, loader=loader)
+    stepcall = importlib.util.module_from_spec(spec)
+    loader.exec_module(stepcall)
+    stepcall.connect(ctypes.cast(lib.cfgzip_decode_step, vp).value, ctypes.cast(lib.cfgzip_engine_step, vp).value)
+    _decode_step, _engine_step = stepcall.decode_step, stepcall.engine_step
     _lib = lib
     return lib
 
@@ -325,7 +338,13 @@ def cfgzip_decode_step(logits: torch.Tensor, cls_bits: torch.Tensor, class_of_to
                        stream=None) -> torch.Tensor:
     """Fused expand + apply on `logits` (in place) and the map of `tok` to representatives, in
     one launch.  Returns rep_out (int32 [B])."""
-    lib = load_library()
+    lib = _lib or load_library()
+    if stream is None:
+        out = _decode_step(logits, cls_bits, class_of_token, C, tok, rep_of_class, tok_bits_out, rep_out, V)
+        if out is not None:
+            if type(out) is int:
+                _check("cfgzip_decode_step", out)
+            return out
     if logits.dim() != 2 or logits.stride(1) != 1 or not logits.is_cuda:
         raise ValueError("logits must be a 2-D GPU tensor with unit column stride")
     if logits.dtype == torch.float32:
@@ -553,7 +572,14 @@ def cfgzip_engine_step(logits: torch.Tensor, state_mask: torch.Tensor, C: int,
     """One decode step of the byte-automaton engine in one launch: advances the states on the
     tokens sampled last (tok_prev, or None at the first step), masks `logits` in place with each
     sequence's class mask, returns the new states (int32 [B], a tensor other than states_in)."""
-    lib = load_library()
+    lib = _lib or load_library()
+    if stream is None:
+        out = _engine_step(logits, state_mask, C, class_of_token, sig_rep, tok_prev, states_in, states_out,
+                           tok_bits_out, V)
+        if out is not None:
+            if type(out) is int:
+                _check("cfgzip_engine_step", out)
+            return out
     if logits.dtype == torch.float32:
         dtype = 0
     elif logits.dtype == torch.bfloat16:

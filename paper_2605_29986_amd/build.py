@@ -6,6 +6,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -33,6 +34,28 @@ def find_hipcc() -> str:
     raise RuntimeError("hipcc not found; libcfgzip.so cannot be built")
 
 
+# the per-step calls of the binding as a CPython extension: host code only, against torch's headers
+STEPCALL_PATH = os.path.join(LIB_DIR, "cfgzip_stepcall.so")
+
+
+def build_stepcall(verbose: bool = False) -> str:
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = STEPCALL_PATH + ".tmp.%d" % os.getpid()
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+           "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(rocm, "include"), "-o", tmp, os.path.join(CSRC, "stepcall.cpp"),
+           "-L", os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+           "-Wl,-rpath," + os.path.join(root, "lib")]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, STEPCALL_PATH)
+    return STEPCALL_PATH
+
+
 TOOL_PATH = os.path.join(LIB_DIR, "gather_rate")  # calibration tool for the walk kernels' roofline
 
 
@@ -44,6 +67,7 @@ def build(verbose: bool = False) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(tmp, LIB_PATH)
+    build_stepcall(verbose)
     tool_flags = [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
     tmp = TOOL_PATH + ".tmp.%d" % os.getpid()
     cmd = [find_hipcc(), *tool_flags, "-o", tmp, os.path.join(CSRC, "tools", "gather_rate.hip")]
