@@ -60,8 +60,8 @@ constexpr int kRun = 1 << kRunBits;
 constexpr int kMaxRuns = kTableMaxTokens / kRun;
 // Up to here the tokens are the entries: every bucket then looks at every token, which takes longer than a launch from
 // about here on (3,000 / 6,000 / 10,000 / 16,000 tokens: merge 6.9 / 10.1 / 12.4 / 15.8 us; gathered first, gather and
-// merge 10.0 / 10.3 / 10.2 / 10.2).
-constexpr int32_t kDirectTokens = 6144;
+// merge 10.0 / 10.3 / 10.2 / 10.2 and the launch; calls of 7,000 tokens 46 to 50 and 50 us, of 8,000 48 and 47).
+constexpr int32_t kDirectTokens = 7168;
 
 // Buckets: at most as many as there are compute units, and 64 tokens in each on average (the lists of groups to be
 // compared, kListedLeast a bucket, then stay small against the vocabulary).
@@ -502,7 +502,7 @@ __device__ __forceinline__ void table_number(const TableSettleArgs &a, unsigned 
 }
 
 constexpr uint32_t kRowPart = 64;  // 16-byte units of a row that a wave compares
-__host__ __device__ inline int64_t table_row_parts(int32_t S) { return (S / 8 + (int)kRowPart - 1) / (int)kRowPart; }
+__host__ __device__ inline int64_t table_row_parts(int32_t S) { return (S + 8 * (int)kRowPart - 1) / (8 * (int)kRowPart); }
 
 // STORE: the comparisons read the walk store, otherwise rows.
 template <bool STORE>
@@ -516,6 +516,16 @@ __global__ __launch_bounds__(kTableThreads) void table_settle_kernel(TableSettle
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint16_t *staged = reinterpret_cast<uint16_t *>(lds) + (size_t)wave * 2 * kWalkStoreMaxStride;  // STORE only
     const int block = (int)blockIdx.x - a.number_blocks;
+    const int group_blocks = STORE ? kGroupBlocks * a.buckets : 0;
+    // where groups are compared: a lane's first group, asked for before the store's header is looked at
+    const int parts = STORE && a.S >= 8 ? kCrossParts : 1;
+    const int teams = kGroupBlocks * (kWaves / parts), team = block % kGroupBlocks * (kWaves / parts) + wave / parts;
+    const int32_t *listed = a.listed_group + (size_t)(block / kGroupBlocks) * a.list_room;
+    int listed_here = 0, next_group = 0;
+    if (block < group_blocks) {
+        listed_here = min(max(a.listed_count[block / kGroupBlocks], 0), a.list_room);
+        next_group = listed[min(team + lane * teams, a.list_room - 1)];
+    }
     uint32_t stride = 0;  // of the walk store
     if (STORE) {
         const int state = walk_store_state(a.store, stride);
@@ -525,22 +535,14 @@ __global__ __launch_bounds__(kTableThreads) void table_settle_kernel(TableSettle
         }
     }
     bool differs = false;
-    const int group_blocks = STORE ? kGroupBlocks * a.buckets : 0;
     if (STORE && block < group_blocks) {
-        // groups against a member of their class, a few workgroups per bucket: kCrossParts waves share a pair (S a
-        // multiple of 8).  A lane looks at a group, and where its smallest member is not its class's the wave compares
+        // groups against a member of their class, a few workgroups per bucket: kCrossParts waves share a pair (S
+        // >= 8).  A lane looks at a group, and where its smallest member is not its class's the wave compares
         // the two
-        const int parts = (a.S % 8) == 0 ? kCrossParts : 1;
-        const int bucket = block / kGroupBlocks;
-        const int count = min(max(a.listed_count[bucket], 0), a.list_room);
-        const int teams = kGroupBlocks * (kWaves / parts), team = block % kGroupBlocks * (kWaves / parts) + wave / parts;
-        for (int x0 = team; x0 < count; x0 += 64 * teams) {
+        for (int x0 = team; x0 < listed_here; x0 += 64 * teams) {
             const int x = x0 + lane * teams;
-            int32_t t = 0, other = 0;
-            if (x < count) {
-                t = a.listed_group[(size_t)bucket * a.list_room + x];
-                other = class_member(a, t);
-            }
+            const int32_t group = x0 == team ? next_group : listed[min(x, listed_here - 1)];
+            const int32_t t = x < listed_here ? group : 0, other = x < listed_here ? class_member(a, group) : 0;
             const uint32_t ra = store_row(a.store, t), rb = store_row(a.store, other);
             for (uint64_t left = __ballot(t != other); left; left &= left - 1) {
                 const int l = __ffsll((unsigned long long)left) - 1;
@@ -595,8 +597,8 @@ __global__ __launch_bounds__(kTableThreads) void table_settle_kernel(TableSettle
             // four rows per wave against their classes' members' rows, which many share (they stay in the caches); what
             // there is to read is every row once.  Of rows of more than kRowPart units a wave takes a part: waves that
             // read whole rows of 8 KB all ask the same memory channels at a time (262 MB in rows of 8 KB: 60 us, 49 us so)
-            const bool vec = (a.S % 8) == 0 && (reinterpret_cast<uintptr_t>(a.sig) % 16) == 0;
-            const uint32_t s8 = (uint32_t)a.S / 8u;  // (262,144 rows of 8,192 units: 31 bits)
+            const bool vec = a.S >= 8;
+            const uint32_t s8 = ((uint32_t)a.S + 7u) / 8u;
             const int64_t parts = vec ? table_row_parts(a.S) : 1, items = ((int64_t)a.n + 3) / 4 * parts;
             for (int64_t x = gw; x < items; x += waves) {
                 const int64_t t0 = x / parts * 4;
@@ -610,14 +612,14 @@ __global__ __launch_bounds__(kTableThreads) void table_settle_kernel(TableSettle
                 }
                 if (!cnt) continue;  // all four are their classes' members (wave-uniform)
                 if (vec) {
-                    const uint4 *rows = reinterpret_cast<const uint4 *>(a.sig);
                     const uint32_t from = (uint32_t)(x % parts) * kRowPart, to = min(s8, from + kRowPart);
                     for (uint32_t j = from + lane; j < to; j += 64) {
-                        uint4 p[4], q[4];
+                        u32x4_any p[4], q[4];
+                        const uint16_t *eight = a.sig + min(8u * j, (uint32_t)a.S - 8u);  // the last eight where fewer are left
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
-                            p[u] = rows[(uint32_t)t[u] * s8 + j];
-                            q[u] = rows[(uint32_t)ref[u] * s8 + j];
+                            p[u] = *reinterpret_cast<const u32x4_any *>(eight + (size_t)t[u] * a.S);
+                            q[u] = *reinterpret_cast<const u32x4_any *>(eight + (size_t)ref[u] * a.S);
                         }
 #pragma unroll
                         for (int u = 0; u < 4; ++u)

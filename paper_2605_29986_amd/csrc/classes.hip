@@ -1024,9 +1024,9 @@ __global__ __launch_bounds__(kThreads) void mark_heads_kernel(MarkArgs a) {
         return;
     }
     if (!a.other_list) return;
-    // kListedParts waves share a link when the signatures are long (S a multiple of 8 only)
+    // kListedParts waves share a link when the signatures are long (S >= 8 only)
     const int wave = threadIdx.x >> 6;
-    const int parts = (a.store.S % 8) == 0 ? kListedParts : 1;
+    const int parts = a.store.S >= 8 ? kListedParts : 1;
     const int count = min(a.ctr->other_rows, a.n);
     uint32_t stride = 0;
     if (walk_store_state(a.store, stride)) return;  // then nothing is listed

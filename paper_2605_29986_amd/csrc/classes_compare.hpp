@@ -77,7 +77,7 @@ __device__ __forceinline__ bool store_same_row_differ(const StoreSource &s, uint
 // empty token's signature is sig[q] = q.  One wave; both vectors are staged in the wave's LDS
 // buffers la, lb (kWalkStoreMaxStride entries each).  Returns whether any entry differs
 // (wave-uniform).  `part` of `parts`: the wave looks only at every parts-th stretch of 512 states,
-// starting with stretch `part` (several waves then share one pair; S a multiple of 8 only).
+// starting with stretch `part` (several waves then share one pair; S >= 8 only).
 __device__ __forceinline__ bool store_other_row_differ(const StoreSource &s, uint32_t stride, int32_t ta, int32_t tb,
                                                        uint32_t ra, uint32_t rb, uint16_t *la,
                                                        uint16_t *lb, int part = 0, int parts = 1) {
@@ -93,15 +93,15 @@ __device__ __forceinline__ bool store_other_row_differ(const StoreSource &s, uin
     // 16 bytes of each index row per lane and step (the identity row is not read); the first are asked for together
     // with the vectors
     constexpr int kAhead = 2;
-    const bool vec = (S % 8) == 0;
-    uint4 xa[kAhead], xb[kAhead];
+    const bool vec = S >= 8;
+    u32x4_any xa[kAhead], xb[kAhead];
     auto fetch = [&](int q0) {
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
-            const int q = min(q0 + 512 * parts * u, S - 8);  // repeats the last ones past the end
-            xa[u] = xb[u] = make_uint4(0, 0, 0, 0);
-            if (!ida) xa[u] = *reinterpret_cast<const uint4 *>(ia + q);
-            if (!idb) xb[u] = *reinterpret_cast<const uint4 *>(ib + q);
+            const int q = min(q0 + 512 * parts * u, S - 8);  // the last eight where fewer are left
+            xa[u] = xb[u] = u32x4_any{0u, 0u, 0u, 0u};
+            if (!ida) xa[u] = *reinterpret_cast<const u32x4_any *>(ia + q);
+            if (!idb) xb[u] = *reinterpret_cast<const u32x4_any *>(ib + q);
         }
     };
     const int first = lane * 8 + 512 * part;
@@ -126,8 +126,8 @@ __device__ __forceinline__ bool store_other_row_differ(const StoreSource &s, uin
             if (q0 != first) fetch(q0);
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
-                const int q = q0 + 512 * parts * u;
-                if (q >= S) continue;
+                if (q0 + 512 * parts * u >= S) continue;
+                const int q = min(q0 + 512 * parts * u, S - 8);
                 const uint32_t ja[8] = {xa[u].x & 0xFFFFu, xa[u].x >> 16, xa[u].y & 0xFFFFu, xa[u].y >> 16,
                                         xa[u].z & 0xFFFFu, xa[u].z >> 16, xa[u].w & 0xFFFFu, xa[u].w >> 16};
                 const uint32_t jb[8] = {xb[u].x & 0xFFFFu, xb[u].x >> 16, xb[u].y & 0xFFFFu, xb[u].y >> 16,

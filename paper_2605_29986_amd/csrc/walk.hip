@@ -25,10 +25,6 @@
 namespace cfgzip {
 namespace {
 
-// native 16-byte vector (the nontemporal builtins do not take HIP's uint4 struct)
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-// the same at any even address
-typedef uint32_t u32x4_pad __attribute__((ext_vector_type(4), aligned(2)));
 
 // threads per workgroup and tokens per chunk
 constexpr int kWalkThreads = 256;
@@ -115,7 +111,7 @@ __global__ __launch_bounds__(1024) void tables_kernel(const uint16_t *__restrict
             present[w] = lo + 32 <= S ? 0xFFFFFFFFu : (lo < S ? (1u << (S - lo)) - 1u : 0u);
         }
         uint16_t *pad = Tt + (size_t)256 * S;
-        for (int i = tid; i < kTablePad / 8; i += 1024) reinterpret_cast<u32x4_pad *>(pad)[i] = u32x4_pad{0u, 0u, 0u, 0u};
+        for (int i = tid; i < kTablePad / 8; i += 1024) reinterpret_cast<u32x4_any *>(pad)[i] = u32x4_any{0u, 0u, 0u, 0u};
         if (store && tid == 0) {
             store->magic = kWalkStoreMagic;
             store->V = V;
@@ -205,7 +201,6 @@ __global__ __launch_bounds__(kWalkThreads) void signatures_kernel(WalkArgs a) {
     uint16_t *w = a.sig_out ? dyn_lds : nullptr;
     const int lane = threadIdx.x & 63;
     const bool first_wave = threadIdx.x < 64;
-    const bool vec = (S % 8) == 0 && (reinterpret_cast<uintptr_t>(a.sig_out) % 16) == 0;
 
     const int64_t n_chunks = ((int64_t)a.V + a.chunk_tokens - 1) / a.chunk_tokens;
     for (int64_t chunk = blockIdx.x; chunk < n_chunks; chunk += gridDim.x) {
@@ -265,24 +260,26 @@ __global__ __launch_bounds__(kWalkThreads) void signatures_kernel(WalkArgs a) {
             }
             if (a.sig_out) {
                 // sig[t][q] = w[idx[row][q]]
-                if (vec) {
-                    // four 16-byte pieces per thread at a time: their index reads are in flight together
-                    const uint32_t s8 = (uint32_t)S / 8;
+                if (S >= 8) {
+                    // four 16-byte pieces per thread at a time: their index reads are in flight together.  A row's last
+                    // piece ends with the row, if need be over part of the one before (60,000 tokens x 700 states with
+                    // entries written one by one: a call of 123 us, 81 so)
+                    const uint32_t s8 = ((uint32_t)S + 7) / 8;
                     const uint32_t items = (uint32_t)k * s8;
                     constexpr int kAhead = 4;
                     for (uint32_t x0 = threadIdx.x; x0 < items; x0 += kAhead * blockDim.x) {
-                        uint4 id[kAhead];
+                        u32x4_any id[kAhead];
 #pragma unroll
                         for (int u = 0; u < kAhead; ++u) {
                             const uint32_t x = min(x0 + u * blockDim.x, items - 1);  // repeats the last past the end
-                            const uint32_t m = x / s8, q0 = (x - m * s8) * 8;
-                            id[u] = *reinterpret_cast<const uint4 *>(a.T.idx + (size_t)B.row[m] * S + q0);
+                            const uint32_t m = x / s8, q0 = min((x - m * s8) * 8, (uint32_t)S - 8);
+                            id[u] = *reinterpret_cast<const u32x4_any *>(a.T.idx + (size_t)B.row[m] * S + q0);
                         }
 #pragma unroll
                         for (int u = 0; u < kAhead; ++u) {
                             const uint32_t x = x0 + u * blockDim.x;
                             if (x < items && B.aux[x / s8]) {
-                                const uint32_t m = x / s8, q0 = (x - m * s8) * 8;
+                                const uint32_t m = x / s8, q0 = min((x - m * s8) * 8, (uint32_t)S - 8);
                                 const uint16_t *wm = w + B.wstart[m];
                                 uint4 o;
                                 o.x = (uint32_t)wm[id[u].x & 0xFFFFu] | ((uint32_t)wm[id[u].x >> 16] << 16);
@@ -291,9 +288,9 @@ __global__ __launch_bounds__(kWalkThreads) void signatures_kernel(WalkArgs a) {
                                 o.w = (uint32_t)wm[id[u].w & 0xFFFFu] | ((uint32_t)wm[id[u].w >> 16] << 16);
                                 // written once, not read again by this call: keep it out of the
                                 // caches that hold the table
-                                const u32x4 ov = {o.x, o.y, o.z, o.w};
+                                const u32x4_any ov = {o.x, o.y, o.z, o.w};
                                 __builtin_nontemporal_store(
-                                    ov, reinterpret_cast<u32x4 *>(a.sig_out + (size_t)(tcur + m) * S + q0));
+                                    ov, reinterpret_cast<u32x4_any *>(a.sig_out + (size_t)(tcur + m) * S + q0));
                             }
                         }
                     }

@@ -43,6 +43,13 @@ constexpr int kMinWalkCap = 8192;   // walks (entries of w) held in LDS per batc
 // 4 -> 130 us, 2 -> 130 us, 1 -> 153 us per signature call).
 constexpr int kWalkGroup = 4;
 
+// Sixteen and eight bytes at any even address: global memory takes such accesses at every alignment, so the rows and tables
+// of an automaton with any number of states are read and written like those of one with a multiple of eight (a row of S
+// entries begins at a multiple of 2 S bytes).
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+typedef unsigned long long u64x2_any __attribute__((ext_vector_type(2), aligned(8)));
+
 struct Tables {
     const uint16_t *Tt;
     const int32_t *nimg;
@@ -256,7 +263,6 @@ __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t 
                                                 uint32_t keep_stride, const uint16_t *kept = nullptr) {
     // every table index fits 32 bits: 257 rows of at most 65536 entries
     const uint32_t nt = blockDim.x, k = B.k, gtotal = B.gtotal, Su = (uint32_t)S;
-    const bool vec4 = (S % 4) == 0;
     for (uint32_t g = threadIdx.x; g < gtotal; g += nt) {
         const uint32_t m = (uint32_t)batch_find(B.gstart, (int)k, (int)g);
         const uint32_t j0 = (g - (uint32_t)B.gstart[m]) * kWalkGroup;
@@ -266,14 +272,15 @@ __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t 
         // (a vector longer than what is kept of it cannot be started from)
         const int32_t par = (kept && n <= keep_stride) ? B.parent[m] : -1;
         const uint32_t skip = par >= 0 ? (uint32_t)B.skip[m] : 1u;
-        // A group's four start states (and its four hash multipliers) lie next to each other: with
-        // S a multiple of 4 they are 8-byte (32-byte) aligned and come in one (two) loads.
+        // A group's four start states (and its four hash multipliers) lie next to each other and come in one (two)
+        // loads; only at the end of a row one by one.
+        const bool whole = j0 + kWalkGroup <= Su;
         static_assert(kWalkGroup == 4, "the vector forms below are written for groups of four");
         if (par >= 0) {  // the prefix's end states are this token's start states
             const uint2 v = *reinterpret_cast<const uint2 *>(kept + (size_t)par * keep_stride + j0);
             cur[0] = v.x & 0xFFFFu, cur[1] = v.x >> 16, cur[2] = v.y & 0xFFFFu, cur[3] = v.y >> 16;
-        } else if (vec4) {
-            const uint2 v = *reinterpret_cast<const uint2 *>(T.img + e0);
+        } else if (whole) {
+            const u32x2_any v = *reinterpret_cast<const u32x2_any *>(T.img + e0);
             cur[0] = v.x & 0xFFFFu, cur[1] = v.x >> 16, cur[2] = v.y & 0xFFFFu, cur[3] = v.y >> 16;
         } else {
 #pragma unroll
@@ -285,11 +292,10 @@ __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t 
         // the hash multipliers are asked for now and used after the walk: off the critical path
         uint64_t mult[kWalkGroup];
         if (HASH) {
-            if (vec4) {
-                const uint4 lo = *reinterpret_cast<const uint4 *>(T.wsum + e0);
-                const uint4 hi = *reinterpret_cast<const uint4 *>(T.wsum + e0 + 2);
-                mult[0] = lo.x | ((uint64_t)lo.y << 32), mult[1] = lo.z | ((uint64_t)lo.w << 32);
-                mult[2] = hi.x | ((uint64_t)hi.y << 32), mult[3] = hi.z | ((uint64_t)hi.w << 32);
+            if (whole) {
+                const u64x2_any lo = *reinterpret_cast<const u64x2_any *>(T.wsum + e0);
+                const u64x2_any hi = *reinterpret_cast<const u64x2_any *>(T.wsum + e0 + 2);
+                mult[0] = lo.x, mult[1] = lo.y, mult[2] = hi.x, mult[3] = hi.y;
             } else {
 #pragma unroll
                 for (int u = 0; u < kWalkGroup; ++u) mult[u] = j0 + u < n ? T.wsum[e0 + u] : 0ull;

@@ -226,3 +226,42 @@ def test_hashes_that_fall_into_one_bucket(lib, V, classes):
                                              dev(_hashes_of_one_bucket(classes)[cls]))
     assert C == classes == len(want_r) and coll == 0
     assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
+
+
+@pytest.mark.parametrize("S", [1, 2, 7, 8, 9, 12, 15, 17, 63, 130, 511, 513, 1021])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_rows_of_any_length_at_any_address(lib, S, shift):
+    """Rows of S entries begin at every even address, and so does the buffer: the signatures (nothing written outside
+    them), and the classes from the kept vectors and from the rows, where one entry of a row is changed as well."""
+    from gpu_util import hash_np, vocab_dev
+    print(f"case S={S} shift={shift}", flush=True)
+    rng = np.random.default_rng(S)
+    table = rng.integers(0, S, size=(S, 256)).astype(np.uint16)
+    table[:, 97:110] = rng.integers(0, S, size=13).astype(np.uint16)  # images of one state
+    vocab = vocab_from_tokens([rng.integers(90, 120, size=int(k), dtype=np.uint8).tobytes()
+                               for k in rng.integers(0, 5, size=301)])
+    V = vocab.V
+    tb, to, tt = vocab_dev(vocab, table)
+    buf = torch.full((V * S + 24,), 0x5A5A, dtype=torch.int16, device="cuda")
+    sig = buf[8 + shift:8 + shift + V * S].view(torch.uint16).view(V, S)
+    ws = torch.empty(lib.load_library().cfgzip_signatures_workspace_bytes(V, S), dtype=torch.uint8, device="cuda")
+    _, h = lib.cfgzip_signatures(tb, to, tt, sig_out=sig, workspace=ws)
+    want_sig = oracle.signatures(vocab.tok_bytes, vocab.tok_off, table)
+    assert (sig.cpu().numpy() == want_sig).all()
+    assert (hash_np(h) == oracle.signature_hash(want_sig, lib.DEFAULT_HASH_SEED)).all()
+    assert bool((buf[:8 + shift] == 0x5A5A).all()) and bool((buf[8 + shift + V * S:] == 0x5A5A).all())
+    want_c, want_r = oracle.build_classes(want_sig, vocab.tok_off)
+    for rows, store in ((None, ws), (sig, None)):
+        c, r, C, coll = lib.cfgzip_build_classes(tb, to, tt, rows, h, signatures_workspace=store)
+        assert C == len(want_r) and coll == 0
+        assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
+    # one entry of a row of a class with several members: the hash still says they are equal, the rows do not
+    members = np.nonzero(np.bincount(want_c)[want_c] > 1)[0]
+    t, q = int(members[-1]), S - 1
+    buf[8 + shift + t * S + q] ^= 0x4000  # (no row has that already: equal rows have equal hashes)
+    changed = want_sig.copy()
+    changed[t, q] ^= 0x4000
+    want_c, want_r = oracle.build_classes(changed, vocab.tok_off)
+    c, r, C, coll = lib.cfgzip_build_classes(tb, to, None, sig, h)
+    assert C == len(want_r) and coll > 0
+    assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
