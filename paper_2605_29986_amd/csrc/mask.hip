@@ -80,7 +80,11 @@ __device__ __forceinline__ uint32_t select_bf16_pair(uint32_t x, uint32_t two_bi
 // LOGITS: which logits to mask (none = mask expansion only).
 // FROM_CLASS: bits_in is a class-level mask gathered through class_of_token.
 // WRITE_BITS: also store the token-level mask.
-template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS>
+// ENGINE: the rows' class masks are those of the automaton states (cfgzip_engine_step).  The way there (state, token, class,
+// signature entry, class mask, LDS) is five dependent accesses, so a thread asks for its class ids and all of its rows
+// before it (512 states, bf16 logits of 128,256 columns: batch 64 7.7 -> 7.2 us, 128 13.9 -> 11.7, 256 24.3 -> 23.6).
+// Where the masks are given (two accesses) that gains nothing: batch 64 8.0 us either way, fp32 15.3 and 15.7.
+template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS, bool ENGINE>
 __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) {
 
     const int ct = blockIdx.x % a.col_tiles;
@@ -88,11 +92,28 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
     const int r0 = rc * a.rows_per_block;
     const int nrows = min(a.rows_per_block, a.B - r0);
     const int col0 = (ct * kThreads + (int)threadIdx.x) * kCols;
+    const int nvalid = min(kCols, max(0, a.V - col0));
+    const uint32_t valid_mask = (1u << nvalid) - 1u;
+    const bool full = nvalid == kCols;
+
+    i32x4_any ids[2];
+    constexpr int kPieces = LOGITS == LOGITS_F32 ? 2 : 1;  // 16-byte pieces of a thread's eight logits
+    u32x4 rows[ENGINE ? kRowsStream : 1][kPieces];
+    if (ENGINE && full) {
+        ids[0] = reinterpret_cast<const i32x4_any *>(a.class_of_token + col0)[0];
+        ids[1] = reinterpret_cast<const i32x4_any *>(a.class_of_token + col0)[1];
+        const char *at = reinterpret_cast<const char *>(a.logits) + ((int64_t)r0 * a.row_stride + col0) * (2 * kPieces);
+#pragma unroll
+        for (int u = 0; u < kRowsStream; ++u)
+            if (u < nrows)
+#pragma unroll
+                for (int k = 0; k < kPieces; ++k) rows[u][k] = load16(at + (int64_t)u * a.row_stride * (2 * kPieces) + 16 * k);
+    }
 
     if (FROM_CLASS) {
         const int n = nrows * a.Wc;
-        if (a.state_mask) {
-            // engine step: advance the rows' automaton states on the representative of the token
+        if (ENGINE) {
+            // advance the rows' automaton states on the representative of the token
             // sampled last, then take each row's class mask from the table of per-state masks
             __shared__ int32_t q_s[kMaxRowsPerBlock];
             if ((int)threadIdx.x < nrows) {
@@ -124,16 +145,12 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
     }
     if (col0 >= a.Wv * 32) return;  // past the padded end of a mask row: nothing to do
 
-    const int nvalid = min(kCols, max(0, a.V - col0));
-    const uint32_t valid_mask = (1u << nvalid) - 1u;
-    const bool full = nvalid == kCols;
-
     uint32_t woff[kCols], shift[kCols];
     if (FROM_CLASS) {
         int32_t k[kCols];
         if (full) {
             const i32x4_any *p = reinterpret_cast<const i32x4_any *>(a.class_of_token + col0);
-            const i32x4_any lo = p[0], hi = p[1];
+            const i32x4_any lo = ENGINE ? ids[0] : p[0], hi = ENGINE ? ids[1] : p[1];
             k[0] = lo.x; k[1] = lo.y; k[2] = lo.z; k[3] = lo.w;
             k[4] = hi.x; k[5] = hi.y; k[6] = hi.z; k[7] = hi.w;
         } else {
@@ -183,6 +200,16 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
                 y.w = select_bf16_pair(x.w, (m >> 6) & 3u);
                 return y;
             };
+            if (ENGINE) {
+#pragma unroll
+                for (int u = 0; u < kRowsStream; ++u) {
+                    if (u >= nrows) break;
+                    const uint32_t m = row_mask(u);
+                    store16(base + (int64_t)u * a.row_stride, masked(rows[ENGINE ? u : 0][0], m));
+                    store_bits(u, m);
+                }
+                return;
+            }
             int r = 0;
             for (; r + kUnroll <= nrows; r += kUnroll) {
                 u32x4 x[kUnroll];
@@ -204,6 +231,28 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
             uint32_t *base = reinterpret_cast<uint32_t *>(a.logits) + (int64_t)r0 * a.row_stride + col0;
             constexpr uint32_t NINF = 0xFF800000u;
             constexpr int U = 4;  // rows in flight (eight 16-byte loads): measured best of 1, 2, 4
+            auto mask_row = [&](int row, u32x4 lo, u32x4 hi) {
+                const uint32_t m = row_mask(row);
+                lo.x = (m & 1u) ? lo.x : NINF;
+                lo.y = (m & 2u) ? lo.y : NINF;
+                lo.z = (m & 4u) ? lo.z : NINF;
+                lo.w = (m & 8u) ? lo.w : NINF;
+                hi.x = (m & 16u) ? hi.x : NINF;
+                hi.y = (m & 32u) ? hi.y : NINF;
+                hi.z = (m & 64u) ? hi.z : NINF;
+                hi.w = (m & 128u) ? hi.w : NINF;
+                store16(base + (int64_t)row * a.row_stride, lo);
+                store16(base + (int64_t)row * a.row_stride + 4, hi);
+                store_bits(row, m);
+            };
+            if (ENGINE) {
+#pragma unroll
+                for (int u = 0; u < kRowsStream; ++u) {
+                    if (u >= nrows) break;
+                    mask_row(u, rows[ENGINE ? u : 0][0], rows[ENGINE ? u : 0][kPieces - 1]);
+                }
+                return;
+            }
             auto do_rows = [&](int r, auto count) {
                 constexpr int N = decltype(count)::value;
                 u32x4 x[N][2];
@@ -213,21 +262,7 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
                     x[u][1] = load16(base + (int64_t)(r + u) * a.row_stride + 4);
                 }
 #pragma unroll
-                for (int u = 0; u < N; ++u) {
-                    const uint32_t m = row_mask(r + u);
-                    u32x4 lo = x[u][0], hi = x[u][1];
-                    lo.x = (m & 1u) ? lo.x : NINF;
-                    lo.y = (m & 2u) ? lo.y : NINF;
-                    lo.z = (m & 4u) ? lo.z : NINF;
-                    lo.w = (m & 8u) ? lo.w : NINF;
-                    hi.x = (m & 16u) ? hi.x : NINF;
-                    hi.y = (m & 32u) ? hi.y : NINF;
-                    hi.z = (m & 64u) ? hi.z : NINF;
-                    hi.w = (m & 128u) ? hi.w : NINF;
-                    store16(base + (int64_t)(r + u) * a.row_stride, lo);
-                    store16(base + (int64_t)(r + u) * a.row_stride + 4, hi);
-                    store_bits(r + u, m);
-                }
+                for (int u = 0; u < N; ++u) mask_row(r + u, x[u][0], x[u][1]);
             };
             int r = 0;
             for (; r + U <= nrows; r += U) do_rows(r, std::integral_constant<int, U>{});
@@ -261,10 +296,10 @@ __device__ __forceinline__ int32_t representative_of(int32_t t, const int32_t *c
     return (k >= 0 && k < C) ? rep_of_class[k] : -1;
 }
 
-template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS>
+template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS, bool ENGINE>
 __global__ __launch_bounds__(kThreads) void mask_kernel(MaskArgs a) {
     extern __shared__ uint32_t cls_lds[];  // [rows_per_block][Wc] when FROM_CLASS
-    mask_tile<LOGITS, FROM_CLASS, WRITE_BITS>(a, cls_lds);
+    mask_tile<LOGITS, FROM_CLASS, WRITE_BITS, ENGINE>(a, cls_lds);
     // The first workgroup is the first to be scheduled and to finish its rows; the B dependent
     // look-ups then overlap with the streaming of all the others.
     if (a.map_tok && blockIdx.x == 0)
@@ -281,9 +316,9 @@ __global__ void map_to_rep_kernel(const int32_t *tok, int32_t B, const int32_t *
 
 constexpr size_t kMaxLds = 160 * 1024;
 
-template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS>
+template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS, bool ENGINE>
 int launch_mask(const MaskArgs &args, int grid, size_t lds_bytes, hipStream_t stream) {
-    auto kern = mask_kernel<LOGITS, FROM_CLASS, WRITE_BITS>;
+    auto kern = mask_kernel<LOGITS, FROM_CLASS, WRITE_BITS, ENGINE>;
     if (lds_bytes > 64 * 1024) {
         CFGZIP_TRY(check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -295,9 +330,14 @@ int launch_mask(const MaskArgs &args, int grid, size_t lds_bytes, hipStream_t st
 
 template <int LOGITS, bool FROM_CLASS>
 int dispatch_mask(const MaskArgs &args, bool write_bits, int grid, size_t lds, hipStream_t stream) {
-    if (write_bits) return launch_mask<LOGITS, FROM_CLASS, true>(args, grid, lds, stream);
-    if (LOGITS == LOGITS_NONE) return CFGZIP_E_INVALID;  // nothing to do
-    return launch_mask<LOGITS, FROM_CLASS, false>(args, grid, lds, stream);
+    if constexpr (LOGITS != LOGITS_NONE && FROM_CLASS) {
+        if (args.state_mask)
+            return write_bits ? launch_mask<LOGITS, FROM_CLASS, true, true>(args, grid, lds, stream)
+                              : launch_mask<LOGITS, FROM_CLASS, false, true>(args, grid, lds, stream);
+    }
+    if (write_bits) return launch_mask<LOGITS, FROM_CLASS, true, false>(args, grid, lds, stream);
+    if constexpr (LOGITS == LOGITS_NONE) return CFGZIP_E_INVALID;  // nothing to do
+    else return launch_mask<LOGITS, FROM_CLASS, false, false>(args, grid, lds, stream);
 }
 
 // Shared host path of cfgzip_expand_mask and cfgzip_apply_mask.
