@@ -191,6 +191,7 @@ __global__ __launch_bounds__(1024) void tables_kernel(const uint16_t *__restrict
         for (uint32_t r = tid; r < n && r < kAccCap; r += 1024) wsum[(size_t)b * S + r] = acc[r];
 }
 
+template <bool SPREAD>
 __global__ __launch_bounds__(kWalkThreads) void signatures_kernel(WalkArgs a) {
     extern __shared__ __align__(16) uint16_t dyn_lds[];  // w: wcap entries when rows are expanded from it, else nothing
     __shared__ Batch B;
@@ -246,8 +247,8 @@ __global__ __launch_bounds__(kWalkThreads) void signatures_kernel(WalkArgs a) {
             uint16_t *keep = a.store.header ? a.store.wvec + (size_t)tcur * stride : nullptr;
             // launch 2 of a composed call: slots with a parent start from its kept vector
             const uint16_t *kept = (a.phase == 2 && a.parent && a.store.header) ? a.store.wvec : nullptr;
-            if (a.hash_out) batch_walk<true>(a.T, tab, S, a.tok_bytes, B, ldsb, w, keep, stride, kept);
-            else batch_walk<false>(a.T, tab, S, a.tok_bytes, B, ldsb, w, keep, stride, kept);
+            if (a.hash_out) batch_walk<true, SPREAD>(a.T, tab, S, a.tok_bytes, B, ldsb, w, keep, stride, kept);
+            else batch_walk<false, SPREAD>(a.T, tab, S, a.tok_bytes, B, ldsb, w, keep, stride, kept);
             __syncthreads();
             if (a.hash_out && (int)threadIdx.x < k && B.aux[threadIdx.x])
                 a.hash_out[tcur + threadIdx.x] = B.hash[threadIdx.x];
@@ -507,15 +508,16 @@ int run_signatures(const uint8_t *tok_bytes, const int64_t *tok_off, int32_t V, 
     a.wcap = std::max(kMinWalkCap, (S + kWalkGroup - 1) / kWalkGroup * kWalkGroup);
     const size_t dyn = sig_out ? (size_t)a.wcap * 2 : 0;
     if (!sig_out) a.wcap = 0x3FFFFFFF;  // no LDS buffer bounds a batch's walks
+    auto kern = S >= kSpreadStates ? signatures_kernel<true> : signatures_kernel<false>;
     if (dyn > 48 * 1024)
-        CFGZIP_TRY(check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(signatures_kernel),
+        CFGZIP_TRY(check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn)));
     // one workgroup per chunk: the hardware hands out chunks as workgroups retire, which
     // balances chunks of very different cost
     const int64_t grid = std::min<int64_t>(n_chunks, 0x7FFFFFFF);
     for (int phase = compose_ws ? 1 : 0; phase <= (compose_ws ? 2 : 0); ++phase) {
         a.phase = phase;
-        hipLaunchKernelGGL(signatures_kernel, dim3((unsigned)grid), dim3(kWalkThreads), dyn, stream, a);
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kWalkThreads), dyn, stream, a);
         CFGZIP_TRY(check_launch());
     }
     return CFGZIP_OK;

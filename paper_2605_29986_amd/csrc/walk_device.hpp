@@ -256,7 +256,14 @@ __device__ __forceinline__ void batch_stage_bytes(const Batch &B, const uint8_t 
 // kWalkGroup; a vector longer than that is not kept).
 // `kept` (or null): kept walk vectors of finished tokens, kept_stride entries apart, from which
 // the slots with a parent start.
-template <bool LDS_BYTES, bool HASH>
+// SPREAD: the walks of a group are not neighbours but lie as far apart as the token has groups, so that the lanes of a wave
+// read, at a time, the successors of neighbouring states: with kSpreadStates states and more a column is 48 lines of
+// memory or more, a read of 26 states a fourth apart touches about as many, of 26 neighbours a third of that, and the
+// lines are what the L1 cache takes one by one.  151,936 tokens x 4,096 states 95.6 -> 88.9 us, 128,256 x 3,500 74.3 and
+// 73.9; but states, multipliers and end states then move one by one (2,500 states 45.6 and 45.9, 1,024 with rows 76.0 and
+// 77.3, 512 29.3 and 31.7).
+constexpr int kSpreadStates = 3072;
+template <bool LDS_BYTES, bool HASH, bool SPREAD>
 __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t *tab, int S,
                                                 const uint8_t *__restrict__ tok_bytes, Batch &B,
                                                 const uint8_t *ldsb, uint16_t *w, uint16_t *keep,
@@ -265,7 +272,9 @@ __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t 
     const uint32_t nt = blockDim.x, k = B.k, gtotal = B.gtotal, Su = (uint32_t)S;
     for (uint32_t g = threadIdx.x; g < gtotal; g += nt) {
         const uint32_t m = (uint32_t)batch_find(B.gstart, (int)k, (int)g);
-        const uint32_t j0 = (g - (uint32_t)B.gstart[m]) * kWalkGroup;
+        // walk u of the group is walk j0 + u * apart of the token
+        const uint32_t apart = SPREAD ? (uint32_t)B.gstart[m + 1] - (uint32_t)B.gstart[m] : 1u;
+        const uint32_t j0 = (g - (uint32_t)B.gstart[m]) * (SPREAD ? 1u : (uint32_t)kWalkGroup);
         const uint32_t n = (uint32_t)B.cnt[m];
         const uint32_t e0 = (uint32_t)B.row[m] * Su + j0;
         uint32_t cur[kWalkGroup];
@@ -274,9 +283,13 @@ __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t 
         const uint32_t skip = par >= 0 ? (uint32_t)B.skip[m] : 1u;
         // A group's four start states (and its four hash multipliers) lie next to each other and come in one (two)
         // loads; only at the end of a row one by one.
-        const bool whole = j0 + kWalkGroup <= Su;
+        const bool whole = !SPREAD && j0 + kWalkGroup <= Su;
         static_assert(kWalkGroup == 4, "the vector forms below are written for groups of four");
-        if (par >= 0) {  // the prefix's end states are this token's start states
+        if (SPREAD) {
+            const uint16_t *from = par >= 0 ? kept + (size_t)par * keep_stride + j0 : T.img + e0;
+#pragma unroll
+            for (int u = 0; u < kWalkGroup; ++u) cur[u] = j0 + u * apart < n ? (uint32_t)from[u * apart] : 0u;
+        } else if (par >= 0) {  // the prefix's end states are this token's start states
             const uint2 v = *reinterpret_cast<const uint2 *>(kept + (size_t)par * keep_stride + j0);
             cur[0] = v.x & 0xFFFFu, cur[1] = v.x >> 16, cur[2] = v.y & 0xFFFFu, cur[3] = v.y >> 16;
         } else if (whole) {
@@ -288,7 +301,7 @@ __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t 
         }
 #pragma unroll
         for (int u = 0; u < kWalkGroup; ++u)
-            if (j0 + u >= n) cur[u] = 0u;  // padding of the token's last group
+            if (j0 + u * apart >= n) cur[u] = 0u;  // padding behind the token's walks
         // the hash multipliers are asked for now and used after the walk: off the critical path
         uint64_t mult[kWalkGroup];
         if (HASH) {
@@ -298,7 +311,7 @@ __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t 
                 mult[0] = lo.x, mult[1] = lo.y, mult[2] = hi.x, mult[3] = hi.y;
             } else {
 #pragma unroll
-                for (int u = 0; u < kWalkGroup; ++u) mult[u] = j0 + u < n ? T.wsum[e0 + u] : 0ull;
+                for (int u = 0; u < kWalkGroup; ++u) mult[u] = j0 + u * apart < n ? T.wsum[e0 + u * apart] : 0ull;
             }
         }
         const uint32_t rem = B.len[m] > 0 ? (uint32_t)B.len[m] - skip : 0u;
@@ -316,32 +329,40 @@ __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t 
         uint64_t term = 0;
 #pragma unroll
         for (int u = 0; u < kWalkGroup; ++u) {
-            if (j0 + u >= n) cur[u] = 0;  // padding
+            if (j0 + u * apart >= n) cur[u] = 0;  // padding
             else if (HASH) term += mult[u] * (uint64_t)cur[u];
         }
-        // the four end states as one 8-byte store each way (both regions are 8-byte aligned: a slot's
-        // region in w starts at a multiple of the group size, a kept vector at a multiple of 8 entries)
-        const uint2 packed = make_uint2(cur[0] | (cur[1] << 16), cur[2] | (cur[3] << 16));
-        if (w) *reinterpret_cast<uint2 *>(w + (uint32_t)B.wstart[m] + j0) = packed;  // null: only hash and `keep` are wanted
-        if (keep && n <= keep_stride) {  // (a vector that does not fit makes the store unusable: nothing of it is kept)
-            uint16_t *kd = keep + (size_t)m * keep_stride + j0;
-            *reinterpret_cast<uint2 *>(kd) = packed;
-            // a kept vector is compared 8 entries at a time: the token's last group also zeroes
-            // what lies between its own end and the next multiple of 8 (keep_stride is one)
-            if (j0 + kWalkGroup >= n && j0 + kWalkGroup < ((n + 7u) & ~7u) && j0 + kWalkGroup < keep_stride)
-                *reinterpret_cast<uint2 *>(kd + kWalkGroup) = make_uint2(0u, 0u);
+        uint16_t *kd = keep && n <= keep_stride ? keep + (size_t)m * keep_stride : nullptr;  // (a vector that does not fit
+                                                                                             // makes the store unusable)
+        const uint32_t padded = ((uint32_t)B.gstart[m + 1] - (uint32_t)B.gstart[m]) * kWalkGroup;
+        if (SPREAD) {
+#pragma unroll
+            for (int u = 0; u < kWalkGroup; ++u) {
+                if (w) w[(uint32_t)B.wstart[m] + j0 + u * apart] = (uint16_t)cur[u];  // null: only hash and `keep` are wanted
+                if (kd) kd[j0 + u * apart] = (uint16_t)cur[u];
+            }
+        } else {
+            // the four end states as one 8-byte store each way (both regions are 8-byte aligned: a slot's
+            // region in w starts at a multiple of the group size, a kept vector at a multiple of 8 entries)
+            const uint2 packed = make_uint2(cur[0] | (cur[1] << 16), cur[2] | (cur[3] << 16));
+            if (w) *reinterpret_cast<uint2 *>(w + (uint32_t)B.wstart[m] + j0) = packed;
+            if (kd) *reinterpret_cast<uint2 *>(kd + j0) = packed;
         }
+        // a kept vector is compared 8 entries at a time: the token's last group also zeroes
+        // what lies between its own end and the next multiple of 8 (keep_stride is one)
+        if (kd && g + 1 == (uint32_t)B.gstart[m + 1] && padded < ((n + 7u) & ~7u) && padded < keep_stride)
+            *reinterpret_cast<uint2 *>(kd + padded) = make_uint2(0u, 0u);
         if (HASH) atomicAdd(&B.hash[m], (unsigned long long)term);
     }
 }
 
-template <bool HASH>
+template <bool HASH, bool SPREAD = false>
 __device__ __forceinline__ void batch_walk(const Tables &T, const uint16_t *tab, int S,
                                            const uint8_t *__restrict__ tok_bytes, Batch &B,
                                            const uint8_t *ldsb, uint16_t *w, uint16_t *keep = nullptr,
                                            uint32_t keep_stride = 0, const uint16_t *kept = nullptr) {
-    if (B.bytes_in_lds) batch_walk_impl<true, HASH>(T, tab, S, tok_bytes, B, ldsb, w, keep, keep_stride, kept);
-    else batch_walk_impl<false, HASH>(T, tab, S, tok_bytes, B, ldsb, w, keep, keep_stride, kept);
+    if (B.bytes_in_lds) batch_walk_impl<true, HASH, SPREAD>(T, tab, S, tok_bytes, B, ldsb, w, keep, keep_stride, kept);
+    else batch_walk_impl<false, HASH, SPREAD>(T, tab, S, tok_bytes, B, ldsb, w, keep, keep_stride, kept);
 }
 
 }  // namespace cfgzip

@@ -265,3 +265,33 @@ def test_rows_of_any_length_at_any_address(lib, S, shift):
     c, r, C, coll = lib.cfgzip_build_classes(tb, to, None, sig, h)
     assert C == len(want_r) and coll > 0
     assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
+
+
+@pytest.mark.parametrize("S", [3071, 3072, 3073, 4096])
+@pytest.mark.parametrize("composed", [False, True])
+def test_walks_that_lie_apart(lib, S, composed):
+    """From 3,072 states on a thread's four walks lie as far apart as their token has groups: images of every size
+    around a group and around what is kept, tokens of no bytes to seven, rows, hashes and classes."""
+    from gpu_util import hash_np, vocab_dev
+    print(f"case S={S} composed={composed}", flush=True)
+    rng = np.random.default_rng(S)
+    table = np.zeros((S, 256), np.uint16)
+    sizes = [1, 2, 3, 4, 5, 6, 7, 8, 9, 15, 16, 17, 63, 511, 512]
+    for b, n in enumerate(sizes):
+        table[:, b] = rng.permutation(S)[:n][rng.integers(0, n, size=S)]
+    vocab = vocab_from_tokens([rng.integers(0, len(sizes), size=int(k), dtype=np.uint8).tobytes()
+                               for k in rng.integers(0, 8, size=403)])
+    tb, to, tt = vocab_dev(vocab, table)
+    raw = lib.load_library()
+    query = raw.cfgzip_signatures_composed_workspace_bytes if composed else raw.cfgzip_signatures_workspace_bytes
+    ws = torch.empty(query(vocab.V, S), dtype=torch.uint8, device="cuda")
+    sig, h = lib.cfgzip_signatures(tb, to, tt, workspace=ws, composed=composed)
+    want_sig = oracle.signatures(vocab.tok_bytes, vocab.tok_off, table)
+    assert (sig.cpu().numpy() == want_sig).all()
+    assert (hash_np(h) == oracle.signature_hash(want_sig, lib.DEFAULT_HASH_SEED)).all()
+    want_c, want_r = oracle.build_classes(want_sig, vocab.tok_off)
+    _, h = lib.cfgzip_signatures(tb, to, tt, want_sig=False, workspace=ws, composed=composed)
+    for rows in (None, sig):
+        c, r, C, coll = lib.cfgzip_build_classes(tb, to, tt, rows, h, signatures_workspace=ws)
+        assert C == len(want_r) and coll == 0
+        assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
