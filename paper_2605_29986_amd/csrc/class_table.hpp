@@ -504,8 +504,9 @@ __device__ __forceinline__ void table_number(const TableSettleArgs &a, unsigned 
 constexpr uint32_t kRowPart = 64;  // 16-byte units of a row that a wave compares
 __host__ __device__ inline int64_t table_row_parts(int32_t S) { return (S + 8 * (int)kRowPart - 1) / (8 * (int)kRowPart); }
 
-// STORE: the comparisons read the walk store, otherwise rows.
-template <bool STORE>
+// STORE: the comparisons read the walk store, otherwise rows.  UNITS: rows of whole 16-byte units at multiples of that (an
+// instance of its own: 128,256 rows of 2 KB 39.5 us; at any address 42, and with both in one kernel's registers 49).
+template <bool STORE, bool UNITS>
 __global__ __launch_bounds__(kTableThreads) void table_settle_kernel(TableSettleArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];  // table_rank_bytes, or the waves' staged vectors
     if ((int)blockIdx.x < a.number_blocks) {
@@ -597,7 +598,7 @@ __global__ __launch_bounds__(kTableThreads) void table_settle_kernel(TableSettle
             // four rows per wave against their classes' members' rows, which many share (they stay in the caches); what
             // there is to read is every row once.  Of rows of more than kRowPart units a wave takes a part: waves that
             // read whole rows of 8 KB all ask the same memory channels at a time (262 MB in rows of 8 KB: 60 us, 49 us so)
-            const bool vec = a.S >= 8;
+            const bool vec = UNITS || a.S >= 8;
             const uint32_t s8 = ((uint32_t)a.S + 7u) / 8u;
             const int64_t parts = vec ? table_row_parts(a.S) : 1, items = ((int64_t)a.n + 3) / 4 * parts;
             for (int64_t x = gw; x < items; x += waves) {
@@ -615,16 +616,22 @@ __global__ __launch_bounds__(kTableThreads) void table_settle_kernel(TableSettle
                     const uint32_t from = (uint32_t)(x % parts) * kRowPart, to = min(s8, from + kRowPart);
                     for (uint32_t j = from + lane; j < to; j += 64) {
                         u32x4_any p[4], q[4];
-                        const uint16_t *eight = a.sig + min(8u * j, (uint32_t)a.S - 8u);  // the last eight where fewer are left
+                        auto piece = [&](uint32_t tok) -> u32x4_any {  // of a token's row
+                            if (UNITS) {
+                                const uint4 v = reinterpret_cast<const uint4 *>(a.sig)[tok * s8 + j];  // (31 bits)
+                                return u32x4_any{v.x, v.y, v.z, v.w};
+                            }
+                            const uint16_t *row = a.sig + (size_t)tok * a.S;
+                            return *reinterpret_cast<const u32x4_any *>(row + min(8u * j, (uint32_t)a.S - 8u));
+                        };
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
-                            p[u] = *reinterpret_cast<const u32x4_any *>(eight + (size_t)t[u] * a.S);
-                            q[u] = *reinterpret_cast<const u32x4_any *>(eight + (size_t)ref[u] * a.S);
+                            p[u] = piece((uint32_t)t[u]);
+                            q[u] = piece((uint32_t)ref[u]);
                         }
 #pragma unroll
                         for (int u = 0; u < 4; ++u)
-                            differs |= (p[u].x != q[u].x) | (p[u].y != q[u].y) | (p[u].z != q[u].z) |
-                                       (p[u].w != q[u].w);
+                            differs |= (p[u].x != q[u].x) | (p[u].y != q[u].y) | (p[u].z != q[u].z) | (p[u].w != q[u].w);
                     }
                 } else {
                     for (int j = lane; j < a.S; j += 64)
