@@ -1,4 +1,5 @@
-"""ctypes binding of libcfgzip.so.  Argument marshalling only.
+"""Binding of libcfgzip.so: ctypes, and an extension for the two calls of every decode step.
+Argument marshalling only.
 
 Tensors are torch CUDA (ROCm) tensors; they supply device memory and the HIP
 stream.  Function names and argument order follow ``include/cfgzip.h``.

@@ -1,4 +1,4 @@
-"""Builds libcfgzip.so (hand-written HIP for gfx950) in-tree with hipcc."""
+"""Builds libcfgzip.so (hand-written HIP for gfx950) with hipcc and the binding's extension with g++, in-tree."""
 
 from __future__ import annotations
 
