@@ -11,6 +11,8 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import sys
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -19,7 +21,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "lib", "libcfgzip.so")
 _lib: Optional[ctypes.CDLL] = None
 _STEPCALL_PATH = os.path.join(_HERE, "lib", "cfgzip_stepcall.so")
-# the two per-step calls without ctypes, set when the library is loaded
+# the two per-step calls without ctypes, set when the library is loaded; they answer None where a call has to go
+# through ctypes
 _decode_step = None
 _engine_step = None
 
@@ -51,15 +54,41 @@ def library_path() -> str:
     return _LIB_PATH
 
 
+def stepcall_path() -> str:
+    return _STEPCALL_PATH
+
+
+def _by_ctypes(*_args) -> None:
+    return None
+
+
+def _load_stepcall(lib: ctypes.CDLL):
+    """The per-step calls of the extension.  They save host time and nothing else: every call goes through ctypes as
+    well, so an extension that is not there, or was built for another torch or Python, is done without."""
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("cfgzip_stepcall", _STEPCALL_PATH)
+        spec = importlib.util.spec_from_file_location("cfgzip_stepcall", _STEPCALL_PATH, loader=loader)
+        stepcall = importlib.util.module_from_spec(spec)
+        loader.exec_module(stepcall)
+        if (stepcall.python, stepcall.torch) != ("%d.%d" % sys.version_info[:2], str(torch.__version__)):
+            raise ImportError(f"it was built for Python {stepcall.python} and torch {stepcall.torch}")
+    except (ImportError, OSError, SystemError, AttributeError) as e:
+        warnings.warn(f"{_STEPCALL_PATH} cannot be used ({e}); cfgzip_decode_step and cfgzip_engine_step are called "
+                      "through ctypes, which takes about 5 us more a step. "
+                      "`python -m paper_2605_29986_amd.build` builds it.", RuntimeWarning, stacklevel=3)
+        return _by_ctypes, _by_ctypes
+    stepcall.connect(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.cfgzip_decode_step, lib.cfgzip_engine_step)))
+    return stepcall.decode_step, stepcall.engine_step
+
+
 def load_library() -> ctypes.CDLL:
     """Loads the built HIP library; raises if it has not been built (there is no fallback)."""
     global _lib, _decode_step, _engine_step
     if _lib is not None:
         return _lib
-    missing = [p for p in (_LIB_PATH, _STEPCALL_PATH) if not os.path.exists(p)]
-    if missing:
+    if not os.path.exists(_LIB_PATH):
         raise RuntimeError(
-            f"{missing[0]} is missing: build it with `python -m paper_2605_29986_amd.build` "
+            f"{_LIB_PATH} is missing: build it with `python -m paper_2605_29986_amd.build` "
             "(hipcc, gfx950). The CFGzip path has no CPU fallback.")
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i32, i64, u64, sz = (ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint64,
@@ -113,12 +142,7 @@ def load_library() -> ctypes.CDLL:
     lib.cfgzip_displacements.restype = ctypes.c_int
     lib.cfgzip_displacements.argtypes = [vp, vp, i32, vp, vp, vp, vp, i32, i32, i32, vp, i32, vp, vp, u64,
                                          vp, sz, vp]
-    loader = importlib.machinery.ExtensionFileLoader("cfgzip_stepcall", _STEPCALL_PATH)
-    spec = importlib.util.spec_from_file_location("cfgzip_stepcall", _STEPCALL_PATH, loader=loader)
-    stepcall = importlib.util.module_from_spec(spec)
-    loader.exec_module(stepcall)
-    stepcall.connect(ctypes.cast(lib.cfgzip_decode_step, vp).value, ctypes.cast(lib.cfgzip_engine_step, vp).value)
-    _decode_step, _engine_step = stepcall.decode_step, stepcall.engine_step
+    _decode_step, _engine_step = _load_stepcall(lib)
     _lib = lib
     return lib
 

@@ -44,7 +44,8 @@ def build_stepcall(verbose: bool = False) -> str:
     tmp = STEPCALL_PATH + ".tmp.%d" % os.getpid()
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
-           "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-DUSE_ROCM=1", "-DBUILT_FOR_TORCH=\"%s\"" % torch.__version__,
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
            "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
            "-isystem", os.path.join(rocm, "include"), "-o", tmp, os.path.join(CSRC, "stepcall.cpp"),
            "-L", os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
@@ -67,7 +68,13 @@ def build(verbose: bool = False) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(tmp, LIB_PATH)
-    build_stepcall(verbose)
+    try:
+        build_stepcall(verbose)
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        # no compiler, headers or torch for it: the binding does without, but not with one that an older source left
+        if os.path.exists(STEPCALL_PATH):
+            os.remove(STEPCALL_PATH)
+        print(f"{STEPCALL_PATH} not built ({e}): the per-step calls go through ctypes", file=sys.stderr, flush=True)
     tool_flags = [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
     tmp = TOOL_PATH + ".tmp.%d" % os.getpid()
     cmd = [find_hipcc(), *tool_flags, "-o", tmp, os.path.join(CSRC, "tools", "gather_rate.hip")]

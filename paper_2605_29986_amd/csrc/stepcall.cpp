@@ -183,4 +183,15 @@ PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "cfgzip_stepcall", nullptr, -1, g
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_cfgzip_stepcall() { return PyModule_Create(&g_module); }
+#define TEXT_OF(x) #x
+#define TEXT(x) TEXT_OF(x)
+// What this was built for, which the binding compares with what it runs in: torch's C++ layouts are those of one version.
+PyMODINIT_FUNC PyInit_cfgzip_stepcall() {
+    PyObject *m = PyModule_Create(&g_module);
+    if (m && (PyModule_AddStringConstant(m, "python", TEXT(PY_MAJOR_VERSION) "." TEXT(PY_MINOR_VERSION)) < 0 ||
+              PyModule_AddStringConstant(m, "torch", BUILT_FOR_TORCH) < 0)) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}
