@@ -158,9 +158,10 @@ int cfgzip_signatures_static(const uint8_t *tok_bytes, const int64_t *tok_off, i
  * Method: tokens are gathered by hash and first byte in a hash table and every token's full
  * signature is compared with that of one member of its group, every group's with one member of
  * its class; if all agree the groups are the classes.  Otherwise (and for very large
- * vocabularies, or with nothing but the automaton to compare by): radix sort by (hash, first
- * byte) with the token id as value, equal-hash
- * segments, then every member's full signature is compared with its left
+ * vocabularies, or with nothing but the automaton to compare by, or if more hashes than there is
+ * room for fall into one part of the table, which neither spread-out nor merely regular ones do):
+ * radix sort by (hash, first byte) with the token id as value, equal-hash segments, then every
+ * member's full signature is compared with its left
  * neighbour's in the segment (equality is transitive); members that differ (a
  * hash collision) start a chain of their own and the chains of a segment are
  * matched against each other in further rounds, so the result is exact for any

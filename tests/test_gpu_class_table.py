@@ -198,20 +198,25 @@ def test_sizes_around_the_runs_and_buckets(lib, V, shape):
     assert coll == 0
 
 
+def _bucket(h):
+    """The bucket, of 256, that classes with these hashes go to."""
+    low, high = (h & np.uint64(0xFFFFFFFF)).astype(np.uint32), ((h >> np.uint64(32)) & np.uint64(31)).astype(np.uint32)
+    x = low ^ ((high << np.uint32(8)) * np.uint32(0x9E3779B1))
+    x = (x ^ (x >> np.uint32(16))) * np.uint32(0x85EBCA6B)
+    x = (x ^ (x >> np.uint32(13))) * np.uint32(0x2C1B3C6D)
+    return x >> np.uint32(24)
+
+
 def _hashes_of_one_bucket(n):
-    """n different values whose bucket, the bytes 1, 5, 11, 29 times added up, is 0 for any number of buckets."""
-    k = np.arange(n, dtype=np.uint64)
-    b1, b2 = k % np.uint64(256), k // np.uint64(256)
-    b0 = (np.uint64(1 << 16) - np.uint64(5) * b1 - np.uint64(11) * b2) % np.uint64(256)
-    return b0 | (b1 << np.uint64(8)) | (b2 << np.uint64(16))
+    """n different values whose bucket is 0 for any number of buckets."""
+    h = np.random.default_rng(n).integers(0, 1 << 63, size=400 * n + 20_000, dtype=np.uint64)
+    h = np.unique(h[_bucket(h) == 0] & np.uint64((1 << 37) - 1))
+    assert h.size >= n
+    return h[:n]
 
 
-@pytest.mark.parametrize("V,classes", [(6000, 900), (6000, 2500), (12_000, 900), (20_000, 900), (20_000, 2049)])
-def test_hashes_that_fall_into_one_bucket(lib, V, classes):
-    """All classes in one bucket: more entries than its list holds (20,000 tokens in runs of 1,024), and more classes than
-    its table does (the sort then takes over)."""
-    from gpu_util import dev
-    print(f"case V={V} classes={classes}", flush=True)
+def _rows_of_classes(V, classes):
+    """(vocabulary bytes, offsets, rows of 16 entries, each token's class)"""
     rng = np.random.default_rng(V + classes)
     cls = np.concatenate([np.arange(classes), rng.integers(0, classes, size=V - classes)])
     rng.shuffle(cls)
@@ -220,7 +225,51 @@ def test_hashes_that_fall_into_one_bucket(lib, V, classes):
     data = rng.integers(0, 256, size=max(1, int(off[-1])), dtype=np.uint8)
     rows = rng.integers(0, 1 << 16, size=(classes, 16), dtype=np.uint16)
     rows[:, 3] = np.arange(classes)
-    rows = np.ascontiguousarray(rows[cls])
+    return data, off, np.ascontiguousarray(rows[cls]), cls
+
+
+REGULAR = {
+    "numbers in a row": lambda k: k,
+    "numbers in a row, upper half": lambda k: k << np.uint64(21),
+    "multiples of 251": lambda k: k * np.uint64(251),
+    "written twice": lambda k: k | (k << np.uint64(16)),
+    "and its complement": lambda k: k | ((k ^ np.uint64(0xFFFF)) << np.uint64(16)),
+    "checksum in the last byte": lambda k: (k << np.uint64(8)) | ((np.uint64(1 << 16) - np.uint64(5) * (k % np.uint64(256))
+                                                                 - np.uint64(11) * (k // np.uint64(256))) % np.uint64(256)),
+}
+
+
+@pytest.mark.parametrize("kind", list(REGULAR))
+@pytest.mark.parametrize("V,classes", [(6000, 2500), (20_000, 2049), (128_000, 4000)])
+def test_regular_hashes_are_grouped_without_the_sort(lib, V, classes, kind):
+    """Any function of the signature may be the hash.  The sort leaves its counters at the end of the workspace, grouping
+    by table does not come there."""
+    from gpu_util import dev
+    print(f"case V={V} classes={classes} {kind}", flush=True)
+    data, off, rows, cls = _rows_of_classes(V, classes)
+    hashes = REGULAR[kind](np.arange(classes, dtype=np.uint64))
+    assert len(np.unique(hashes & np.uint64((1 << 37) - 1))) == classes
+    want_c, want_r = oracle.build_classes(rows, off)
+
+    def build(h):
+        ws = torch.full((lib.load_library().cfgzip_build_classes_workspace_bytes(V, 16),), 0xA5, dtype=torch.uint8, device="cuda")
+        c, r, C, coll = lib.cfgzip_build_classes(dev(data), dev(off), None, dev(rows), dev(h[cls]), workspace=ws)
+        assert C == classes == len(want_r)
+        assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
+        return coll, bool((ws[-256:] == 0xA5).all())
+
+    assert build(hashes) == (0, True)
+    coll, by_table = build(hashes % np.uint64(64))  # the sort
+    assert coll > 0 and not by_table
+
+
+@pytest.mark.parametrize("V,classes", [(6000, 900), (6000, 2500), (12_000, 900), (20_000, 900), (20_000, 2049)])
+def test_hashes_that_fall_into_one_bucket(lib, V, classes):
+    """All classes in one bucket: more entries than its list holds (20,000 tokens in runs of 1,024), and more classes than
+    its table does (the sort then takes over)."""
+    from gpu_util import dev
+    print(f"case V={V} classes={classes}", flush=True)
+    data, off, rows, cls = _rows_of_classes(V, classes)
     want_c, want_r = oracle.build_classes(rows, off)
     c, r, C, coll = lib.cfgzip_build_classes(dev(data), dev(off), None, dev(rows),
                                              dev(_hashes_of_one_bucket(classes)[cls]))
