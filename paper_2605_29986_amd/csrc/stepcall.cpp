@@ -80,30 +80,43 @@ bool logits_of(PyObject *o, PyObject *V, Logits *out) {
     return true;
 }
 
-// What the call returns: the tensor handed in or a new one like `like`, or the status if it is not 0.
-PyObject *finish(int rc, PyObject *given, const at::Tensor &made) {
-    if (rc != 0) return PyLong_FromLong(rc);
-    if (given != Py_None) {
-        Py_INCREF(given);
-        return given;
-    }
-    return THPVariable_Wrap(made);
+// What the call returns, made before the launch, behind which nothing can fail any more: the tensor handed in, or the new
+// one around `made`.  Null: a Python error is set.
+PyObject *result_of(PyObject *given, const at::Tensor &made) {
+    if (given == Py_None) return THPVariable_Wrap(made);
+    Py_INCREF(given);
+    return given;
+}
+// The same, or the status of the launch if it is not 0.
+PyObject *finish(int rc, PyObject *result) {
+    if (rc == 0) return result;
+    Py_DECREF(result);
+    return PyLong_FromLong(rc);
+}
+// Nothing has been launched: the general way meets the same error (one that a dispatch mode raises is also set in the
+// interpreter) and says so.
+PyObject *leave_it() {
+    PyErr_Clear();
+    Py_RETURN_NONE;
 }
 
 // (logits, cls_bits, class_of_token, C, tok, rep_of_class, tok_bits_out, rep_out, V)
 PyObject *decode_step(PyObject *, PyObject *const *args, Py_ssize_t n) {
     if (n != 9 || !g_decode_step || at::impl::torch_function_mode_enabled()) Py_RETURN_NONE;
+    Logits l;
+    int32_t C = 0, *tok_bits = nullptr, *rep_out = nullptr;
+    const int32_t *bits_p = nullptr, *cls_p = nullptr, *tok_p = nullptr, *rep_p = nullptr;
+    void *stream = nullptr;
+    PyObject *result = nullptr;
     try {
-        Logits l;
         if (!logits_of(args[0], args[8], &l)) Py_RETURN_NONE;
-        const int64_t C = small_int(args[3]);
+        C = (int32_t)small_int(args[3]);
         const at::Tensor *bits = plain(args[1], at::kInt), *cls = plain(args[2], at::kInt),
                          *tok = plain(args[4], at::kInt), *rep = plain(args[5], at::kInt);
-        int32_t *tok_bits = nullptr, *rep_out = nullptr;
         if (!C || !bits || !cls || !tok || !rep || !plain_or_none(args[6], at::kInt, &tok_bits) ||
             !plain_or_none(args[7], at::kInt, &rep_out))
             Py_RETURN_NONE;
-        if (bits->dim() != 2 || bits->size(0) != l.B || bits->size(1) != (C + 31) / 32 || tok->numel() != l.B ||
+        if (bits->dim() != 2 || bits->size(0) != l.B || bits->size(1) != ((int64_t)C + 31) / 32 || tok->numel() != l.B ||
             rep->numel() != C || cls->numel() != l.V)
             Py_RETURN_NONE;
         at::Tensor made;
@@ -111,29 +124,35 @@ PyObject *decode_step(PyObject *, PyObject *const *args, Py_ssize_t n) {
             made = tok->dim() == 1 ? at::empty_like(*tok) : at::empty({l.B}, tok->options());
             rep_out = static_cast<int32_t *>(made.data_ptr());
         }
-        void *stream = c10::hip::getCurrentHIPStream().stream();
-        const auto *bits_p = static_cast<const int32_t *>(bits->data_ptr()), *cls_p = static_cast<const int32_t *>(cls->data_ptr()),
-                   *tok_p = static_cast<const int32_t *>(tok->data_ptr()), *rep_p = static_cast<const int32_t *>(rep->data_ptr());
-        int rc = 0;
-        Py_BEGIN_ALLOW_THREADS
-        rc = g_decode_step(l.data, l.type, l.B, l.V, l.stride, bits_p, cls_p, (int32_t)C, tok_bits, tok_p, rep_p, rep_out, stream);
-        Py_END_ALLOW_THREADS
-        return finish(rc, args[7], made);
-    } catch (...) {  // before the launch: the general way meets the same and says so
-        Py_RETURN_NONE;
+        bits_p = static_cast<const int32_t *>(bits->data_ptr());
+        cls_p = static_cast<const int32_t *>(cls->data_ptr());
+        tok_p = static_cast<const int32_t *>(tok->data_ptr());
+        rep_p = static_cast<const int32_t *>(rep->data_ptr());
+        stream = c10::hip::getCurrentHIPStream().stream();
+        result = result_of(args[7], made);
+    } catch (...) {
     }
+    if (!result) return leave_it();
+    int rc = 0;
+    Py_BEGIN_ALLOW_THREADS
+    rc = g_decode_step(l.data, l.type, l.B, l.V, l.stride, bits_p, cls_p, C, tok_bits, tok_p, rep_p, rep_out, stream);
+    Py_END_ALLOW_THREADS
+    return finish(rc, result);
 }
 
 // (logits, state_mask, C, class_of_token, sig_rep, tok_prev, states_in, states_out, tok_bits_out, V)
 PyObject *engine_step(PyObject *, PyObject *const *args, Py_ssize_t n) {
     if (n != 10 || !g_engine_step || at::impl::torch_function_mode_enabled()) Py_RETURN_NONE;
+    Logits l;
+    int32_t S = 0, C = 0, *tok_prev = nullptr, *out = nullptr, *tok_bits = nullptr;
+    uint16_t *sig_rep = nullptr;
+    const int32_t *mask_p = nullptr, *cls_p = nullptr, *in_p = nullptr;
+    void *stream = nullptr;
+    PyObject *result = nullptr;
     try {
-        Logits l;
         if (!logits_of(args[0], args[9], &l)) Py_RETURN_NONE;
-        const int64_t C = small_int(args[2]);
+        C = (int32_t)small_int(args[2]);
         const at::Tensor *mask = plain(args[1], at::kInt), *cls = plain(args[3], at::kInt), *in = plain(args[6], at::kInt);
-        uint16_t *sig_rep = nullptr;
-        int32_t *tok_prev = nullptr, *out = nullptr, *tok_bits = nullptr;
         if (!C || !mask || mask->dim() < 1 || mask->size(0) > kMost || !cls || !in ||
             !plain_or_none(args[4], at::kUInt16, &sig_rep) || !plain_or_none(args[5], at::kInt, &tok_prev) ||
             !plain_or_none(args[7], at::kInt, &out) || !plain_or_none(args[8], at::kInt, &tok_bits))
@@ -143,19 +162,20 @@ PyObject *engine_step(PyObject *, PyObject *const *args, Py_ssize_t n) {
             made = at::empty_like(*in);
             out = static_cast<int32_t *>(made.data_ptr());
         }
-        void *stream = c10::hip::getCurrentHIPStream().stream();
-        const auto *mask_p = static_cast<const int32_t *>(mask->data_ptr()), *cls_p = static_cast<const int32_t *>(cls->data_ptr()),
-                   *in_p = static_cast<const int32_t *>(in->data_ptr());
-        const int32_t S = (int32_t)mask->size(0);
-        int rc = 0;
-        Py_BEGIN_ALLOW_THREADS
-        rc = g_engine_step(l.data, l.type, l.B, l.V, l.stride, mask_p, S, (int32_t)C, cls_p, sig_rep, tok_prev, in_p, out,
-                           tok_bits, stream);
-        Py_END_ALLOW_THREADS
-        return finish(rc, args[7], made);
+        mask_p = static_cast<const int32_t *>(mask->data_ptr());
+        cls_p = static_cast<const int32_t *>(cls->data_ptr());
+        in_p = static_cast<const int32_t *>(in->data_ptr());
+        S = (int32_t)mask->size(0);
+        stream = c10::hip::getCurrentHIPStream().stream();
+        result = result_of(args[7], made);
     } catch (...) {
-        Py_RETURN_NONE;
     }
+    if (!result) return leave_it();
+    int rc = 0;
+    Py_BEGIN_ALLOW_THREADS
+    rc = g_engine_step(l.data, l.type, l.B, l.V, l.stride, mask_p, S, C, cls_p, sig_rep, tok_prev, in_p, out, tok_bits, stream);
+    Py_END_ALLOW_THREADS
+    return finish(rc, result);
 }
 
 // (address of cfgzip_decode_step, address of cfgzip_engine_step), of the library that the binding has loaded
