@@ -9,6 +9,7 @@ import ctypes
 import numpy as np
 import pytest
 
+from oracle import displacement as D
 from synthetic_inputs.grammar import (grammar_from_productions, make_bracket_gnf, make_json_gnf, make_random_gnf,
                                       make_token_strings)
 from synthetic_inputs.vocab import vocab_from_tokens
@@ -89,8 +90,8 @@ def test_deep_stacks_behind_exhausted_tables(lib):
 
 
 def test_rounds_of_more_bytes_than_are_staged(lib):
-    """A wave keeps up to 256 bytes of the tokens it has taken in LDS: single tokens around that, and rounds of three
-    tokens that only together have more."""
+    """Single tokens around 256 bytes and of 700, and a third of a vocabulary of 80 to 140 among tokens of a few bytes.
+    (A workgroup keeps up to 6,144 bytes of a batch in LDS, which none of these comes to: see below.)"""
     g = grammar_from_productions(1, [(0, ord("a"), (0,)), (0, ord("a"), ()), (0, ord("b"), (0,))])
     rng = np.random.default_rng(5)
     long_ones = [b"ab" * 127 + b"a", b"ab" * 128, b"ab" * 128 + b"a", b"a" * 700, b"b" * 255 + b"z" + b"a" * 40]
@@ -138,17 +139,46 @@ def test_rows_that_are_only_8_byte_aligned(lib):
     assert torch.equal(h, want_hash) and torch.equal(st, want_status)
 
 
-@pytest.mark.parametrize("V,longest", [(32_768, 6), (32_769, 6), (33_100, 80), (262_144, 4), (262_401, 4)])
-def test_groups_around_the_sorted_batches(lib, V, longest):
-    """128 tokens for a workgroup, which its waves take at once, and 129, which are sorted by length; more bytes than are
-    staged (tokens of up to 80); a whole batch of 1,024 tokens and one more.  The vocabulary repeats 700 strings: theirs are
-    compared with the oracle, and every row, hash and status with its string's."""
-    print(f"case V={V} longest={longest}", flush=True)
-    g = make_json_gnf()
-    few = make_token_strings(V, 700, b'{}[]",:0123456789.eE+-truefalsn \\ua', longest)
+STAGED = 6144  # bytes of a batch's tokens that a workgroup keeps in LDS
+
+
+def _batch_bytes(off, n_cu):
+    """The bytes of every batch of up to 1,024 tokens, workgroup after workgroup."""
+    V = len(off) - 1
+    per_group = -(-V // min(n_cu, -(-V // 16)))
+    return [[int(off[min(b + 1024, g + per_group, V)] - off[b]) for b in range(g, min(g + per_group, V), 1024)]
+            for g in range(0, V, per_group)]
+
+
+def _n_cu():
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+@pytest.mark.parametrize("total", [STAGED - 1, STAGED, STAGED + 1, 20_000])
+@pytest.mark.parametrize("V", [1, 2, 16])
+def test_bytes_around_what_is_staged(lib, V, total):
+    """One workgroup whose tokens have so many bytes together; beyond what is staged they are read from memory.  Every
+    byte permutes five symbols, so a token's set says all of its bytes' product."""
+    from gpu_util import dev, hash_np
+    print(f"case V={V} total={total}", flush=True)
+    rng = np.random.default_rng(total + V)
+    g = grammar_from_productions(5, [(A, b, (int(B),)) for b in b"abcd" for A, B in enumerate(rng.permutation(5))])
+    ends = np.sort(rng.integers(0, total + 1, size=V - 1))
+    data = rng.integers(97, 101, size=total, dtype=np.uint8).tobytes()
+    vocab = vocab_from_tokens([data[a:b] for a, b in zip([0, *ends], [*ends, total])])
+    assert _batch_bytes(vocab.tok_off, _n_cu()) == [[total]]
+    rows, hashes, status = lib.cfgzip_displacements(dev(vocab.tok_bytes), dev(vocab.tok_off), *_grammar_dev(g), g.N, hash_seed=9)
+    prods = g.productions()
+    for t, tok in enumerate(vocab.tokens()):
+        # (step by step: Algorithm 1's recursion goes as deep as the token is long)
+        row, h, st = D.encode_displacement(D.displacement_within_limits(tuple(tok), prods, D.stack_adjacency(prods)), t, 9, 256)
+        assert st == D.DISP_OK == int(status[t]) and int(hash_np(hashes)[t]) == h
+        assert (rows[t].cpu().numpy() == np.asarray(row, np.uint16)).all()
+
+
+def _check_repeated(lib, g, few, pick):
+    """The vocabulary of the strings few[pick]: every row, hash and status are its string's (and those the oracle's)."""
     _check_rows(lib, g, few, expect_overflow=None)
-    rng = np.random.default_rng(V)
-    pick = rng.integers(0, few.V, size=V)
     strings = few.tokens()
     vocab = vocab_from_tokens([strings[i] for i in pick])
     gd = _grammar_dev(g)
@@ -164,7 +194,36 @@ def test_groups_around_the_sorted_batches(lib, V, longest):
     ok = many_status == 0  # a token that overflows has a row and a hash of its own
     assert bool(ok.any())
     assert bool((many_h == h[p])[ok].all())
-    for a in range(0, V, 1 << 16):
-        part = slice(a, min(V, a + (1 << 16)))
+    for a in range(0, vocab.V, 1 << 16):
+        part = slice(a, min(vocab.V, a + (1 << 16)))
         same = (many_rows[part].view(torch.int16) == rows.view(torch.int16)[p[part]]).all(dim=1)
         assert bool(same[ok[part]].all())
+    return vocab
+
+
+def test_staged_and_unstaged_batches_one_after_the_other(lib):
+    """Workgroups of 1,100 tokens, a batch of 1,024 and one of 76: both with their bytes in LDS, either one, and neither."""
+    n_cu, per_group = _n_cu(), 1100
+    rng = np.random.default_rng(8)
+    few = vocab_from_tokens([bytes(rng.integers(97, 100, size=int(m), dtype=np.uint8)) for m in rng.integers(0, 5, size=300)]
+                            + [bytes(rng.integers(97, 99, size=int(m), dtype=np.uint8)) for m in rng.integers(90, 130, size=80)])
+    pick = rng.integers(0, 300, size=(n_cu, per_group))
+    for g in range(n_cu):
+        if g & 1:
+            pick[g, rng.choice(1024, size=70, replace=False)] = rng.integers(300, few.V, size=70)
+        if g & 2:
+            pick[g, 1024:] = rng.integers(300, few.V, size=per_group - 1024)
+    g = grammar_from_productions(5, [(A, b, (int(B),)) for b in b"abc" for A, B in enumerate(rng.permutation(5))])
+    vocab = _check_repeated(lib, g, few, pick.ravel())
+    kinds = {(first > STAGED, second > STAGED) for first, second in _batch_bytes(vocab.tok_off, n_cu)}
+    assert len(kinds) == 4
+
+
+@pytest.mark.parametrize("V,longest", [(32_768, 6), (32_769, 6), (33_100, 80), (262_144, 4), (262_401, 4)])
+def test_groups_around_the_sorted_batches(lib, V, longest):
+    """128 tokens for a workgroup, which its waves take at once, and 129, which are sorted by length; tokens of up to 80 bytes;
+    a whole batch of 1,024 tokens and one more.  The vocabulary repeats 700 strings: theirs are compared with the oracle, and
+    every row, hash and status with its string's."""
+    print(f"case V={V} longest={longest}", flush=True)
+    few = make_token_strings(V, 700, b'{}[]",:0123456789.eE+-truefalsn \\ua', longest)
+    _check_repeated(lib, make_json_gnf(), few, np.random.default_rng(V).integers(0, few.V, size=V))
