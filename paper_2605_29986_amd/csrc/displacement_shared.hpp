@@ -64,8 +64,13 @@ constexpr int kShBatch = 1024;      // tokens a workgroup sorts by length at a t
 constexpr int kShBytes = 6144;      // their bytes, kept in LDS; if there are more they are read from memory
 constexpr int kShLengths = 64;      // lengths told apart in sorting
 constexpr int kShTakeMost = 16;     // tokens a wave takes at a time
-// Tokens for every wave up to which they are not sorted and a wave takes its share at once: then every token is begun at
-// the start anyway (32,000 tokens over the statement grammar, 125 a workgroup: 101 us, sorted 110).
+// Tokens for every wave up to which they are not sorted and a wave takes its share at once.  Calls sorted / not, us, mean
+// of vocabularies of four seeds with rows of 256 entries:
+//   tokens a workgroup      63         78         94        109        125        141        156        188
+//   statement grammar    118 /  99  121 / 108  128 / 129  123 / 117  125 / 125  125 / 121  131 / 127  135 / 137
+//   JSON grammar         159 / 161  159 / 164  160 / 168  159 / 165  160 / 171  159 / 169  159 / 171  159 / 174
+// The statement grammar's tokens are of much the same length, and what sorting costs it from 94 to 156 the JSON grammar
+// gains; the line lies in between.
 constexpr int kShOnce = 8;
 constexpr int kShSeen = 256;        // slots of a wave's table of the successors found so far: at most half full
 constexpr int kShProbes = 48;       // slots looked at before a table counts as full
@@ -800,8 +805,8 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
                 if (L.byte_like[b] != b) continue;
                 const int lo = (int)L.byte_off[b], hi = (int)L.byte_off[b + 1];
                 if (i > lo && packed_head(L.prods[i - 1]) == head) continue;
-                int end = i + 1;
-                while (end < hi && packed_head(L.prods[end]) == head) ++end;
+                int end = i + 1;  // (a thread for all of them: 676 productions of one pair, counted out, took it 50 us)
+                while (end < hi && end - i < 64 && packed_head(L.prods[end]) == head) ++end;
                 if (end - i < 64) L.pair[L.byte_number[b] * (uint32_t)a.g.N + head] = (uint16_t)(i | ((end - i) << 10));
                 else L.pairs_kept = 0;  // more than six bits
             }
@@ -979,7 +984,7 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
                 if (lane == 0) taken = (int)atomicAdd(&L.cursor, (uint32_t)want);
                 taken = __builtin_amdgcn_readfirstlane(taken);
                 const int count = min(want, in_batch - taken);
-                more = count > 0;
+                more = sorted && count > 0;  // (else the wave has had all that is its)
                 const int rank_idle = (int)__popcll(idle & ((1ull << lane) - 1ull));
                 if (token < 0 && rank_idle < count) {
                     token = (int)L.order[taken + rank_idle];

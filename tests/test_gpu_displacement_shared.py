@@ -5,6 +5,7 @@ exhaust its tables, so that some tokens are taken alone by the passes behind it.
 displacement: status, row and hash of every token against the oracle, and the classes."""
 
 import ctypes
+import itertools
 
 import numpy as np
 import pytest
@@ -53,6 +54,19 @@ def test_grammars_around_what_is_kept_in_lds(lib, n_nt, n_prod):
     g = make_random_gnf(n_nt + n_prod, n_nt, alphabet, n_prod, 5)
     _check_adjacency(lib, g)
     _check_rows(lib, g, make_token_strings(7, 300, alphabet, 5), row_len=512)
+
+
+@pytest.mark.parametrize("n", [62, 63, 64, 65, 100, 129])
+def test_many_productions_of_one_symbol_and_byte(lib, n):
+    """Up to 63 productions of a (byte, symbol) pair are looked up together; with more of one pair, none are.  The pair lies
+    first, last and between others among the productions of its byte."""
+    print(f"case n={n}", flush=True)
+    for head in (0, n // 2, n + 1):
+        prods = [(head, ord("a"), (B,)) for B in range(n)] + [(A, ord("a"), ()) for A in range(n + 2) if A != head]
+        prods += [(A, ord("b"), (head,)) for A in range(0, n + 2, 3)] + [(A, ord("c"), ()) for A in range(1, n + 2, 40)]
+        g = grammar_from_productions(n + 2, prods)
+        vocab = vocab_from_tokens([bytes(w) for k in range(4) for w in itertools.product(b"abc", repeat=k)] + [b"z", b"az"])
+        _check_rows(lib, g, vocab, row_len=1024)
 
 
 def test_bytes_with_equal_productions(lib):
