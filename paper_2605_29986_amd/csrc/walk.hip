@@ -199,7 +199,7 @@ __global__ __launch_bounds__(kWalkThreads) void signatures_kernel(WalkArgs a) {
     const int S = a.S;
     const uint16_t *tab = a.T.Tt;
     // the walk vectors go through LDS only when rows are expanded from them
-    uint16_t *w = a.sig_out ? dyn_lds : nullptr;
+    uint16_t *w = !SPREAD && a.sig_out ? dyn_lds : nullptr;
     const int lane = threadIdx.x & 63;
     const bool first_wave = threadIdx.x < 64;
 
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kWalkThreads) void signatures_kernel(WalkArgs a) {
                 // (the empty token's identity vector is never looked at: its row says it all)
                 if ((uint32_t)B.cnt[m] > stride && B.row[m] != 256) a.store.header->overflow = 1;
             }
-            if (a.sig_out) {
+            if (!SPREAD && a.sig_out) {
                 // sig[t][q] = w[idx[row][q]]
                 if (S >= 8) {
                     // four 16-byte pieces per thread at a time: their index reads are in flight together.  A row's last
@@ -508,7 +508,7 @@ int run_signatures(const uint8_t *tok_bytes, const int64_t *tok_off, int32_t V, 
     a.wcap = std::max(kMinWalkCap, (S + kWalkGroup - 1) / kWalkGroup * kWalkGroup);
     const size_t dyn = sig_out ? (size_t)a.wcap * 2 : 0;
     if (!sig_out) a.wcap = 0x3FFFFFFF;  // no LDS buffer bounds a batch's walks
-    auto kern = S >= kSpreadStates ? signatures_kernel<true> : signatures_kernel<false>;
+    auto kern = S >= kSpreadStates && !sig_out ? signatures_kernel<true> : signatures_kernel<false>;
     if (dyn > 48 * 1024)
         CFGZIP_TRY(check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn)));

@@ -256,13 +256,20 @@ __device__ __forceinline__ void batch_stage_bytes(const Batch &B, const uint8_t 
 // kWalkGroup; a vector longer than that is not kept).
 // `kept` (or null): kept walk vectors of finished tokens, kept_stride entries apart, from which
 // the slots with a parent start.
-// SPREAD: the walks of a group are not neighbours but lie as far apart as the token has groups, so that the lanes of a wave
-// read, at a time, the successors of neighbouring states: with kSpreadStates states and more a column is 48 lines of
-// memory or more, a read of 26 states a fourth apart touches about as many, of 26 neighbours a third of that, and the
-// lines are what the L1 cache takes one by one.  151,936 tokens x 4,096 states 95.6 -> 88.9 us, 128,256 x 3,500 74.3 and
-// 73.9; but states, multipliers and end states then move one by one (2,500 states 45.6 and 45.9, 1,024 with rows 76.0 and
-// 77.3, 512 29.3 and 31.7).
+// SPREAD (only where no rows are written, so without `w`): the walks of a group are not neighbours but lie as far apart as
+// the token has groups, so that the lanes of a wave read, at a time, the successors of neighbouring states: with
+// kSpreadStates states and more a column is 48 lines of memory or more, a read of 26 states a fourth apart touches about as
+// many, of 26 neighbours a third of that, and the lines are what the L1 cache takes one by one.  Start states, multipliers
+// and end states then move one by one, which pays off where a token's walks are few: of more than kSpreadMost (an automaton
+// without structure) a wave is within one token anyway, and they stay neighbours.  Calls for hashes alone, neighbours /
+// spread, us, lexers of
+//   states           2,500       3,072        3,500        4,096        5,000        6,000        8,192
+//   151,936 tokens   71 / 73   81.8 / 78.6  91.4 / 88.8   103 / 94.7   118 / 113    140 / 142    181 / 151
+//    30,000 tokens   31 / 31   33.3 / 32.1  38.1 / 36.8  41.2 / 38.7  46.6 / 44.8  53.6 / 53.6  66.2 / 59.4
+// (6,000 and 151,936 is the one pair seen where it loses), and of 4,096 states without structure (2,600 walks a token) 344 /
+// 345, with all of them spread 362.  With rows, where the end states go through LDS, lexers are within 1 % either way.
 constexpr int kSpreadStates = 3072;
+constexpr uint32_t kSpreadMost = 512;
 template <bool LDS_BYTES, bool HASH, bool SPREAD>
 __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t *tab, int S,
                                                 const uint8_t *__restrict__ tok_bytes, Batch &B,
@@ -272,10 +279,11 @@ __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t 
     const uint32_t nt = blockDim.x, k = B.k, gtotal = B.gtotal, Su = (uint32_t)S;
     for (uint32_t g = threadIdx.x; g < gtotal; g += nt) {
         const uint32_t m = (uint32_t)batch_find(B.gstart, (int)k, (int)g);
+        const uint32_t n = (uint32_t)B.cnt[m], groups = (uint32_t)B.gstart[m + 1] - (uint32_t)B.gstart[m];
+        const bool spread = SPREAD && n <= kSpreadMost;
         // walk u of the group is walk j0 + u * apart of the token
-        const uint32_t apart = SPREAD ? (uint32_t)B.gstart[m + 1] - (uint32_t)B.gstart[m] : 1u;
-        const uint32_t j0 = (g - (uint32_t)B.gstart[m]) * (SPREAD ? 1u : (uint32_t)kWalkGroup);
-        const uint32_t n = (uint32_t)B.cnt[m];
+        const uint32_t apart = spread ? groups : 1u;
+        const uint32_t j0 = (g - (uint32_t)B.gstart[m]) * (spread ? 1u : (uint32_t)kWalkGroup);
         const uint32_t e0 = (uint32_t)B.row[m] * Su + j0;
         uint32_t cur[kWalkGroup];
         // (a vector longer than what is kept of it cannot be started from)
@@ -283,9 +291,9 @@ __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t 
         const uint32_t skip = par >= 0 ? (uint32_t)B.skip[m] : 1u;
         // A group's four start states (and its four hash multipliers) lie next to each other and come in one (two)
         // loads; only at the end of a row one by one.
-        const bool whole = !SPREAD && j0 + kWalkGroup <= Su;
+        const bool whole = !spread && j0 + kWalkGroup <= Su;
         static_assert(kWalkGroup == 4, "the vector forms below are written for groups of four");
-        if (SPREAD) {
+        if (spread) {
             const uint16_t *from = par >= 0 ? kept + (size_t)par * keep_stride + j0 : T.img + e0;
 #pragma unroll
             for (int u = 0; u < kWalkGroup; ++u) cur[u] = j0 + u * apart < n ? (uint32_t)from[u * apart] : 0u;
@@ -334,18 +342,16 @@ __device__ __forceinline__ void batch_walk_impl(const Tables &T, const uint16_t 
         }
         uint16_t *kd = keep && n <= keep_stride ? keep + (size_t)m * keep_stride : nullptr;  // (a vector that does not fit
                                                                                              // makes the store unusable)
-        const uint32_t padded = ((uint32_t)B.gstart[m + 1] - (uint32_t)B.gstart[m]) * kWalkGroup;
-        if (SPREAD) {
+        const uint32_t padded = groups * kWalkGroup;
+        if (spread) {
+            if (kd)
 #pragma unroll
-            for (int u = 0; u < kWalkGroup; ++u) {
-                if (w) w[(uint32_t)B.wstart[m] + j0 + u * apart] = (uint16_t)cur[u];  // null: only hash and `keep` are wanted
-                if (kd) kd[j0 + u * apart] = (uint16_t)cur[u];
-            }
+                for (int u = 0; u < kWalkGroup; ++u) kd[j0 + u * apart] = (uint16_t)cur[u];
         } else {
             // the four end states as one 8-byte store each way (both regions are 8-byte aligned: a slot's
             // region in w starts at a multiple of the group size, a kept vector at a multiple of 8 entries)
             const uint2 packed = make_uint2(cur[0] | (cur[1] << 16), cur[2] | (cur[3] << 16));
-            if (w) *reinterpret_cast<uint2 *>(w + (uint32_t)B.wstart[m] + j0) = packed;
+            if (w) *reinterpret_cast<uint2 *>(w + (uint32_t)B.wstart[m] + j0) = packed;  // null: only hash and `keep` are wanted
             if (kd) *reinterpret_cast<uint2 *>(kd + j0) = packed;
         }
         // a kept vector is compared 8 entries at a time: the token's last group also zeroes

@@ -344,3 +344,33 @@ def test_walks_that_lie_apart(lib, S, composed):
         c, r, C, coll = lib.cfgzip_build_classes(tb, to, tt, rows, h, signatures_workspace=ws)
         assert C == len(want_r) and coll == 0
         assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
+
+
+@pytest.mark.parametrize("S", [3072, 4097])
+@pytest.mark.parametrize("composed", [False, True])
+def test_walks_that_lie_apart_beside_such_that_do_not(lib, S, composed):
+    """Tokens of up to 512 distinct states walk spread, those of more as neighbours: both in one batch, images of every size
+    around the line and around a whole group, hashes alone and with rows."""
+    from gpu_util import hash_np, vocab_dev
+    print(f"case S={S} composed={composed}", flush=True)
+    rng = np.random.default_rng(S + 1)
+    table = np.zeros((S, 256), np.uint16)
+    sizes = [3, 26, 507, 508, 509, 510, 511, 512, 513, 514, 515, 516, 517, 1023, 1024, 2600, S]
+    for b, n in enumerate(sizes):
+        states = rng.permutation(S)[:n]
+        table[:, b] = states[np.concatenate([np.arange(n), rng.integers(0, n, size=S - n)])][rng.permutation(S)]
+    vocab = vocab_from_tokens([rng.integers(0, len(sizes), size=int(k), dtype=np.uint8).tobytes()
+                               for k in rng.integers(0, 7, size=500)])
+    tb, to, tt = vocab_dev(vocab, table)
+    raw = lib.load_library()
+    query = raw.cfgzip_signatures_composed_workspace_bytes if composed else raw.cfgzip_signatures_workspace_bytes
+    ws = torch.empty(query(vocab.V, S), dtype=torch.uint8, device="cuda")
+    want_sig = oracle.signatures(vocab.tok_bytes, vocab.tok_off, table)
+    want_hash = oracle.signature_hash(want_sig, lib.DEFAULT_HASH_SEED)
+    want_c, want_r = oracle.build_classes(want_sig, vocab.tok_off)
+    for rows in (True, False):
+        sig, h = lib.cfgzip_signatures(tb, to, tt, want_sig=rows, workspace=ws, composed=composed)
+        assert (hash_np(h) == want_hash).all() and (not rows or (sig.cpu().numpy() == want_sig).all())
+        c, r, C, coll = lib.cfgzip_build_classes(tb, to, tt, sig, h, signatures_workspace=ws)
+        assert C == len(want_r) and coll == 0
+        assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
