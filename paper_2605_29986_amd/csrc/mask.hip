@@ -28,6 +28,9 @@ constexpr int kRowsExpand = 16;                // rows per workgroup for mask ex
 constexpr int kMaxRowsPerBlock = 16;           // the larger of the two
 
 enum : int { LOGITS_NONE = 0, LOGITS_BF16 = 1, LOGITS_F32 = 2 };
+// where a row's class mask comes from: handed in, or from the row's automaton state (engine step), there with the class ids
+// and the rows of logits, kRowsStream at the most, asked for behind the states or before
+enum : int { MASKS_GIVEN = 0, MASKS_OF_STATES = 1, MASKS_OF_STATES_EARLY = 2 };
 
 // native 16-byte vector (the nontemporal builtins do not take HIP's uint4 struct), and the same at any even address:
 // global memory takes 16-byte accesses at every alignment, and a wave's 1 KB run then touches one cache line more.
@@ -80,11 +83,23 @@ __device__ __forceinline__ uint32_t select_bf16_pair(uint32_t x, uint32_t two_bi
 // LOGITS: which logits to mask (none = mask expansion only).
 // FROM_CLASS: bits_in is a class-level mask gathered through class_of_token.
 // WRITE_BITS: also store the token-level mask.
-// ENGINE: the rows' class masks are those of the automaton states (cfgzip_engine_step).  The way there (state, token, class,
-// signature entry, class mask, LDS) is five dependent accesses, so a thread asks for its class ids and all of its rows
-// before it (512 states, bf16 logits of 128,256 columns: batch 64 7.7 -> 7.2 us, 128 13.9 -> 11.7, 256 24.3 -> 23.6).
+// MASKS: where the rows' class masks come from.  For those of the automaton states (cfgzip_engine_step) the way there (state,
+// token, class, signature entry, class mask, LDS) is five dependent accesses, so a thread may ask for its class ids and all
+// of its rows before it.  A wave's loads come back in order, though, so the five then wait for the rows.  Kernels back to
+// back, us, 512 states, rows behind / before the states, on one buffer and on 600 MB of them in turn:
+//   bf16  64 x 128,256   7.2 /  6.5    8.2 /  7.2          fp32  64 x 128,256  14.4 / 15.5   16.0 / 19.9
+//        128 x 128,256  12.9 / 10.7   14.4 / 11.9               128 x 128,256  27.0 / 30.7   28.2 / 33.2
+//        256 x 128,256  23.2 / 22.7   24.3 / 23.7               256 x  32,000  15.0 / 15.5   16.0 / 20.0
+//        256 x  32,000   7.6 /  6.8    8.3 /  7.4               256 x  20,000   9.6 /  8.8   11.7 / 11.5
+//         96 x  50,000   6.3 /  6.6    6.7 /  6.4
+// So bf16 rows are asked for early, and fp32 rows, twice the bytes, where they always were.  Rows that do not begin at
+// multiples of 16 bytes take longer to come back, which only large batches make up for (one buffer, 50,003 columns: batch 4
+// 4.7 / 5.0, 32 5.4 / 5.7, 96 7.1 / 7.7, 192 10.5 / 9.8; 128,257 columns: 32 6.4 / 6.5, 48 7.1 / 7.0, 96 11.1 / 10.2): they
+// are from kEarlyGroups workgroups on, three for every compute unit.  (A switch in one kernel instead of two: its registers
+// cost 256 x 128,256 2 us.)
 // Where the masks are given (two accesses) that gains nothing: batch 64 8.0 us either way, fp32 15.3 and 15.7.
-template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS, bool ENGINE>
+constexpr int kEarlyGroups = 768;
+template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS, int MASKS>
 __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) {
 
     const int ct = blockIdx.x % a.col_tiles;
@@ -96,18 +111,17 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
     const uint32_t valid_mask = (1u << nvalid) - 1u;
     const bool full = nvalid == kCols;
 
+    constexpr bool ENGINE = MASKS != MASKS_GIVEN, EARLY = MASKS == MASKS_OF_STATES_EARLY;
+    static_assert(!EARLY || LOGITS == LOGITS_BF16, "");
     i32x4_any ids[2];
-    constexpr int kPieces = LOGITS == LOGITS_F32 ? 2 : 1;  // 16-byte pieces of a thread's eight logits
-    u32x4 rows[ENGINE ? kRowsStream : 1][kPieces];
-    if (ENGINE && full) {
+    u32x4 rows[EARLY ? kRowsStream : 1];
+    if (EARLY && full) {
         ids[0] = reinterpret_cast<const i32x4_any *>(a.class_of_token + col0)[0];
         ids[1] = reinterpret_cast<const i32x4_any *>(a.class_of_token + col0)[1];
-        const char *at = reinterpret_cast<const char *>(a.logits) + ((int64_t)r0 * a.row_stride + col0) * (2 * kPieces);
+        const uint16_t *at = reinterpret_cast<const uint16_t *>(a.logits) + (int64_t)r0 * a.row_stride + col0;
 #pragma unroll
         for (int u = 0; u < kRowsStream; ++u)
-            if (u < nrows)
-#pragma unroll
-                for (int k = 0; k < kPieces; ++k) rows[u][k] = load16(at + (int64_t)u * a.row_stride * (2 * kPieces) + 16 * k);
+            if (u < nrows) rows[u] = load16(at + (int64_t)u * a.row_stride);
     }
 
     if (FROM_CLASS) {
@@ -149,8 +163,11 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
     if (FROM_CLASS) {
         int32_t k[kCols];
         if (full) {
-            const i32x4_any *p = reinterpret_cast<const i32x4_any *>(a.class_of_token + col0);
-            const i32x4_any lo = ENGINE ? ids[0] : p[0], hi = ENGINE ? ids[1] : p[1];
+            if (!EARLY) {
+                ids[0] = reinterpret_cast<const i32x4_any *>(a.class_of_token + col0)[0];
+                ids[1] = reinterpret_cast<const i32x4_any *>(a.class_of_token + col0)[1];
+            }
+            const i32x4_any lo = ids[0], hi = ids[1];
             k[0] = lo.x; k[1] = lo.y; k[2] = lo.z; k[3] = lo.w;
             k[4] = hi.x; k[5] = hi.y; k[6] = hi.z; k[7] = hi.w;
         } else {
@@ -200,12 +217,12 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
                 y.w = select_bf16_pair(x.w, (m >> 6) & 3u);
                 return y;
             };
-            if (ENGINE) {
+            if (EARLY) {
 #pragma unroll
                 for (int u = 0; u < kRowsStream; ++u) {
                     if (u >= nrows) break;
                     const uint32_t m = row_mask(u);
-                    store16(base + (int64_t)u * a.row_stride, masked(rows[ENGINE ? u : 0][0], m));
+                    store16(base + (int64_t)u * a.row_stride, masked(rows[EARLY ? u : 0], m));
                     store_bits(u, m);
                 }
                 return;
@@ -245,14 +262,6 @@ __device__ __forceinline__ void mask_tile(const MaskArgs &a, uint32_t *cls_lds) 
                 store16(base + (int64_t)row * a.row_stride + 4, hi);
                 store_bits(row, m);
             };
-            if (ENGINE) {
-#pragma unroll
-                for (int u = 0; u < kRowsStream; ++u) {
-                    if (u >= nrows) break;
-                    mask_row(u, rows[ENGINE ? u : 0][0], rows[ENGINE ? u : 0][kPieces - 1]);
-                }
-                return;
-            }
             auto do_rows = [&](int r, auto count) {
                 constexpr int N = decltype(count)::value;
                 u32x4 x[N][2];
@@ -296,10 +305,10 @@ __device__ __forceinline__ int32_t representative_of(int32_t t, const int32_t *c
     return (k >= 0 && k < C) ? rep_of_class[k] : -1;
 }
 
-template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS, bool ENGINE>
+template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS, int MASKS>
 __global__ __launch_bounds__(kThreads) void mask_kernel(MaskArgs a) {
     extern __shared__ uint32_t cls_lds[];  // [rows_per_block][Wc] when FROM_CLASS
-    mask_tile<LOGITS, FROM_CLASS, WRITE_BITS, ENGINE>(a, cls_lds);
+    mask_tile<LOGITS, FROM_CLASS, WRITE_BITS, MASKS>(a, cls_lds);
     // The first workgroup is the first to be scheduled and to finish its rows; the B dependent
     // look-ups then overlap with the streaming of all the others.
     if (a.map_tok && blockIdx.x == 0)
@@ -316,9 +325,9 @@ __global__ void map_to_rep_kernel(const int32_t *tok, int32_t B, const int32_t *
 
 constexpr size_t kMaxLds = 160 * 1024;
 
-template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS, bool ENGINE>
+template <int LOGITS, bool FROM_CLASS, bool WRITE_BITS, int MASKS>
 int launch_mask(const MaskArgs &args, int grid, size_t lds_bytes, hipStream_t stream) {
-    auto kern = mask_kernel<LOGITS, FROM_CLASS, WRITE_BITS, ENGINE>;
+    auto kern = mask_kernel<LOGITS, FROM_CLASS, WRITE_BITS, MASKS>;
     if (lds_bytes > 64 * 1024) {
         CFGZIP_TRY(check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -331,13 +340,19 @@ int launch_mask(const MaskArgs &args, int grid, size_t lds_bytes, hipStream_t st
 template <int LOGITS, bool FROM_CLASS>
 int dispatch_mask(const MaskArgs &args, bool write_bits, int grid, size_t lds, hipStream_t stream) {
     if constexpr (LOGITS != LOGITS_NONE && FROM_CLASS) {
-        if (args.state_mask)
-            return write_bits ? launch_mask<LOGITS, FROM_CLASS, true, true>(args, grid, lds, stream)
-                              : launch_mask<LOGITS, FROM_CLASS, false, true>(args, grid, lds, stream);
+        if (args.state_mask) {
+            if constexpr (LOGITS == LOGITS_BF16) {
+                if ((aligned_to(args.logits, 16) && args.row_stride % 8 == 0) || grid >= kEarlyGroups)
+                    return write_bits ? launch_mask<LOGITS, FROM_CLASS, true, MASKS_OF_STATES_EARLY>(args, grid, lds, stream)
+                                      : launch_mask<LOGITS, FROM_CLASS, false, MASKS_OF_STATES_EARLY>(args, grid, lds, stream);
+            }
+            return write_bits ? launch_mask<LOGITS, FROM_CLASS, true, MASKS_OF_STATES>(args, grid, lds, stream)
+                              : launch_mask<LOGITS, FROM_CLASS, false, MASKS_OF_STATES>(args, grid, lds, stream);
+        }
     }
-    if (write_bits) return launch_mask<LOGITS, FROM_CLASS, true, false>(args, grid, lds, stream);
+    if (write_bits) return launch_mask<LOGITS, FROM_CLASS, true, MASKS_GIVEN>(args, grid, lds, stream);
     if constexpr (LOGITS == LOGITS_NONE) return CFGZIP_E_INVALID;  // nothing to do
-    else return launch_mask<LOGITS, FROM_CLASS, false, false>(args, grid, lds, stream);
+    else return launch_mask<LOGITS, FROM_CLASS, false, MASKS_GIVEN>(args, grid, lds, stream);
 }
 
 // Shared host path of cfgzip_expand_mask and cfgzip_apply_mask.

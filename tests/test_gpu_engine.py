@@ -270,6 +270,48 @@ def test_engine_step_on_rows_of_any_alignment(lib, dtype, extra, shift):
     assert (logits_bits(buf) == want).all()
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("B,V,stride,shift", [
+    (3, 40_000, 40_000, 0),     # whole 16-byte units: the rows are asked for before the states
+    (5, 40_003, 40_008, 0),     # and a ragged end
+    (7, 40_008, 40_008, 1),     # off them, few workgroups: behind the states
+    (7, 40_003, 40_003, 0),
+    (188, 32_766, 32_766, 0),   # off them, 752 and 768 workgroups
+    (192, 32_766, 32_766, 0),
+    (190, 32_767, 32_769, 3)])
+def test_engine_step_before_and_behind_the_states(lib, B, V, stride, shift, dtype):
+    """The instances of the engine's kernel, on both sides of the line between them, against the three calls it stands for;
+    states and tokens out of range among them."""
+    from gpu_util import dev
+    print(f"case B={B} V={V} stride={stride} shift={shift} {dtype}", flush=True)
+    rng = np.random.default_rng(B + V)
+    C, S = 333, 40
+    words = {torch.bfloat16: torch.int16, torch.float32: torch.int32}[dtype]
+    buf = torch.randn(B * stride + shift + 8, device="cuda", generator=torch.Generator("cuda").manual_seed(B)).to(dtype)
+    logits = buf[shift:shift + B * stride].view(B, stride)[:, :V]
+    c = dev(rng.integers(0, C, size=V).astype(np.int32))
+    sig_rep = dev(rng.integers(0, S, size=(C, S)).astype(np.uint16))
+    state_mask = dev(rng.integers(0, 1 << 32, size=(S, words_for(C)), dtype=np.uint32))
+    tok, states = rng.integers(0, V, size=B).astype(np.int32), rng.integers(0, S, size=B).astype(np.int32)
+    tok[B // 2], states[B // 3] = V, S
+    tok, states = dev(tok), dev(states)
+    for given in (None, tok):
+        for bits in (None, torch.full((B, words_for(V)), -1, dtype=torch.int32, device="cuda")):
+            mine = buf.clone()
+            rows = mine[shift:shift + B * stride].view(B, stride)[:, :V]
+            got = lib.cfgzip_engine_step(rows, state_mask, C, c, sig_rep, given, states, tok_bits_out=bits)
+            want_states = states.clone()
+            if given is not None:
+                lib.cfgzip_advance_states(sig_rep, c, given, want_states)
+            cls = lib.cfgzip_class_masks(state_mask, C, want_states)
+            want_bits = lib.cfgzip_expand_mask(cls, C, c)
+            want = buf.clone()
+            lib.cfgzip_apply_mask(want[shift:shift + B * stride].view(B, stride)[:, :V], want_bits)
+            assert torch.equal(got, want_states)
+            assert torch.equal(mine.view(words), want.view(words))  # (what lies between and around the rows as well)
+            assert bits is None or torch.equal(bits, want_bits)
+
+
 def test_engine_step_argument_errors(lib):
     raw = lib.load_library()
     t = torch.zeros(256, dtype=torch.int32, device="cuda")
