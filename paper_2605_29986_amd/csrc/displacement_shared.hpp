@@ -805,10 +805,13 @@ __global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(Displac
                 if (L.byte_like[b] != b) continue;
                 const int lo = (int)L.byte_off[b], hi = (int)L.byte_off[b + 1];
                 if (i > lo && packed_head(L.prods[i - 1]) == head) continue;
-                int end = i + 1;  // (a thread for all of them: 676 productions of one pair, counted out, took it 50 us)
-                while (end < hi && end - i < 64 && packed_head(L.prods[end]) == head) ++end;
-                if (end - i < 64) L.pair[L.byte_number[b] * (uint32_t)a.g.N + head] = (uint16_t)(i | ((end - i) << 10));
-                else L.pairs_kept = 0;  // more than six bits
+                if (i + 63 < hi && packed_head(L.prods[i + 63]) == head) {  // more than six bits say
+                    L.pairs_kept = 0;  // (not counted out: of one pair's 676 productions that took 50 us)
+                    continue;
+                }
+                int end = i + 1;
+                while (end < hi && packed_head(L.prods[end]) == head) ++end;
+                L.pair[L.byte_number[b] * (uint32_t)a.g.N + head] = (uint16_t)(i | ((end - i) << 10));
             }
     }
     put_in_order();
