@@ -201,10 +201,10 @@ def test_sizes_around_the_runs_and_buckets(lib, V, shape):
 def _bucket(h):
     """The bucket, of 256, that classes with these hashes go to."""
     low, high = (h & np.uint64(0xFFFFFFFF)).astype(np.uint32), ((h >> np.uint64(32)) & np.uint64(31)).astype(np.uint32)
-    x = low ^ ((high << np.uint32(8)) * np.uint32(0x9E3779B1))
-    x = (x ^ (x >> np.uint32(16))) * np.uint32(0x85EBCA6B)
-    x = (x ^ (x >> np.uint32(13))) * np.uint32(0x2C1B3C6D)
-    return x >> np.uint32(24)
+    x = (low & np.uint32(0xFFFFFF)) * np.uint32(0x9E3779) + (low >> np.uint32(8))
+    x ^= x >> np.uint32(11)
+    x = (x & np.uint32(0xFFFFFF)) * np.uint32(0x85EBCB) + (x >> np.uint32(7))
+    return ((x >> np.uint32(24)) + np.uint32(37) * high) & np.uint32(255)
 
 
 def _hashes_of_one_bucket(n):
