@@ -514,15 +514,17 @@ __device__ __forceinline__ void table_number(const TableSettleArgs &a, unsigned 
 constexpr uint32_t kRowPart = 64;  // 16-byte units of a row that a wave compares
 __host__ __device__ inline int64_t table_row_parts(int32_t S) { return (S + 8 * (int)kRowPart - 1) / (8 * (int)kRowPart); }
 
-// STORE: the comparisons read the walk store, otherwise rows.  UNITS: rows of whole 16-byte units at multiples of that (an
-// instance of its own: 128,256 rows of 2 KB 39.5 us; at any address 42, and with both in one kernel's registers 49).
-template <bool STORE, bool UNITS>
+// What the comparisons read: the walk store, rows of whole 16-byte units at multiples of that, or rows at any address (an
+// instance each: 128,256 rows of 2 KB 39.5 us in whole units; at any address 42, and with both in one kernel's registers 49).
+enum : int { SETTLE_STORE, SETTLE_UNITS, SETTLE_ROWS };
+template <int FROM>
 __global__ __launch_bounds__(kTableThreads) void table_settle_kernel(TableSettleArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];  // table_rank_bytes, or the waves' staged vectors
     if ((int)blockIdx.x < a.number_blocks) {
         table_number(a, lds);
         return;
     }
+    constexpr bool STORE = FROM == SETTLE_STORE, UNITS = FROM == SETTLE_UNITS;
     constexpr int kWaves = kTableThreads / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint16_t *staged = reinterpret_cast<uint16_t *>(lds) + (size_t)wave * 2 * kWalkStoreMaxStride;  // STORE only

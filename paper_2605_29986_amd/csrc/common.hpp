@@ -11,6 +11,13 @@ namespace cfgzip {
 
 constexpr int kWave = 64;  // CDNA wavefront width
 
+// Sixteen and eight bytes at any address of whole elements: global memory takes such accesses at every alignment (a wave's
+// 1 KB run then touches one cache line more), so rows of any length are read and written like those of whole units.
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned long long u64x2_any __attribute__((ext_vector_type(2), aligned(8)));
+
 // Per-host-thread record of the last failing HIP status.
 void set_last_hip_error(hipError_t e);
 

@@ -32,13 +32,10 @@ enum : int { LOGITS_NONE = 0, LOGITS_BF16 = 1, LOGITS_F32 = 2 };
 // and the rows of logits, kRowsStream at the most, asked for behind the states or before
 enum : int { MASKS_GIVEN = 0, MASKS_OF_STATES = 1, MASKS_OF_STATES_EARLY = 2 };
 
-// native 16-byte vector (the nontemporal builtins do not take HIP's uint4 struct), and the same at any even address:
-// global memory takes 16-byte accesses at every alignment, and a wave's 1 KB run then touches one cache line more.
-// So rows of an odd length take the same path as aligned ones (64 rows of 50,003 bf16 logits, one by one where
-// unaligned: 11.2 us).
+// native 16-byte vector (the nontemporal builtins do not take HIP's uint4 struct).  In memory it may lie at any element
+// (u32x4_any): rows of an odd length take the same path as aligned ones (64 rows of 50,003 bf16 logits, one by one
+// where unaligned: 11.2 us).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
-typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 // streaming 16-byte accesses: every logit is touched exactly once per call
 __device__ __forceinline__ u32x4 load16(const void *p) {

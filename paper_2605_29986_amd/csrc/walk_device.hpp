@@ -29,6 +29,8 @@
 
 #include <type_traits>
 
+#include "common.hpp"
+
 namespace cfgzip {
 
 // Tt is over-allocated by this many entries so that a table entry >= S (a
@@ -42,13 +44,6 @@ constexpr int kMinWalkCap = 8192;   // walks (entries of w) held in LDS per batc
 // token, so a wave's table reads fall into fewer columns (measured on 4,096 states: 8 -> 147 us,
 // 4 -> 130 us, 2 -> 130 us, 1 -> 153 us per signature call).
 constexpr int kWalkGroup = 4;
-
-// Sixteen and eight bytes at any even address: global memory takes such accesses at every alignment, so the rows and tables
-// of an automaton with any number of states are read and written like those of one with a multiple of eight (a row of S
-// entries begins at a multiple of 2 S bytes).
-typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
-typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
-typedef unsigned long long u64x2_any __attribute__((ext_vector_type(2), aligned(8)));
 
 struct Tables {
     const uint16_t *Tt;
