@@ -347,7 +347,9 @@ int dispatch_mask(const MaskArgs &args, bool write_bits, int grid, size_t lds, h
                               : launch_mask<LOGITS, FROM_CLASS, false, MASKS_OF_STATES>(args, grid, lds, stream);
         }
     }
-    if (write_bits) return launch_mask<LOGITS, FROM_CLASS, true, MASKS_GIVEN>(args, grid, lds, stream);
+    if constexpr (FROM_CLASS) {  // (token masks handed in are not written again)
+        if (write_bits) return launch_mask<LOGITS, FROM_CLASS, true, MASKS_GIVEN>(args, grid, lds, stream);
+    }
     if constexpr (LOGITS == LOGITS_NONE) return CFGZIP_E_INVALID;  // nothing to do
     else return launch_mask<LOGITS, FROM_CLASS, false, MASKS_GIVEN>(args, grid, lds, stream);
 }
