@@ -518,7 +518,7 @@ __host__ __device__ inline int64_t table_row_parts(int32_t S) { return (S + 8 * 
 // instance each: 128,256 rows of 2 KB 39.5 us in whole units; at any address 42, and with both in one kernel's registers 49).
 enum : int { SETTLE_STORE, SETTLE_UNITS, SETTLE_ROWS };
 template <int FROM>
-__global__ __launch_bounds__(kTableThreads) void table_settle_kernel(TableSettleArgs a) {
+__global__ __launch_bounds__(kTableThreads) CFGZIP_OWN_PAGES void table_settle_kernel(TableSettleArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];  // table_rank_bytes, or the waves' staged vectors
     if ((int)blockIdx.x < a.number_blocks) {
         table_number(a, lds);

@@ -11,6 +11,12 @@ namespace cfgzip {
 
 constexpr int kWave = 64;  // CDNA wavefront width
 
+// A kernel whose code lies at multiples of 8 KB wherever the library is loaded.  Code objects lie behind each other in
+// pages of 4 KB, so a kernel's place changes with the size of any code before it, and a large kernel that runs once
+// between others that stream hundreds of MB comes cold from memory each time: displacements and classes of 128,256 tokens
+// with rows of 2 KB 242 us where the two kernels marked so begin at even pages, 247 to 253 at odd ones.
+#define CFGZIP_OWN_PAGES __attribute__((aligned(8192)))
+
 // Sixteen and eight bytes at any address of whole elements: global memory takes such accesses at every alignment (a wave's
 // 1 KB run then touches one cache line more), so rows of any length are read and written like those of whole units.
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));

@@ -25,12 +25,22 @@
 //
 // Measured: 128,256 tokens over the JSON grammar with rows of 1,024 entries 149 us (a wave per token took 510 us for
 // most tokens and 276 us for long digit runs), 32,000 over the statement grammar with rows of 256 100 us (210 us).
-// What bounds it: working out new sets (97 steps in a workgroup with 125 tokens over the JSON grammar, 165 with 501), as
-// much by the instructions of a step as by its chain of LDS accesses: a wave waits in 45 % of its cycles and issues
-// in 39 %, 14 vector and 14 scalar instructions for every LDS one.  A step takes 2.5 us on average and up to 3.4 on sets
-// of 45 configurations, and the longest token of a workgroup needs 25 to 32 one after the other.  Then writing the rows
-// (262 MB, 39-45 us).  Slower: the pairs of a step found by bit masks a lane instead of listed (185 us), the symbols of a
-// set's lists in registers to bring them into order (154 us; 5 to 10 % on grammars with large sets).
+// What bounds it is the slowest of the workgroups, and in it a chain of sets that nobody has met.  By the clock, us, with
+// rows of 256 entries:
+//                                                 JSON, 128,000 tokens   JSON, 32,000   statement, 32,000
+//   workgroups done, on average / the last              115 / 144           88 / 151        70 / 107
+//   last set worked out in them, on average / in any    102 / 131           76 / 133        60 /  93
+//   a wave, of its time                                  94                 49              52
+//     set-up                                              6.0                5.4             5.6
+//     steps worked out: how many, time               10.2, 24.2          5.9, 14.1       7.7, 18.5
+//     sets written out: how many, time                3.1, 17.2          1.5,  8.9       1.7,  7.9
+//     rows copied                                        10.9                2.8             2.6
+//     the rest, look-ups and waits for other waves       36                 18              17
+// A step takes 2.4 us on average and up to 3.4 on sets of 45 configurations, as much by its instructions as by its chain of
+// LDS accesses: a wave waits in 45 % of its cycles and issues in 39 %, 14 vector and 14 scalar instructions for every LDS
+// one.  Then, on a large vocabulary, the rows (262 MB, 39-45 us).  Slower: the pairs of a step found by bit masks a lane
+// instead of listed (185 us), the symbols of a set's lists in registers to bring them into order (154 us; 5 to 10 % on
+// grammars with large sets), a wave of few tokens that waits for all of them before it writes any (JSON 1 to 5 %).
 //
 // Everything in LDS is bounded.  A token that would need more (more than 128 successors at a byte, more cells,
 // sets or row entries than there is room for) goes to the list of the passes behind this one, which take it alone.
@@ -693,7 +703,7 @@ __device__ __forceinline__ u64 sh_write_set(const DisplacementArgs &a, SharedLds
 // there is none, writes the rows of those that are through; if none is, takes more tokens; and waits only if there are
 // none left.
 template <bool ROWS16>  // rows start at multiples of 16 bytes
-__global__ __launch_bounds__(kShThreads) void displacement_shared_kernel(DisplacementArgs a, int per_group) {
+__global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shared_kernel(DisplacementArgs a, int per_group) {
     __shared__ SharedLds L;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t group0 = (int64_t)blockIdx.x * per_group;
