@@ -189,7 +189,7 @@ def test_sort_starts_over_when_the_store_cannot_be_used(lib, case, stored):
 @pytest.mark.parametrize("shape", ["one class", "last byte", "distinct"])
 @pytest.mark.parametrize("V", [63, 64, 6143, 6144, 6145, 7168, 7169])
 def test_sizes_around_the_runs_and_buckets(lib, V, shape):
-    """Up to 6,144 tokens the buckets look at the tokens themselves, above at the entries of runs of 1,024."""
+    """Up to 7,168 tokens the buckets look at the tokens themselves, above at the entries of runs of 1,024 (6,144: whole runs)."""
     print(f"case V={V} {shape}", flush=True)
     vocab, table = _case(shape, V, V + 1)
     _, coll = _check_build(lib, vocab, table)
