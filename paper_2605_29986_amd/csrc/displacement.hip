@@ -247,17 +247,6 @@ __global__ __launch_bounds__(1024) void byte_like_kernel(Grammar g, GrammarWorks
     find_like_bytes(g, w, w.byte_off, hash, [&](int i) { return w.prod_packed[i]; });
 }
 
-// OR over the 64 lanes (all of them active), the same for every lane.
-__device__ __forceinline__ uint32_t wave_or32(uint32_t v) {
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, true);
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, true);
-    return __builtin_amdgcn_readlane(v, 63);
-}
-
 // All tables of a small grammar in one launch, by one workgroup with the two matrices in LDS (eleven launches
 // otherwise, each a few us of waiting for the one before).
 constexpr int kSmallSymbols = 128;

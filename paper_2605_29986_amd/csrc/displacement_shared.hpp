@@ -23,24 +23,19 @@
 // What a token's set is written as (the canonical row and its hash) is worked out once per set too; writing a row
 // is then a copy out of LDS, and writing the rows is what bounds the kernel on a large vocabulary.
 //
-// Measured: 128,256 tokens over the JSON grammar with rows of 1,024 entries 149 us (a wave per token took 510 us for
-// most tokens and 276 us for long digit runs), 32,000 over the statement grammar with rows of 256 100 us (210 us).
-// What bounds it is the slowest of the workgroups, and in it a chain of sets that nobody has met.  By the clock, us, with
-// rows of 256 entries:
-//                                                 JSON, 128,000 tokens   JSON, 32,000   statement, 32,000
-//   workgroups done, on average / the last              115 / 144           88 / 151        70 / 107
-//   last set worked out in them, on average / in any    102 / 131           76 / 133        60 /  93
-//   a wave, of its time                                  94                 49              52
-//     set-up                                              6.0                5.4             5.6
-//     steps worked out: how many, time               10.2, 24.2          5.9, 14.1       7.7, 18.5
-//     sets written out: how many, time                3.1, 17.2          1.5,  8.9       1.7,  7.9
-//     rows copied                                        10.9                2.8             2.6
-//     the rest, look-ups and waits for other waves       36                 18              17
-// A step takes 2.4 us on average and up to 3.4 on sets of 45 configurations, as much by its instructions as by its chain of
-// LDS accesses: a wave waits in 45 % of its cycles and issues in 39 %, 14 vector and 14 scalar instructions for every LDS
-// one.  Then, on a large vocabulary, the rows (262 MB, 39-45 us).  Slower: the pairs of a step found by bit masks a lane
-// instead of listed (185 us), the symbols of a set's lists in registers to bring them into order (154 us; 5 to 10 % on
-// grammars with large sets), a wave of few tokens that waits for all of them before it writes any (JSON 1 to 5 %).
+// Measured: 128,256 tokens over the JSON grammar with rows of 1,024 entries 116 us (a wave per token took 510 us for
+// most tokens and 276 us for long digit runs), 32,000 over the statement grammar with rows of 256 80 us (210 us).
+// What bounds it is instruction issue (the vector units are busy for 60 % of the kernel, the scalar one about as long), and
+// in the workgroup that is done last a chain of sets that nobody has met.  A step alone in its compute unit takes 2.2 us,
+// 670 instructions and twenty LDS accesses (the steps of 32 digits over the JSON grammar, sets of 20 to 51 configurations;
+// 3.75 us with the pairs of configuration and production listed in LDS, the next set looked up and loaded again, and a
+// production read through a pointer that may be global, which waits for all rows on their way to memory).  A wave of the
+// JSON workload, us: set-up 10, steps 23 (ten of them), sets written out 18 (three), rows 23, the rest, look-ups and waits
+// for other waves, 27; of the statement grammar 8, 18 (eight), 7 (two), 3 and 11, and the workgroup that is done last takes
+// half as long again as the average one.  Slower: longest tokens first for some of the waves and shortest first for the
+// others (JSON call 213 to 242 us, 208 so; the rows then go out earlier, but the chain is what counts), rows two at a time,
+// claims asked for ahead of a step's first look-ups (2 %: more instructions), the symbols of a set's lists in registers to
+// bring them into order, a wave of few tokens that waits for all of them before it writes any (JSON 1 to 5 %).
 //
 // Everything in LDS is bounded.  A token that would need more (more than 128 successors at a byte, more cells,
 // sets or row entries than there is room for) goes to the list of the passes behind this one, which take it alone.
@@ -70,6 +65,9 @@ constexpr int kShOut = 18432;       // row entries of all sets written so far (3
 constexpr int kShProds = 1024;      // productions kept in LDS (8 KB); of a larger grammar none are
 constexpr int kShAdj = 512;         // words of the relation kept in LDS (2 KB); of a larger one none are
 constexpr int kShPairs = 2048;      // (byte, symbol) pairs whose productions are looked up directly (4 KB)
+constexpr int kShFollow = 2048;     // (byte, symbol consumed last) pairs whose backtracks are looked up directly, and a word
+                                    // a byte (8 KB)
+constexpr int kShFew = 32;          // productions a byte has at the most where they are: a bit each
 constexpr int kShBatch = 1024;      // tokens a workgroup sorts by length at a time
 constexpr int kShBytes = 6144;      // their bytes, kept in LDS; if there are more they are read from memory
 constexpr int kShLengths = 64;      // lengths told apart in sorting
@@ -119,63 +117,111 @@ constexpr uint32_t kWorkedOut = 0x3FFC; // another wave is at it
 constexpr uint32_t kByTheWave = 0x3FFB; // never published: what follows takes a whole wave to work out
 constexpr uint32_t kNextEmpty = ~0u;
 
-// what a set is written as: position of its row entries (in units of four), their number, or one of these
-constexpr u64 kRowUnknown = ~0ull;
-constexpr u64 kRowGiveUp = ~0ull - 1;
-constexpr u64 kRowTooLong = ~0ull - 2;
-constexpr u64 kRowWorkedOut = ~0ull - 3;  // another wave is at it
+// what a set is written as: position of its row entries (in units of eight) above their number (13 bits), or one of these
+constexpr uint32_t kRowUnknown = ~0u;
+constexpr uint32_t kRowGiveUp = ~0u - 1;
+constexpr uint32_t kRowTooLong = ~0u - 2;
+constexpr uint32_t kRowWorkedOut = ~0u - 3;  // another wave is at it
+constexpr int kRowBits = 13;
+static_assert(kShOut / 8 < 1 << (32 - kRowBits - 1), "no place looks like one of these");
+__device__ __forceinline__ uint32_t row_entries(uint32_t row) { return row & ((1u << kRowBits) - 1u); }
+__device__ __forceinline__ uint32_t row_at(uint32_t row) { return (row >> kRowBits) * 8u; }
 
 struct SharedLds {
     __align__(16) uint16_t out[kShOut];
     uint32_t pool[kShPool];
     u64 sets[kShSets];
-    u64 row[kShSets];
+    uint32_t row[kShSets];
     u64 row_hash[kShSets];
-    uint32_t work[kShWaves][2 * kShFrontier];
+    __align__(16) uint32_t work[kShWaves][2 * kShFrontier];
     uint32_t seen[kShWaves][kShSeen];
     uint32_t cells[kShCells];
     uint32_t next[kShNext];
     u64 prods[kShProds];
-    uint32_t adj[kShAdj];
+    union {
+        uint32_t adj[kShAdj];   // as long as `follow` is not kept
+        uint32_t follow[kShFollow];  // [number of the byte][symbol consumed last, N: none]: which of the byte's productions may
+    };                          // come next where the stack is empty, a bit each; [N + 1]: the first of them
     uint32_t byte_off[257];
     uint16_t pair[kShPairs];  // [number of the byte among those with productions of their own][symbol]: first production
                               // (10 bits), how many (6)
-    uint8_t byte_number[256];
-    uint32_t own[8];          // bytes that are their own byte_like
+    uint8_t byte_number[256];  // the bytes that are the first with their productions numbered, the others as the first
+    uint32_t own[8];           // bytes that are their own byte_like
     uint32_t pairs_kept;      // whether `pair` holds what the productions say
+    uint32_t few_each;        // no byte has more productions than `follow` has bits
+    uint32_t follow_kept;     // whether `follow` holds what the relation says
     uint32_t pool_top, out_top, cursor;
     uint32_t scattered;      // some token's bytes do not lie where the token before ends
     uint32_t of_length[kShLengths];
     uint16_t order[kShBatch], start[kShBatch + 2];  // the batch's tokens, longest first; where each one's bytes begin
-    uint8_t byte_like[256];  // the first byte with the same productions
-    uint8_t bytes[kShBytes];  // already as byte_like has them
+    uint8_t like_of[256];  // [number]: the byte that has it
+    uint8_t bytes[kShBytes];  // already as byte_number has them
 };
+
+// The kernel's arguments (its first), loaded anew: where they are seldom needed they then take no scalar registers in
+// between, of which the walk has too few (107 of them moved to and from vector registers otherwise, and back).
+__device__ __forceinline__ DisplacementArgs sh_arguments() {
+    auto from = reinterpret_cast<const __attribute__((address_space(4))) uint32_t *>(
+        reinterpret_cast<uintptr_t>(__builtin_amdgcn_kernarg_segment_ptr()));
+    asm volatile("" : "+s"(from));
+    DisplacementArgs a;
+    static_assert(sizeof(a) % 4 == 0, "");
+#pragma unroll
+    for (size_t i = 0; i < sizeof(a) / 4; ++i) {
+        const uint32_t w = from[i];
+        __builtin_memcpy(reinterpret_cast<char *>(&a) + 4 * i, &w, 4);
+    }
+    return a;
+}
 
 template <typename T>
 __device__ __forceinline__ T lds_look(const T *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-// what this wave has written to LDS comes before what it publishes next, and what it reads after a look at
-// something published is what was written before that (LDS operations of a wave are done in order)
-__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup"); }
+// What this wave has written to LDS comes before what it publishes next, and what it reads after a look at something
+// published is what was written before that: LDS does the operations of a wave in the order in which they are issued, so
+// only the compiler has to be told (a fence for the workgroup also waits until all of them are done, an access's time each).
+__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 __device__ __forceinline__ uint32_t wave_read(uint32_t v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
 __device__ __forceinline__ u64 wave_read64(u64 v, int lane) {
     return ((u64)wave_read((uint32_t)(v >> 32), lane) << 32) | wave_read((uint32_t)v, lane);
 }
-__device__ __forceinline__ u64 wave_sum64(u64 v) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
 // Sum over the 64 lanes (all of them active), the same for every lane: row shifts by 1, 2, 4, 8, then across rows.
-__device__ __forceinline__ uint32_t wave_sum32(uint32_t v) {
+__device__ __forceinline__ u64 wave_sum64(u64 v) {
+    auto moved = [](u64 x, auto ctrl, auto rows) -> u64 {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, decltype(ctrl)::value, decltype(rows)::value, 0xF, true);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), decltype(ctrl)::value, decltype(rows)::value, 0xF, true);
+        return ((u64)hi << 32) | lo;
+    };
+    v += moved(v, std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{});
+    v += moved(v, std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{});
+    v += moved(v, std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{});
+    v += moved(v, std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{});
+    v += moved(v, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});
+    v += moved(v, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});
+    return wave_read64(v, 63);
+}
+// Sum over the lanes up to this one (all 64 are active): row shifts by 1, 2, 4, 8, then across rows.
+__device__ __forceinline__ uint32_t wave_upto32(uint32_t v) {
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, true);
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, true);
+    return v;
+}
+// Sum over all of them, the same for every lane.
+__device__ __forceinline__ uint32_t wave_sum32(uint32_t v) { return wave_read(wave_upto32(v), 63); }
+// OR over the 64 lanes (all of them active), the same for every lane.
+__device__ __forceinline__ uint32_t wave_or32(uint32_t v) {
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, true);
     return wave_read(v, 63);
 }
 
@@ -201,25 +247,35 @@ __device__ __forceinline__ uint32_t cell_slot(uint32_t w) {
     static_assert(kShCells == 1 << 11, "eleven bits of hash; a number (slot + 1) fits twelve");
     return (w * 0x9E3779B1u) >> (32 - 11);
 }
-// The number of the cell `w` whose slot `at` was found to hold `seen` after an attempt to claim it (0: claimed); 0 if
-// the table is full (`full` is set).
-__device__ __forceinline__ uint32_t sh_settle_cell(SharedLds &L, uint32_t w, uint32_t at, uint32_t seen, bool &full) {
-    for (int probe = 0; probe < kShProbes; ++probe) {
-        if (seen == 0u || seen == w) return at + 1;
-        at = (at + 1) & (kShCells - 1);
-        seen = atomicCAS(&L.cells[at], 0u, w);
+// The numbers of two cells, of which either may be 0 (none wanted, none comes back); 0 and `full` if the table is full.
+// They are claimed together, so that the attempts of one do not wait for the other's.
+__device__ __forceinline__ void sh_two_cells(SharedLds &L, uint32_t w0, uint32_t w1, uint32_t &id0, uint32_t &id1, bool &full) {
+    uint32_t at0 = cell_slot(w0), at1 = cell_slot(w1), seen0 = 0, seen1 = 0;
+    if (w0) seen0 = atomicCAS(&L.cells[at0], 0u, w0);
+    if (w1) seen1 = atomicCAS(&L.cells[at1], 0u, w1);
+    bool open0 = seen0 != 0u && seen0 != w0, open1 = seen1 != 0u && seen1 != w1;
+#pragma unroll 1
+    for (int probe = 1; (open0 || open1) && probe < kShProbes; ++probe) {
+        if (open0) {
+            at0 = (at0 + 1) & (kShCells - 1);
+            seen0 = atomicCAS(&L.cells[at0], 0u, w0);
+        }
+        if (open1) {
+            at1 = (at1 + 1) & (kShCells - 1);
+            seen1 = atomicCAS(&L.cells[at1], 0u, w1);
+        }
+        open0 = open0 && seen0 != 0u && seen0 != w0;
+        open1 = open1 && seen1 != 0u && seen1 != w1;
     }
-    full = true;
-    return 0;
+    full = full || open0 || open1;
+    id0 = w0 && !open0 ? at0 + 1 : 0u;
+    id1 = w1 && !open1 ? at1 + 1 : 0u;
 }
 // The number of the list of `length` symbols that is `symbol` in front of `rest`; 0 if the table is full.
 __device__ __forceinline__ uint32_t sh_cons(SharedLds &L, uint32_t rest, uint32_t symbol, uint32_t length, bool &full) {
-    const uint32_t w = cell_word(rest, symbol, length), at = cell_slot(w);
-    return sh_settle_cell(L, w, at, atomicCAS(&L.cells[at], 0u, w), full);
-}
-
-__device__ __forceinline__ uint32_t list_length(const SharedLds &L, uint32_t id) {
-    return id ? cell_length(lds_look(&L.cells[id - 1])) : 0u;
+    uint32_t id, none;
+    sh_two_cells(L, cell_word(rest, symbol, length), 0u, id, none, full);
+    return id;
 }
 
 __device__ __forceinline__ uint32_t next_slot(uint32_t key) { return (key * 0x9E3779B1u) >> (32 - 11); }
@@ -229,6 +285,7 @@ static_assert(kShNext == 1 << 11, "eleven bits of hash");
 __device__ __forceinline__ uint32_t sh_known(const SharedLds &L, uint32_t set, uint32_t like) {
     const uint32_t key = (set << 8) | like;
     uint32_t at = next_slot(key);
+#pragma unroll 1
     for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShNext - 1)) {
         const uint32_t w = lds_look(&L.next[at]);
         if (w == kNextEmpty) return kNextEmpty;
@@ -237,11 +294,12 @@ __device__ __forceinline__ uint32_t sh_known(const SharedLds &L, uint32_t set, u
     return kNextEmpty;
 }
 
-// Takes on working out what follows `set` on `like`: the slot to publish it in, -1 if another wave was faster, -2
-// if the table is full (the successor is then worked out again by everybody who comes here).
+// Takes on working out what follows `set` on `like`: the slot to publish it in, -1 if it is known or another wave was
+// faster, -2 if the table is full (the successor is then worked out again by everybody who comes here).
 __device__ __forceinline__ int sh_claim(SharedLds &L, uint32_t set, uint32_t like) {
     const uint32_t key = (set << 8) | like;
     uint32_t at = next_slot(key);
+#pragma unroll 1
     for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShNext - 1)) {
         const uint32_t seen = atomicCAS(&L.next[at], kNextEmpty, (key << kNextBits) | kWorkedOut);
         if (seen == kNextEmpty) return (int)at;
@@ -254,6 +312,7 @@ __device__ __forceinline__ int sh_claim(SharedLds &L, uint32_t set, uint32_t lik
 __device__ __forceinline__ void sh_publish(SharedLds &L, uint32_t set, uint32_t like, uint32_t following) {
     const uint32_t key = (set << 8) | like;
     uint32_t at = next_slot(key);
+#pragma unroll 1
     for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShNext - 1)) {
         const uint32_t seen = atomicCAS(&L.next[at], kNextEmpty, (key << kNextBits) | following);
         if (seen == kNextEmpty || (seen >> kNextBits) == key) return;
@@ -262,10 +321,11 @@ __device__ __forceinline__ void sh_publish(SharedLds &L, uint32_t set, uint32_t 
 
 // Different words of a wave, two a lane at the most: which of them are the first of their value, where they go when
 // packed, how many there are, and a hash that does not depend on their order.
+template <int PER>
 struct Different {
-    uint32_t word[2];
-    bool first[2];
-    int at[2];
+    uint32_t word[PER];
+    bool first[PER];
+    int at[PER];
     int n;
     uint32_t sum;
 };
@@ -280,18 +340,18 @@ static_assert(kShSeen == 256, "eight bits of hash");
 // `seen` starts empty (all kNoWord) and holds the words afterwards; seen_clear empties it.  One pass of
 // compare-and-swaps instead of a sort: comparing 45 words with each other one readlane after the other took as long as
 // all the rest of a step.
-__device__ __forceinline__ Different find_different(uint32_t *seen, uint32_t a, uint32_t b, int lane) {
-    Different d;
-    d.word[0] = a;
-    d.word[1] = b;
+template <int PER>
+__device__ __forceinline__ Different<PER> find_different(uint32_t *seen, const uint32_t (&words)[PER], int lane) {
+    Different<PER> d;
     uint32_t h = 0;
     d.n = 0;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const uint32_t w = d.word[u];
+    for (int u = 0; u < PER; ++u) {
+        const uint32_t w = d.word[u] = words[u];
         d.first[u] = false;
         if (w != kNoWord) {
             uint32_t at = seen_slot(w);
+#pragma unroll 1
             for (int probe = 0; probe < kShSeen; ++probe, at = (at + 1) & (kShSeen - 1)) {
                 const uint32_t old = atomicCAS(&seen[at], kNoWord, w);
                 d.first[u] = old == kNoWord;
@@ -323,32 +383,51 @@ __device__ __forceinline__ void seen_clear(uint32_t *seen, int lane) {
 
 __device__ __forceinline__ uint32_t set_hash(uint32_t sum, uint32_t n) { return (sum ^ (sum >> 15)) * 0x2C1B3C6Du + n; }
 
+// Room in the pool that a wave has reserved and not used yet.
+struct PoolRoom {
+    int at, n;
+    bool none_left;
+};
+// Sees to it that there is room for n configurations, as far as there is any.  Asked for before it is known whether the set
+// is new, so that nobody waits for the answer; what a known set leaves unused is there for the next.
+__device__ __forceinline__ void sh_reserve(SharedLds &L, PoolRoom &room, int n, int lane) {
+    if (room.n >= n || room.none_left) return;
+    int top = 0;
+    if (lane == 0) top = (int)atomicAdd(&L.pool_top, (uint32_t)n);
+    room.at = __builtin_amdgcn_readfirstlane(top);
+    room.n = n;
+}
 // The number of the set of the words `d` (which `seen` holds); kGiveUp if there is no room.  Two sets of equal size
 // are equal if each word of one is in the other.
-__device__ __forceinline__ uint32_t sh_set_number(SharedLds &L, const uint32_t *seen, const Different &d, int lane) {
-    const uint32_t h = set_hash(d.sum, (uint32_t)d.n);
-    const u64 tag = (u64)(h >> 8) << 24;
-    uint32_t at = h & (kShSets - 1);
-    int reserved = -1;
-    for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShSets - 1)) {
-        // one lane's look for the whole wave: the lanes of a read need not see the same moment of a slot that another
-        // wave is filling, and the branch below takes the whole wave (its words go to the pool together)
-        u64 found = wave_read64(lds_look(&L.sets[at]), 0);
-        if (found == kShEmpty) {
-            if (reserved < 0) {
-                int top = 0;
-                if (lane == 0) top = (int)atomicAdd(&L.pool_top, (uint32_t)d.n);
-                reserved = __builtin_amdgcn_readfirstlane(top);
-                if (reserved + d.n > kShPool) return kGiveUp;
+template <int PER>
+__device__ __forceinline__ uint32_t sh_set_number(SharedLds &L, PoolRoom &room, const uint32_t *seen, const Different<PER> &d,
+                                                  int lane) {
+    if (room.n && room.at + room.n > kShPool) {
+        room.n = 0;
+        room.none_left = true;
+    }
+    const bool fits = d.n <= room.n;
+    if (fits) {
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    if (d.first[u]) L.pool[reserved + d.at[u]] = d.word[u];
-                lds_order();
-            }
-            const u64 w = tag | ((u64)reserved << 8) | (u64)d.n;
-            if (lane == 0) found = atomicCAS(&L.sets[at], kShEmpty, w);
-            found = wave_read64(found, 0);
-            if (found == kShEmpty) return at;
+        for (int u = 0; u < PER; ++u)
+            if (d.first[u]) L.pool[room.at + d.at[u]] = d.word[u];
+        lds_order();
+    }
+    const uint32_t h = set_hash(d.sum, (uint32_t)d.n);
+    const u64 tag = (u64)(h >> 8) << 24, mine = tag | ((u64)room.at << 8) | (u64)d.n;
+    uint32_t at = h & (kShSets - 1);
+#pragma unroll 1
+    for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShSets - 1)) {
+        // one lane's access for the whole wave: the lanes of a read need not see the same moment of a slot that another
+        // wave is filling, and the branches below take the whole wave
+        u64 found = 0;
+        if (lane == 0) found = fits ? atomicCAS(&L.sets[at], kShEmpty, mine) : lds_look(&L.sets[at]);
+        found = wave_read64(found, 0);
+        if (found == kShEmpty) {
+            if (!fits) return kGiveUp;
+            room.at += d.n;
+            room.n -= d.n;
+            return at;
         }
         if ((found >> 24 << 24) == tag && (int)set_size(found) == d.n) {
             lds_order();
@@ -362,51 +441,64 @@ __device__ __forceinline__ uint32_t sh_set_number(SharedLds &L, const uint32_t *
 }
 
 __device__ __forceinline__ u64 sh_production(const DisplacementArgs &a, const SharedLds &L, int i) {
-    return a.g.P <= kShProds ? L.prods[i] : a.prod_packed[i];
+    // (looks that the compiler cannot join into one access through a generic pointer, which would wait for the rows too)
+    return a.g.P <= kShProds ? lds_look(&L.prods[i]) : a.prod_packed[i];
 }
 // Whether the head of production `p` may come right after the symbol `last` when the stack is empty.
 __device__ __forceinline__ bool sh_may_follow(const DisplacementArgs &a, const SharedLds &L, u64 p, uint32_t last) {
     const uint32_t word = packed_head(p) * (uint32_t)a.g.W + (last >> 5);
-    return ((a.g.N * a.g.W <= kShAdj ? L.adj[word] : a.adj[word]) >> (last & 31)) & 1u;
+    return ((a.g.N * a.g.W <= kShAdj && !L.follow_kept ? lds_look(&L.adj[word]) : a.adj[word]) >> (last & 31)) & 1u;
 }
 
-// A configuration after production i.  `crossed`: a bound of the interface is broken; `full`: there is no room.
-__device__ __forceinline__ uint32_t sh_carry_out(const DisplacementArgs &a, SharedLds &L, uint32_t config, int i,
-                                                 bool &full, bool &crossed) {
-    const Grammar &g = a.g;
-    const u64 p = sh_production(a, L, i);
-    const uint32_t head = packed_head(p), stack = sh_stack(config);
-    uint32_t queue = sh_queue(config), rest = 0, rest_length = 0;
-    const uint32_t cell = stack ? lds_look(&L.cells[stack - 1]) : (queue ? lds_look(&L.cells[queue - 1]) : 0u);
-    int length = (int)packed_length(p);
-    const bool is_long = length == (int)kLongBody;
-    if (is_long) length = body_len(g, i);
-    uint32_t queued = 0;
-    if (stack) {
-        rest = cell_rest(cell);
-        rest_length = cell_length(cell) - 1u;
-    } else {
-        queued = cell_length(cell) + 1u;
-    }
+// Where `follow` has what may come after the symbol `last` on a byte; behind a byte's symbols, the byte's first production.
+__device__ __forceinline__ uint32_t sh_follow(const DisplacementArgs &a, uint32_t byte_number, uint32_t last) {
+    return byte_number * (uint32_t)(a.g.N + 2) + (last == kNoSymbol ? (uint32_t)a.g.N : last);
+}
+__device__ __forceinline__ uint32_t sh_follow_first(const DisplacementArgs &a, uint32_t byte_number) {
+    return byte_number * (uint32_t)(a.g.N + 2) + (uint32_t)a.g.N + 1u;
+}
+
+// The cell that says what may come next of a configuration: the top of its stack, or the end of its queue where the
+// stack is empty; 0 where both are.
+__device__ __forceinline__ uint32_t sh_end_cell(const SharedLds &L, uint32_t config) {
+    const uint32_t id = sh_stack(config) ? sh_stack(config) : sh_queue(config);
+    return id ? lds_look(&L.cells[id - 1]) : 0u;
+}
+
+// A configuration, whose end is `cell`, after a production with the head `head` and a body of `length` symbols.
+// `crossed`: a bound of the interface is broken; `full`: there is no room.
+template <typename Symbol>
+__device__ __forceinline__ uint32_t sh_carry_out(SharedLds &L, uint32_t config, uint32_t cell, uint32_t head, int length,
+                                                 const Symbol &symbol, bool &full, bool &crossed) {
+    const bool pops = sh_stack(config) != 0u;
+    uint32_t queue = sh_queue(config), rest = pops ? cell_rest(cell) : 0u, rest_length = pops ? cell_length(cell) - 1u : 0u;
+    const uint32_t queued = pops ? 0u : cell_length(cell) + 1u;
     if (queued > (uint32_t)kShMaxList || rest_length + (uint32_t)length > (uint32_t)kShMaxList) {
         crossed = true;
         return kNoWord;
     }
-    const int off = is_long ? g.body_off[i] : 0;
-    auto symbol = [&](int k) -> uint32_t { return is_long ? (uint32_t)g.body[off + k] & 0xFFu : packed_symbol(p, k); };
-    // the queue's new cell and the stack's first are claimed together: neither needs the other
-    const uint32_t wq = cell_word(queue, head, queued), ws = length ? cell_word(rest, symbol(length - 1), rest_length + 1u) : 0u;
-    const uint32_t at_q = cell_slot(wq), at_s = cell_slot(ws);
-    uint32_t seen_q = 0, seen_s = 0;
-    if (queued) seen_q = atomicCAS(&L.cells[at_q], 0u, wq);
-    if (length) seen_s = atomicCAS(&L.cells[at_s], 0u, ws);
-    if (queued) queue = sh_settle_cell(L, wq, at_q, seen_q, full);
+    // the queue's new cell and the stack's first: neither needs the other
+    uint32_t queue_end, top;
+    sh_two_cells(L, queued ? cell_word(queue, head, queued) : 0u,
+                 length ? cell_word(rest, symbol(length - 1), rest_length + 1u) : 0u, queue_end, top, full);
+    if (queued) queue = queue_end;
     if (length) {
-        rest = sh_settle_cell(L, ws, at_s, seen_s, full);
+        rest = top;
         ++rest_length;
+#pragma unroll 1
         for (int k = length - 2; k >= 0; --k) rest = sh_cons(L, rest, symbol(k), ++rest_length, full);
     }
     return sh_config(queue, rest, head);
+}
+// The same after production i, whose body may be of any length.
+__device__ __forceinline__ uint32_t sh_carry_out(const DisplacementArgs &a, SharedLds &L, uint32_t config, uint32_t cell, int i,
+                                                 bool &full, bool &crossed) {
+    const u64 p = sh_production(a, L, i);
+    const bool is_long = packed_length(p) == kLongBody;
+    const int off = is_long ? a.g.body_off[i] : 0;
+    return sh_carry_out(
+        L, config, cell, packed_head(p), is_long ? body_len(a.g, i) : (int)packed_length(p),
+        [&](int k) -> uint32_t { return is_long ? (uint32_t)a.g.body[off + k] & 0xFFu : packed_symbol(p, k); }, full, crossed);
 }
 
 // One byte of Algorithm 1 by one lane, where it is simple enough: a set of one configuration that one production at
@@ -416,20 +508,24 @@ __device__ __forceinline__ uint32_t sh_carry_out(const DisplacementArgs &a, Shar
 // per token, without the shared walk, 125, 172, 220.  What is left is that the tables fill up (from 8 bytes on) and that
 // every token's row is its own.  Nothing is claimed first: two lanes that work out the same come to the same.
 constexpr int kFewProductions = 4;
-__device__ __forceinline__ uint32_t sh_step_alone(const DisplacementArgs &a, SharedLds &L, uint32_t set, uint32_t like,
+__device__ __forceinline__ uint32_t sh_step_alone(const DisplacementArgs &a, SharedLds &L, uint32_t set, uint32_t number,
                                                   uint32_t dead) {
     const u64 w = lds_look(&L.sets[set]);
     lds_order();
     if (set_size(w) != 1u) return kByTheWave;
-    const uint32_t config = L.pool[set_at(w)], stack = sh_stack(config), last = sh_last(config);
+    const uint32_t config = L.pool[set_at(w)], stack = sh_stack(config), last = sh_last(config), cell = sh_end_cell(L, config);
     int i = 0, n = 0;
     if (stack) {
         if (L.pairs_kept == 0u) return kByTheWave;
-        const uint32_t top = cell_symbol(lds_look(&L.cells[stack - 1]));
-        const uint32_t e = L.pair[L.byte_number[like] * (uint32_t)a.g.N + top];
+        const uint32_t e = L.pair[number * (uint32_t)a.g.N + cell_symbol(cell)];
         i = (int)(e & 0x3FFu);
         n = (int)(e >> 10);
+    } else if (L.follow_kept) {
+        const uint32_t may = L.follow[sh_follow(a, number, last)];
+        n = __popc(may);
+        i = (int)L.follow[sh_follow_first(a, number)] + (n ? __ffs(may) - 1 : 0);
     } else {
+        const uint32_t like = L.like_of[number];
         const int lo = (int)L.byte_off[like], hi = (int)L.byte_off[like + 1];
         if (hi - lo > kFewProductions) return kByTheWave;
         for (int k = lo; k < hi; ++k) {
@@ -441,13 +537,14 @@ __device__ __forceinline__ uint32_t sh_step_alone(const DisplacementArgs &a, Sha
     if (n == 0) return dead;
     if (n > 1) return kByTheWave;
     bool full = false, crossed = false;
-    const uint32_t word = sh_carry_out(a, L, config, i, full, crossed);
+    const uint32_t word = sh_carry_out(a, L, config, cell, i, full, crossed);
     if (crossed) return kCrossed;
     if (full) return kGiveUp;
     const uint32_t h = set_hash(word_hash(word), 1u);
     const u64 tag = (u64)(h >> 8) << 24;
     uint32_t at = h & (kShSets - 1);
     int reserved = -1;
+#pragma unroll 1
     for (int probe = 0; probe < kShProbes; ++probe, at = (at + 1) & (kShSets - 1)) {
         u64 found = lds_look(&L.sets[at]);
         if (found == kShEmpty) {
@@ -469,16 +566,16 @@ __device__ __forceinline__ uint32_t sh_step_alone(const DisplacementArgs &a, Sha
 // The pairs of the set's configurations and the productions of `ch` that apply to them, listed in `work`: how many there
 // are (of more than kShFrontier only the first are listed).  `seen` starts empty and is left so.
 __device__ __forceinline__ int sh_list_pairs(const DisplacementArgs &a, SharedLds &L, uint32_t *work, uint32_t *seen,
-                                             uint32_t set, int ch, int lane) {
+                                             uint32_t set, int byte_number, int lane) {
     const Grammar &g = a.g;
     const u64 w = wave_read64(lds_look(&L.sets[set]), 0);  // (what is the same for every lane: in scalar registers)
     lds_order();
     const int n = (int)set_size(w);
     const uint32_t *configs = L.pool + set_at(w);
+    const int ch = (int)L.like_of[byte_number];
     const int lo = __builtin_amdgcn_readfirstlane((int)L.byte_off[ch]);
     const int hi = __builtin_amdgcn_readfirstlane((int)L.byte_off[ch + 1]), per = hi - lo;
     const bool pairs_kept = __builtin_amdgcn_readfirstlane(L.pairs_kept) != 0u;
-    const uint32_t byte_number = __builtin_amdgcn_readfirstlane((uint32_t)L.byte_number[ch]);
     auto prod = [&](int i) -> u64 { return sh_production(a, L, i); };
     const u64 below = (1ull << lane) - 1ull;
     uint32_t *pair_config = work, *pair_production = work + kShFrontier, *empty = seen;
@@ -499,7 +596,7 @@ __device__ __forceinline__ int sh_list_pairs(const DisplacementArgs &a, SharedLd
         uint32_t top = 0;
         if (stack) top = cell_symbol(lds_look(&L.cells[stack - 1]));
         if (pairs_kept) {
-            const uint32_t e = stack ? L.pair[byte_number * (uint32_t)g.N + top] : 0u;
+            const uint32_t e = stack ? L.pair[(uint32_t)byte_number * (uint32_t)g.N + top] : 0u;
             const int first = (int)(e & 0x3FFu), count = (int)(e >> 10);
             for (int k = 0; __ballot(k < count); ++k) list(k < count, config, first + k);
         } else {
@@ -565,8 +662,8 @@ __device__ __forceinline__ int sh_list_pairs(const DisplacementArgs &a, SharedLd
 // One byte of Algorithm 1 on a whole set, by the whole wave: the number of the set that follows.  The listed pairs are
 // carried out together, a lane each: the chain of LDS accesses is what this costs, and it is gone through once.
 __device__ __forceinline__ uint32_t sh_step(const DisplacementArgs &a, SharedLds &L, uint32_t *work, uint32_t *seen,
-                                            uint32_t set, int ch, int lane) {
-    const int m = sh_list_pairs(a, L, work, seen, set, ch, lane);
+                                            PoolRoom &room, uint32_t set, int number_of_byte, int lane) {
+    const int m = sh_list_pairs(a, L, work, seen, set, number_of_byte, lane);
     // (the passes behind this one also find whether a bound is broken)
     if (m > kShFrontier) return kGiveUp;
     lds_order();
@@ -574,17 +671,107 @@ __device__ __forceinline__ uint32_t sh_step(const DisplacementArgs &a, SharedLds
     bool full = false, crossed = false;
     auto carry_out = [&](int x) -> uint32_t {
         if (x >= m) return kNoWord;
-        return sh_carry_out(a, L, pair_config[x], (int)pair_production[x], full, crossed);
+        return sh_carry_out(a, L, pair_config[x], sh_end_cell(L, pair_config[x]), (int)pair_production[x], full, crossed);
     };
-    const uint32_t first = carry_out(lane);
-    uint32_t second = kNoWord;
-    if (m > 64) second = carry_out(lane + 64);
+    uint32_t words[2] = {carry_out(lane), kNoWord};
+    if (m > 64) words[1] = carry_out(lane + 64);
     if (__ballot(crossed)) return kCrossed;
     if (__ballot(full)) return kGiveUp;
-    const Different d = find_different(seen, first, second, lane);
-    const uint32_t number = sh_set_number(L, seen, d, lane);
+    const Different<2> d = find_different<2>(seen, words, lane);
+    sh_reserve(L, room, d.n, lane);
+    const uint32_t number = sh_set_number(L, room, seen, d, lane);
     seen_clear(seen, lane);
     return number;
+}
+
+// The place of the k-th (from 0) of the bits that are set in `w`, which has more than k of them.
+__device__ __forceinline__ int nth_bit(uint32_t w, int k) {
+    int at = 0;
+#pragma unroll
+    for (int half = 16; half; half >>= 1) {
+        const int below = __popc(w & ((1u << half) - 1u));
+        const bool up = k >= below;
+        k -= up ? below : 0;
+        at += up ? half : 0;
+        w = up ? w >> half : w;
+    }
+    return at;
+}
+
+// A set whose configurations the lanes hold, one each (kNoWord: none), with the cells that their ends are.
+struct LaneSet {
+    uint32_t word, cell;
+};
+
+// One byte of Algorithm 1 on such a set, where `pair` and `follow` are kept: the number of the set that follows, which the
+// lanes then hold; kByTheWave, and nothing is done, if it takes more than 64 successors or a long body to make it.  Which productions
+// apply to a configuration is one look-up of a bit for each of the byte's productions; the successors are dealt out to the
+// lanes by a prefix sum of how many there are.  JSON call 237 -> 208 us, statement grammar 157 -> 143 with the sets' order by
+// a word of their first symbols, 2,000 to 64,000 tokens with the JSON grammar 0.71 to 0.80 of the time.
+__device__ __forceinline__ uint32_t sh_step_lanes(const DisplacementArgs &a, SharedLds &L, uint32_t *work, uint32_t *seen,
+                                                  PoolRoom &room, LaneSet &set, uint32_t byte_number, uint32_t dead, int lane) {
+    const uint32_t lo = L.follow[sh_follow_first(a, byte_number)];  // (the same for every lane)
+    uint32_t may = 0;
+    if (set.word != kNoWord) {
+        if (sh_stack(set.word)) {
+            const uint32_t e = L.pair[byte_number * (uint32_t)a.g.N + cell_symbol(set.cell)];
+            may = ((1u << (e >> 10)) - 1u) << (((e & 0x3FFu) - lo) & 31u);
+            may = e >> 10 == 32u ? ~0u : may;
+        } else {
+            may = L.follow[sh_follow(a, byte_number, sh_last(set.word))];
+        }
+    }
+    uint4 *each = reinterpret_cast<uint4 *>(work);
+    static_assert(sizeof(uint4) * 64 <= sizeof(uint32_t) * 2 * kShFrontier, "");
+    const int count = __popc(may);
+    const int upto = (int)wave_upto32((uint32_t)count), m = __builtin_amdgcn_readlane(upto, 63), first = upto - count;
+    if (m > 64) return kByTheWave;
+    if (!m) return dead;
+    sh_reserve(L, room, m, lane);
+    // a configuration that something applies to is put where its first successor comes to stand, and the lanes of those look
+    // which it is
+    each[lane].w = 0;
+    lds_order();
+    if (count) each[first] = make_uint4(set.word, set.cell, may, 1u);
+    lds_order();
+    const u64 begins = __ballot(each[lane].w != 0u);
+    const int from = 63 - __clzll(begins & (~0ull >> (63 - lane)));  // (lane 0's begins)
+    uint4 e = make_uint4(0, 0, 0, 0);
+    u64 p = 0;
+    if (lane < m) {
+        e = each[from];
+        p = L.prods[lo + nth_bit(e.z, lane - from)];
+    }
+    lds_order();
+    // (a body of more than four symbols lies in memory, and what waits for that waits for the rows on their way there)
+    if (__ballot(packed_length(p) == kLongBody)) return kByTheWave;
+    uint32_t words[1] = {kNoWord};
+    bool full = false, crossed = false;
+    if (lane < m)
+        words[0] = sh_carry_out(L, e.x, e.y, packed_head(p), (int)packed_length(p),
+                                [&](int k) -> uint32_t { return packed_symbol(p, k); }, full, crossed);
+    if (__ballot(crossed)) return kCrossed;
+    if (__ballot(full)) return kGiveUp;
+    const Different<1> d = find_different<1>(seen, words, lane);
+    set.word = d.first[0] ? words[0] : kNoWord;
+    set.cell = d.first[0] ? sh_end_cell(L, set.word) : 0u;
+    const uint32_t number = sh_set_number(L, room, seen, d, lane);
+    seen_clear(seen, lane);
+    return number;
+}
+// The lanes take a set of up to 64 configurations.
+__device__ __forceinline__ bool sh_load_set(const SharedLds &L, uint32_t number, LaneSet &set, int lane) {
+    const u64 w = wave_read64(lds_look(&L.sets[number]), 0);
+    lds_order();
+    const int n = (int)set_size(w);
+    set.word = kNoWord;
+    set.cell = 0;
+    if (n > 64) return false;
+    if (lane < n) {
+        set.word = L.pool[set_at(w) + lane];
+        set.cell = sh_end_cell(L, set.word);
+    }
+    return true;
 }
 
 // Which of two different lists of one length comes first: queues (a cell holds the LAST symbol) ...
@@ -609,47 +796,63 @@ __device__ __forceinline__ bool stack_less(const SharedLds &L, uint32_t x, uint3
     return false;
 }
 
-// What the set is written as: the row's entries and the hash, by the whole wave.
-__device__ __forceinline__ u64 sh_write_set(const DisplacementArgs &a, SharedLds &L, uint32_t *work, uint32_t *seen,
-                                            uint32_t set, int lane) {
-    const u64 w = lds_look(&L.sets[set]);
+// What the set is written as: the row's entries and the hash, by the whole wave.  The canonical order is (length of the
+// queue, of the stack), then the queue's and the stack's symbols, front first: one word of the two lengths and the first
+// six and a half symbols is compared with everybody's, and only records that are alike so far are compared list by list.
+__device__ __forceinline__ void sh_write_set(const DisplacementArgs &a, SharedLds &L, uint32_t *work, uint32_t *seen,
+                                             uint32_t set, int lane) {
+    const u64 w = wave_read64(lds_look(&L.sets[set]), 0);
     lds_order();
     int n = (int)set_size(w);
     // the displacement forgets the symbol consumed last
     constexpr uint32_t kPair = (1u << (2 * kCellIdBits)) - 1;
     const uint32_t *configs = L.pool + set_at(w);
     {
-        const Different d = find_different(seen, lane < n ? configs[lane] & kPair : kNoWord,
-                                           lane + 64 < n ? configs[lane + 64] & kPair : kNoWord, lane);
+        const uint32_t pairs[2] = {lane < n ? configs[lane] & kPair : kNoWord,
+                                   lane + 64 < n ? configs[lane + 64] & kPair : kNoWord};
+        const Different<2> d = find_different<2>(seen, pairs, lane);
         n = d.n;
 #pragma unroll
         for (int u = 0; u < 2; ++u)
             if (d.first[u]) work[d.at[u]] = d.word[u];
         seen_clear(seen, lane);
     }
-    // canonical order by counting: a record starts behind all smaller ones
-    uint32_t mine[2], order[2], start[2] = {1, 1}, total = 1;
+    uint32_t mine[2], ni[2], no[2], start[2] = {1, 1}, total = 1;
+    u64 key[2] = {0, 0};
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
+        mine[u] = ni[u] = no[u] = 0;
+        if (64 * u >= n) break;  // the same for every lane
         mine[u] = lane + 64 * u < n ? work[lane + 64 * u] : 0u;
-        order[u] = (list_length(L, sh_queue(mine[u])) << 8) | list_length(L, sh_stack(mine[u]));
-    }
-    for (int j = 0; j < n; ++j) {
-        const uint32_t c = j < 64 ? wave_read(mine[0], j) : wave_read(mine[1], j - 64);
-        const uint32_t other = j < 64 ? wave_read(order[0], j) : wave_read(order[1], j - 64);
-        const uint32_t entries = 2 + (other >> 8) + (other & 0xFFu);
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (64 * u >= n) break;  // the same for every lane
-            bool before = other < order[u];
-            if (other == order[u] && c != mine[u] && lane + 64 * u < n)
-                before = sh_queue(c) != sh_queue(mine[u]) ? queue_less(L, sh_queue(c), sh_queue(mine[u]))
-                                                          : stack_less(L, sh_stack(c), sh_stack(mine[u]));
-            start[u] += before ? entries : 0u;
+        uint32_t queue = sh_queue(mine[u]), stack = sh_stack(mine[u]);
+        uint32_t q = queue ? lds_look(&L.cells[queue - 1]) : 0u, s = stack ? lds_look(&L.cells[stack - 1]) : 0u;
+        ni[u] = cell_length(q), no[u] = cell_length(s);
+        if (n == 1) break;  // alone it is the first
+        u64 front = 0, behind = 0;  // the first eight symbols of the queue, of the stack
+        int shift = 56;
+        while (q || (s && shift >= 0)) {
+            if (q) front = (front >> 8) | ((u64)cell_symbol(q) << 56);
+            if (shift >= 0) behind |= (u64)cell_symbol(s) << shift;
+            shift -= 8;
+            queue = cell_rest(q);
+            stack = cell_rest(s);
+            q = queue ? lds_look(&L.cells[queue - 1]) : 0u;
+            s = stack && shift >= 0 ? lds_look(&L.cells[stack - 1]) : 0u;
         }
+        if (ni[u] < 8) front |= behind >> (8 * ni[u]);
+        key[u] = ((u64)ni[u] << 58) | ((u64)no[u] << 52) | (front >> 12);
+        static_assert(kShMaxList < 64, "a length fits six bits");
+    }
+    auto entries_of = [](u64 k) -> uint32_t { return 2u + (uint32_t)(k >> 58) + ((uint32_t)(k >> 52) & 63u); };
+    if (n == 1) total += 2u + wave_read(ni[0], 0) + wave_read(no[0], 0);
+    for (int j = 0; n > 1 && j < n; ++j) {
+        const u64 other = j < 64 ? wave_read64(key[0], j) : wave_read64(key[1], j - 64);
+        const uint32_t entries = entries_of(other);
+        start[0] += other < key[0] ? entries : 0u;
+        if (n > 64) start[1] += other < key[1] ? entries : 0u;
         total += entries;
     }
-    u64 result;
+    uint32_t result;
     if (total > (uint32_t)a.row_len) {
         result = kRowTooLong;
     } else {
@@ -660,40 +863,67 @@ __device__ __forceinline__ u64 sh_write_set(const DisplacementArgs &a, SharedLds
         if (at + room > (uint32_t)kShOut) {
             result = kRowGiveUp;
         } else {
+            // records that are alike so far have come to the same place
+            bool tie = false;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (lane + 64 * u < n && n > 1) L.out[at + start[u]] = (uint16_t)(lane + 64 * u);
+            lds_order();
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (lane + 64 * u < n && n > 1) tie = tie || L.out[at + start[u]] != (uint16_t)(lane + 64 * u);
+            lds_order();
+            if (__ballot(tie)) {
+                for (int j = 0; j < n; ++j) {
+                    const u64 other = j < 64 ? wave_read64(key[0], j) : wave_read64(key[1], j - 64);
+                    const uint32_t c = j < 64 ? wave_read(mine[0], j) : wave_read(mine[1], j - 64);
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+                        if (lane + 64 * u < n && other == key[u] && c != mine[u] &&
+                            (sh_queue(c) != sh_queue(mine[u]) ? queue_less(L, sh_queue(c), sh_queue(mine[u]))
+                                                              : stack_less(L, sh_stack(c), sh_stack(mine[u]))))
+                            start[u] += entries_of(other);
+                }
+            }
             if (lane == 0) L.out[at] = (uint16_t)n;
             if (lane < 8 && total + lane < room) L.out[at + total + lane] = 0;
             u64 h = 0;
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 if (lane + 64 * u >= n) continue;
-                const uint32_t ni = order[u] >> 8, no = order[u] & 0xFFu;
                 uint16_t *rec = L.out + at + start[u];
-                rec[0] = (uint16_t)ni;
-                rec[1] = (uint16_t)no;
-                uint32_t id = sh_queue(mine[u]);
-                for (int k = (int)ni - 1; k >= 0; --k) {
-                    const uint32_t cell = lds_look(&L.cells[id - 1]);
-                    rec[2 + k] = (uint16_t)cell_symbol(cell);
-                    id = cell_rest(cell);
+                rec[0] = (uint16_t)ni[u];
+                rec[1] = (uint16_t)no[u];
+                uint32_t queue = sh_queue(mine[u]), stack = sh_stack(mine[u]);
+                for (int k = 0; queue || stack; ++k) {
+                    const uint32_t q = queue ? lds_look(&L.cells[queue - 1]) : 0u;
+                    const uint32_t s = stack ? lds_look(&L.cells[stack - 1]) : 0u;
+                    if (queue) rec[1 + (int)ni[u] - k] = (uint16_t)cell_symbol(q);
+                    if (stack) rec[2 + (int)ni[u] + k] = (uint16_t)cell_symbol(s);
+                    queue = cell_rest(q);
+                    stack = cell_rest(s);
                 }
-                id = sh_stack(mine[u]);
-                for (uint32_t k = 0; k < no; ++k) {
-                    const uint32_t cell = lds_look(&L.cells[id - 1]);
-                    rec[2 + ni + k] = (uint16_t)cell_symbol(cell);
-                    id = cell_rest(cell);
-                }
+                lds_order();
                 RecordMix mix(a.seed);
-                for (uint32_t k = 0; k < 2 + ni + no; ++k) mix.add(rec[k]);
+                const int length = 2 + (int)ni[u] + (int)no[u];
+                constexpr int kAhead = 8;  // reads that wait for nothing
+                for (int k0 = 0; k0 < length; k0 += kAhead) {
+                    uint32_t x[kAhead];
+#pragma unroll
+                    for (int k = 0; k < kAhead; ++k) x[k] = rec[min(k0 + k, length - 1)];
+#pragma unroll
+                    for (int k = 0; k < kAhead; ++k)
+                        if (k0 + k < length) mix.add(x[k]);
+                }
                 h += mix.done();
             }
             h = wave_sum64(h);
             if (lane == 0) L.row_hash[set] = h;
-            result = ((u64)at << 16) | total;
+            result = ((at / 8u) << kRowBits) | total;
         }
     }
     lds_order();
     if (lane == 0) __hip_atomic_store(&L.row[set], result, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    return result;
 }
 
 // A workgroup takes `per_group` consecutive tokens, the longest first: what a token of 25 bytes needs, set after set that
@@ -747,10 +977,12 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
             if (sorted) rank = atomicAdd(&L.of_length[shorter], 1u);
             if (begins < 0 || ends < begins || ends > bytes_here) L.scattered = 1;
         }
+    };
+    auto stage_bytes = [&]() {
         if (fit())
 #pragma unroll
             for (int k = 0; k < kShare; ++k)
-                if (tid + k * kShThreads < bytes_here) L.bytes[tid + k * kShThreads] = L.byte_like[share[k]];
+                if (tid + k * kShThreads < bytes_here) L.bytes[tid + k * kShThreads] = L.byte_number[share[k]];
     };
     auto sum_lengths = [&]() {
         if (!sorted || wave != 0) return;
@@ -777,8 +1009,9 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
         L.sets[i] = kShEmpty;
         L.row[i] = kRowUnknown;
     }
+    uint32_t like = 0;  // of the byte `tid`
     if (!invalid) {
-        if (tid < 256) L.byte_like[tid] = a.byte_like[tid];
+        if (tid < 256) like = a.byte_like[tid];
         if (tid < 257) L.byte_off[tid] = (uint32_t)a.byte_off[tid];
         if (a.g.P <= kShProds)
             for (int i = tid; i < a.g.P; i += kShThreads) L.prods[i] = a.prod_packed[i];
@@ -790,29 +1023,38 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
     if (tid == 0) {
         L.pool_top = 0;
         L.out_top = 0;
+        L.few_each = 1;
+        L.follow_kept = 0;
     }
     clear_batch();
     __syncthreads();
     count_lengths();
-    if (!invalid && tid < 256 && L.byte_like[tid] == tid) atomicOr(&L.own[tid >> 5], 1u << (tid & 31));
+    if (!invalid && tid < 256 && (int)like == tid) atomicOr(&L.own[tid >> 5], 1u << (tid & 31));
     __syncthreads();
+    int follows = 0;  // entries of `follow`
     {
         // the productions of a (byte, symbol) lie behind each other: where, if all of this fits
         int own = 0;
         for (int w = 0; w < 8; ++w) own += __popc(L.own[w]);
         const bool fits = !invalid && a.g.P <= kShProds && own * a.g.N <= kShPairs;
+        follows = fits && own * (a.g.N + 2) <= kShFollow && a.g.N * a.g.W <= kShAdj ? own * (a.g.N + 2) : 0;
         if (tid == 0) L.pairs_kept = fits ? 1u : 0u;
         if (tid < 256) {
             int number = 0;
-            for (int w = 0; w < (tid >> 5); ++w) number += __popc(L.own[w]);
-            L.byte_number[tid] = (uint8_t)(number + __popc(L.own[tid >> 5] & ((1u << (tid & 31)) - 1u)));
+            for (int w = 0; w < (int)(like >> 5); ++w) number += __popc(L.own[w]);
+            number += __popc(L.own[like >> 5] & ((1u << (like & 31)) - 1u));
+            L.byte_number[tid] = (uint8_t)number;
+            if ((int)like == tid) {
+                L.like_of[number] = (uint8_t)tid;
+                if (fits && L.byte_off[tid + 1] - L.byte_off[tid] > (uint32_t)kShFew) L.few_each = 0;
+            }
         }
         sum_lengths();
         __syncthreads();
         if (fits)
             for (int i = tid; i < a.g.P; i += kShThreads) {
                 const uint32_t b = a.g.byte[i], head = packed_head(L.prods[i]);
-                if (L.byte_like[b] != b) continue;
+                if (!((L.own[b >> 5] >> (b & 31)) & 1u)) continue;
                 const int lo = (int)L.byte_off[b], hi = (int)L.byte_off[b + 1];
                 if (i > lo && packed_head(L.prods[i - 1]) == head) continue;
                 if (i + 63 < hi && packed_head(L.prods[i + 63]) == head) {  // more than six bits say
@@ -825,15 +1067,40 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
             }
     }
     put_in_order();
+    stage_bytes();
+    // which of a byte's productions may come right after a symbol: where this fits it takes the relation's place
+    constexpr int kFollowEach = kShFollow / kShThreads;
+    uint32_t may[kFollowEach];
+#pragma unroll
+    for (int u = 0; u < kFollowEach; ++u) {
+        const int x = tid + u * kShThreads;
+        may[u] = 0;
+        if (x >= follows) continue;
+        const int number = x / (a.g.N + 2), last = x - number * (a.g.N + 2), b = (int)L.like_of[number];
+        const int lo = (int)L.byte_off[b], count = last <= a.g.N ? min((int)L.byte_off[b + 1] - lo, kShFew) : 0;
+        for (int k = 0; k < count; ++k)
+            if (last == a.g.N || sh_may_follow(a, L, L.prods[lo + k], (uint32_t)last)) may[u] |= 1u << k;
+        if (last > a.g.N) may[u] = (uint32_t)lo;
+    }
+    __syncthreads();
+    const bool follow_kept = follows && L.pairs_kept && L.few_each;  // the same for everybody
+    if (follow_kept) {
+#pragma unroll
+        for (int u = 0; u < kFollowEach; ++u)
+            if (tid + u * kShThreads < follows) L.follow[tid + u * kShThreads] = may[u];
+        if (tid == 0) L.follow_kept = 1;
+    }
     __syncthreads();
     uint32_t *work = L.work[wave], *seen = L.seen[wave];
     seen_clear(seen, lane);
     // the start set: nothing consumed, nothing pushed; and the set that no configuration is left in (there is room
     // for these two: they are the first)
-    const Different one = find_different(seen, lane == 0 ? sh_config(0, 0, kNoSymbol) : kNoWord, kNoWord, lane);
-    const uint32_t start = sh_set_number(L, seen, one, lane);
+    const uint32_t one[1] = {lane == 0 ? sh_config(0, 0, kNoSymbol) : kNoWord}, none[1] = {kNoWord};
+    PoolRoom room = {0, 0, false};
+    sh_reserve(L, room, 1, lane);
+    const uint32_t start = sh_set_number(L, room, seen, find_different<1>(seen, one, lane), lane);
     seen_clear(seen, lane);
-    const uint32_t dead = sh_set_number(L, seen, find_different(seen, kNoWord, kNoWord, lane), lane);
+    const uint32_t dead = sh_set_number(L, room, seen, find_different<1>(seen, none, lane), lane);
 
     int steps = 0;  // that this wave has worked out
     for (int batch0 = 0; batch0 < in_group; batch0 += kShBatch) {
@@ -845,6 +1112,7 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
             clear_batch();
             __syncthreads();
             count_lengths();
+            stage_bytes();
             __syncthreads();
             sum_lengths();
             __syncthreads();
@@ -852,7 +1120,7 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
             __syncthreads();
         }
         const bool staged = fit() && L.scattered == 0;
-        auto byte_at = [&](int64_t p) -> uint32_t { return staged ? L.bytes[p] : L.byte_like[a.tok_bytes[from_byte + p]]; };
+        auto byte_at = [&](int64_t p) -> uint32_t { return staged ? (uint32_t)lds_look(&L.bytes[p]) : (uint32_t)L.byte_number[sh_arguments().tok_bytes[from_byte + p]]; };
 
         // the lane's token
         int token = -1;                         // its number in the batch, -1: none
@@ -860,7 +1128,7 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
         uint32_t set = start, like = 0, after = 0;  // where it is, the next byte and the one behind it
         bool give_up = false, crossed = false;
         bool by_the_wave = false;               // the next step has turned out to take a whole wave
-        u64 row = kRowUnknown;
+        uint32_t row = kRowUnknown;
         // how many the wave takes next: of sorted ones the longest one by one, else all that are its
         int take = sorted ? 1 : (in_group + kShWaves - 1) / kShWaves;
         bool more = true;
@@ -893,7 +1161,7 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
             const bool alone = waits == kNextEmpty && !by_the_wave && steps > kShShared;
             if (__ballot(alone)) {
                 if (alone) {
-                    const uint32_t following = sh_step_alone(a, L, set, like, dead);
+                    const uint32_t following = sh_step_alone(sh_arguments(), L, set, like, dead);
                     if (following == kByTheWave) {
                         by_the_wave = true;
                     } else {
@@ -910,18 +1178,33 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
                 const uint32_t key = waits == kNextEmpty ? (to_go << 6) | (uint32_t)(lane ^ 63) : 0u;
                 const int chosen = sorted ? (int)(wave_max32(key) & 63u) ^ 63
                                           : __ffsll(__ballot(waits == kNextEmpty)) - 1;
-                const uint32_t from = wave_read(set, chosen), on = wave_read(like, chosen);
-                int slot = 0;
-                if (lane == 0) slot = sh_claim(L, from, on);
-                slot = __builtin_amdgcn_readfirstlane(slot);
-                if (slot == -1) continue;  // taken meanwhile
-                const uint32_t following = sh_step(a, L, work, seen, from, (int)on, lane);
-                ++steps;
-                lds_order();
-                if (slot >= 0 && lane == 0)
-                    __hip_atomic_store(&L.next[slot], (((from << 8) | on) << kNextBits) | following, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (waits && set == from && like == on) advance(following);
+                uint32_t from = wave_read(set, chosen), on = wave_read(like, chosen);
+                LaneSet held;
+                bool holds = false;  // the lanes have the set's configurations
+                for (;;) {
+                    int slot = 0;
+                    if (lane == 0) slot = sh_claim(L, from, on);
+                    slot = __builtin_amdgcn_readfirstlane(slot);
+                    if (slot == -1) break;  // known, or taken meanwhile
+                    if (follow_kept && !holds) holds = sh_load_set(L, from, held, lane);
+                    uint32_t following = kByTheWave;
+                    if (holds) following = sh_step_lanes(a, L, work, seen, room, held, on, dead, lane);
+                    if (following == kByTheWave) {
+                        holds = false;
+                        following = sh_step(sh_arguments(), L, work, seen, room, from, (int)on, lane);
+                    }
+                    ++steps;
+                    lds_order();
+                    if (slot >= 0 && lane == 0)
+                        __hip_atomic_store(&L.next[slot], (((from << 8) | on) << kNextBits) | following, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                    if (pos < end && set == from && like == on) advance(following);
+                    // The token's next byte right away: where a token makes set after set that nobody has met, that chain
+                    // is what the workgroup waits for
+                    if (!((__ballot(pos < end) >> chosen) & 1ull) || following == dead) break;
+                    from = following;
+                    on = wave_read(like, chosen);
+                }
                 continue;
             }
             // What the sets reached are written as.
@@ -932,12 +1215,13 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
                 const u64 unknown = __ballot(wanted && row == kRowUnknown);
                 if (!unknown) break;
                 const uint32_t s = wave_read(set, __ffsll(unknown) - 1);
-                u64 state = 0;
+                uint32_t state = 0;
                 if (lane == 0) state = atomicCAS(&L.row[s], kRowUnknown, kRowWorkedOut);
-                if (wave_read64(state, 0) == kRowUnknown) sh_write_set(a, L, work, seen, s, lane);
+                if (wave_read(state, 0) == kRowUnknown) sh_write_set(sh_arguments(), L, work, seen, s, lane);
             }
             if (wanted && row == kRowWorkedOut) through = false;  // another wave is at it
             if (__ballot(through)) {
+                const DisplacementArgs a = sh_arguments();
                 lds_order();
                 const int64_t t = first_token + token;
                 if (wanted && row == kRowGiveUp) give_up = true;
@@ -971,9 +1255,9 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
                     const int64_t tk = first_token + (int)wave_read((uint32_t)token, k);
                     uint16_t *out_row = a.rows + (size_t)tk * a.row_len;
                     const bool copy = (plain >> k) & 1ull;
-                    const u64 rk = wave_read64(row, k);
-                    const uint32_t units = copy ? (((uint32_t)rk & 0xFFFFu) + 7u) / 8u : 0u;  // 16 bytes each
-                    const uint4 *src = reinterpret_cast<const uint4 *>(L.out + (copy ? (uint32_t)(rk >> 16) : 0u));
+                    const uint32_t rk = wave_read(row, k);
+                    const uint32_t units = copy ? (row_entries(rk) + 7u) / 8u : 0u;  // 16 bytes each
+                    const uint4 *src = reinterpret_cast<const uint4 *>(L.out + (copy ? row_at(rk) : 0u));
                     const bool marked = !copy && !invalid;  // the row of a token that overflowed
                     for (uint32_t u = lane; u < (uint32_t)a.row_len / 8u; u += 64) {
                         uint4 v = make_uint4(0, 0, 0, 0);
@@ -1007,6 +1291,7 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
                     } else {
                         pos = end = 0;
                         if (!invalid) {
+                            const DisplacementArgs a = sh_arguments();
                             pos = a.tok_off[first_token + token] - from_byte;
                             end = a.tok_off[first_token + token + 1] - from_byte;
                         }

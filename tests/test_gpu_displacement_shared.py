@@ -69,6 +69,44 @@ def test_many_productions_of_one_symbol_and_byte(lib, n):
         _check_rows(lib, g, vocab, row_len=1024)
 
 
+@pytest.mark.parametrize("n", [31, 32, 33])
+def test_productions_of_a_byte_around_a_bit_each(lib, n):
+    """Up to 32 productions of a byte are told by a bit each: pops of the first and the last of them, of runs of one symbol,
+    and backtracks that all, some or none of them may take."""
+    print(f"case n={n}", flush=True)
+    prods = [(A, ord("a"), (A, (A + 1) % n)) for A in range(n)] + [(0, ord("b"), (B,)) for B in range(n)]
+    prods += [(n - 1, ord("c"), ())] + [(A, ord("d"), ()) for A in range(0, n, 3)] + [(1, ord("d"), (B,)) for B in (0, n - 1)]
+    g = grammar_from_productions(n, prods)
+    vocab = vocab_from_tokens([bytes(w) for k in range(4) for w in itertools.product(b"abcd", repeat=k)] + [b"z", b"ddddd"])
+    _check_rows(lib, g, vocab, row_len=1024)
+
+
+@pytest.mark.parametrize("own", [31, 32, 33])
+def test_pairs_of_byte_and_symbol_around_what_is_kept(lib, own):
+    """62 symbols and two entries more for each of `own` bytes: up to 2,048 are kept."""
+    print(f"case own={own}", flush=True)
+    rng = np.random.default_rng(own)
+    prods = [(A, 40 + (A * 7) % own, ()) for A in range(62)]
+    prods += [(int(rng.integers(0, 62)), 40 + b, tuple(int(x) for x in rng.integers(0, 62, size=int(rng.integers(1, 4)))))
+              for b in range(own) for _ in range(3)]
+    g = grammar_from_productions(62, sorted(set(prods)))
+    _check_rows(lib, g, make_token_strings(own, 900, bytes(range(40, 40 + own)) + b"~", 5), row_len=512)
+
+
+def test_records_that_differ_late(lib):
+    """Queues and stacks of equal lengths whose first eight and more symbols are alike, in sets of a few and of more than 64
+    records, and bodies of more than four symbols among short ones."""
+    n = 40
+    prods = [(0, ord("a"), ())] + [(k, ord("b"), ()) for k in range(1, n)] + [(n, ord("s"), (0, k)) for k in range(n)]
+    prods += [(n + 1, ord("q"), (n + 1, 0, 0, 0)), (n + 1, ord("r"), ())]
+    prods += [(n + 2, ord("x"), (n + 1, j)) for j in range(1, 6)] + [(n + 2, ord("y"), (n + 1, 0, j)) for j in range(1, n)]
+    prods += [(n + 2, ord("y"), (n + 1, 1, j)) for j in range(1, n)] + [(n + 2, ord("y"), (n + 1, 1, 2, 3, 4, j)) for j in (7, 8)]
+    g = grammar_from_productions(n + 3, sorted(set(prods)))
+    toks = [b"a" * k + t for k in range(0, 14) for t in (b"", b"b", b"ba")]
+    toks += [h + b"q" * k + t for h in (b"x", b"y") for k in range(6) for t in (b"", b"r", b"raa", b"raab")]
+    _check_rows(lib, g, vocab_from_tokens(toks), row_len=4096)
+
+
 def test_bytes_with_equal_productions(lib):
     """Digits 0-4 behave alike, 5 differs in a body, 6 in the fifth symbol of a long one, 7 in the number of
     productions."""
