@@ -1,4 +1,4 @@
-"""Binding of libcfgzip.so: ctypes, and an extension for the two calls of every decode step.
+"""Binding of libcfgzip.so: ctypes, and an extension for the calls of every decode step and of the pre-computation.
 Argument marshalling only.
 
 Tensors are torch CUDA (ROCm) tensors; they supply device memory and the HIP
@@ -21,10 +21,15 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "lib", "libcfgzip.so")
 _lib: Optional[ctypes.CDLL] = None
 _STEPCALL_PATH = os.path.join(_HERE, "lib", "cfgzip_stepcall.so")
-# the two per-step calls without ctypes, set when the library is loaded; they answer None where a call has to go
+# the extension's calls without ctypes, set when the library is loaded; they answer None where a call has to go
 # through ctypes
 _decode_step = None
 _engine_step = None
+_signatures = None
+_build_classes = None
+_displacements = None
+_nfa_signatures = None
+_CALLS = ("decode_step", "engine_step", "signatures", "build_classes", "displacements", "nfa_signatures")
 
 DEFAULT_HASH_SEED = 0x5EED_CF62_1234_ABCD
 
@@ -63,7 +68,7 @@ def _by_ctypes(*_args) -> None:
 
 
 def _load_stepcall(lib: ctypes.CDLL):
-    """The per-step calls of the extension.  They save host time and nothing else: every call goes through ctypes as
+    """The calls of the extension.  They save host time and nothing else: every call goes through ctypes as
     well, so an extension that is not there, or was built for another torch or Python, is done without."""
     try:
         loader = importlib.machinery.ExtensionFileLoader("cfgzip_stepcall", _STEPCALL_PATH)
@@ -73,17 +78,17 @@ def _load_stepcall(lib: ctypes.CDLL):
         if (stepcall.python, stepcall.torch) != ("%d.%d" % sys.version_info[:2], str(torch.__version__)):
             raise ImportError(f"it was built for Python {stepcall.python} and torch {stepcall.torch}")
     except (ImportError, OSError, SystemError, AttributeError) as e:
-        warnings.warn(f"{_STEPCALL_PATH} cannot be used ({e}); cfgzip_decode_step and cfgzip_engine_step are called "
-                      "through ctypes, which takes about 5 us more a step. "
+        warnings.warn(f"{_STEPCALL_PATH} cannot be used ({e}); calls go through ctypes, which takes "
+                      "about 5 us more each. "
                       "`python -m paper_2605_29986_amd.build` builds it.", RuntimeWarning, stacklevel=3)
-        return _by_ctypes, _by_ctypes
-    stepcall.connect(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.cfgzip_decode_step, lib.cfgzip_engine_step)))
-    return stepcall.decode_step, stepcall.engine_step
+        return (_by_ctypes,) * len(_CALLS)
+    stepcall.connect(*(ctypes.cast(getattr(lib, "cfgzip_" + f), ctypes.c_void_p).value for f in _CALLS))
+    return tuple(getattr(stepcall, f) for f in _CALLS)
 
 
 def load_library() -> ctypes.CDLL:
     """Loads the built HIP library; raises if it has not been built (there is no fallback)."""
-    global _lib, _decode_step, _engine_step
+    global _lib, _decode_step, _engine_step, _signatures, _build_classes, _displacements, _nfa_signatures
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -142,7 +147,7 @@ def load_library() -> ctypes.CDLL:
     lib.cfgzip_displacements.restype = ctypes.c_int
     lib.cfgzip_displacements.argtypes = [vp, vp, i32, vp, vp, vp, vp, i32, i32, i32, vp, i32, vp, vp, u64,
                                          vp, sz, vp]
-    _decode_step, _engine_step = _load_stepcall(lib)
+    _decode_step, _engine_step, _signatures, _build_classes, _displacements, _nfa_signatures = _load_stepcall(lib)
     _lib = lib
     return lib
 
@@ -200,7 +205,13 @@ def cfgzip_signatures(tok_bytes: torch.Tensor, tok_off: torch.Tensor, table: tor
     (int64 tensor holding the uint64 bit patterns, [V]).  composed=True calls
     cfgzip_signatures_composed (same results; longer tokens continue the walk of a short token
     that is a prefix of theirs); its workspace is larger."""
-    lib = load_library()
+    lib = _lib or load_library()
+    if stream is None and workspace is not None and not composed:
+        out = _signatures(tok_bytes, tok_off, table, want_sig, want_hash, hash_seed, sig_out, hash_out, workspace)
+        if out is not None:
+            if type(out) is int:
+                _check("cfgzip_signatures", out)
+            return out
     entry = lib.cfgzip_signatures_composed if composed else lib.cfgzip_signatures
     query = lib.cfgzip_signatures_composed_workspace_bytes if composed else lib.cfgzip_signatures_workspace_bytes
     V = tok_off.numel() - 1
@@ -258,7 +269,15 @@ def cfgzip_build_classes(tok_bytes: torch.Tensor, tok_off: torch.Tensor,
     cfgzip_signatures call that produced `hash` (its compressed signatures are compared
     instead of `sig` rows or a second walk).  With table=None the rows of `sig` (any row
     length) are grouped as they are."""
-    lib = load_library()
+    lib = _lib or load_library()
+    if stream is None and workspace is not None:
+        out = _build_classes(tok_bytes, tok_off, table, sig, hash, class_of_token, rep_of_class, workspace,
+                             signatures_workspace)
+        if out is not None:
+            if type(out) is int:
+                _check("cfgzip_build_classes", out)
+            class_of_token, rep_of_class, C, collisions = out
+            return class_of_token, rep_of_class[:C], C, collisions
     V = tok_off.numel() - 1
     S = table.shape[0] if table is not None else (sig.shape[1] if sig is not None else 0)
     dev = tok_off.device
@@ -486,7 +505,14 @@ def cfgzip_displacements(tok_bytes: torch.Tensor, tok_off: torch.Tensor, prod_he
                          hash_seed: int = DEFAULT_HASH_SEED,
                          workspace: Optional[torch.Tensor] = None, stream=None):
     """(rows uint16 [V, row_len], hash int64 [V] holding uint64 bit patterns, status int32 [V])."""
-    lib = load_library()
+    lib = _lib or load_library()
+    if stream is None and workspace is not None and body_total is None:
+        out = _displacements(tok_bytes, tok_off, prod_head, prod_byte, prod_body_off, prod_body, N, row_len, hash_seed,
+                             workspace)
+        if out is not None:
+            if type(out) is int:
+                _check("cfgzip_displacements", out)
+            return out
     V = tok_off.numel() - 1
     dev = tok_off.device
     rows = torch.empty((V, row_len), dtype=torch.uint16, device=dev)
@@ -509,7 +535,13 @@ def cfgzip_displacements(tok_bytes: torch.Tensor, tok_off: torch.Tensor, prod_he
 def cfgzip_nfa_signatures(tok_bytes: torch.Tensor, tok_off: torch.Tensor, nfa: torch.Tensor, *,
                           want_hash: bool = True, hash_seed: int = DEFAULT_HASH_SEED, stream=None):
     """(rel int32 [V, S, W(S)], hash int64 [V] or None) for nfa int32 [256, S, W(S)]."""
-    lib = load_library()
+    lib = _lib or load_library()
+    if stream is None:
+        out = _nfa_signatures(tok_bytes, tok_off, nfa, want_hash, hash_seed)
+        if out is not None:
+            if type(out) is int:
+                _check("cfgzip_nfa_signatures", out)
+            return out
     V = tok_off.numel() - 1
     S = nfa.shape[1]
     if nfa.shape != (256, S, words_for(S)):
