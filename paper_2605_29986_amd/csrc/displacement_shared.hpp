@@ -152,6 +152,7 @@ struct SharedLds {
     uint32_t few_each;        // no byte has more productions than `follow` has bits
     uint32_t follow_kept;     // whether `follow` holds what the relation says
     uint32_t pool_top, out_top, cursor;
+    uint32_t start_set, dead_set;  // nothing consumed and nothing pushed; no configuration left
     uint32_t handed;         // tokens on the workgroup's list of those that it takes alone
     uint32_t scattered;      // some token's bytes do not lie where the token before ends
     uint32_t of_length[kShLengths];
@@ -1012,8 +1013,21 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
             if (bytes_here <= kShBytes && x < bytes_here) share[k] = a.tok_bytes[from_byte + x];
         }
     };
+    // the tables, an entry each: asked for before anything that was asked for is waited for (of an invalid grammar they hold
+    // anything, and nothing looks at them)
+    const int relation_words = a.g.N * a.g.W;
+    int32_t invalid_there = a.hdr->invalid;
+    uint32_t like = a.byte_like[tid & 255], first_of_byte = (uint32_t)a.byte_off[min(tid, 256)], relation = 0;
+    uint32_t byte_of = 0;
+    u64 production = 0;
+    static_assert(kShProds <= kShThreads && kShAdj <= kShThreads, "an entry each");
+    if (a.g.P <= kShProds) {
+        production = a.prod_packed[min(tid, a.g.P - 1)];
+        byte_of = a.g.byte[min(tid, a.g.P - 1)];
+    }
+    if (relation_words <= kShAdj) relation = a.adj[min(tid, relation_words - 1)];
     fetch(0);
-    const bool invalid = a.hdr->invalid != 0;  // the same for everybody
+    const bool invalid = invalid_there != 0;  // the same for everybody
     const bool sorted = in_group > kShOnce * kShWaves;  // otherwise every wave takes its tokens at once
     // sorting a batch: four parts with a barrier between them
     uint32_t shorter = 0, rank = 0;
@@ -1040,13 +1054,7 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
     auto sum_lengths = [&]() {
         if (!sorted || wave != 0) return;
         const uint32_t count = L.of_length[lane];
-        uint32_t before = count;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t x = __shfl_up(before, off, 64);
-            before += lane >= off ? x : 0u;
-        }
-        L.of_length[lane] = before - count;
+        L.of_length[lane] = wave_upto32(count) - count;
     };
     auto put_in_order = [&]() {
         if (tid >= batch_size) return;
@@ -1062,16 +1070,16 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
         L.sets[i] = kShEmpty;
         L.row[i] = kRowUnknown;
     }
-    uint32_t like = 0;  // of the byte `tid`
-    if (!invalid) {
-        if (tid < 256) like = a.byte_like[tid];
-        if (tid < 257) L.byte_off[tid] = (uint32_t)a.byte_off[tid];
-        if (a.g.P <= kShProds)
-            for (int i = tid; i < a.g.P; i += kShThreads) L.prods[i] = a.prod_packed[i];
-        if (a.g.N * a.g.W <= kShAdj)
-            for (int i = tid; i < a.g.N * a.g.W; i += kShThreads) L.adj[i] = a.adj[i];
+    if (tid < 257) L.byte_off[tid] = first_of_byte;
+    if (tid < a.g.P && a.g.P <= kShProds) L.prods[tid] = production;
+    if (tid < relation_words && relation_words <= kShAdj) L.adj[tid] = relation;
+    {
+        const u64 own = __ballot(!invalid && (int)like == tid);  // bytes that are their own like
+        if (wave < 4 && lane == 0) {
+            L.own[2 * wave] = (uint32_t)own;
+            L.own[2 * wave + 1] = (uint32_t)(own >> 32);
+        }
     }
-    if (tid < 8) L.own[tid] = 0;
     for (int i = tid; i < kShPairs; i += kShThreads) L.pair[i] = 0;
     if (tid == 0) {
         L.pool_top = 0;
@@ -1080,49 +1088,58 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
         L.few_each = 1;
         L.follow_kept = 0;
     }
+    uint32_t *work = L.work[wave], *seen = L.seen[wave];
+    seen_clear(seen, lane);
     clear_batch();
     __syncthreads();
     count_lengths();
-    if (!invalid && tid < 256 && (int)like == tid) atomicOr(&L.own[tid >> 5], 1u << (tid & 31));
-    __syncthreads();
-    int follows = 0;  // entries of `follow`
-    {
-        // the productions of a (byte, symbol) lie behind each other: where, if all of this fits
-        int own = 0;
-        for (int w = 0; w < 8; ++w) own += __popc(L.own[w]);
-        const bool fits = !invalid && a.g.P <= kShProds && own * a.g.N <= kShPairs;
-        follows = fits && own * (a.g.N + 2) <= kShFollow && a.g.N * a.g.W <= kShAdj ? own * (a.g.N + 2) : 0;
-        if (tid == 0) L.pairs_kept = fits ? 1u : 0u;
-        if (tid < 256) {
-            int number = 0;
-            for (int w = 0; w < (int)(like >> 5); ++w) number += __popc(L.own[w]);
-            number += __popc(L.own[like >> 5] & ((1u << (like & 31)) - 1u));
-            L.byte_number[tid] = (uint8_t)number;
-            if ((int)like == tid) {
-                L.like_of[number] = (uint8_t)tid;
-                if (fits && L.byte_off[tid + 1] - L.byte_off[tid] > (uint32_t)kShFew) L.few_each = 0;
-            }
+    PoolRoom room = {0, 0, false};
+    if (wave == kShWaves - 1) {
+        // the start set: nothing consumed, nothing pushed; and the set that no configuration is left in (there is room
+        // for these two: they are the first)
+        const uint32_t one[1] = {lane == 0 ? sh_config(0, 0, kNoSymbol) : kNoWord}, none[1] = {kNoWord};
+        sh_reserve(L, room, 1, lane);
+        const uint32_t first = sh_set_number(L, room, seen, find_different<1>(seen, one, lane), lane);
+        seen_clear(seen, lane);
+        const uint32_t second = sh_set_number(L, room, seen, find_different<1>(seen, none, lane), lane);
+        if (lane == 0) {
+            L.start_set = first;
+            L.dead_set = second;
         }
-        sum_lengths();
-        __syncthreads();
-        if (fits)
-            for (int i = tid; i < a.g.P; i += kShThreads) {
-                const uint32_t b = a.g.byte[i], head = packed_head(L.prods[i]);
-                if (!((L.own[b >> 5] >> (b & 31)) & 1u)) continue;
-                const int lo = (int)L.byte_off[b], hi = (int)L.byte_off[b + 1];
-                if (i > lo && packed_head(L.prods[i - 1]) == head) continue;
-                if (i + 63 < hi && packed_head(L.prods[i + 63]) == head) {  // more than six bits say
-                    L.pairs_kept = 0;  // (not counted out: of one pair's 676 productions that took 50 us)
-                    continue;
-                }
+    }
+    // the productions of a (byte, symbol) lie behind each other: where, if all of this fits
+    int own = 0;
+    for (int w = 0; w < 8; ++w) own += __popc(L.own[w]);
+    const bool fits = !invalid && a.g.P <= kShProds && own * a.g.N <= kShPairs;
+    if (tid == 0) L.pairs_kept = fits ? 1u : 0u;
+    if (tid < 256) {
+        int number = 0;
+        for (int w = 0; w < (int)(like >> 5); ++w) number += __popc(L.own[w]);
+        number += __popc(L.own[like >> 5] & ((1u << (like & 31)) - 1u));
+        L.byte_number[tid] = (uint8_t)number;
+        if ((int)like == tid) {
+            L.like_of[number] = (uint8_t)tid;
+            if (fits && L.byte_off[tid + 1] - L.byte_off[tid] > (uint32_t)kShFew) L.few_each = 0;
+        }
+    }
+    __syncthreads();
+    sum_lengths();
+    if (fits && tid < a.g.P && ((L.own[byte_of >> 5] >> (byte_of & 31)) & 1u)) {
+        const int i = tid, lo = (int)L.byte_off[byte_of], hi = (int)L.byte_off[byte_of + 1];
+        const uint32_t head = packed_head(production);
+        if (i == lo || packed_head(L.prods[i - 1]) != head) {
+            if (i + 63 < hi && packed_head(L.prods[i + 63]) == head) {  // more than six bits say
+                L.pairs_kept = 0;  // (not counted out: of one pair's 676 productions that took 50 us)
+            } else {
                 int end = i + 1;
                 while (end < hi && packed_head(L.prods[end]) == head) ++end;
-                L.pair[L.byte_number[b] * (uint32_t)a.g.N + head] = (uint16_t)(i | ((end - i) << 10));
+                L.pair[L.byte_number[byte_of] * (uint32_t)a.g.N + head] = (uint16_t)(i | ((end - i) << 10));
             }
+        }
     }
-    put_in_order();
     stage_bytes();
     // which of a byte's productions may come right after a symbol: where this fits it takes the relation's place
+    const int follows = fits && L.few_each && own * (a.g.N + 2) <= kShFollow && relation_words <= kShAdj ? own * (a.g.N + 2) : 0;
     constexpr int kFollowEach = kShFollow / kShThreads;
     uint32_t may[kFollowEach];
 #pragma unroll
@@ -1137,7 +1154,8 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
         if (last > a.g.N) may[u] = (uint32_t)lo;
     }
     __syncthreads();
-    const bool follow_kept = follows && L.pairs_kept && L.few_each;  // the same for everybody
+    put_in_order();
+    const bool follow_kept = follows && L.pairs_kept;  // the same for everybody
     if (follow_kept) {
 #pragma unroll
         for (int u = 0; u < kFollowEach; ++u)
@@ -1145,16 +1163,7 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
         if (tid == 0) L.follow_kept = 1;
     }
     __syncthreads();
-    uint32_t *work = L.work[wave], *seen = L.seen[wave];
-    seen_clear(seen, lane);
-    // the start set: nothing consumed, nothing pushed; and the set that no configuration is left in (there is room
-    // for these two: they are the first)
-    const uint32_t one[1] = {lane == 0 ? sh_config(0, 0, kNoSymbol) : kNoWord}, none[1] = {kNoWord};
-    PoolRoom room = {0, 0, false};
-    sh_reserve(L, room, 1, lane);
-    const uint32_t start = sh_set_number(L, room, seen, find_different<1>(seen, one, lane), lane);
-    seen_clear(seen, lane);
-    const uint32_t dead = sh_set_number(L, room, seen, find_different<1>(seen, none, lane), lane);
+    const uint32_t start = __builtin_amdgcn_readfirstlane(L.start_set), dead = __builtin_amdgcn_readfirstlane(L.dead_set);
 
     int steps = 0;  // that this wave has worked out
     for (int batch0 = 0; batch0 < in_group; batch0 += kShBatch) {
