@@ -67,7 +67,10 @@ struct DisplacementArgs {
 struct RecordMix {
     uint64_t h;
     __device__ explicit RecordMix(uint64_t seed) : h(seed ^ 0x9E3779B97F4A7C15ull) {}
-    __device__ void add(uint32_t x) { h = (h ^ x) * 0x100000001B3ull; }
+    __device__ void add(uint32_t x) {  // times 0x100000001B3
+        h ^= x;
+        h = h * 0x1B3ull + (h << 40);
+    }
     __device__ uint64_t done() const {
         uint64_t z = h;
         z ^= z >> 30;

@@ -822,30 +822,62 @@ __device__ __forceinline__ void sh_write_set(const DisplacementArgs &a, SharedLd
     }
     uint32_t mine[2], ni[2], no[2], start[2] = {1, 1}, total = 1;
     u64 key[2] = {0, 0};
+    uint32_t q[2] = {0, 0}, t[2] = {0, 0};  // the lists' first cells
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         mine[u] = ni[u] = no[u] = 0;
         if (64 * u >= n) break;  // the same for every lane
         mine[u] = lane + 64 * u < n ? work[lane + 64 * u] : 0u;
-        uint32_t queue = sh_queue(mine[u]), stack = sh_stack(mine[u]);
-        uint32_t q = queue ? lds_look(&L.cells[queue - 1]) : 0u, s = stack ? lds_look(&L.cells[stack - 1]) : 0u;
-        ni[u] = cell_length(q), no[u] = cell_length(s);
-        if (n == 1) break;  // alone it is the first
-        u64 front = 0, behind = 0;  // the first eight symbols of the queue, of the stack
-        int shift = 56;
-        while (q || (s && shift >= 0)) {
-            if (q) front = (front >> 8) | ((u64)cell_symbol(q) << 56);
-            if (shift >= 0) behind |= (u64)cell_symbol(s) << shift;
-            shift -= 8;
-            queue = cell_rest(q);
-            stack = cell_rest(s);
-            q = queue ? lds_look(&L.cells[queue - 1]) : 0u;
-            s = stack && shift >= 0 ? lds_look(&L.cells[stack - 1]) : 0u;
-        }
-        if (ni[u] < 8) front |= behind >> (8 * ni[u]);
-        key[u] = ((u64)ni[u] << 58) | ((u64)no[u] << 52) | (front >> 12);
-        static_assert(kShMaxList < 64, "a length fits six bits");
+        if (sh_queue(mine[u])) q[u] = lds_look(&L.cells[sh_queue(mine[u]) - 1]);
+        if (sh_stack(mine[u])) t[u] = lds_look(&L.cells[sh_stack(mine[u]) - 1]);
+        ni[u] = cell_length(q[u]), no[u] = cell_length(t[u]);
     }
+    lds_order();
+    // The lists' symbols, front first: four of a lane's in a word, the words of all lanes behind each other.  (The records'
+    // places are known only when all have been compared, and going through the lists a second time took as long as the first.)
+    constexpr int kNotedWords = 2 * kShFrontier / 64;  // in `work`, and as many in `seen`
+    static_assert(kNotedWords >= 2 && kNotedWords * 64 <= kShSeen, "");
+    const bool noted = n <= 64 && __ballot(ni[0] + no[0] > 8u * kNotedWords) == 0ull;
+    const bool past_work = __ballot(ni[0] + no[0] > 4u * kNotedWords) != 0ull;
+    if (noted) {
+        auto note = [&](uint32_t at, uint32_t symbol) {
+            uint32_t *words = at < 4u * kNotedWords ? work : seen;
+            reinterpret_cast<uint8_t *>(words)[((at / 4u) % kNotedWords) * 256u + (uint32_t)lane * 4u + at % 4u] = (uint8_t)symbol;
+        };
+        work[lane] = work[64 + lane] = 0;  // where the comparison looks
+        lds_order();
+        uint32_t qc = q[0], tc = t[0], at_q = ni[0], at_t = ni[0];
+        while (qc | tc) {
+            if (qc) note(--at_q, cell_symbol(qc));
+            if (tc) note(at_t++, cell_symbol(tc));
+            const uint32_t queue = cell_rest(qc), stack = cell_rest(tc);
+            qc = queue ? lds_look(&L.cells[queue - 1]) : 0u;
+            tc = stack ? lds_look(&L.cells[stack - 1]) : 0u;
+        }
+        lds_order();
+        const uint32_t w0 = __builtin_bswap32(work[lane]), w1 = __builtin_bswap32(work[64 + lane]);
+        key[0] = ((u64)ni[0] << 58) | ((u64)no[0] << 52) | ((((u64)w0 << 32) | w1) >> 12);
+    } else {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (64 * u >= n) break;
+            uint32_t queue, stack, qc = q[u], tc = t[u];
+            u64 front = 0, behind = 0;  // the first eight symbols of the queue, of the stack
+            int shift = 56;
+            while (qc || (tc && shift >= 0)) {
+                if (qc) front = (front >> 8) | ((u64)cell_symbol(qc) << 56);
+                if (shift >= 0) behind |= (u64)cell_symbol(tc) << shift;
+                shift -= 8;
+                queue = cell_rest(qc);
+                stack = cell_rest(tc);
+                qc = queue ? lds_look(&L.cells[queue - 1]) : 0u;
+                tc = stack && shift >= 0 ? lds_look(&L.cells[stack - 1]) : 0u;
+            }
+            if (ni[u] < 8) front |= behind >> (8 * ni[u]);
+            key[u] = ((u64)ni[u] << 58) | ((u64)no[u] << 52) | (front >> 12);
+        }
+    }
+    static_assert(kShMaxList < 64, "a length fits six bits");
     auto entries_of = [](u64 k) -> uint32_t { return 2u + (uint32_t)(k >> 58) + ((uint32_t)(k >> 52) & 63u); };
     if (n == 1) total += 2u + wave_read(ni[0], 0) + wave_read(no[0], 0);
     for (int j = 0; n > 1 && j < n; ++j) {
@@ -891,40 +923,67 @@ __device__ __forceinline__ void sh_write_set(const DisplacementArgs &a, SharedLd
             if (lane == 0) L.out[at] = (uint16_t)n;
             if (lane < 8 && total + lane < room) L.out[at + total + lane] = 0;
             u64 h = 0;
+            if (noted) {
+                if (lane < n) {
+                    uint16_t *rec = L.out + at + start[0];
+                    rec[0] = (uint16_t)ni[0];
+                    rec[1] = (uint16_t)no[0];
+                    const uint32_t symbols = ni[0] + no[0];
+                    RecordMix mix(a.seed);
+                    mix.add(ni[0]);
+                    mix.add(no[0]);
+#pragma unroll 1
+                    for (uint32_t k0 = 0; k0 < symbols; k0 += 4) {
+                        const uint32_t *words = k0 < 4u * kNotedWords ? work : seen;
+                        const uint32_t four = words[((k0 / 4u) % kNotedWords) * 64u + (uint32_t)lane];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                if (lane + 64 * u >= n) continue;
-                uint16_t *rec = L.out + at + start[u];
-                rec[0] = (uint16_t)ni[u];
-                rec[1] = (uint16_t)no[u];
-                uint32_t queue = sh_queue(mine[u]), stack = sh_stack(mine[u]);
-                for (int k = 0; queue || stack; ++k) {
-                    const uint32_t q = queue ? lds_look(&L.cells[queue - 1]) : 0u;
-                    const uint32_t s = stack ? lds_look(&L.cells[stack - 1]) : 0u;
-                    if (queue) rec[1 + (int)ni[u] - k] = (uint16_t)cell_symbol(q);
-                    if (stack) rec[2 + (int)ni[u] + k] = (uint16_t)cell_symbol(s);
-                    queue = cell_rest(q);
-                    stack = cell_rest(s);
+                        for (uint32_t k = 0; k < 4; ++k) {
+                            const uint32_t symbol = (four >> (8 * k)) & 0xFFu;
+                            if (k0 + k < symbols) {
+                                rec[2 + k0 + k] = (uint16_t)symbol;
+                                mix.add(symbol);
+                            }
+                        }
+                    }
+                    h = mix.done();
                 }
-                lds_order();
-                RecordMix mix(a.seed);
-                const int length = 2 + (int)ni[u] + (int)no[u];
-                constexpr int kAhead = 8;  // reads that wait for nothing
-                for (int k0 = 0; k0 < length; k0 += kAhead) {
-                    uint32_t x[kAhead];
+            } else {
 #pragma unroll
-                    for (int k = 0; k < kAhead; ++k) x[k] = rec[min(k0 + k, length - 1)];
+                for (int u = 0; u < 2; ++u) {
+                    if (lane + 64 * u >= n) continue;
+                    uint16_t *rec = L.out + at + start[u];
+                    rec[0] = (uint16_t)ni[u];
+                    rec[1] = (uint16_t)no[u];
+                    uint32_t queue = sh_queue(mine[u]), stack = sh_stack(mine[u]);
+                    for (int k = 0; queue || stack; ++k) {
+                        const uint32_t q = queue ? lds_look(&L.cells[queue - 1]) : 0u;
+                        const uint32_t s = stack ? lds_look(&L.cells[stack - 1]) : 0u;
+                        if (queue) rec[1 + (int)ni[u] - k] = (uint16_t)cell_symbol(q);
+                        if (stack) rec[2 + (int)ni[u] + k] = (uint16_t)cell_symbol(s);
+                        queue = cell_rest(q);
+                        stack = cell_rest(s);
+                    }
+                    lds_order();
+                    RecordMix mix(a.seed);
+                    const int length = 2 + (int)ni[u] + (int)no[u];
+                    constexpr int kAhead = 8;  // reads that wait for nothing
+                    for (int k0 = 0; k0 < length; k0 += kAhead) {
+                        uint32_t x[kAhead];
 #pragma unroll
-                    for (int k = 0; k < kAhead; ++k)
-                        if (k0 + k < length) mix.add(x[k]);
+                        for (int k = 0; k < kAhead; ++k) x[k] = rec[min(k0 + k, length - 1)];
+#pragma unroll
+                        for (int k = 0; k < kAhead; ++k)
+                            if (k0 + k < length) mix.add(x[k]);
+                    }
+                    h += mix.done();
                 }
-                h += mix.done();
             }
             h = wave_sum64(h);
             if (lane == 0) L.row_hash[set] = h;
             result = ((at / 8u) << kRowBits) | total;
         }
     }
+    if (noted && past_work) seen_clear(seen, lane);
     lds_order();
     if (lane == 0) __hip_atomic_store(&L.row[set], result, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
