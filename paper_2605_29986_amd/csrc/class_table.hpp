@@ -28,7 +28,7 @@
 //     32,000 tokens in   683 classes        22 (2 + 8 + 7 + 4)             20 (gather 6, merge 5, settle 9)
 //    151,936 tokens in 2,559 classes        48 (5.5 + 15 + 23 + 4)         37 (7 + 6 + 24)
 //    128,256 rows of 2 KB in 150 classes    56 (5.4 + 7 + 39 + 4.4)        49 (5 + 5 + 39)
-//     32,000 rows of 8 KB                   73 (5 + 12 + 52 + 4)           59 (5.4 + 5 + 49)
+//     32,000 rows of 8 KB                   73 (5 + 12 + 52 + 4)           51 (5.4 + 5 + 40.5)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -511,8 +511,14 @@ __device__ __forceinline__ void table_number(const TableSettleArgs &a, unsigned 
     }
 }
 
-constexpr uint32_t kRowPart = 64;  // 16-byte units of a row that a wave compares
-__host__ __device__ inline int64_t table_row_parts(int32_t S) { return (S + 8 * (int)kRowPart - 1) / (8 * (int)kRowPart); }
+// 16-byte units of a row that a wave compares at a time: of four rows each, or, where a row has that many, four times as many
+// of one, so that what it asks for lies together.
+constexpr uint32_t kRowPart = 64;
+constexpr int kLongRow = 4 * 8 * (int)kRowPart;  // entries
+__host__ __device__ inline int64_t table_row_items(int32_t n, int32_t S) {
+    if (S >= kLongRow) return (int64_t)n * ((S + kLongRow - 1) / kLongRow);
+    return ((int64_t)n + 3) / 4 * ((S + 8 * (int)kRowPart - 1) / (8 * (int)kRowPart));
+}
 
 // What the comparisons read: the walk store, rows of whole 16-byte units at multiples of that, or rows at any address (an
 // instance each: 128,256 rows of 2 KB 39.5 us in whole units; at any address 42, and with both in one kernel's registers 49).
@@ -607,30 +613,33 @@ __global__ __launch_bounds__(kTableThreads) CFGZIP_OWN_PAGES void table_settle_k
                 }
             }
         } else {
-            // four rows per wave against their classes' members' rows, which many share (they stay in the caches); what
-            // there is to read is every row once.  Of rows of more than kRowPart units a wave takes a part: waves that
-            // read whole rows of 8 KB all ask the same memory channels at a time (262 MB in rows of 8 KB: 60 us, 49 us so)
+            // rows against their classes' members' rows, which many share (they stay in the caches); what there is to read is
+            // every row once.  A wave takes four rows at a time, 1 KB of each, or 4 KB of one where a row has that: of rows of 8
+            // KB (262 MB in all) whole rows, which all begin at the same memory channels, took 60 us, 1 KB of four rows each 48.4,
+            // and so 40.5; rows of 2 KB, four at a time, 39
             const bool vec = UNITS || a.S >= 8;
             const uint32_t s8 = ((uint32_t)a.S + 7u) / 8u;
-            const int64_t parts = vec ? table_row_parts(a.S) : 1, items = ((int64_t)a.n + 3) / 4 * parts;
+            const bool long_rows = a.S >= kLongRow;
+            const int64_t items = table_row_items(a.n, vec ? a.S : 1), per = long_rows ? a.n : ((int64_t)a.n + 3) / 4, parts = items / per;
             for (int64_t x = gw; x < items; x += waves) {
-                const int64_t t0 = x / parts * 4;
+                const int64_t t0 = x / parts * (long_rows ? 1 : 4);
                 int32_t t[4], ref[4];
                 int cnt = 0;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    t[u] = (int32_t)min(t0 + u, (int64_t)a.n - 1);  // repeats the last one past the end
+                    t[u] = (int32_t)min(t0 + (long_rows ? 0 : u), (int64_t)a.n - 1);  // repeats the last one past the end
                     ref[u] = class_member(a, t[u]);
                     cnt += ref[u] != t[u];
                 }
                 if (!cnt) continue;  // all four are their classes' members (wave-uniform)
                 if (vec) {
-                    const uint32_t from = (uint32_t)(x % parts) * kRowPart, to = min(s8, from + kRowPart);
-                    for (uint32_t j = from + lane; j < to; j += 64) {
+                    const uint32_t apart = long_rows ? kRowPart : 0u;  // of the four pieces, in their row
+                    const uint32_t from = (uint32_t)(x % parts) * (long_rows ? 4u * kRowPart : kRowPart) + lane;
+                    if (long_rows || from < s8) {
                         u32x4_any p[4], q[4];
-                        auto piece = [&](uint32_t tok) -> u32x4_any {  // of a token's row
+                        auto piece = [&](uint32_t tok, uint32_t j) -> u32x4_any {  // of a token's row
                             if (UNITS) {
-                                const uint4 v = reinterpret_cast<const uint4 *>(a.sig)[tok * s8 + j];  // (31 bits)
+                                const uint4 v = reinterpret_cast<const uint4 *>(a.sig)[tok * s8 + min(j, s8 - 1u)];  // (31 bits)
                                 return u32x4_any{v.x, v.y, v.z, v.w};
                             }
                             const uint16_t *row = a.sig + (size_t)tok * a.S;
@@ -638,8 +647,8 @@ __global__ __launch_bounds__(kTableThreads) CFGZIP_OWN_PAGES void table_settle_k
                         };
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
-                            p[u] = piece((uint32_t)t[u]);
-                            q[u] = piece((uint32_t)ref[u]);
+                            p[u] = piece((uint32_t)t[u], from + u * apart);
+                            q[u] = piece((uint32_t)ref[u], from + u * apart);
                         }
 #pragma unroll
                         for (int u = 0; u < 4; ++u)

@@ -1365,7 +1365,7 @@ extern "C" int cfgzip_build_classes(const uint8_t *tok_bytes, const int64_t *tok
             hipLaunchKernelGGL(table_settle_kernel<SETTLE_STORE>, dim3((unsigned)(sa.number_blocks + kGroupBlocks * sa.buckets + pair_blocks)),
                                dim3(kTableThreads), lds, stream, sa);
         } else {
-            const int pair_blocks = (int)std::min<int64_t>(ceil_div(ceil_div(n, 4) * std::max<int64_t>(1, table_row_parts(S)), kWaves), 8192);
+            const int pair_blocks = (int)std::min<int64_t>(ceil_div(table_row_items(n, S), kWaves), 8192);
             const bool units = S % 8 == 0 && aligned_to(sig, 16);
             auto kern = units ? table_settle_kernel<SETTLE_UNITS> : table_settle_kernel<SETTLE_ROWS>;
             hipLaunchKernelGGL(kern, dim3((unsigned)(sa.number_blocks + pair_blocks)), dim3(kTableThreads), lds, stream, sa);

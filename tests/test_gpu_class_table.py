@@ -316,6 +316,35 @@ def test_rows_of_any_length_at_any_address(lib, S, shift):
     assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
 
 
+@pytest.mark.parametrize("S", [2040, 2047, 2048, 2049, 2056, 4095, 4096, 4104, 6150])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_an_entry_anywhere_in_a_long_row(lib, S, shift):
+    """Rows around those that a wave compares one at a time and not four: in whole units and at any address, rows that differ
+    from their class's first in one entry, at the first, the last, and around every 64th unit."""
+    print(f"case S={S} shift={shift}", flush=True)
+    rng = np.random.default_rng(S + shift)
+    places = sorted({0, S - 1, *(q for k in range(512, S, 512) for q in (k - 1, k, k + 7) if q < S)})
+    distinct = rng.integers(0, 1 << 16, size=(3, S)).astype(np.uint16)
+    of = rng.integers(0, 3, size=5 + 2 * len(places))
+    rows = distinct[of]
+    for i, q in enumerate(places):
+        rows[4 + 2 * i, q] ^= 1 + i
+    V = len(rows)
+    buf = torch.zeros(V * S + 8, dtype=torch.int16, device="cuda")
+    sig = buf[shift:shift + V * S].view(torch.uint16).view(V, S)
+    sig.view(torch.int16).copy_(torch.from_numpy(rows.view(np.int16)).cuda())
+    tb, to = torch.zeros(V, dtype=torch.uint8, device="cuda"), torch.arange(V + 1, dtype=torch.int64, device="cuda")
+    off = np.arange(V + 1, dtype=np.int64)
+    for hashes in (of.astype(np.int64) * 0x9E3779B97F4A7C1, None):  # as if the changed rows were their classes', and by the rows
+        if hashes is None:
+            _, inv = np.unique(rows, axis=0, return_inverse=True)
+            hashes = inv.ravel().astype(np.int64) * 0x9E3779B97F4A7C1
+        c, r, C, coll = lib.cfgzip_build_classes(tb, to, None, sig, torch.from_numpy(hashes).cuda())
+        want_c, want_r = oracle.build_classes(rows, off)
+        assert C == len(want_r) and (coll > 0) == (len(np.unique(hashes)) < C)
+        assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
+
+
 @pytest.mark.parametrize("S", [3071, 3072, 3073, 4096])
 @pytest.mark.parametrize("composed", [False, True])
 def test_walks_that_lie_apart(lib, S, composed):
