@@ -52,8 +52,6 @@ constexpr unsigned long long kTokenMask = kTableMaxTokens - 1;
 constexpr unsigned long long kNoEntry = ~0ull;
 static_assert(kTableHashBits + 8 + kTokenBits < 64, "an entry is never all ones");
 constexpr int kCrossParts = 4;   // waves that share one comparison across two image rows
-constexpr int kGroupBlocks = 4;  // workgroups that share the comparisons of a bucket's groups
-
 // Runs of tokens that the gathering workgroups take, a token per thread.
 constexpr int kRunBits = 10;
 constexpr int kRun = 1 << kRunBits;
@@ -69,6 +67,13 @@ constexpr int kMergeThreads = 1024;
 constexpr int kMergeWaves = kMergeThreads / 64;
 constexpr int kMaxBuckets = 256;
 constexpr int kBucketTokens = 64;
+// Workgroups that share the comparisons of a bucket's groups, and those that compare tokens with their groups' members, at
+// the most: what a chip takes at a time is 768, and a workgroup costs its start.  Settling 151,936 / 128,256 tokens from the
+// walk store with 4 and 2,048 23.8 / 17.2 us, 2 and 2,048 21.9 / 16.3, 2 and 1,280 21.6 / 15.4, 2 and 768 23.3 / 15.7, 1 and
+// 2,048 26.0 / 18.6.  With fewer buckets than there may be the chip is not full, and four are better (a call on 4,096 tokens
+// 38.9 us, with two 39.9).
+constexpr int kPairBlocks = 1280;
+inline int table_group_shift(int buckets) { return buckets < kMaxBuckets ? 2 : 1; }  // as a power of two
 // A bucket's LDS table.  262,144 tokens of a class each put 1,024 into a bucket, give or take 32, and half full a run
 // of kTableProbes taken slots has a chance of 1e-11 in each place.
 constexpr int kTableSlotBits = 11;
@@ -423,7 +428,7 @@ struct TableSettleArgs {
     const uint8_t *tok_head;
     int n;
     int number_blocks, buckets;  // the first workgroups number, the next compare a bucket's groups, the rest tokens
-    int list_room;
+    int list_room, group_shift;
     const int32_t *listed_group, *listed_count;
     StoreSource store;    // from the walk store
     const uint16_t *sig;  // from rows: [n][S]
@@ -535,14 +540,14 @@ __global__ __launch_bounds__(kTableThreads) CFGZIP_OWN_PAGES void table_settle_k
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint16_t *staged = reinterpret_cast<uint16_t *>(lds) + (size_t)wave * 2 * kWalkStoreMaxStride;  // STORE only
     const int block = (int)blockIdx.x - a.number_blocks;
-    const int group_blocks = STORE ? kGroupBlocks * a.buckets : 0;
+    const int group_blocks = STORE ? a.buckets << a.group_shift : 0, share = block & ((1 << a.group_shift) - 1);
     // where groups are compared: a lane's first group, asked for before the store's header is looked at
     const int parts = STORE && a.S >= 8 ? kCrossParts : 1;
-    const int teams = kGroupBlocks * (kWaves / parts), team = block % kGroupBlocks * (kWaves / parts) + wave / parts;
-    const int32_t *listed = a.listed_group + (size_t)(block / kGroupBlocks) * a.list_room;
+    const int teams = (kWaves / parts) << a.group_shift, team = share * (kWaves / parts) + wave / parts;
+    const int32_t *listed = a.listed_group + (size_t)(block >> a.group_shift) * a.list_room;
     int listed_here = 0, next_group = 0;
     if (block < group_blocks) {
-        listed_here = min(max(a.listed_count[block / kGroupBlocks], 0), a.list_room);
+        listed_here = min(max(a.listed_count[block >> a.group_shift], 0), a.list_room);
         next_group = listed[min(team + lane * teams, a.list_room - 1)];
     }
     uint32_t stride = 0;  // of the walk store

@@ -1359,10 +1359,11 @@ extern "C" int cfgzip_build_classes(const uint8_t *tok_bytes, const int64_t *tok
         constexpr int kWaves = kTableThreads / 64;
         size_t lds = table_rank_bytes(n);
         if (source == FROM_STORE) {
-            const int pair_blocks = (int)std::min<int64_t>(ceil_div(n, 8 * kWaves), 2048);
+            const int pair_blocks = (int)std::min<int64_t>(ceil_div(n, 8 * kWaves), kPairBlocks);
             sa.buckets = ma.buckets;
+            sa.group_shift = table_group_shift(ma.buckets);
             lds = std::max(lds, (size_t)kWaves * 2 * kWalkStoreMaxStride * sizeof(uint16_t));
-            hipLaunchKernelGGL(table_settle_kernel<SETTLE_STORE>, dim3((unsigned)(sa.number_blocks + kGroupBlocks * sa.buckets + pair_blocks)),
+            hipLaunchKernelGGL(table_settle_kernel<SETTLE_STORE>, dim3((unsigned)(sa.number_blocks + (sa.buckets << sa.group_shift) + pair_blocks)),
                                dim3(kTableThreads), lds, stream, sa);
         } else {
             const int pair_blocks = (int)std::min<int64_t>(ceil_div(table_row_items(n, S), kWaves), 8192);
