@@ -23,19 +23,17 @@
 // What a token's set is written as (the canonical row and its hash) is worked out once per set too; writing a row
 // is then a copy out of LDS, and writing the rows is what bounds the kernel on a large vocabulary.
 //
-// Measured: 128,256 tokens over the JSON grammar with rows of 1,024 entries 116 us (a wave per token took 510 us for
-// most tokens and 276 us for long digit runs), 32,000 over the statement grammar with rows of 256 80 us (210 us).
-// What bounds it is instruction issue (the vector units are busy for 60 % of the kernel, the scalar one about as long), and
-// in the workgroup that is done last a chain of sets that nobody has met.  A step alone in its compute unit takes 2.2 us,
-// 670 instructions and twenty LDS accesses (the steps of 32 digits over the JSON grammar, sets of 20 to 51 configurations;
-// 3.75 us with the pairs of configuration and production listed in LDS, the next set looked up and loaded again, and a
-// production read through a pointer that may be global, which waits for all rows on their way to memory).  A wave of the
-// JSON workload, us: set-up 10, steps 23 (ten of them), sets written out 18 (three), rows 23, the rest, look-ups and waits
-// for other waves, 27; of the statement grammar 8, 18 (eight), 7 (two), 3 and 11, and the workgroup that is done last takes
-// half as long again as the average one.  Slower: longest tokens first for some of the waves and shortest first for the
-// others (JSON call 213 to 242 us, 208 so; the rows then go out earlier, but the chain is what counts), rows two at a time,
-// claims asked for ahead of a step's first look-ups (2 %: more instructions), the symbols of a set's lists in registers to
-// bring them into order, a wave of few tokens that waits for all of them before it writes any (JSON 1 to 5 %).
+// Measured: 128,256 tokens over the JSON grammar with rows of 1,024 entries 109 us (a wave per token took 510 us for
+// most tokens and 276 us for long digit runs), 32,000 over the statement grammar with rows of 256 74 us (210 us).
+// What bounds it is instruction issue (with the JSON grammar the vector units are busy for 60 % of the kernel, and the scalar
+// one about as long), and in the workgroup that is done last a chain of sets that nobody has met.  A step alone in its compute
+// unit takes 2.2 us, 670 instructions and twenty LDS accesses (the steps of 32 digits over the JSON grammar, sets of 20 to 51
+// configurations; 3.75 us with the pairs of configuration and production listed in LDS, the next set looked up and loaded
+// again, and a production read through a pointer that may be global, which waits for all rows on their way to memory).  Slower:
+// longest tokens first for some of the waves and shortest first for the others (JSON call 213 to 242 us, 208 otherwise; the
+// rows then go out earlier, but the chain is what counts), rows two at a time, claims asked for ahead of a step's first
+// look-ups (2 %: more instructions), the symbols of a set's lists in registers to bring them into order, a wave of few tokens
+// that waits for all of them before it writes any (JSON 1 to 5 %).
 //
 // Everything in LDS is bounded.  A token that would need more (more than 128 successors at a byte, more cells,
 // sets or row entries than there is room for) goes to the list of the passes behind this one, which take it alone.
@@ -59,7 +57,7 @@ constexpr int kShNext = 2048;       // known successors (8 KB)
 constexpr int kShSets = 1024;       // sets (8 KB, and 16 KB for what they are written as)
 // Steps that a wave works out before its lanes try alone.  The waves of a workgroup with 125 tokens over the JSON or the
 // statement grammar work out 6 to 8 steps, with 501 tokens 10 to 14; from the first step on it costs them 1.3 %, from
-// the 7th 0.8, from here nothing that could be measured.
+// the 7th 0.8, from here nothing that could be measured (from the 25th on tokens that share no sets take 5 to 30 % longer).
 constexpr int kShShared = 12;
 constexpr int kShPool = 6144;       // configurations of all sets (24 KB)
 constexpr int kShOut = 18432;       // row entries of all sets written so far (36 KB)
@@ -72,15 +70,19 @@ constexpr int kShFew = 32;          // productions a byte has at the most where 
 constexpr int kShBatch = 1024;      // tokens a workgroup sorts by length at a time
 constexpr int kShBytes = 6144;      // their bytes, kept in LDS; if there are more they are read from memory
 constexpr int kShLengths = 64;      // lengths told apart in sorting
-constexpr int kShTakeMost = 16;     // tokens a wave takes at a time
-// Tokens for every wave up to which they are not sorted and a wave takes its share at once.  Calls sorted / not, us, mean
-// of vocabularies of four seeds with rows of 256 entries:
-//   tokens a workgroup      63         78         94        109        125        141        156        188
-//   statement grammar    118 /  99  121 / 108  128 / 129  123 / 117  125 / 125  125 / 121  131 / 127  135 / 137
-//   JSON grammar         159 / 161  159 / 164  160 / 168  159 / 165  160 / 171  159 / 169  159 / 171  159 / 174
-// The statement grammar's tokens are of much the same length, and what sorting costs it from 94 to 156 the JSON grammar
-// gains; the line lies in between.
-constexpr int kShOnce = 8;
+// Sorted tokens that a wave takes at a time, at the most: where the workgroup has up to kShFewTokens of them, and where it has
+// more.  Few at a time spread the steps over the waves, many make the look-ups of short tokens cheaper: 4 / 8 / 16 / 32, calls,
+// us, 125 tokens a workgroup over the statement grammar 115 / 117 / 119 / -, 501 over the JSON grammar 188 / 183 / 187 / 197.
+constexpr int kShTakeFew = 4, kShTakeMost = 8;
+constexpr int kShFewTokens = 16 * kShWaves;
+// Tokens for every wave up to which they are not sorted and a wave takes its share at once.  Calls sorted / not, rows of 1,024
+// entries with the JSON grammar, of 256 with the statement grammar, us:
+//   tokens a workgroup       47          63          78          94         109         125
+//   statement grammar     71 /  67    75 /  72    85 /  82    79 /  85    88 /  94    80 /  87
+//   JSON grammar         104 / 113   104 / 107   105 / 115   105 / 116   106 / 123   106 / 129
+// The statement grammar's tokens are of much the same length, and what sorting costs it up to 78 tokens the JSON grammar
+// gains; tokens that share no sets lose 2 to 7 % from the line on (32,000 of 4 / 8 / 12 bytes).
+constexpr int kShOnce = 4;
 constexpr int kShSeen = 256;        // slots of a wave's table of the successors found so far: at most half full
 constexpr int kShProbes = 48;       // slots looked at before a table counts as full
 constexpr int kShFrontier = 128;    // successors of a set at one byte: two a lane
@@ -707,9 +709,9 @@ struct LaneSet {
 };
 
 // One byte of Algorithm 1 on such a set, where `pair` and `follow` are kept: the number of the set that follows, which the
-// lanes then hold; kByTheWave, and nothing is done, if it takes more than 64 successors or a long body to make it.  Which productions
-// apply to a configuration is one look-up of a bit for each of the byte's productions; the successors are dealt out to the
-// lanes by a prefix sum of how many there are.  JSON call 237 -> 208 us, statement grammar 157 -> 143 with the sets' order by
+// lanes then hold; kByTheWave, and nothing is done, if it takes more than 64 successors or a long body to make it.  Which
+// productions apply to a configuration is one look-up of a bit for each of the byte's productions; the successors are dealt
+// out to the lanes by a prefix sum of how many there are.  JSON call 237 -> 208 us, statement grammar 157 -> 143 with the sets' order by
 // a word of their first symbols, 2,000 to 64,000 tokens with the JSON grammar 0.71 to 0.80 of the time.
 __device__ __forceinline__ uint32_t sh_step_lanes(const DisplacementArgs &a, SharedLds &L, uint32_t *work, uint32_t *seen,
                                                   PoolRoom &room, LaneSet &set, uint32_t byte_number, uint32_t dead, int lane) {
@@ -1040,11 +1042,10 @@ __device__ __forceinline__ void sh_take_alone(const DisplacementArgs &a, AloneLd
 }
 
 // A workgroup takes `per_group` consecutive tokens, the longest first: what a token of 25 bytes needs, set after set that
-// nobody has met, is a chain that nothing shortens, and begun last it was what the workgroup waited for (128,256 tokens
-// over the JSON grammar, in the order they come in, eight a wave at a time: the waves done after 106 us on average, the
-// last one after 177; so 149).  The lanes of a wave hold tokens in all stages.  The wave works out a step that one of them waits for, of the token with most bytes to go; if
-// there is none, writes the rows of those that are through; if none is, takes more tokens; and waits only if there are
-// none left.
+// nobody has met, is a chain that nothing shortens, and begun last it is what the workgroup waits for.  The lanes of a wave
+// hold tokens in all stages.  The wave works out a step that one of them waits for, of the token with most bytes to go, and
+// the steps behind it; if there is none, writes the rows of those that are through; if none is, takes more tokens; and waits
+// only if there are none left.
 template <bool ROWS16>  // rows start at multiples of 16 bytes
 __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shared_kernel(DisplacementArgs a, int per_group) {
     __shared__ SharedLds L;
@@ -1425,7 +1426,7 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
                     if (pos < end) like = byte_at(pos);
                     if (pos + 1 < end) after = byte_at(pos + 1);
                 }
-                take = min(2 * take, kShTakeMost);
+                take = min(2 * take, in_group > kShFewTokens ? kShTakeMost : kShTakeFew);
                 continue;
             }
             if (idle == ~0ull) break;

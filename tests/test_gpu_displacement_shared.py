@@ -271,9 +271,11 @@ def test_staged_and_unstaged_batches_one_after_the_other(lib):
     assert len(kinds) == 4
 
 
-@pytest.mark.parametrize("V,longest", [(32_768, 6), (32_769, 6), (33_100, 80), (262_144, 4), (262_401, 4)])
+@pytest.mark.parametrize("V,longest", [(16_384, 6), (16_385, 6), (32_768, 6), (32_769, 6), (33_100, 80), (65_536, 5),
+                                       (65_537, 5), (262_144, 4), (262_401, 4)])
 def test_groups_around_the_sorted_batches(lib, V, longest):
-    """128 tokens for a workgroup, which its waves take at once, and 129, which are sorted by length; tokens of up to 80 bytes;
+    """64 tokens for a workgroup, which its waves take at once, and 65, which are sorted by length; 256 and 257, of which a wave
+    takes more at a time; tokens of up to 80 bytes;
     a whole batch of 1,024 tokens and one more.  The vocabulary repeats 700 strings: theirs are compared with the oracle, and
     every row, hash and status with its string's."""
     print(f"case V={V} longest={longest}", flush=True)
