@@ -24,7 +24,7 @@
 // is then a copy out of LDS, and writing the rows is what bounds the kernel on a large vocabulary.
 //
 // Measured: 128,256 tokens over the JSON grammar with rows of 1,024 entries 109 us (a wave per token took 510 us for
-// most tokens and 276 us for long digit runs), 32,000 over the statement grammar with rows of 256 74 us (210 us).
+// most tokens and 276 us for long digit runs), 32,000 over the statement grammar with rows of 256 71 us (210 us).
 // What bounds it is instruction issue (with the JSON grammar the vector units are busy for 60 % of the kernel, and the scalar
 // one about as long), and in the workgroup that is done last a chain of sets that nobody has met.  A step alone in its compute
 // unit takes 2.2 us, 670 instructions and twenty LDS accesses (the steps of 32 digits over the JSON grammar, sets of 20 to 51
@@ -1302,6 +1302,9 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
                 const int chosen = sorted ? (int)(wave_max32(key) & 63u) ^ 63
                                           : __ffsll(__ballot(waits == kNextEmpty)) - 1;
                 uint32_t from = wave_read(set, chosen), on = wave_read(like, chosen);
+                // Before the waves that look things up or wait for this one: calls of 20,000 to 64,000 tokens 2 to 4 % (statement
+                // grammar, 32,000 tokens, with classes 115.8 -> 112.7 us); also where sets are written out: no more.
+                __builtin_amdgcn_s_setprio(2);
                 LaneSet held;
                 bool holds = false;  // the lanes have the set's configurations
                 for (;;) {
@@ -1328,6 +1331,7 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
                     from = following;
                     on = wave_read(like, chosen);
                 }
+                __builtin_amdgcn_s_setprio(0);
                 continue;
             }
             // What the sets reached are written as.
