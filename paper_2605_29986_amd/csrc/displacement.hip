@@ -8,8 +8,8 @@
 //   2. displacement_alone.hpp: the tokens whose sets did not fit there, one wave each, under small caps (little LDS, many
 //      waves per compute unit);
 //   3. what crosses those, again one wave each, under the caps that the interface states.
-// They are one launch: a workgroup takes what its own walk has handed on.  With more than 255 symbols there is no shared
-// walk, and the two passes behind it are launches of their own over all tokens.
+// The second and the third are one launch.  With more than 255 symbols there is no shared walk, and the two passes behind it
+// are launches of their own over all tokens.
 //
 // Everything is bounded: queue, stack, number of successors per byte and row length each have
 // a cap.  A token that crosses the interface's caps, or whose set does not fit the row,
@@ -419,6 +419,69 @@ int enqueue_grammar_tables(const Grammar &g, const GrammarWorkspace &w, bool lik
     return check_launch();
 }
 
+// ---- what the shared walk hands on ---------------------------------------------------------
+
+// What the passes behind the shared walk hold, as many waves as there is LDS for.
+constexpr int kAloneThreads = 1024;
+struct AloneLds {
+    using First = TokenLds<uint8_t, Rec<uint8_t, kLists1<uint8_t>, kLists1<uint8_t>>, kFrontier1, false>;
+    using Last = TokenLds<uint8_t, Rec<uint8_t, kIn2, kOut2>, kFrontier2, true>;
+    static constexpr int kRoom = 160 * 1024 - 16, kWaves = kAloneThreads / 64;
+    static constexpr int kFirst = kRoom / (int)sizeof(First) < kWaves ? kRoom / (int)sizeof(First) : kWaves;
+    static constexpr int kLast = kRoom / (int)sizeof(Last) < kWaves ? kRoom / (int)sizeof(Last) : kWaves;
+    __align__(16) uint32_t next[2];  // of the workgroup's two lists
+    uint32_t left;                   // entries of the second
+    union {
+        First first[kFirst];
+        Last last[kLast];
+    };
+};
+static_assert(sizeof(AloneLds) <= 160 * 1024 && AloneLds::kFirst >= 11 && AloneLds::kLast >= 4, "");
+
+// The tokens that the shared walk has no room for: a wave each, under small caps, and those that cross them once more under
+// the interface's.  They are on one list for all workgroups: workgroup b takes entries b, b + grid, ...  Where such tokens lie
+// together in a vocabulary the workgroups of the walk that had them would otherwise be the only ones that work: 128,256 tokens
+// over the JSON grammar of which the last 8,000 (of 12 bytes) share no sets 1,430 us a call, 389 so; 120,556 of which the last
+// 300 (of 28 bytes, most of which take the wide caps) 7,400 and 550.  What it costs is a launch that usually has nothing to
+// do: 2 us of 50 with 2,000 tokens over the statement grammar, 2 to 3 of 105 to 125 with 32,000 and 128,256 over the JSON
+// grammar.  (Lists offered by each workgroup to those that are through with their walk save the launch, but these are gone by
+// then, or all at one cursor: 1,620 us, 10,900, and 32,000 tokens that share no sets 7,140 where it is 415.)
+__global__ __launch_bounds__(kAloneThreads) void displacement_alone_kernel(DisplacementArgs a) {
+    __shared__ AloneLds A;
+    const int count = min(a.hdr->retry_count[0], a.V), grid = (int)gridDim.x, block = (int)blockIdx.x;
+    if (block >= count) return;
+    const int mine = (count - 1 - block) / grid + 1;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x == 0) A.next[0] = A.next[1] = A.left = 0;
+    __syncthreads();
+    // the next entry of the workgroup's list `which`, -1 behind its end
+    auto take = [&](int which, int n) -> int {
+        int i = 0;
+        if (lane == 0) i = (int)atomicAdd(&A.next[which], 1u);
+        i = __builtin_amdgcn_readfirstlane(i);
+        if (i >= n) return -1;
+        const int32_t *entry = a.retry_list[which] + block + (int64_t)i * grid;  // (of the second: another wave of the workgroup wrote it)
+        return __builtin_amdgcn_readfirstlane(__hip_atomic_load(entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    };
+    if (wave < AloneLds::kFirst)
+        for (int t; (t = take(0, mine)) >= 0;) {
+            const bool crosses = token_displacement<uint8_t, kLists1<uint8_t>, kLists1<uint8_t>, kFrontier1, false>(a, t, A.first[wave], false);
+            if (crosses && lane == 0) a.retry_list[1][block + (int64_t)atomicAdd(&A.left, 1u) * grid] = t;
+            wave_order();
+        }
+    __syncthreads();
+    const int left = (int)__builtin_amdgcn_readfirstlane(A.left);
+    if (wave >= AloneLds::kLast || wave >= left) return;
+    AloneLds::Last &lds = A.last[wave];
+    const bool adj_in_lds = a.g.N * a.g.W <= kAdjLdsWords;
+    if (adj_in_lds)
+        for (int i = lane; i < a.g.N * a.g.W; i += 64) lds.adj[i] = a.adj[i];
+    for (int t; (t = take(1, left)) >= 0;) {
+        token_displacement<uint8_t, kIn2, kOut2, kFrontier2, true>(a, t, lds, adj_in_lds);
+        wave_order();
+    }
+}
+
 // ---- more than 255 symbols ----------------------------------------------------------------
 
 // Entries of a long list that a workgroup of the second pass takes at a time.  The atomics on the list's one cursor are
@@ -491,6 +554,8 @@ int launch_displacements(const DisplacementArgs &a, int n_cu, hipStream_t stream
             hipLaunchKernelGGL(displacement_shared_kernel<true>, dim3(grid), dim3(kShThreads), 0, stream, a, per_group);
         else
             hipLaunchKernelGGL(displacement_shared_kernel<false>, dim3(grid), dim3(kShThreads), 0, stream, a, per_group);
+        CFGZIP_TRY(check_launch());
+        hipLaunchKernelGGL(displacement_alone_kernel, dim3((unsigned)std::min<int64_t>(n_cu, a.V)), dim3(kAloneThreads), 0, stream, a);
         return check_launch();
     }
     // more symbols than a shared cell holds: every token is taken alone

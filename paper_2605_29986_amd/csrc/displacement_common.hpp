@@ -14,7 +14,8 @@ constexpr int kStatusBadGrammar = 2;
 
 struct GrammarHeader {
     int32_t invalid;      // set by the index kernel when the productions break a stated rule
-    // two lists of tokens handed on: by the shared walk, and by the pass after it
+    // two lists of tokens: those that the shared walk hands on, or with more than 255 symbols all, and then those that the
+    // pass over them hands on
     int32_t retry_count[2];
     int32_t retry_next[2];  // next entry of each list to be taken
     int32_t pad[59];

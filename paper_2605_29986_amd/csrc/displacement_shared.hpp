@@ -155,7 +155,6 @@ struct SharedLds {
     uint32_t follow_kept;     // whether `follow` holds what the relation says
     uint32_t pool_top, out_top, cursor;
     uint32_t start_set, dead_set;  // nothing consumed and nothing pushed; no configuration left
-    uint32_t handed;         // tokens on the workgroup's list of those that it takes alone
     uint32_t scattered;      // some token's bytes do not lie where the token before ends
     uint32_t of_length[kShLengths];
     uint16_t order[kShBatch], start[kShBatch + 2];  // the batch's tokens, longest first; where each one's bytes begin
@@ -990,57 +989,6 @@ __device__ __forceinline__ void sh_write_set(const DisplacementArgs &a, SharedLd
     if (lane == 0) __hip_atomic_store(&L.row[set], result, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// What the passes behind the walk hold, as many waves as there is LDS for.
-struct AloneLds {
-    using First = TokenLds<uint8_t, Rec<uint8_t, kLists1<uint8_t>, kLists1<uint8_t>>, kFrontier1, false>;
-    using Last = TokenLds<uint8_t, Rec<uint8_t, kIn2, kOut2>, kFrontier2, true>;
-    static constexpr int kRoom = (int)sizeof(SharedLds) - 16;
-    static constexpr int kFirst = kRoom / (int)sizeof(First) < kShWaves ? kRoom / (int)sizeof(First) : kShWaves;
-    static constexpr int kLast = kRoom / (int)sizeof(Last) < kShWaves ? kRoom / (int)sizeof(Last) : kShWaves;
-    __align__(16) uint32_t next[2];  // of the two lists
-    uint32_t left;                   // entries of the second
-    union {
-        First first[kFirst];
-        Last last[kLast];
-    };
-};
-static_assert(sizeof(AloneLds) <= sizeof(SharedLds) && AloneLds::kFirst >= 11 && AloneLds::kLast >= 4, "");
-
-// The `handed` tokens of the workgroup's list that its walk has no room for: a wave each, under small caps, and those that
-// cross them once more under the interface's.  As launches of their own over one list of all workgroups' tokens these took
-// 4.6 us each where there were none, and the atomics on the list's cursor were served one after the other (14 ns each).
-__device__ __forceinline__ void sh_take_alone(const DisplacementArgs &a, AloneLds &A, int64_t group0, int handed) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (threadIdx.x == 0) A.next[0] = A.next[1] = A.left = 0;
-    __syncthreads();
-    // the next entry of list `which`, -1 behind its end
-    auto take = [&](int which, int count) -> int {
-        int i = 0;
-        if (lane == 0) i = (int)atomicAdd(&A.next[which], 1u);
-        i = __builtin_amdgcn_readfirstlane(i);
-        if (i >= count) return -1;
-        const int32_t *entry = a.retry_list[which] + group0 + i;  // (another wave of the workgroup wrote it)
-        return __builtin_amdgcn_readfirstlane(__hip_atomic_load(entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-    };
-    if (wave < AloneLds::kFirst)
-        for (int t; (t = take(0, handed)) >= 0;) {
-            const bool crosses = token_displacement<uint8_t, kLists1<uint8_t>, kLists1<uint8_t>, kFrontier1, false>(a, t, A.first[wave], false);
-            if (crosses && lane == 0) a.retry_list[1][group0 + atomicAdd(&A.left, 1u)] = t;
-            wave_order();
-        }
-    __syncthreads();
-    const int left = (int)__builtin_amdgcn_readfirstlane(A.left);
-    if (wave >= AloneLds::kLast || wave >= left) return;
-    AloneLds::Last &lds = A.last[wave];
-    const bool adj_in_lds = a.g.N * a.g.W <= kAdjLdsWords;
-    if (adj_in_lds)
-        for (int i = lane; i < a.g.N * a.g.W; i += 64) lds.adj[i] = a.adj[i];
-    for (int t; (t = take(1, left)) >= 0;) {
-        token_displacement<uint8_t, kIn2, kOut2, kFrontier2, true>(a, t, lds, adj_in_lds);
-        wave_order();
-    }
-}
-
 // A workgroup takes `per_group` consecutive tokens, the longest first: what a token of 25 bytes needs, set after set that
 // nobody has met, is a chain that nothing shortens, and begun last it is what the workgroup waits for.  The lanes of a wave
 // hold tokens in all stages.  The wave works out a step that one of them waits for, of the token with most bytes to go, and
@@ -1144,7 +1092,6 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
     if (tid == 0) {
         L.pool_top = 0;
         L.out_top = 0;
-        L.handed = 0;
         L.few_each = 1;
         L.follow_kept = 0;
     }
@@ -1371,10 +1318,10 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
                 const u64 handed = __ballot(through && give_up);
                 if (handed) {
                     int32_t at = 0;
-                    if (lane == 0) at = (int32_t)atomicAdd(&L.handed, (uint32_t)__popcll(handed));
+                    if (lane == 0) at = (int32_t)atomicAdd(&a.hdr->retry_count[0], (int32_t)__popcll(handed));
                     at = __builtin_amdgcn_readfirstlane(at);
                     if (through && give_up)
-                        a.retry_list[0][group0 + at + __popcll(handed & ((1ull << lane) - 1ull))] = (int32_t)t;
+                        a.retry_list[0][at + __popcll(handed & ((1ull << lane) - 1ull))] = (int32_t)t;
                 }
                 // the rows, one after the other by the whole wave
                 const u64 plain = __ballot(done && !invalid && !crossed);
@@ -1437,11 +1384,6 @@ __global__ __launch_bounds__(kShThreads) CFGZIP_OWN_PAGES void displacement_shar
             __builtin_amdgcn_s_sleep(2);  // another wave is at all that is left; it waits for nothing while it works
         }
     }
-    __syncthreads();
-    const int handed = (int)__builtin_amdgcn_readfirstlane(L.handed);
-    if (handed == 0) return;
-    __syncthreads();  // everybody knows: the walk's LDS is done with
-    sh_take_alone(sh_arguments(), *reinterpret_cast<AloneLds *>(&L), group0, handed);
 }
 
 }  // namespace

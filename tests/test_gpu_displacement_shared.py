@@ -281,3 +281,48 @@ def test_groups_around_the_sorted_batches(lib, V, longest):
     print(f"case V={V} longest={longest}", flush=True)
     few = make_token_strings(V, 700, b'{}[]",:0123456789.eE+-truefalsn \\ua', longest)
     _check_repeated(lib, make_json_gnf(), few, np.random.default_rng(V).integers(0, few.V, size=V))
+
+
+def _hard_grammar(n):
+    """The JSON grammar, and n bytes that stand for a symbol each, which may all follow each other: every string of those is
+    a queue of its own.  The grammar and the bytes."""
+    json = make_json_gnf()
+    taken = {int(b) for b in json.byte}
+    free = [b for b in range(1, 32) if b not in taken]
+    own, pairs = free[:n], free[n:2 * n]
+    prods = json.productions()
+    for i in range(n):
+        prods.append((json.N + i, own[i], ()))
+        prods += [(json.N + n, pairs[i], (json.N + i, json.N + j)) for j in range(n)]
+    return grammar_from_productions(json.N + n + 1, prods), own
+
+
+def _call_us(lib, g, vocab, row_len):
+    gd = _grammar_dev(g)
+    tb, to = torch.from_numpy(vocab.tok_bytes).cuda(), torch.from_numpy(vocab.tok_off).cuda()
+    times = []
+    for _ in range(7):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        lib.cfgzip_displacements(tb, to, *gd, g.N, row_len=row_len)
+        end.record()
+        end.synchronize()
+        times.append(begin.elapsed_time(end) * 1e3)
+    return sorted(times)[3]
+
+
+def test_tokens_that_share_no_sets_side_by_side(lib):
+    """300 tokens behind each other that one workgroup has no room for, most of which need the widest caps: their results, and
+    that the whole chip takes part.  (Three times what the same tokens take spread over the vocabulary, whose walks have room
+    for them; 38 times with one workgroup at work.)"""
+    g, own = _hard_grammar(9)
+    rng = np.random.default_rng(12)
+    easy = make_token_strings(31, 400, b'{}[]",:0123456789.eE+-truefalsn \\ua', 8).tokens()
+    hard = [bytes(own[i] for i in rng.integers(0, 9, size=28)) for _ in range(300)]
+    few = vocab_from_tokens(easy + hard)
+    pick = np.concatenate([rng.integers(0, 400, size=120_000), np.arange(400, 700)])
+    vocab = _check_repeated(lib, g, few, pick)
+    spread = vocab_from_tokens([few.token(i) for i in rng.permutation(pick)])
+    together, apart = _call_us(lib, g, vocab, 256), _call_us(lib, g, spread, 256)
+    print(f"together {together:.0f} us, apart {apart:.0f} us", flush=True)
+    assert together < 12 * apart
