@@ -393,7 +393,9 @@ struct PoolRoom {
     bool none_left;
 };
 // Sees to it that there is room for n configurations, as far as there is any.  Asked for before it is known whether the set
-// is new, so that nobody waits for the answer; what a known set leaves unused is there for the next.
+// is new; what a known set leaves unused is there for the next.  As many as are different, and not as there are successors, for
+// what is left of too little is lost: over a grammar with 64 successors for sets of eight the pool was full after a hundred
+// steps, and 19,700 of 32,000 tokens were handed on (965 us a call; 360 of them and 292 us so).
 __device__ __forceinline__ void sh_reserve(SharedLds &L, PoolRoom &room, int n, int lane) {
     if (room.n >= n || room.none_left) return;
     int top = 0;
@@ -731,7 +733,6 @@ __device__ __forceinline__ uint32_t sh_step_lanes(const DisplacementArgs &a, Sha
     const int upto = (int)wave_upto32((uint32_t)count), m = __builtin_amdgcn_readlane(upto, 63), first = upto - count;
     if (m > 64) return kByTheWave;
     if (!m) return dead;
-    sh_reserve(L, room, m, lane);
     // a configuration that something applies to is put where its first successor comes to stand, and the lanes of those look
     // which it is
     each[lane].w = 0;
@@ -757,6 +758,7 @@ __device__ __forceinline__ uint32_t sh_step_lanes(const DisplacementArgs &a, Sha
     if (__ballot(crossed)) return kCrossed;
     if (__ballot(full)) return kGiveUp;
     const Different<1> d = find_different<1>(seen, words, lane);
+    sh_reserve(L, room, d.n, lane);
     set.word = d.first[0] ? words[0] : kNoWord;
     set.cell = d.first[0] ? sh_end_cell(L, set.word) : 0u;
     const uint32_t number = sh_set_number(L, room, seen, d, lane);

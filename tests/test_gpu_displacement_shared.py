@@ -326,3 +326,19 @@ def test_tokens_that_share_no_sets_side_by_side(lib):
     together, apart = _call_us(lib, g, vocab, 256), _call_us(lib, g, spread, 256)
     print(f"together {together:.0f} us, apart {apart:.0f} us", flush=True)
     assert together < 12 * apart
+
+
+def test_room_for_sets_with_many_successors_alike(lib):
+    """Sets of eight configurations with 64 successors of which eight are different: the tokens fit the shared walk's room (the
+    second word of the workspace says how many did not; room for all successors was there for 12,000 of the 32,000)."""
+    top, first, alike, marks = 0, 1, range(2, 10), range(10, 14)
+    prods = [(first, ord("a"), (t,)) for t in alike] + [(t, ord("y"), (top,)) for t in alike]
+    prods += [(top, ord("0") + i, (t, m)) for i, m in enumerate(marks) for t in alike] + [(m, ord("v"), ()) for m in marks]
+    g = grammar_from_productions(14, prods)
+    few = vocab_from_tokens([b"a" + b"".join(b"y" + c for c in w) for w in itertools.product((b"0", b"1", b"2", b"3"), repeat=4)])
+    pick = np.random.default_rng(6).integers(0, few.V, size=32_000)
+    vocab = _check_repeated(lib, g, few, pick)
+    ws = torch.zeros(lib.load_library().cfgzip_displacements_workspace_bytes(vocab.V, g.N, g.P), dtype=torch.uint8, device="cuda")
+    lib.cfgzip_displacements(torch.from_numpy(vocab.tok_bytes).cuda(), torch.from_numpy(vocab.tok_off).cuda(), *_grammar_dev(g),
+                             g.N, workspace=ws)
+    assert int(ws[:8].view(torch.int32)[1]) < 3_200
