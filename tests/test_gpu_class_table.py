@@ -403,3 +403,49 @@ def test_walks_that_lie_apart_beside_such_that_do_not(lib, S, composed):
         c, r, C, coll = lib.cfgzip_build_classes(tb, to, tt, sig, h, signatures_workspace=ws)
         assert C == len(want_r) and coll == 0
         assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
+
+
+@pytest.mark.parametrize("V", [8_192, 16_383, 16_384, 20_000, 81_920, 81_921, 90_001])
+def test_one_pair_of_equal_hashes_from_the_walk_store(lib, V):
+    """Below 16,384 tokens four workgroups share a bucket's groups and above two, and from 81,920 on the waves that compare
+    tokens go round more than once.  A mistake there shows only where nothing else finds the pair, so two classes have one hash
+    in one place at a time: a class of one group (the tokens with a first byte) and one of others, and a class of one token
+    and one of others with its first byte."""
+    from gpu_util import dev, vocab_dev
+    print(f"case V={V}", flush=True)
+    rng = np.random.default_rng(V)
+    # a token's last byte is its signature: up to 200 they are everybody's, 16 are those of tokens that begin with a byte
+    # of their own, and the rest are of a token each
+    first, last = rng.integers(0, 240, size=V), rng.integers(0, 200, size=V)
+    single = sorted({0, 1, 62, 63, 1_023, V // 3, V // 2, V - 64, V - 9, V - 2, V - 1, *(int(t) for t in rng.integers(0, V, size=20)),
+                     *(t for t in range(81_916, 81_922) if t < V)})
+    last[single] = 216 + np.arange(len(single))
+    odd = np.setdiff1d(rng.permutation(V)[:80], single)
+    first[odd] = 240 + np.arange(len(odd)) % 16
+    last[odd] = 200 + np.arange(len(odd)) % 16
+    vocab = vocab_from_tokens([bytes((int(a), int(b))) for a, b in zip(first, last)])
+    table = np.tile(np.arange(256).astype(np.uint16), (256, 1))
+    _, at, of = np.unique(last, return_index=True, return_inverse=True)
+    rank = np.empty(len(at), np.int32)
+    rank[np.argsort(at)] = np.arange(len(at))
+    want_c, want_r = rank[of], np.sort(at)
+    tb, to, tt = vocab_dev(vocab, table)
+    ws = torch.empty(lib.load_library().cfgzip_signatures_workspace_bytes(V, 256), dtype=torch.uint8, device="cuda")
+    _, h = lib.cfgzip_signatures(tb, to, tt, want_sig=False, workspace=ws)
+    h = h.cpu().numpy()
+
+    def collisions(who, other):
+        """The tokens `who` are a class; it gets the hash of the token `other`'s."""
+        changed = h.copy()
+        changed[who] = h[other]
+        c, r, C, coll = lib.cfgzip_build_classes(tb, to, tt, None, dev(changed), signatures_workspace=ws)
+        assert C == len(want_r)
+        assert (c.cpu().numpy() == want_c).all() and (r.cpu().numpy() == want_r).all()
+        return coll
+
+    assert collisions([0], 0) == 0
+    for f in range(16):
+        assert collisions(last == 200 + f, int(np.nonzero(last == 12 * f)[0][0])) > 0, f
+    for t in single:
+        others = np.nonzero((first == first[t]) & (last != last[t]))[0]
+        assert collisions([t], int(others[t % len(others)])) > 0, t
