@@ -34,7 +34,8 @@ def find_hipcc() -> str:
     raise RuntimeError("hipcc not found; libcfgzip.so cannot be built")
 
 
-# the per-step calls of the binding as a CPython extension: host code only, against torch's headers
+# the binding's calls of every decode step and of the pre-computation as a CPython extension: host code only, against
+# torch's headers
 STEPCALL_PATH = os.path.join(LIB_DIR, "cfgzip_stepcall.so")
 
 
@@ -74,7 +75,7 @@ def build(verbose: bool = False) -> str:
         # no compiler, headers or torch for it: the binding does without, but not with one that an older source left
         if os.path.exists(STEPCALL_PATH):
             os.remove(STEPCALL_PATH)
-        print(f"{STEPCALL_PATH} not built ({e}): the per-step calls go through ctypes", file=sys.stderr, flush=True)
+        print(f"{STEPCALL_PATH} not built ({e}): the calls that it has go through ctypes", file=sys.stderr, flush=True)
     tool_flags = [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
     tmp = TOOL_PATH + ".tmp.%d" % os.getpid()
     cmd = [find_hipcc(), *tool_flags, "-o", tmp, os.path.join(CSRC, "tools", "gather_rate.hip")]

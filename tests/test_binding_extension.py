@@ -1,5 +1,5 @@
 """The binding's extension saves host time and nothing else: where it is missing, no library, or built for something
-else, the library loads, says so once, and the two per-step calls go through ctypes."""
+else, the library loads, says so once, and the calls that it has go through ctypes."""
 
 import ctypes
 import os
@@ -17,16 +17,21 @@ def binding(monkeypatch):
     from paper_2605_29986_amd import binding, build
     if not (os.path.exists(binding.library_path()) and os.path.exists(binding.stepcall_path())):
         build.build()
-    for name in ("_lib", "_decode_step", "_engine_step"):
+    for name in ("_lib", *CALLS):
         monkeypatch.setattr(binding, name, None)
     return binding
+
+
+# the extension's calls, and how many arguments each takes
+CALLS = {"_decode_step": 9, "_engine_step": 10, "_signatures": 9, "_build_classes": 9, "_displacements": 10, "_nfa_signatures": 5}
 
 
 def _goes_through_ctypes(binding):
     with pytest.warns(RuntimeWarning, match="through ctypes"):
         lib = binding.load_library()
     assert isinstance(lib, ctypes.CDLL) and binding.cfgzip_version() >= 100
-    assert binding._decode_step(*range(9)) is None and binding._engine_step(*range(10)) is None
+    for name, n in CALLS.items():
+        assert getattr(binding, name) is binding._by_ctypes and getattr(binding, name)(*range(n)) is None
     logits = torch.zeros((1, 8))
     ids = torch.zeros(8, dtype=torch.int32)
     with pytest.raises(ValueError, match="GPU tensor"):
@@ -39,9 +44,10 @@ def test_the_extension_is_used_where_it_is_there(binding):
     with warnings.catch_warnings():
         warnings.simplefilter("error")
         binding.load_library()
-    assert binding._decode_step.__module__ == binding._engine_step.__module__ == "cfgzip_stepcall"
-    # what is not plain tensors in GPU memory is left to ctypes
-    assert binding._decode_step(*range(9)) is None and binding._engine_step(*range(10)) is None
+    assert list(CALLS) == ["_" + name for name in binding._CALLS]
+    for name, n in CALLS.items():
+        assert getattr(binding, name).__module__ == "cfgzip_stepcall"
+        assert getattr(binding, name)(*range(n)) is None  # what is not plain tensors in GPU memory is left to ctypes
 
 
 def test_without_the_extension(binding, monkeypatch, tmp_path):
