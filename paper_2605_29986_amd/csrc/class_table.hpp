@@ -619,9 +619,16 @@ __global__ __launch_bounds__(kTableThreads) CFGZIP_OWN_PAGES void table_settle_k
             }
         } else {
             // rows against their classes' members' rows, which many share (they stay in the caches); what there is to read is
-            // every row once.  A wave takes four rows at a time, 1 KB of each, or 4 KB of one where a row has that: of rows of 8
-            // KB (262 MB in all) whole rows, which all begin at the same memory channels, took 60 us, 1 KB of four rows each 48.4,
-            // and so 40.5; rows of 2 KB, four at a time, 39
+            // every row once.  A wave takes four rows at a time, 1 KB of each, or 4 KB of one where a row has that: whole rows of
+            // 8 KB, which all begin at the same memory channels, took longer than either.  Four rows / one, calls on rows in whole
+            // units, us, with 150, 1,500 and 6,000 classes:
+            //   32,000 rows of 4.5 KB    44.3 / 48.2    57.3 / 57.4    59.9 / 58.3
+            //   32,000 rows of 8 KB      63.7 / 63.6    88.3 / 87.2    88.1 / 82.7
+            //   16,000 rows of 16 KB     62.0 / 69.5    85.5 / 86.2    80.7 / 72.5
+            //    4,000 rows of 60 KB     78.2 / 71.0    70.8 / 62.0    51.0 / 40.6
+            // and relations with their classes, 32,000 x 256 states 162 / 157, 8,000 x 512 1,133 / 1,122.  Lanes behind the end of a row
+            // read nothing: what a row of a little over 4 KB has in its last part is a few units, and asked for by all lanes they
+            // made 60,000 rows of 2,056 entries 71 us instead of 67, of 2,055 (at any address) 106 instead of 79.
             const bool vec = UNITS || a.S >= 8;
             const uint32_t s8 = ((uint32_t)a.S + 7u) / 8u;
             const bool long_rows = a.S >= kLongRow;
@@ -640,11 +647,11 @@ __global__ __launch_bounds__(kTableThreads) CFGZIP_OWN_PAGES void table_settle_k
                 if (vec) {
                     const uint32_t apart = long_rows ? kRowPart : 0u;  // of the four pieces, in their row
                     const uint32_t from = (uint32_t)(x % parts) * (long_rows ? 4u * kRowPart : kRowPart) + lane;
-                    if (long_rows || from < s8) {
+                    if (from < s8) {
                         u32x4_any p[4], q[4];
                         auto piece = [&](uint32_t tok, uint32_t j) -> u32x4_any {  // of a token's row
                             if (UNITS) {
-                                const uint4 v = reinterpret_cast<const uint4 *>(a.sig)[tok * s8 + min(j, s8 - 1u)];  // (31 bits)
+                                const uint4 v = reinterpret_cast<const uint4 *>(a.sig)[tok * s8 + j];  // (31 bits)
                                 return u32x4_any{v.x, v.y, v.z, v.w};
                             }
                             const uint16_t *row = a.sig + (size_t)tok * a.S;
@@ -652,6 +659,8 @@ __global__ __launch_bounds__(kTableThreads) CFGZIP_OWN_PAGES void table_settle_k
                         };
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
+                            p[u] = q[u] = u32x4_any{0u, 0u, 0u, 0u};
+                            if (from + u * apart >= s8) continue;  // behind the row: of its last part there may be little
                             p[u] = piece((uint32_t)t[u], from + u * apart);
                             q[u] = piece((uint32_t)ref[u], from + u * apart);
                         }
