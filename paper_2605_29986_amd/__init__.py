@@ -1,7 +1,7 @@
 """MI355X-native hot path of CFGzip (token-vocabulary compression for
 grammar-constrained decoding): a C-ABI HIP library, ``lib/libcfgzip.so``, and a
-thin binding with the same entry-point names (ctypes; the two calls of every decode
-step through a CPython extension, ``lib/cfgzip_stepcall.so``).
+thin binding with the same entry-point names (ctypes; the calls of every decode step
+and of the pre-computation through a CPython extension, ``lib/cfgzip_stepcall.so``).
 
 The binding only marshals arguments (device pointers of torch tensors, sizes,
 the current HIP stream); every step of the path runs in the library's kernels.

@@ -70,7 +70,8 @@ constexpr int kBucketTokens = 64;
 // Workgroups that share the comparisons of a bucket's groups, and those that compare tokens with their groups' members, at
 // the most: what a chip takes at a time is 768, and a workgroup costs its start.  Settling 151,936 / 128,256 tokens from the
 // walk store with 4 and 2,048 23.8 / 17.2 us, 2 and 2,048 21.9 / 16.3, 2 and 1,280 21.6 / 15.4, 2 and 768 23.3 / 15.7, 1 and
-// 2,048 26.0 / 18.6.  With fewer buckets than there may be the chip is not full, and four are better (a call on 4,096 tokens
+// 2,048 26.0 / 18.6; whole builds with 2 and 768 / 1,280 / 2,048, 64,000 tokens 32.5 / 32.7 / 32.6, 96,000 35.5 / 35.5 / 35.8,
+// 128,256 38.1 / 38.0 / 39.0, 151,936 44.2 / 43.5 / 43.9.  With fewer buckets than there may be the chip is not full, and four are better (a call on 4,096 tokens
 // 38.9 us, with two 39.9).
 constexpr int kPairBlocks = 1280;
 inline int table_group_shift(int buckets) { return buckets < kMaxBuckets ? 2 : 1; }  // as a power of two

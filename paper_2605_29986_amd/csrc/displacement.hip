@@ -444,8 +444,12 @@ static_assert(sizeof(AloneLds) <= 160 * 1024 && AloneLds::kFirst >= 11 && AloneL
 // over the JSON grammar of which the last 8,000 (of 12 bytes) share no sets 1,430 us a call, 389 so; 120,556 of which the last
 // 300 (of 28 bytes, most of which take the wide caps) 7,400 and 550.  What it costs is a launch that usually has nothing to
 // do: 2 us of 50 with 2,000 tokens over the statement grammar, 2 to 3 of 105 to 125 with 32,000 and 128,256 over the JSON
-// grammar.  (Lists offered by each workgroup to those that are through with their walk save the launch, but these are gone by
-// then, or all at one cursor: 1,620 us, 10,900, and 32,000 tokens that share no sets 7,140 where it is 415.)
+// grammar; and where all workgroups have such tokens, they are not taken while others still walk: 32,000 tokens over the
+// statement grammar five and eight times over 677 and 1,028 us, each by its own workgroup 595 and 845.  (A workgroup that keeps
+// its own up to twice the average: 600 and 850, but who leaves its own to all then waits behind those who do not, random
+// grammars up to 1.7 times as long.  Lists offered by each workgroup to those that are through with their walk save the
+// launch, but these are gone by then, or all at one cursor: 1,620 us, 10,900, and 32,000 tokens that share no sets 7,140 where
+// it is 420.)
 __global__ __launch_bounds__(kAloneThreads) void displacement_alone_kernel(DisplacementArgs a) {
     __shared__ AloneLds A;
     const int count = min(a.hdr->retry_count[0], a.V), grid = (int)gridDim.x, block = (int)blockIdx.x;

@@ -26,12 +26,12 @@ namespace {
 constexpr int kRowChunk = 256;                 // row entries staged in LDS at a time
 constexpr int kMaxByteSymbols = 255;           // up to here a symbol (and "none") fits a byte
 
-
 // caps of the second pass (over what the shared walk hands on) and of the third (over what the second could not
 // finish), which are the interface's
-// The second pass's queue and stack: what a token needs there sets how many waves a compute unit holds.  8-bit symbols:
-// 24 (12 waves; 32,000 tokens that share no sets, of 8, 12, 24 bytes: 303, 591, 1,050 us; 32: 296, 644, 1,180; 12, which
-// 20 waves fit with: 326, 504, 2,830, the last because the third pass then takes them all).
+// The second pass's queue and stack: what a token needs there sets how many waves a compute unit holds.  8-bit symbols: 24
+// (eleven waves), up to which tokens of as many bytes stay out of the third pass, which takes four at a time.  16 / 20 / 24, calls
+// on 32,000 tokens that share no sets, us: of 8 bytes 197 / 199 / 200, of 12 357 / 389 / 421, of 18 1,514 / 535 / 594, of 24 2,318 /
+// 2,475 / 833.
 template <typename Sym>
 constexpr int kLists1 = sizeof(Sym) == 1 ? 24 : 12;
 constexpr int kFrontier1 = 128;

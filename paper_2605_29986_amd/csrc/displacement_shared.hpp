@@ -30,7 +30,7 @@
 // unit takes 2.2 us, 670 instructions and twenty LDS accesses (the steps of 32 digits over the JSON grammar, sets of 20 to 51
 // configurations; 3.75 us with the pairs of configuration and production listed in LDS, the next set looked up and loaded
 // again, and a production read through a pointer that may be global, which waits for all rows on their way to memory).  Slower:
-// longest tokens first for some of the waves and shortest first for the others (JSON call 213 to 242 us, 208 otherwise; the
+// longest tokens first for some of the waves and shortest first for the others (JSON call 2 to 16 %; the
 // rows then go out earlier, but the chain is what counts), rows two at a time, claims asked for ahead of a step's first
 // look-ups (2 %: more instructions), the symbols of a set's lists in registers to bring them into order, a wave of few tokens
 // that waits for all of them before it writes any (JSON 1 to 5 %).
@@ -71,8 +71,12 @@ constexpr int kShBatch = 1024;      // tokens a workgroup sorts by length at a t
 constexpr int kShBytes = 6144;      // their bytes, kept in LDS; if there are more they are read from memory
 constexpr int kShLengths = 64;      // lengths told apart in sorting
 // Sorted tokens that a wave takes at a time, at the most: where the workgroup has up to kShFewTokens of them, and where it has
-// more.  Few at a time spread the steps over the waves, many make the look-ups of short tokens cheaper: 4 / 8 / 16 / 32, calls,
-// us, 125 tokens a workgroup over the statement grammar 115 / 117 / 119 / -, 501 over the JSON grammar 188 / 183 / 187 / 197.
+// more.  Few at a time spread the steps over the waves, many make the look-ups of short tokens cheaper.  Calls, four / eight at a
+// time, us:
+//   tokens a workgroup         188           250           256           313           375           501
+//   statement grammar     94.0 /  96.7  101.0 / 104.7  102.3 / 106.1  113.4 / 113.2  118.9 / 117.9  136.6 / 131.9
+//   JSON grammar         108.0 / 108.3  109.0 / 109.0  108.4 / 108.9  109.9 / 110.5  115.0 / 113.3  130.0 / 126.2
+// (16 and 32 at a time 2 to 7 % more than eight with 501 over the JSON grammar.)
 constexpr int kShTakeFew = 4, kShTakeMost = 8;
 constexpr int kShFewTokens = 16 * kShWaves;
 // Tokens for every wave up to which they are not sorted and a wave takes its share at once.  Calls sorted / not, rows of 1,024
@@ -510,8 +514,8 @@ __device__ __forceinline__ uint32_t sh_carry_out(const DisplacementArgs &a, Shar
 // One byte of Algorithm 1 by one lane, where it is simple enough: a set of one configuration that one production at
 // the most applies to.  The number of the set that follows, or kByTheWave.  Every lane has a token of its own here, so
 // a vocabulary whose tokens share no sets (every prefix of every token a set of its own: 32,000 tokens of 4, 8, 12 bytes
-// over such a grammar) is not worked out one token after the other: 185, 303, 591 us (227, 495, 722 before); a wave
-// per token, without the shared walk, 125, 172, 220.  What is left is that the tables fill up (from 8 bytes on) and that
+// over such a grammar) is not worked out one token after the other: 111, 200, 420 us; a wave per token, without the shared
+// walk, 125, 172, 220.  What is left is that the tables fill up (from 8 bytes on) and that
 // every token's row is its own.  Nothing is claimed first: two lanes that work out the same come to the same.
 constexpr int kFewProductions = 4;
 __device__ __forceinline__ uint32_t sh_step_alone(const DisplacementArgs &a, SharedLds &L, uint32_t set, uint32_t number,

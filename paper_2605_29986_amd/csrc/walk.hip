@@ -266,7 +266,7 @@ __global__ __launch_bounds__(kWalkThreads) void signatures_kernel(WalkArgs a) {
                     // piece ends with the row, if need be over part of the one before (60,000 tokens x 700 states with
                     // entries written one by one: a call of 123 us, 81 so).  Which token a piece belongs to is worked out
                     // once, by a product: three divisions a piece were a third of the kernel's vector instructions
-                    // (128,256 tokens x 1,024 states: 26.6 M a wave, 72 us; 18.4 M, 69 us so).
+                    // (128,256 tokens x 1,024 states, all waves together: 26.6 M, 72 us; 18.4 M, 69 us so).
                     const uint32_t s8 = ((uint32_t)S + 7) / 8, inverse = 0xFFFFFFFFu / s8 + 1u;  // 2^32 / s8, rounded up
                     const uint32_t items = (uint32_t)k * s8;  // times s8 below 2^32: the product is exact
                     static_assert((uint64_t)kWalkChunkTokens * 8192 * 8192 < 1ull << 32, "up to 65,536 states");
