@@ -518,11 +518,11 @@ __device__ __forceinline__ void table_number(const TableSettleArgs &a, unsigned 
 }
 
 // 16-byte units of a row that a wave compares at a time: of four rows each, or, where a row has that many, four times as many
-// of one, so that what it asks for lies together.
+// of one, so that what it asks for lies together.  Items go by fours of rows, then by parts, then, of long rows, by the four.
 constexpr uint32_t kRowPart = 64;
 constexpr int kLongRow = 4 * 8 * (int)kRowPart;  // entries
 __host__ __device__ inline int64_t table_row_items(int32_t n, int32_t S) {
-    if (S >= kLongRow) return (int64_t)n * ((S + kLongRow - 1) / kLongRow);
+    if (S >= kLongRow) return ((int64_t)n + 3) / 4 * 4 * ((S + kLongRow - 1) / kLongRow);
     return ((int64_t)n + 3) / 4 * ((S + 8 * (int)kRowPart - 1) / (8 * (int)kRowPart));
 }
 
@@ -621,21 +621,27 @@ __global__ __launch_bounds__(kTableThreads) CFGZIP_OWN_PAGES void table_settle_k
         } else {
             // rows against their classes' members' rows, which many share (they stay in the caches); what there is to read is
             // every row once.  A wave takes four rows at a time, 1 KB of each, or 4 KB of one where a row has that: whole rows of
-            // 8 KB, which all begin at the same memory channels, took longer than either.  Four rows / one, calls on rows in whole
-            // units, us, with 150, 1,500 and 6,000 classes:
-            //   32,000 rows of 4.5 KB    44.3 / 48.2    57.3 / 57.4    59.9 / 58.3
-            //   32,000 rows of 8 KB      63.7 / 63.6    88.3 / 87.2    88.1 / 82.7
-            //   16,000 rows of 16 KB     62.0 / 69.5    85.5 / 86.2    80.7 / 72.5
-            //    4,000 rows of 60 KB     78.2 / 71.0    70.8 / 62.0    51.0 / 40.6
-            // and relations with their classes, 32,000 x 256 states 162 / 157, 8,000 x 512 1,133 / 1,122.  Lanes behind the end of a row
-            // read nothing: what a row of a little over 4 KB has in its last part is a few units, and asked for by all lanes they
-            // made 60,000 rows of 2,056 entries 71 us instead of 67, of 2,055 (at any address) 106 instead of 79.
+            // 8 KB, which all begin at the same memory channels, took longer than either.  Four waves next to each other then take
+            // the same part of four rows, and so workgroups that go to different XCDs different parts: with rows of a power of two an
+            // XCD's cache holds a part of every member's row, and not all of them.  Four rows / one, its parts by waves next to each
+            // other / one, as here; calls on rows in whole units, us, with 150, 1,500 and 6,000 classes:
+            //   32,000 rows of 4.5 KB     50.9 / 49.9 / 50.3     63.0 / 58.1 / 58.4     65.2 / 58.8 / 59.4
+            //   32,000 rows of 8 KB       67.9 / 62.4 / 62.5     90.4 / 84.2 / 84.3     91.2 / 80.9 / 80.8
+            //   30,000 rows of 16 KB     117.4 / 117.0 / 111.7  143.6 / 141.8 / 136.8  141.2 / 129.1 / 128.2
+            //   16,000 rows of 16 KB      67.1 / 69.2 / 61.9     88.0 / 83.9 / 81.2     83.1 / 71.0 / 70.8
+            //    8,000 rows of 32 KB      66.7 / 77.2 / 61.2     84.4 / 79.2 / 75.7
+            //    4,000 rows of 60 KB      80.4 / 73.6 / 74.9     74.1 / 61.2 / 61.8
+            // (eight rows, a part to a workgroup, 3 to 5 us less where rows are multiples of 8 KB, but up to 30 % more where the last
+            // part has little: its workgroups have nothing to do), and relations with their classes, 32,000 x 256 states, 155.3 either
+            // way of one.  Lanes behind the end of a row read nothing: what a row of a little over 4 KB has in its last part is a few
+            // units, and asked for by all lanes they made 60,000 rows of 2,056 entries 71 us instead of 67, of 2,055 (at any address)
+            // 106 instead of 79.
             const bool vec = UNITS || a.S >= 8;
             const uint32_t s8 = ((uint32_t)a.S + 7u) / 8u;
             const bool long_rows = a.S >= kLongRow;
-            const int64_t items = table_row_items(a.n, vec ? a.S : 1), per = long_rows ? a.n : ((int64_t)a.n + 3) / 4, parts = items / per;
+            const int64_t items = table_row_items(a.n, vec ? a.S : 1), parts = items / (((int64_t)a.n + 3) / 4) / (long_rows ? 4 : 1);
             for (int64_t x = gw; x < items; x += waves) {
-                const int64_t t0 = x / parts * (long_rows ? 1 : 4);
+                const int64_t fours = long_rows ? x / 4 : x, t0 = fours / parts * 4 + (long_rows ? x % 4 : 0);
                 int32_t t[4], ref[4];
                 int cnt = 0;
 #pragma unroll
@@ -647,7 +653,7 @@ __global__ __launch_bounds__(kTableThreads) CFGZIP_OWN_PAGES void table_settle_k
                 if (!cnt) continue;  // all four are their classes' members (wave-uniform)
                 if (vec) {
                     const uint32_t apart = long_rows ? kRowPart : 0u;  // of the four pieces, in their row
-                    const uint32_t from = (uint32_t)(x % parts) * (long_rows ? 4u * kRowPart : kRowPart) + lane;
+                    const uint32_t from = (uint32_t)(fours % parts) * (long_rows ? 4u * kRowPart : kRowPart) + lane;
                     if (from < s8) {
                         u32x4_any p[4], q[4];
                         auto piece = [&](uint32_t tok, uint32_t j) -> u32x4_any {  // of a token's row
